@@ -15,10 +15,9 @@
 //   * two LDS stages of up to 72 KB (three smaller ones for the 128- and 64-row tiles).  Rows are
 //     128 bytes; 16-byte chunk c of row r is stored at chunk position c ^ ((r >> 1) & 7), which makes sixteen consecutive rows reading the same
 //     logical chunk cover all 64 banks exactly once.
-//   * per k-step a wave runs four groups of MFMAs; the fragments of group g+1 are read from LDS
-//     while group g executes.  The workgroup barrier sits before the last group, whose MFMAs
-//     are interleaved one-to-one with the DMA instructions that prefetch tile k+2 into the
-//     stage that was just vacated, and overlap the first fragment reads of tile k+1.
+//   * the fragment reads are spread over the MFMAs of a k-step.  A barrier after its first steps releases the
+//     weights' part of the stage, one before its last steps the activations' part; the DMA instructions that
+//     prefetch tile k+2 follow each of them, spread over MFMAs (mfma_pipeline.hpp).
 //
 // In gemm1 a workgroup's 256 weight rows are 128 gate rows plus the 128 matching up rows,
 // arranged so that each lane holds gate and up of the same output element; SwiGLU is applied
@@ -206,13 +205,11 @@ __global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __rest
 }
 
 template <int MI, int NI>
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[MI][NI]) {
+__device__ __forceinline__ void zero_acc(f32x4 (&acc)[2 * MI][2 * NI]) {
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+  for (int i = 0; i < 2 * MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < 2 * NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 
@@ -331,48 +328,51 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
                     return min(max(pair, 0) / src.k, src.n_tokens - 1);
                   },
                   voff);
-  // weight tile row j: wave column block q = j / (2 HALF); inside it HALF gate rows, then the HALF up rows
-  dma_offsets<2 * NI>(wv, lane, H * 2,
-                      [&](int j) {
-                        int q = j / (2 * HALF), r = j % (2 * HALF);
-                        int f = min(n0 + HALF * q + (r % HALF), F - 1);  // columns past F are masked at the store
-                        return (r < HALF) ? f : F + f;
-                      },
-                      voff + MI);
-  f32x16 acc[MI][NI];
+  // weight tile row j: wave column block q = j / (2 HALF), row r inside it.  NI = 2: HALF gate rows, then the HALF
+  // up rows (B fragments 0, 1 / 2, 3 of the wave).  NI = 1: gate and up rows in alternating runs of four, which makes
+  // the main loop's fragment 0 the sixteen gate rows and fragment 1 the up rows.
+  dma_offsets<2 * NI, true>(wv, lane, H * 2,
+                            [&](int j) {
+                              const int q = j / (2 * HALF), r = j % (2 * HALF);
+                              const bool up = NI == 2 ? r >= HALF : (r >> 2) & 1;
+                              const int c = NI == 2 ? r % HALF : ((r >> 3) << 2) | (r & 3);
+                              const int f = min(n0 + HALF * q + c, F - 1);  // columns past F are masked at the store
+                              return up ? F + f : f;
+                            },
+                            voff + MI);
+  f32x4 acc[2 * MI][2 * NI];
   zero_acc<MI, NI>(acc);
   const bool drew =
       gemm_mainloop<MI, NI, 1, NST, true, DRAW>(rA, rB, voff, 0, H, smem, wv, lane, acc, draw_counter, draw_slot);
 
-  // Accumulator registers 8g .. 8g+7 of a lane are eight consecutive output columns of one output
-  // row (see gemm_mainloop, PERM): one 16-byte store each.  The stores go through a buffer
+  // NI = 2: acc[i][0..1] are eight consecutive gate columns of one output row, acc[i][2..3] the up columns (see
+  // gemm_mainloop, PERM): one 16-byte store.  NI = 1: four of each, 8 bytes.  The stores go through a buffer
   // descriptor that ends with the tile's last valid row, so rows past it are dropped by the
   // bounds check instead of a branch.
   const int valid = min(rows, 64 * MI);
   __amdgpu_buffer_rsrc_t rH = make_rsrc(hbuf + static_cast<size_t>(row0) * F, static_cast<size_t>(valid) * F * 2);
-  const int row_in = 32 * MI * wm + (lane & 31);
-  const int cbase = n0 + HALF * wn + 8 * (lane >> 5);
+  const int row_in = 32 * MI * wm + (lane & 15);
+  const int cbase = n0 + HALF * wn + 4 * NI * (lane >> 4);
+  if (cbase < F) {  // F % 8 == 0: a group of 4 * NI columns is in or out as a whole
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
-    const int off = ((row_in + 32 * mi) * F + cbase) * 2;
+    for (int i = 0; i < 2 * MI; ++i) {
+      const int off = ((row_in + 16 * i) * F + cbase) * 2;
+      uint32_t pk[2 * NI];
 #pragma unroll
-    for (int g = 0; g < NI; ++g) {
-      if (cbase + 16 * g < F) {  // F % 8 == 0: an 8-column group is in or out as a whole
-        float hv[8];
+      for (int j = 0; j < NI; ++j) {
+        float hv[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          // NI = 2: fragment 0 holds the gate rows, fragment 1 the up rows; NI = 1: registers 0..7 / 8..15
-          float gt = NI == 2 ? acc[mi][0][8 * g + e] : acc[mi][0][e];
-          float up = NI == 2 ? acc[mi][NI - 1][8 * g + e] : acc[mi][0][8 + e];
+        for (int e = 0; e < 4; ++e) {
+          const float gt = acc[i][j][e], up = acc[i][NI + j][e];
           hv[e] = gt / (1.f + __expf(-gt)) * up;
         }
-        u32x4 pk;
-        pk[0] = pack_bf16x2(hv[0], hv[1]);
-        pk[1] = pack_bf16x2(hv[2], hv[3]);
-        pk[2] = pack_bf16x2(hv[4], hv[5]);
-        pk[3] = pack_bf16x2(hv[6], hv[7]);
-        __builtin_amdgcn_raw_buffer_store_b128(pk, rH, off + 32 * g, 0, 0);
+        pk[2 * j] = pack_bf16x2(hv[0], hv[1]);
+        pk[2 * j + 1] = pack_bf16x2(hv[2], hv[3]);
       }
+      if constexpr (NI == 2)
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{pk[0], pk[1], pk[2], pk[3]}, rH, off, 0, 0);
+      else
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{pk[0], pk[1]}, rH, off, 0, 0);
     }
   }
   return drew;
@@ -445,31 +445,28 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
   __amdgpu_buffer_rsrc_t rB = make_rsrc(w2, static_cast<size_t>(H) * F * 2);
   int voff[MI + 2 * NI];
   dma_offsets<MI>(wv, lane, F * 2, [&](int r) { return r; }, voff);  // rows past the slot read as zeros (out of range)
-  dma_offsets<2 * NI>(wv, lane, F * 2, [&](int j) { return min(n0 + j, H - 1); }, voff + MI);
-  f32x16 acc[MI][NI];
+  dma_offsets<2 * NI, true>(wv, lane, F * 2, [&](int j) { return min(n0 + j, H - 1); }, voff + MI);
+  f32x4 acc[2 * MI][2 * NI];
   zero_acc<MI, NI>(acc);
   const bool drew =
       gemm_mainloop<MI, NI, 1, NST, true, DRAW>(rA, rB, voff, 0, F, smem, wv, lane, acc, draw_counter, draw_slot);
 
   const int valid = min(rows, 64 * MI);  // rows past it are dropped by the descriptor's bounds check
   __amdgpu_buffer_rsrc_t rY = make_rsrc(y + static_cast<size_t>(row0) * H, static_cast<size_t>(valid) * H * 2);
-  const int row_in = 32 * MI * wm + (lane & 31);
+  const int row_in = 32 * MI * wm + (lane & 15);
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
+  for (int i = 0; i < 2 * MI; ++i) {
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      const int cbase = n0 + 32 * NI * wn + 32 * ni + 8 * (lane >> 5);
-      const int off = ((row_in + 32 * mi) * H + cbase) * 2;
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        if (cbase + 16 * g < H) {
-          u32x4 pk;
-          pk[0] = pack_bf16x2(acc[mi][ni][8 * g + 0], acc[mi][ni][8 * g + 1]);
-          pk[1] = pack_bf16x2(acc[mi][ni][8 * g + 2], acc[mi][ni][8 * g + 3]);
-          pk[2] = pack_bf16x2(acc[mi][ni][8 * g + 4], acc[mi][ni][8 * g + 5]);
-          pk[3] = pack_bf16x2(acc[mi][ni][8 * g + 6], acc[mi][ni][8 * g + 7]);
-          __builtin_amdgcn_raw_buffer_store_b128(pk, rY, off + 32 * g, 0, 0);
-        }
+    for (int q = 0; q < NI; ++q) {
+      const int cbase = n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4);
+      const int off = ((row_in + 16 * i) * H + cbase) * 2;
+      if (cbase < H) {
+        u32x4 pk;
+        pk[0] = pack_bf16x2(acc[i][2 * q][0], acc[i][2 * q][1]);
+        pk[1] = pack_bf16x2(acc[i][2 * q][2], acc[i][2 * q][3]);
+        pk[2] = pack_bf16x2(acc[i][2 * q + 1][0], acc[i][2 * q + 1][1]);
+        pk[3] = pack_bf16x2(acc[i][2 * q + 1][2], acc[i][2 * q + 1][3]);
+        __builtin_amdgcn_raw_buffer_store_b128(pk, rY, off, 0, 0);
       }
     }
   }

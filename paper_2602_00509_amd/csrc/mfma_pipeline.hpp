@@ -1,4 +1,4 @@
-// Software-pipelined NT bf16 GEMM main loop on v_mfma_f32_32x32x16_bf16, shared by the grouped FFN
+// Software-pipelined NT bf16 GEMM main loop on v_mfma_f32_16x16x32_bf16, shared by the grouped FFN
 // and the gate.  See the comments of ffn.hip for the pipeline; this header only holds the loop.
 #pragma once
 
@@ -19,32 +19,53 @@ __device__ __forceinline__ void wait_vm_lgkm0() {  // s_waitcnt vmcnt(N) lgkmcnt
 // ---- shared main loop -----------------------------------------------------------------
 // 8 waves as 2 (rows) x 4 (columns).  The A tile has 64*MI rows; the B tile has PL planes of
 // 128*NI rows each (plane p, column c at B-tile row p*128*NI + c).  The calling wave accumulates
-//   acc[i][j] += sum_p  A[32*MI*wm + 32*i .. +32, :] * B_p[32*NI*wn + 32*j .. +32, :]^T
+//   acc[i][j] += sum_p  A[32*MI*wm + 16*i .. +16, :] * B_p[32*NI*wn + 16*j .. +16, :]^T
 // (PL = 1: a plain GEMM; PL = 3: one logical weight held as three bf16 planes).
 // rA / rB are buffer descriptors of the tile's first A row / of the weight matrix; voff[j] is
 // this lane's byte offset for DMA instruction j (MI instructions for A, then BW for B); k0 is
 // the first k of this call's K range and K its length (a multiple of 64).
 // NST = LDS stages (2 or 3); a DMA batch is issued NST k-steps ahead of its use.
 //
-// Accumulator layout.  The B fragment is the MFMA's row operand, so with PERM = false registers
-// 4q .. 4q+3 of lane l hold output row (l % 32) of the A block and the four consecutive output
-// columns 8q + 4(l / 32) .. +3 of the B block.  With PERM = true, MFMA row position i is fed B row
-// i with bits 2 and 3 exchanged; registers 8g .. 8g+7 then hold the EIGHT consecutive columns
-// 16g + 8(l / 32) .. +7, a 16-byte bf16 store per lane and 32 contiguous bytes per row and store
-// instruction.  Sixteen consecutive positions still read sixteen consecutive LDS rows, so the
-// fragment reads stay free of bank conflicts.
+// What bounds it: matrix cores under the chip's power limit, and next to them the way of the weights from HBM.  With all
+// k offsets pinned to 0 (every load an L2 hit) the previous form of this loop ran at 1.40 instead of 1.18 PFLOP/s on the
+// 8-expert prefill, with only the weights' offsets pinned at 1.35; releasing the weights' part of a stage early
+// (EARLY below) took that case from 1.18 to 1.27, and 36 slots of 512 rows from 1.08 to 1.20 PFLOP/s.  Releasing them
+// half-way through the k-step instead costs 3 %, together with half of the activations 5 %; issuing
+// the activations' DMA in one burst instead of spread over the last steps costs 3 %.
+//
+// Why 16x16x32 and not 32x32x16: the chip is power-limited under matrix work, and per flop the 16x16x32 form
+// reads and writes half as many accumulator bits (each accumulator is touched once per 32 k instead of once per
+// 16) for twice the operand reads.  A loop of nothing but MFMAs on N(0,1) x N(0,0.02) operands in registers runs at
+// 1.79 PFLOP/s with 32x32x16 and at 2.05 PFLOP/s with 16x16x32 (2.01 when every row of accumulators starts over at
+// column 0 instead of running back and forth, which keeps one operand of every consecutive pair the same).
+//
+// Accumulator layout.  The B fragment is the MFMA's row operand, so with PERM = false registers 0..3 of lane l
+// hold output row (l % 16) of the 16-row A fragment and the four consecutive output columns 4(l / 16) .. +3 of the
+// 16-column B fragment.  With PERM = true, position p of B fragment 2q + f is fed B row 32q + 8(p / 4) + 4f + p % 4, so
+// acc[i][2q] and acc[i][2q + 1] together hold the EIGHT consecutive columns 32q + 8(l / 16) .. +7: a 16-byte bf16
+// store per lane and 64 contiguous bytes per row and store instruction.
 //
 // DRAW: thread 0 of the workgroup draws the next ticket of a work queue (atomic add of 1 on *draw_counter) at the
 // start of the second-to-last k-step, which issues no DMA and ends with a wait for everything in flight, and
 // leaves it in *draw_slot (LDS) before that step's barrier; after the loop every thread can read it.  Returns
 // whether that happened (it needs K >= 128).  After the barrier of the last k-step no wave reads the LDS stages.
+
+// 16-byte chunk c of tile row r is stored at chunk position c ^ key(r), so that the sixteen rows of a fragment reading
+// the same logical chunk cover all 64 banks exactly once: sixteen consecutive rows, or (PERM) the rows 8a + b + const,
+// a and b = 0..3.
+template <bool PERM>
+__device__ __forceinline__ int lds_key(int row) {
+  return PERM ? ((row >> 1) & 1) | (((row >> 3) & 3) << 1) : (row >> 1) & 7;
+}
+
 template <int MI, int NI, int PL, int NST, bool PERM = false, bool DRAW = false>
 __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgpu_buffer_rsrc_t rB,
                                               const int (&voff)[MI + NI * PL * 2], int k0, int K,
-                                              u32x4* smem, int wv, int lane, f32x16 (&acc)[MI][NI],
+                                              u32x4* smem, int wv, int lane, f32x4 (&acc)[2 * MI][2 * NI],
                                               int32_t* draw_counter = nullptr, volatile int* draw_slot = nullptr) {
   constexpr int WN = 4, BROWS = 128 * NI * PL, AW = MI, BW = BROWS / 64, LPW = AW + BW, BM = 64 * MI;
-  constexpr int NB = NI * PL;             // B fragments per k16
+  constexpr int BF = 2 * NI;              // B fragments of a plane
+  constexpr int NB = BF * PL;             // B fragments per k32
   constexpr int kStage = (BM + BROWS) * 8;  // 16-byte units per stage
   static_assert(NST == 2 || NST == 3, "two or three stages");
   static_assert(NST * kStage * 16 <= 160 * 1024, "LDS budget");
@@ -62,39 +83,48 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
 #pragma unroll
     for (int j = 0; j < LPW; ++j) issue_one(st, j, (k0 + kt * FBK) * 2);
   };
-  int offA[MI], offB[NB];
-  const int brow = PERM ? ((lane & 19) | ((lane & 4) << 1) | ((lane & 8) >> 1)) : (lane & 31);
-#pragma unroll
-  for (int i = 0; i < MI; ++i) offA[i] = (32 * MI * wm + 32 * i + (lane & 31)) * 8;
-#pragma unroll
-  for (int j = 0; j < NI; ++j)
+  const int arow = 32 * MI * wm + (lane & 15);
+  const int brow = 32 * NI * wn + (PERM ? ((lane & 12) << 1) | (lane & 3) : (lane & 15));
+  const int akey = lds_key<false>(arow), bkey = lds_key<PERM>(brow);
+  // A k-step is STEPS = 4 * MI steps; a step multiplies one A fragment by all B fragments at one of the two k32 of the
+  // step.  Fragments are taken in pairs: (2p, k32 0) (2p + 1, k32 0) (2p, k32 1) (2p + 1, k32 1).
+  //   * A fragments live in a ring of W register sets: as soon as the MFMAs of a step are issued, its set is loaded with
+  //     the fragment needed W steps later, so the LDS reads are spread evenly over the MFMAs.  (Reading the fragments of
+  //     a quarter k-step at once, double-buffered, needs 20 more registers: the 320-row tile then spills in the loop.)
+  //   * The B fragments of both k32 stay in registers for the whole k-step: those of k32 1 are read at its start, those
+  //     of k32 0 of the next k-step during its last two steps.  The B part of a stage is therefore free after a fifth
+  //     to a third of its k-step, and with EARLY the DMA of the weights due NST k-steps later starts there, behind a
+  //     barrier of its own, instead of at the end: weights come from HBM and take longest to arrive.
+  constexpr int STEPS = 4 * MI, W = MI == 5 ? 5 : (MI == 1 ? 2 : (MI == 3 ? 6 : 4)), BAR = STEPS - W + (W > 2 ? 1 : 0);
+  constexpr bool EARLY = MI >= 3;
+  constexpr int FREE_B = 4;  // EARLY: the step before which B's part of the stage is released
+  static_assert(STEPS % W == 0, "ring positions repeat every k-step");
+  static_assert(!EARLY || FREE_B < BAR, "B is released before A");
+  constexpr auto frag_of = [](int t) { return 2 * (t / 4) + (t & 1); };
+  constexpr auto k32_of = [](int t) { return (t >> 1) & 1; };
+  auto read_a = [&](int st, int t) {
+    return smem[st * kStage + (arow + 16 * frag_of(t)) * 8 + ((4 * k32_of(t) + (lane >> 4)) ^ akey)];
+  };
+  auto read_b = [&](int st, int kk, int r) {
+    const int p = r / BF, j = r % BF;
+    const int row = p * 128 * NI + (PERM ? 32 * (j >> 1) + 4 * (j & 1) : 16 * j);
+    return smem[st * kStage + (BM + brow + row) * 8 + ((4 * kk + (lane >> 4)) ^ bkey)];
+  };
+  u32x4 a[W], b[2][NB];
+  // plane slowest, so consecutive MFMAs hit different accumulators; columns run back and forth, so the MFMAs on either
+  // side of a step's end share an operand.  The weight fragment is the row operand.
+  auto mfma_step = [&](int t) {
+    const int i = frag_of(t), kk = k32_of(t);
 #pragma unroll
     for (int p = 0; p < PL; ++p)
-      offB[j * PL + p] = BM * 8 + (p * 128 * NI + 32 * NI * wn + 32 * j + brow) * 8;
-  const int swz = ((lane & 31) >> 1) & 7;  // (row >> 1) & 7: every 32-row block starts at a multiple of 32
-  const int swzB = (brow >> 1) & 7;
-  auto read_frags = [&](int st, int kk, u32x4(&a)[MI], u32x4(&b)[NB]) {
-    const u32x4* sbase = smem + st * kStage;
-    const int pc = (2 * kk + (lane >> 5)) ^ swz, pcB = (2 * kk + (lane >> 5)) ^ swzB;
 #pragma unroll
-    for (int i = 0; i < MI; ++i) a[i] = sbase[offA[i] + pc];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] = sbase[offB[j] + pcB];
-  };
-  // the weight fragment is the row operand: a lane's accumulator registers 4q..4q+3 are four
-  // consecutive output columns of one output row
-  // MFMA number t of a group: plane slowest, so consecutive MFMAs hit different accumulators
-  auto mfma_t = [&](int t, u32x4(&a)[MI], u32x4(&b)[NB]) {
-    const int p = t / (MI * NI), i = (t / NI) % MI, j = t % NI;
-    acc[i][j] = mfma_32x32x16(b[j * PL + p], a[i], acc[i][j]);
-  };
-  auto mma = [&](u32x4(&a)[MI], u32x4(&b)[NB]) {
-#pragma unroll
-    for (int t = 0; t < MI * NI * PL; ++t) mfma_t(t, a, b);
+      for (int c = 0; c < BF; ++c) {
+        const int j = ((t + p) & 1) ? BF - 1 - c : c;
+        acc[i][j] = mfma_16x16x32(b[kk][p * BF + j], a[t % W], acc[i][j]);
+      }
   };
 
   const int KT = K / FBK;
-  u32x4 a0[MI], b0[NB], a1[MI], b1[NB];
   // prologue: NST batches in flight, wait for the first
   issue_all(0, 0);
   if (KT > 1) issue_all(1, 1);
@@ -111,7 +141,10 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
   }
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  read_frags(0, 0, a0, b0);
+#pragma unroll
+  for (int r = 0; r < NB; ++r) b[0][r] = read_b(0, 0, r);
+#pragma unroll
+  for (int t = 0; t < W; ++t) a[t] = read_a(0, t);
   // One k-step on stage `cur`.  DMA: issue tile kt+NST into the stage being vacated.
   // YOUNGER: a batch younger than tile kt+1 is in flight at the barrier (it may stay in flight).
   // NEXT: tile kt+1 exists.
@@ -120,46 +153,58 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
     constexpr bool DMA = decltype(dma_c)::value, YOUNGER = decltype(younger_c)::value,
                    NEXT = decltype(next_c)::value;
     const int nxt = (cur + 1 == NST) ? 0 : cur + 1;
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): a0/b0 have arrived
-    read_frags(cur, 1, a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-    mma(a0, b0);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    read_frags(cur, 2, a0, b0);
-    __builtin_amdgcn_sched_barrier(0);
-    mma(a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    read_frags(cur, 3, a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-    mma(a0, b0);
-    __builtin_amdgcn_sched_barrier(0);
-    // every read of stage cur is issued: wait for them and for this wave's share of tile kt+1
-    if constexpr (YOUNGER) wait_vm_lgkm0<LPW>(); else wait_vm_lgkm0<0>();
-    hook();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    if constexpr (NEXT) read_frags(nxt, 0, a0, b0);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (DMA) {
-      const int kbytes = (k0 + (kt + NST) * FBK) * 2;
-      constexpr int NM = MI * NI * PL;
+    const int kbytes = (k0 + (kt + NST) * FBK) * 2;
+    // DMA instructions are spread over the steps after the barrier that releases their part of the stage
+    constexpr int ASTEPS = STEPS - BAR, BSTEPS = EARLY ? BAR - FREE_B : ASTEPS;
 #pragma unroll
-      for (int t = 0; t < NM; ++t) {
-        mfma_t(t, a1, b1);
-        if (t < LPW) issue_one(cur, t, kbytes);
+    for (int t = 0; t < STEPS; ++t) {
+      if (t == 0) {
+#pragma unroll
+        for (int r = 0; r < NB; ++r) b[1][r] = read_b(cur, 1, r);
+        __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int t = NM; t < LPW; ++t) issue_one(cur, t, kbytes);
-#pragma unroll
-      for (int t = 0; t < (NM < LPW ? NM : LPW); ++t) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // one VMEM read
+      if (DMA && EARLY && t == FREE_B) {  // b[1] was used by the last two steps: every B read of the stage has arrived
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
       }
-    } else {
-      mma(a1, b1);
+      if (t == BAR) {
+        // every read of stage cur is issued: wait for them and for this wave's share of tile kt+1; what was issued
+        // after that share may stay in flight
+        wait_vm_lgkm0<(YOUNGER ? LPW : 0) + (DMA && EARLY ? BW : 0)>();
+        hook();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if constexpr (NEXT) {
+#pragma unroll
+          for (int u = STEPS - W; u < BAR; ++u) a[u % W] = read_a(nxt, u + W - STEPS);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (NEXT) {
+        if (t == STEPS - 2) {
+#pragma unroll
+          for (int r = 0; r < NB; ++r) b[0][r] = read_b(nxt, 0, r);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      mfma_step(t);
+      __builtin_amdgcn_sched_barrier(0);
+      if (t + W < STEPS) {
+        a[t % W] = read_a(cur, t + W);
+      } else if constexpr (NEXT) {
+        if (t >= BAR) a[t % W] = read_a(nxt, t + W - STEPS);
+      }
+      if constexpr (DMA) {
+        const int u = EARLY ? t - FREE_B : t - BAR;
+#pragma unroll
+        for (int j = 0; j < BW; ++j)
+          if (u >= 0 && u < BSTEPS && j * BSTEPS / BW == u) issue_one(cur, AW + j, kbytes);
+#pragma unroll
+        for (int j = 0; j < AW; ++j)
+          if (t >= BAR && j * ASTEPS / AW == t - BAR) issue_one(cur, j, kbytes);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   using T_ = std::integral_constant<bool, true>;
@@ -212,19 +257,27 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
 }
 
 // Raw buffer descriptor over [base, base + bytes): loads past the end return zero.
+// base and bytes are the same for every lane; saying so (readfirstlane) keeps the compiler from wrapping each access in
+// a loop over the distinct descriptors of the wave, which it does when a value came through LDS or a vector register.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, size_t bytes) {
-  unsigned n = bytes > 0xffffffffull ? 0xffffffffu : static_cast<unsigned>(bytes);
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, static_cast<int>(n), 0x00020000);
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(p));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(p >> 32));
+  const int n = __builtin_amdgcn_readfirstlane(
+      static_cast<int>(bytes > 0xffffffffull ? 0xffffffffu : static_cast<unsigned>(bytes)));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(static_cast<uint64_t>(hi) << 32 | lo), 0, n,
+                                           0x00020000);
 }
 
 // Per-lane byte offsets of the DMA instructions of this wave: instruction j covers tile rows
 // (wv*CNT + j)*8 .. +8; lane l reads row +l/8, the chunk that belongs at LDS position l%8.
-template <int CNT, typename RowFn>
+// PERM as in gemm_mainloop for the weight tile, false for the activation tile.
+template <int CNT, bool PERM = false, typename RowFn>
 __device__ __forceinline__ void dma_offsets(int wv, int lane, int row_bytes, RowFn row_of, int* out) {
 #pragma unroll
   for (int j = 0; j < CNT; ++j) {
     int row = (wv * CNT + j) * 8 + (lane >> 3);
-    int c = (lane & 7) ^ ((row >> 1) & 7);
+    int c = (lane & 7) ^ lds_key<PERM>(row);
     out[j] = row_of(row) * row_bytes + c * 16;
   }
 }

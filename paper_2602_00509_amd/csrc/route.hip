@@ -195,30 +195,27 @@ __global__ __launch_bounds__(512, 2) void gate_gemm_dma_kernel(const bf16_t* __r
   dma_offsets<MI>(wv, lane, H * 2, [&](int r) { return min(r, rows - 1); }, voff);
   // B-tile row j: plane j / 128, expert n0 + j % 128 (clamped; columns past E are masked at the store)
   dma_offsets<2 * PL>(wv, lane, H * 2, [&](int j) { return (j >> 7) * E + min(n0 + (j & 127), E - 1); }, voff + MI);
-  f32x16 acc[MI][1];
+  f32x4 acc[2 * MI][2];
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][0][r] = 0.f;
+  for (int i = 0; i < 2 * MI; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   gemm_mainloop<MI, 1, PL, 2>(rA, rB, voff, kbeg, klen, smem, wv, lane, acc);
 
   const bool vec = (E & 3) == 0;
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
-    const int row = 32 * MI * wm + 32 * mi + (lane & 31);
+  for (int i = 0; i < 2 * MI; ++i) {
+    const int row = 32 * MI * wm + 16 * i + (lane & 15);
     if (row < rows) {
       float* dst = partial + (static_cast<long>(ks) * T + m0 + row) * E;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = n0 + 32 * wn + 8 * q + 4 * (lane >> 5);
+      for (int j = 0; j < 2; ++j) {
+        const int col = n0 + 32 * wn + 16 * j + 4 * (lane >> 4);
         if (vec) {
           if (col < E)
-            *reinterpret_cast<float4*>(dst + col) =
-                make_float4(acc[mi][0][4 * q], acc[mi][0][4 * q + 1], acc[mi][0][4 * q + 2], acc[mi][0][4 * q + 3]);
+            *reinterpret_cast<float4*>(dst + col) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if (col + e < E) dst[col + e] = acc[mi][0][4 * q + e];
+            if (col + e < E) dst[col + e] = acc[i][j][e];
         }
       }
     }

@@ -303,6 +303,15 @@ def test_ffn_every_tile_height_at_full_depth(oracle, probe, G):
     _ffn_against_oracle(oracle, probe, G, cfg, [320, 256, 192, 128, 64, 37, 0, 321], 3, seed=77)
 
 
+@pytest.mark.parametrize("H,F", [(64, 256), (320, 64), (256, 128)])
+def test_ffn_every_tile_height_at_shallow_depth(oracle, probe, G, H, F):
+    """One slot per tile height at depths of 1, 2, 4 and 5 steps of the main loop, where its first and last steps
+    (which load fewer tiles ahead) are all there is: every output element against the oracle."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=99)
+    print("case shallow depth H=%d F=%d" % (H, F), flush=True)
+    _ffn_against_oracle(oracle, probe, G, cfg, [320, 256, 192, 128, 64, 37, 0, 321], 4, seed=H * 7 + F)
+
+
 @pytest.mark.parametrize("cid", [1, 4])
 def test_ffn_with_rows_gathered_on_load_equals_ffn_on_the_permuted_copy(oracle, probe, G, cid):
     """probe_permute without the row copy + probe_grouped_ffn_gather give bit for bit the y of the standard
