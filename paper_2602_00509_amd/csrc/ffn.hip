@@ -24,6 +24,7 @@
 // on the accumulators.  Ragged row counts: a tile row past the slot's last row lies past the end
 // of the activation tile's buffer descriptor, so its loads return zeros, and its stores are
 // dropped the same way; the row space is never padded.
+#include <algorithm>
 #include <mutex>
 
 #include "common.hpp"
@@ -301,13 +302,17 @@ struct RowSource {
   int k, n_tokens;
 };
 
+__device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1.f + __expf(-gate)) * up; }
+
 // NI = 32-row weight fragments per wave: 2 = a column block of 128 h columns (128 gate + 128 up weight
 // rows per workgroup), 1 = 64 h columns (the skinny tiles of the decode schedule).  NST = LDS stages.
-template <int MI, bool GATHER, int NI = 2, int NST = (MI >= 3 ? 2 : 3), bool DRAW = false>
+template <int MI, bool GATHER, int NI = 2, int NST = (MI >= 3 ? 2 : 3), bool DRAW = false, bool SPLIT = false>
 __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* __restrict__ w13,
                                            int row0, int rows, int n0, int H, int F,
                                            bf16_t* __restrict__ hbuf, u32x4* smem, int32_t* draw_counter = nullptr,
-                                           volatile int* draw_slot = nullptr) {
+                                           volatile int* draw_slot = nullptr, int k0 = 0, int klen = 0,
+                                           float* partial = nullptr) {
+  // SPLIT: only k0 .. k0 + klen - 1 of the contraction; the fp32 sums go to partial[row of the tile][gate F | up F].
   // rows = valid rows from row0 to the end of the slot (may exceed the tile height)
   constexpr int HALF = 16 * NI;  // h columns per wave; its 32*NI weight rows are HALF gate rows, then the HALF up rows
   const int lane = threadIdx.x & 63;
@@ -343,7 +348,8 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
   f32x4 acc[2 * MI][2 * NI];
   zero_acc<MI, NI>(acc);
   const bool drew =
-      gemm_mainloop<MI, NI, 1, NST, true, DRAW>(rA, rB, voff, 0, H, smem, wv, lane, acc, draw_counter, draw_slot);
+      gemm_mainloop<MI, NI, 1, NST, true, DRAW>(rA, rB, voff, SPLIT ? k0 : 0, SPLIT ? klen : H, smem, wv, lane, acc,
+                                                draw_counter, draw_slot);
 
   // NI = 2: acc[i][0..1] are eight consecutive gate columns of one output row, acc[i][2..3] the up columns (see
   // gemm_mainloop, PERM): one 16-byte store.  NI = 1: four of each, 8 bytes.  The stores go through a buffer
@@ -353,6 +359,19 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
   __amdgpu_buffer_rsrc_t rH = make_rsrc(hbuf + static_cast<size_t>(row0) * F, static_cast<size_t>(valid) * F * 2);
   const int row_in = 32 * MI * wm + (lane & 15);
   const int cbase = n0 + HALF * wn + 4 * NI * (lane >> 4);
+  if constexpr (SPLIT) {
+    static_assert(NI == 1, "four columns per lane");
+    __amdgpu_buffer_rsrc_t rP = make_rsrc(partial, static_cast<size_t>(valid) * 2 * F * 4);
+    if (cbase < F) {
+#pragma unroll
+      for (int i = 0; i < 2 * MI; ++i) {
+        const int off = ((row_in + 16 * i) * 2 * F + cbase) * 4;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][0]), rP, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][1]), rP, off + F * 4, 0, 0);
+      }
+    }
+    return drew;
+  }
   if (cbase < F) {  // F % 8 == 0: a group of 4 * NI columns is in or out as a whole
 #pragma unroll
     for (int i = 0; i < 2 * MI; ++i) {
@@ -364,7 +383,7 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float gt = acc[i][j][e], up = acc[i][NI + j][e];
-          hv[e] = gt / (1.f + __expf(-gt)) * up;
+          hv[e] = swiglu(gt, up);
         }
         pk[2 * j] = pack_bf16x2(hv[0], hv[1]);
         pk[2 * j + 1] = pack_bf16x2(hv[2], hv[3]);
@@ -433,11 +452,13 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm1_kernel(RowSource src, const 
 }
 
 // ---- 2. gemm2 -------------------------------------------------------------------------
-template <int MI, int NI = 2, int NST = (MI >= 3 ? 2 : 3), bool DRAW = false>
+template <int MI, int NI = 2, int NST = (MI >= 3 ? 2 : 3), bool DRAW = false, bool SPLIT = false>
 __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, const bf16_t* __restrict__ w2,
                                            int row0, int rows, int n0, int H, int F,
                                            bf16_t* __restrict__ y, u32x4* smem, int32_t* draw_counter = nullptr,
-                                           volatile int* draw_slot = nullptr) {
+                                           volatile int* draw_slot = nullptr, int k0 = 0, int klen = 0,
+                                           float* partial = nullptr) {
+  // SPLIT: only k0 .. k0 + klen - 1 of the contraction; the fp32 sums go to partial[row of the tile][H].
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wv / 4, wn = wv % 4;
@@ -449,11 +470,28 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
   f32x4 acc[2 * MI][2 * NI];
   zero_acc<MI, NI>(acc);
   const bool drew =
-      gemm_mainloop<MI, NI, 1, NST, true, DRAW>(rA, rB, voff, 0, F, smem, wv, lane, acc, draw_counter, draw_slot);
+      gemm_mainloop<MI, NI, 1, NST, true, DRAW>(rA, rB, voff, SPLIT ? k0 : 0, SPLIT ? klen : F, smem, wv, lane, acc,
+                                                draw_counter, draw_slot);
 
   const int valid = min(rows, 64 * MI);  // rows past it are dropped by the descriptor's bounds check
   __amdgpu_buffer_rsrc_t rY = make_rsrc(y + static_cast<size_t>(row0) * H, static_cast<size_t>(valid) * H * 2);
   const int row_in = 32 * MI * wm + (lane & 15);
+  if constexpr (SPLIT) {
+    __amdgpu_buffer_rsrc_t rP = make_rsrc(partial, static_cast<size_t>(valid) * H * 4);
+#pragma unroll
+    for (int i = 0; i < 2 * MI; ++i) {
+#pragma unroll
+      for (int q = 0; q < NI; ++q) {
+        const int cbase = n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4);
+        const int off = ((row_in + 16 * i) * H + cbase) * 4;
+        if (cbase < H) {
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q]), rP, off, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q + 1]), rP, off + 16, 0, 0);
+        }
+      }
+    }
+    return drew;
+  }
 #pragma unroll
   for (int i = 0; i < 2 * MI; ++i) {
 #pragma unroll
@@ -534,18 +572,46 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm2_kernel(const bf16_t* __restr
 constexpr int kSkinnyLdsBytes = 3 * (64 + 128) * 128;  // 72 KB
 constexpr int kSkinnyCols1 = 64, kSkinnyCols2 = 128;   // h columns / y columns per work item
 
-// Tile number -> (slot, first row, rows to the end of the slot, weight pointer) without a tile table: slots
+// Few tiles.  A call with one or two active slots (a single token; a shared expert) has fewer items than the chip has
+// CUs, and an item streams its weights no faster than about 50 GB/s.  The contraction is then cut into pieces, as many
+// as give every CU one item: each leaves its fp32 sums in the workspace, and a second kernel adds the
+// pieces in ascending order.  The number of tiles is known on the device only; the host merely decides whether it can be
+// small (skinny_may_split) and then launches the adding kernel, which ends at once if nothing was split.
+// One token, two experts of 4096 x 14336: FFN 194 -> 137 us (gemm2 104 -> 41, adding 5); 512 items instead of 256: 141,
+// 1024: 161.  One slot of 75 rows, 7168 x 2048: 125 -> 45 us.
+constexpr int kSkinnyItems = 256;
+constexpr int kSkinnyMinSteps = 16;      // k-steps of a piece at least
+constexpr int kSkinnySplitSteps = 64;    // k-steps from which a contraction may be cut: a shorter one is read in the time
+                                         // that the launch of the adding kernel takes (about 5 us)
+constexpr int kSkinnyFewItems = 512;     // items at capacity up to which tiles can be few
+constexpr size_t kSkinnyPartialBytes = static_cast<size_t>(kSkinnyItems) * 64 * 128 * sizeof(float);
+
+// how many items the capacity of the row space allows: every 64 rows of it and every slot can give a tile
+static bool skinny_may_split(int max_tiles, int n_cols, int steps) {
+  return steps >= kSkinnySplitSteps && static_cast<long>(max_tiles) * n_cols <= kSkinnyFewItems;
+}
+// k-steps per piece, for n_tiles row tiles of n_cols column blocks; steps: the whole contraction
+__device__ __forceinline__ int skinny_steps(bool may_split, int n_tiles, int n_cols, int steps) {
+  int split = may_split ? kSkinnyItems / max(n_tiles * n_cols, 1) : 1;
+  split = max(min(split, steps / kSkinnyMinSteps), 1);
+  return (steps + split - 1) / split;
+}
+
+// Item number -> (slot, first row, rows to the end of the slot, weight pointer, piece of K) without a tile table: slots
 // in their own order, ceil(M / 64) tiles each.  Every workgroup finds its own tile with one scan over the
 // (at most 1024) slots, two per thread, so the decode schedule needs no schedule kernel in front of it.
-// Returns false if the tile number is past the last tile (the launch is sized for the capacity).
+// Returns false if the item number is past the last item (the launch is sized for the capacity).
 struct SkinnyTile {
   int row0, rows;
+  int tile, col, piece, pieces, piece_steps;
   const void* w;
 };
 
+// REDUCE: `item` is a tile number (column and piece are not looked at)
+template <bool REDUCE>
 __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_offsets,
-                                              const void* const* __restrict__ w_ptrs, int S, int tile,
-                                              SkinnyTile& out) {
+                                              const void* const* __restrict__ w_ptrs, int S, int item, int n_cols,
+                                              int steps, bool may_split, SkinnyTile& out) {
   __shared__ int32_t wave_tot[8];
   __shared__ int32_t found_row0, found_rows;
   __shared__ const void* found_w;
@@ -561,7 +627,7 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
     if (sl < S) {
       first[i] = slot_offsets[sl];
       m[i] = max(slot_offsets[sl + 1] - first[i], 0);
-      w[i] = w_ptrs[sl];
+      if (!REDUCE) w[i] = w_ptrs[sl];
     }
     t[i] = (m[i] + 63) >> 6;
   }
@@ -574,8 +640,19 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
   }
   if (lane == kWave - 1) wave_tot[wv] = incl;
   __syncthreads();
-  int excl = incl - local;
-  for (int i = 0; i < wv; ++i) excl += wave_tot[i];
+  int excl = incl - local, n_tiles = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    excl += i < wv ? wave_tot[i] : 0;
+    n_tiles += wave_tot[i];
+  }
+  n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
+  out.piece_steps = skinny_steps(may_split, n_tiles, n_cols, steps);
+  out.pieces = (steps + out.piece_steps - 1) / out.piece_steps;
+  out.col = item % n_cols;
+  out.piece = (item / n_cols) % out.pieces;
+  const int tile = REDUCE ? item : item / (n_cols * out.pieces);
+  out.tile = tile;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if (tile >= excl && tile < excl + t[i]) {  // true for exactly one (thread, i) when the tile exists
@@ -587,58 +664,123 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
     excl += t[i];
   }
   __syncthreads();
-  out.row0 = found_row0;
-  out.rows = found_rows;
-  out.w = found_w;
-  return found_rows > 0;
+  out.row0 = __builtin_amdgcn_readfirstlane(found_row0);
+  out.rows = __builtin_amdgcn_readfirstlane(found_rows);
+  if (!REDUCE) out.w = found_w;
+  return out.rows > 0;
+}
+
+// where piece p of a tile leaves its sums: [tile][piece][64][ld] floats
+__device__ __forceinline__ float* skinny_partial(float* partial, const SkinnyTile& e, int piece, int ld) {
+  return partial + static_cast<size_t>(e.tile * e.pieces + piece) * 64 * ld;
 }
 
 template <bool GATHER>
 __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w13_ptrs, int S,
-                                                                  int H, int F, bf16_t* __restrict__ hbuf) {
+                                                                  int H, int F, int may_split,
+                                                                  bf16_t* __restrict__ hbuf, float* partial) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
-  const int n_cols = (F + kSkinnyCols1 - 1) / kSkinnyCols1;
-  const int tile = blockIdx.x / n_cols, col = blockIdx.x % n_cols;
   SkinnyTile e;
-  if (!skinny_locate(slot_offsets, w13_ptrs, S, tile, e)) return;
-  gemm1_tile<1, GATHER, 1, 3>(src, static_cast<const bf16_t*>(e.w), e.row0, e.rows, col * kSkinnyCols1, H, F, hbuf,
-                              smem);
+  if (!skinny_locate<false>(slot_offsets, w13_ptrs, S, blockIdx.x, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
+                            may_split, e))
+    return;
+  const bf16_t* w = static_cast<const bf16_t*>(e.w);
+  if (e.pieces == 1) {
+    gemm1_tile<1, GATHER, 1, 3>(src, w, e.row0, e.rows, e.col * kSkinnyCols1, H, F, hbuf, smem);
+  } else {
+    const int k0 = e.piece * e.piece_steps * FBK;
+    gemm1_tile<1, GATHER, 1, 3, false, true>(src, w, e.row0, e.rows, e.col * kSkinnyCols1, H, F, hbuf, smem, nullptr,
+                                             nullptr, k0, min(H - k0, e.piece_steps * FBK),
+                                             skinny_partial(partial, e, e.piece, 2 * F));
+  }
 #endif
 }
 
 __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* __restrict__ hbuf,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w2_ptrs, int S,
-                                                                  int H, int F, bf16_t* __restrict__ y) {
+                                                                  int H, int F, int may_split,
+                                                                  bf16_t* __restrict__ y, float* partial) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
-  const int n_cols = (H + kSkinnyCols2 - 1) / kSkinnyCols2;
-  const int tile = blockIdx.x / n_cols, col = blockIdx.x % n_cols;
   SkinnyTile e;
-  if (!skinny_locate(slot_offsets, w2_ptrs, S, tile, e)) return;
-  gemm2_tile<1, 1, 3>(hbuf, static_cast<const bf16_t*>(e.w), e.row0, e.rows, col * kSkinnyCols2, H, F, y, smem);
+  if (!skinny_locate<false>(slot_offsets, w2_ptrs, S, blockIdx.x, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK,
+                            may_split, e))
+    return;
+  const bf16_t* w = static_cast<const bf16_t*>(e.w);
+  if (e.pieces == 1) {
+    gemm2_tile<1, 1, 3>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem);
+  } else {
+    const int k0 = e.piece * e.piece_steps * FBK;
+    gemm2_tile<1, 1, 3, false, true>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem, nullptr, nullptr, k0,
+                                     min(F - k0, e.piece_steps * FBK), skinny_partial(partial, e, e.piece, H));
+  }
 #endif
+}
+
+// The adding kernel: workgroup b adds the pieces of row b % 64 of tile b / 64, four columns per thread at a time.
+// SWIGLU: partial rows are [gate F | up F] and the result is h; otherwise [H] and the result is y.
+template <bool SWIGLU>
+__global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __restrict__ partial,
+                                                             const int32_t* __restrict__ slot_offsets, int S,
+                                                             int n_cols, int steps, int out_cols,
+                                                             bf16_t* __restrict__ out) {
+  SkinnyTile e;
+  const int row = blockIdx.x & 63;
+  if (!skinny_locate<true>(slot_offsets, nullptr, S, blockIdx.x >> 6, n_cols, steps, true, e)) return;
+  if (e.pieces == 1 || row >= e.rows) return;
+  const int ld = SWIGLU ? 2 * out_cols : out_cols;
+  const float* base = partial + static_cast<size_t>(e.tile * e.pieces) * 64 * ld + static_cast<size_t>(row) * ld;
+  const size_t piece = static_cast<size_t>(64) * ld;
+  for (int c = threadIdx.x * 4; c < out_cols; c += 512 * 4) {
+    f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+    constexpr int BATCH = 8;  // pieces whose loads are in flight together
+    for (int p0 = 0; p0 < e.pieces; p0 += BATCH) {
+      f32x4 va[BATCH], vb[BATCH];
+#pragma unroll
+      for (int q = 0; q < BATCH; ++q) {
+        const float* src = base + min(p0 + q, e.pieces - 1) * piece + c;
+        va[q] = *reinterpret_cast<const f32x4*>(src);
+        if constexpr (SWIGLU) vb[q] = *reinterpret_cast<const f32x4*>(src + out_cols);
+      }
+#pragma unroll
+      for (int q = 0; q < BATCH; ++q)
+        if (p0 + q < e.pieces) {
+          a += va[q];
+          if constexpr (SWIGLU) b += vb[q];
+        }
+    }
+    if constexpr (SWIGLU) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = swiglu(a[j], b[j]);
+    }
+    *reinterpret_cast<u32x2*>(out + static_cast<size_t>(e.row0 + row) * out_cols + c) =
+        u32x2{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3])};
+  }
 }
 
 struct FfnShape {
   bool skinny;  // the decode schedule
   int max_tiles;
-  size_t h_bytes, table_bytes;
+  size_t h_bytes, table_bytes, partial_bytes;
 };
 
 // The decode schedule is chosen on the host from the capacity of the row space alone (the row counts live
-// on the device): at most kSkinnyRowsPerSlot rows per slot on average even if every pair were local.
+// on the device): at most kSkinnyRowsPerSlot rows per slot on average even if every pair were local, or so few tiles
+// that even 64-row ones leave the chip half empty (a shared expert's single slot).
 constexpr int kSkinnyRowsPerSlot = 64;
 
 static FfnShape ffn_shape(int S, int F, int max_rows) {
   FfnShape s;
-  s.skinny = static_cast<long>(max_rows) <= static_cast<long>(kSkinnyRowsPerSlot) * S;
+  s.skinny = static_cast<long>(max_rows) <= static_cast<long>(kSkinnyRowsPerSlot) * S ||
+             (static_cast<long>(max_rows) / 64 + S) * ((F + kSkinnyCols1 - 1) / kSkinnyCols1) <= kSkinnyFewItems;
   s.max_tiles = s.skinny ? max_rows / 64 + S : max_rows / 256 + S;
   s.h_bytes = align_up(static_cast<size_t>(max_rows > 0 ? max_rows : 1) * F * sizeof(bf16_t), 256);
   s.table_bytes = align_up(kTableHeaderInts * sizeof(int32_t) + static_cast<size_t>(s.max_tiles) * sizeof(TileEntry), 256);
+  s.partial_bytes = s.skinny ? kSkinnyPartialBytes : 0;
   return s;
 }
 
@@ -695,7 +837,7 @@ extern "C" size_t probe_grouped_ffn_workspace_bytes(int S, int H, int F, int max
   (void)H;
   if (S <= 0 || F <= 0 || max_rows < 0) return 0;
   probe::FfnShape s = probe::ffn_shape(S, F, max_rows);
-  return s.h_bytes + s.table_bytes;
+  return s.h_bytes + s.table_bytes + s.partial_bytes;
 }
 
 namespace probe {
@@ -725,9 +867,9 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
   PROBE_REQUIRE(aligned16(act_bf16) && aligned16(y_bf16), PROBE_EALIGN,
                 "%s: activations and y must be 16-byte aligned", name);
   FfnShape sh = ffn_shape(S, F, max_rows);
-  PROBE_REQUIRE(workspace && aligned16(workspace) && workspace_bytes >= sh.h_bytes + sh.table_bytes,
+  PROBE_REQUIRE(workspace && aligned16(workspace) && workspace_bytes >= sh.h_bytes + sh.table_bytes + sh.partial_bytes,
                 PROBE_EWORKSPACE, "%s: workspace too small or misaligned (%zu < %zu)", name, workspace_bytes,
-                sh.h_bytes + sh.table_bytes);
+                sh.h_bytes + sh.table_bytes + sh.partial_bytes);
   PROBE_REQUIRE(static_cast<long>(sh.max_tiles + 8) * ((F + 127) / 128 + 4) < (1l << 30) &&
                     static_cast<long>(sh.max_tiles + 8) * ((H + 255) / 256 + 4) < (1l << 30),
                 PROBE_EUNSUPPORTED, "%s: max_rows too large (%d)", name, max_rows);
@@ -743,16 +885,30 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
   src.k = gather ? k : 1;
   src.n_tokens = gather ? T : 0;
   if (sh.skinny) {
-    const dim3 g1(sh.max_tiles * ((F + kSkinnyCols1 - 1) / kSkinnyCols1));
-    const dim3 g2(sh.max_tiles * ((H + kSkinnyCols2 - 1) / kSkinnyCols2));
+    float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + sh.h_bytes + sh.table_bytes);
+    bf16_t* y = static_cast<bf16_t*>(y_bf16);
+    const int tiles = std::min(sh.max_tiles, max_rows);  // a tile has at least one row
+    const int n1 = (F + kSkinnyCols1 - 1) / kSkinnyCols1, n2 = (H + kSkinnyCols2 - 1) / kSkinnyCols2;
+    const int split1 = skinny_may_split(tiles, n1, H / FBK), split2 = skinny_may_split(tiles, n2, F / FBK);
+    // a split call has at most kSkinnyItems items, one that is not split tiles * n
+    const dim3 g1(split1 ? std::max(tiles * n1, kSkinnyItems) : tiles * n1);
+    const dim3 g2(split2 ? std::max(tiles * n2, kSkinnyItems) : tiles * n2);
+    // tiles that can be split at all: two pieces or more need kSkinnyItems / 2 items or fewer
+    const int add1 = split1 ? std::min(tiles, kSkinnyItems / 2 / n1) : 0, add2 = split2 ? std::min(tiles, kSkinnyItems / 2 / n2) : 0;
     if (gather)
       hipLaunchKernelGGL(ffn_gemm1_skinny_kernel<true>, g1, dim3(512), kSkinnyLdsBytes, st, src, slot_offsets,
-                         w13_ptrs, S, H, F, hbuf);
+                         w13_ptrs, S, H, F, split1, hbuf, partial);
     else
       hipLaunchKernelGGL(ffn_gemm1_skinny_kernel<false>, g1, dim3(512), kSkinnyLdsBytes, st, src, slot_offsets,
-                         w13_ptrs, S, H, F, hbuf);
+                         w13_ptrs, S, H, F, split1, hbuf, partial);
+    if (add1 > 0)
+      hipLaunchKernelGGL(ffn_skinny_add_kernel<true>, dim3(add1 * 64), dim3(512), 0, st, partial, slot_offsets, S, n1,
+                         H / FBK, F, hbuf);
     hipLaunchKernelGGL(ffn_gemm2_skinny_kernel, g2, dim3(512), kSkinnyLdsBytes, st, hbuf, slot_offsets, w2_ptrs, S, H,
-                       F, static_cast<bf16_t*>(y_bf16));
+                       F, split2, y, partial);
+    if (add2 > 0)
+      hipLaunchKernelGGL(ffn_skinny_add_kernel<false>, dim3(add2 * 64), dim3(512), 0, st, partial, slot_offsets, S, n2,
+                         F / FBK, H, y);
     return check_launch(name);
   }
   hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(256), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S, sh.max_tiles,

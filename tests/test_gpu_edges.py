@@ -294,6 +294,16 @@ def test_ffn_decode_schedule_every_element(oracle, probe, G):
         _ffn_against_oracle(oracle, probe, G, cfg, sizes, 4, seed=H + F)
 
 
+@pytest.mark.parametrize("sizes,H,F", [([1], 4096, 4160), ([75], 6016, 192), ([1, 0, 0, 2], 320, 5120), ([64, 65], 4480, 256),
+                                       ([300], 4096, 576), ([0, 17, 0], 8192, 64)])
+def test_ffn_few_tiles_every_element(oracle, probe, G, sizes, H, F):
+    """So few tiles that the contraction is cut into pieces whose sums a second kernel adds: one, some or all
+    of the two GEMMs, pieces of unequal length, a last column block that is not full."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=100)
+    print("case few tiles", sizes, H, F, flush=True)
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, len(sizes), seed=H + F, extra_rows=0 if sizes == [1] else 9)
+
+
 def test_ffn_every_tile_height_at_full_depth(oracle, probe, G):
     """One slot per tile height (320, 256, 192, 128, 64 rows) and a ragged one, at the depth of the benchmark's
     main configuration (K = 7168 in the first GEMM, 2048 in the second: 112 and 32 steps of the main loop):
