@@ -9,7 +9,8 @@
 //
 //   1. split    w_gate -> planes[3][E][H] bf16 in the workspace (skipped by the *_packed entry points,
 //               which are handed planes made once by probe_pack_gate)
-//   2. gemm     split-K tiled GEMM (128 tokens x 128 experts x 64 k per step), three MFMAs per
+//   2. gemm     split-K tiled GEMM (128 tokens x 128 experts x 64 k per step; small batches and gates of at most 16
+//               experts go straight from global memory to the matrix cores), three MFMAs per
 //               operand pair (one per plane) into one accumulator  -> partial[KS][T][E] fp32;
 //               its first workgroup clears the expert counts
 //               H % 64 == 0: DMA-to-LDS software pipeline shared with the grouped FFN;
@@ -27,6 +28,7 @@
 //   d. that GEMM; its split-K slices are written behind the gate's own, and step 3 sums them all
 #include <limits.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "common.hpp"
@@ -69,7 +71,7 @@ template <int PL>
 __global__ __launch_bounds__(256, 2) void gate_gemm_kernel(const bf16_t* __restrict__ x,
                                                            const bf16_t* __restrict__ planes,
                                                            int T, int H, int E, int k_chunk,
-                                                           float* __restrict__ partial,
+                                                           float* __restrict__ partial, int ld,
                                                            int32_t* __restrict__ zero0, int32_t* __restrict__ zero1,
                                                            int n_zero) {
   __shared__ u32x4 sA[GBM * 8];
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(256, 2) void gate_gemm_kernel(const bf16_t* __restr
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         int row = m0 + 64 * wm + 32 * mi + mfma32_row(r, lane);
-        if (row < T && col < E) partial[(static_cast<long>(ks) * T + row) * E + col] = acc[mi][ni][r];
+        if (row < T && col < ld) partial[(static_cast<long>(ks) * T + row) * ld + col] = acc[mi][ni][r];
       }
     }
 }
@@ -176,7 +178,7 @@ template <int MI, int PL>
 __global__ __launch_bounds__(512, 2) void gate_gemm_dma_kernel(const bf16_t* __restrict__ x,
                                                                const bf16_t* __restrict__ planes,
                                                                int T, int H, int E, int k_chunk,
-                                                               float* __restrict__ partial,
+                                                               float* __restrict__ partial, int ld,
                                                                int32_t* __restrict__ zero0,
                                                                int32_t* __restrict__ zero1, int n_zero) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -200,27 +202,132 @@ __global__ __launch_bounds__(512, 2) void gate_gemm_dma_kernel(const bf16_t* __r
   for (int i = 0; i < 2 * MI; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   gemm_mainloop<MI, 1, PL, 2>(rA, rB, voff, kbeg, klen, smem, wv, lane, acc);
 
-  const bool vec = (E & 3) == 0;
 #pragma unroll
   for (int i = 0; i < 2 * MI; ++i) {
     const int row = 32 * MI * wm + 16 * i + (lane & 15);
     if (row < rows) {
-      float* dst = partial + (static_cast<long>(ks) * T + m0 + row) * E;
+      float* dst = partial + (static_cast<long>(ks) * T + m0 + row) * ld;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int col = n0 + 32 * wn + 16 * j + 4 * (lane >> 4);
-        if (vec) {
-          if (col < E)
-            *reinterpret_cast<float4*>(dst + col) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (col + e < E) dst[col + e] = acc[i][j][e];
-        }
+        if (col < ld) *reinterpret_cast<f32x4*>(dst + col) = acc[i][j];
       }
     }
   }
 #endif
+}
+
+// ---- 2c. gemm straight from global memory to the matrix cores --------------------------------------
+// Small batches, and gates of at most 16 experts at any batch.  There the product is a stream of the gate (3 planes
+// of E x H, 3..11 MB) or of x, and what the tiled kernels above lose is latency: at 128 tokens they are 16..32
+// workgroups that each pull 64 KB per k-step, four to seven steps one after another.  Here a wave multiplies one
+// fragment of 16 experts (three planes) by NT fragments of 16 tokens over a few k32 of its own, with every operand
+// loaded from global memory in the layout of v_mfma_f32_16x16x32_bf16 (16 rows x 64 bytes per instruction) and all
+// loads of KU k32 in flight together; the eight waves of a workgroup split its K range and add their sums in LDS in
+// fixed order.  No barrier before that, 64..256 workgroups.  128 tokens: 10.4 -> 6 us at 128 x 4096, 14.4 -> 9 us at
+// 256 x 7168; one token: 3.5 and 4.3 us.
+// A lane's eight k lie inside or outside of H as a whole (H % 8 == 0), so any such H is served.
+// SPLIT_W: `w` is the fp32 gate (the second of two stacked gates in w_next) and the planes are made in registers; every weight
+// is read by ceil(T / (16 NT)) waves, so below two token blocks that is less work than a launch that writes the planes
+// first.  The planes are bit for bit those of gate_split_kernel.
+struct GateRows {
+  const bf16_t* planes;  // [PL][N][H]
+  const float* w;        // SPLIT_W: fp32 [n_first][H] and, stacked below it, w_next [N - n_first][H]
+  const float* w_next;
+  int n_first;
+};
+
+template <int PL, bool SPLIT_W>
+__device__ __forceinline__ void gate_fragment(const GateRows& g, int row, int N, int H, int k, bool in,
+                                              u32x4 (&a)[PL]) {
+#pragma unroll
+  for (int p = 0; p < PL; ++p) a[p] = u32x4{0u, 0u, 0u, 0u};
+  if (!in) return;
+  if constexpr (!SPLIT_W) {
+#pragma unroll
+    for (int p = 0; p < PL; ++p)
+      a[p] = *reinterpret_cast<const u32x4*>(g.planes + (static_cast<long>(p) * N + row) * H + k);
+  } else {
+    static_assert(!SPLIT_W || PL == 3, "the fp32 gate is three planes");
+    const float* src = row < g.n_first ? g.w + static_cast<long>(row) * H : g.w_next + static_cast<long>(row - g.n_first) * H;
+    const float4 lo4 = *reinterpret_cast<const float4*>(src + k), hi4 = *reinterpret_cast<const float4*>(src + k + 4);
+    const float v[8] = {lo4.x, lo4.y, lo4.z, lo4.w, hi4.x, hi4.y, hi4.z, hi4.w};
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+      float p1[2], p2[2], p3[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        p1[i] = bf16_to_f32(f32_to_bf16(v[j + i]));
+        const float r1 = v[j + i] - p1[i];  // exact
+        p2[i] = bf16_to_f32(f32_to_bf16(r1));
+        p3[i] = r1 - p2[i];                 // exact
+      }
+      a[0][j / 2] = pack_bf16x2(p1[0], p1[1]);
+      a[PL > 1 ? 1 : 0][j / 2] = pack_bf16x2(p2[0], p2[1]);
+      a[PL > 2 ? 2 : 0][j / 2] = pack_bf16x2(p3[0], p3[1]);
+    }
+  }
+}
+
+// One wave's part: acc[i] += experts row0 .. +15 times tokens t0 + 16 i .. +15 over k32 numbers s0 .. s1 - 1.
+template <int NT, int KU, int PL, bool SPLIT_W>
+__device__ __forceinline__ void gate_direct_wave(const bf16_t* __restrict__ x, const GateRows& g, int T, int H, int N,
+                                                 int n0, int t0, int s0, int s1, int lane, f32x4 (&acc)[NT]) {
+  const int row = min(n0 + (lane & 15), N - 1);
+  const bf16_t* xt[NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i) xt[i] = x + static_cast<long>(min(t0 + 16 * i + (lane & 15), T - 1)) * H;
+  for (int s = s0; s < s1; s += KU) {
+    u32x4 a[KU][PL], b[KU][NT];
+#pragma unroll
+    for (int u = 0; u < KU; ++u) {
+      const int k = (s + u) * 32 + 8 * (lane >> 4);
+      const bool in = s + u < s1 && k < H;
+      gate_fragment<PL, SPLIT_W>(g, row, N, H, k, in, a[u]);
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        b[u][i] = u32x4{0u, 0u, 0u, 0u};
+        if (in) b[u][i] = *reinterpret_cast<const u32x4*>(xt[i] + k);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < KU; ++u)
+#pragma unroll
+      for (int p = 0; p < PL; ++p)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) acc[i] = mfma_16x16x32(a[u][p], b[u][i], acc[i]);
+  }
+}
+
+// position of the four experts 4c .. 4c+3 of a token in a [token][16] LDS tile, in floats: the sixteen tokens that a
+// fragment stores at once cover all 64 banks
+__device__ __forceinline__ int direct_pos(int token, int c) { return token * 16 + 4 * (c ^ ((token >> 2) & 3)); }
+
+template <int NT, int KU, int PL, bool SPLIT_W>
+__global__ __launch_bounds__(512) void gate_direct_kernel(const bf16_t* __restrict__ x, GateRows g, int T, int H, int N,
+                                                          int k32_per_wave, float* __restrict__ partial, int ld,
+                                                          int32_t* __restrict__ zero0, int32_t* __restrict__ zero1,
+                                                          int n_zero) {
+  __shared__ float sums[8][16 * NT * 16];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int n0 = blockIdx.x * 16, ks = blockIdx.y, t0 = blockIdx.z * 16 * NT;
+  zero_counts(zero0, zero1, n_zero);
+  const int steps = (H + 31) / 32, s0 = (ks * 8 + wv) * k32_per_wave;
+  f32x4 acc[NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  gate_direct_wave<NT, KU, PL, SPLIT_W>(x, g, T, H, N, n0, t0, s0, min(s0 + k32_per_wave, steps), lane, acc);
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+    *reinterpret_cast<f32x4*>(&sums[wv][direct_pos(16 * i + (lane & 15), lane >> 4)]) = acc[i];
+  __syncthreads();
+  for (int q = tid; q < 16 * NT * 4; q += 512) {
+    const int token = q >> 2, c = q & 3, t = t0 + token, col = n0 + 4 * c;
+    f32x4 v = *reinterpret_cast<const f32x4*>(&sums[0][direct_pos(token, c)]);
+#pragma unroll
+    for (int w = 1; w < 8; ++w) v += *reinterpret_cast<const f32x4*>(&sums[w][direct_pos(token, c)]);
+    if (t < T && col < ld) *reinterpret_cast<f32x4*>(partial + (static_cast<long>(ks) * T + t) * ld + col) = v;
+  }
 }
 
 static int gate_prepare() {
@@ -318,6 +425,8 @@ __device__ __forceinline__ int tree_min(const int (&v)[N]) {
   return t[0];
 }
 
+__device__ __forceinline__ bool aligned_f4(const float* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
 // Logit row pieces of U tokens: the KS split-K slices are added in ascending order, then the bias row
 // of the token's group.  Lane `sub` receives the experts 64*i + 4*sub + j; entries past E are zero.
 template <int NV, int U, int R = 2>
@@ -326,11 +435,27 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
                                                 bool vec, int sub, const int (&tt)[U], float (&l)[U][NV * 4]) {
   constexpr int NL = NV * 4;
   if (vec) {
-    float4 accv[U][NV];
+    float4 accv[U][NV], bv[U][NV];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) {
+      const int g = bias ? min(tt[u] / tpg, G - 1) : 0;
 #pragma unroll
-      for (int i = 0; i < NV; ++i) accv[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int i = 0; i < NV; ++i) {
+        const int e0 = 64 * i + 4 * sub;
+        accv[u][i] = bv[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (bias && e0 < E) {
+          const float* src = bias + static_cast<long>(g) * E + e0;
+          if ((E & 3) == 0) {
+            bv[u][i] = *reinterpret_cast<const float4*>(src);
+          } else {
+            bv[u][i].x = src[0];
+            bv[u][i].y = e0 + 1 < E ? src[1] : 0.f;
+            bv[u][i].z = e0 + 2 < E ? src[2] : 0.f;
+            bv[u][i].w = e0 + 3 < E ? src[3] : 0.f;
+          }
+        }
+      }
+    }
     for (int q0 = 0; q0 < KS; q0 += R) {
       // all loads of a round of R split-K slices (of every token of the row) are issued before any is consumed
       float4 tmp[R][U][NV];
@@ -341,7 +466,7 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
         for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int i = 0; i < NV; ++i) {
-            const int e0 = min(64 * i + 4 * sub, E - 4);
+            const int e0 = min(64 * i + 4 * sub, ((E + 3) & ~3) - 4);
             tmp[r][u][i] = *reinterpret_cast<const float4*>(partial + (static_cast<long>(q) * T + tt[u]) * ld + e0);
           }
       }
@@ -359,17 +484,12 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      int g = 0;
-      if (bias) g = min(tt[u] / tpg, G - 1);
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
-        const int e0 = 64 * i + 4 * sub;
-        float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (bias && e0 < E) bv = *reinterpret_cast<const float4*>(bias + static_cast<long>(g) * E + e0);
-        l[u][4 * i] = accv[u][i].x + bv.x;
-        l[u][4 * i + 1] = accv[u][i].y + bv.y;
-        l[u][4 * i + 2] = accv[u][i].z + bv.z;
-        l[u][4 * i + 3] = accv[u][i].w + bv.w;
+        l[u][4 * i] = accv[u][i].x + bv[u][i].x;
+        l[u][4 * i + 1] = accv[u][i].y + bv[u][i].y;
+        l[u][4 * i + 2] = accv[u][i].z + bv[u][i].z;
+        l[u][4 * i + 3] = accv[u][i].w + bv[u][i].w;
       }
     }
   } else {
@@ -408,7 +528,8 @@ __global__ __launch_bounds__(256) void gate_softmax_topk_kernel(
   hist[tid] = 0;
   __syncthreads();
   const float ninf = -__builtin_inff(), fmin_ = -3.402823466e38f;
-  const bool vec = (E & 3) == 0 && (ld & 3) == 0;
+  const bool vec = (E & 3) == 0;
+  const bool vec_in = (ld & 3) == 0 && aligned_f4(partial);
   const int tokens_per_pass = gridDim.x * 16 * U;
   for (int t0 = ((blockIdx.x * 4 + wv) * U) * 4 + grp; t0 < T; t0 += tokens_per_pass) {
     // token u of this row is t0 + 4u; the rows of a wave are independent under DPP row operations
@@ -420,7 +541,7 @@ __global__ __launch_bounds__(256) void gate_softmax_topk_kernel(
       live[u] = t0 + 4 * u < T;
       tt[u] = live[u] ? t0 + 4 * u : t0;
     }
-    load_logit_rows<NV, U, R>(partial, ld, KS, bias, G, tpg, T, E, vec, sub, tt, l);
+    load_logit_rows<NV, U, R>(partial, ld, KS, bias, G, tpg, T, E, vec_in, sub, tt, l);
     float mx[U], inv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -525,20 +646,21 @@ __device__ __forceinline__ void top2_merge(float& m1, float& m2) {
 // experts, gating values from s.  Every decision is an arg-max over a DPP row with ties to the
 // lower index, so all sixteen lanes of a token agree bit for bit.  Lane j keeps the score of group
 // j (n_group <= 16); sets of groups and of consumed entries are bit masks.
-template <int NV>
+template <int NV, int U, int R>
 __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
     const float* __restrict__ partial, int ld, int KS, const float* __restrict__ bias, int G, int tpg,
     const float* __restrict__ select_bias, int T, int E, int k, int scoring, int n_group, int topk_group,
     int group_top, int renorm, float routed_scale, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
     float* __restrict__ scores, int32_t* __restrict__ counts) {
-  constexpr int U = 2, NL = NV * 4;
+  constexpr int NL = NV * 4;
   __shared__ int32_t hist[PROBE_MAX_EXPERTS];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int sub = lane & 15, grp = lane >> 4;
   hist[tid] = 0;
   __syncthreads();
   const float ninf = -__builtin_inff(), fmin_ = -3.402823466e38f;
-  const bool vec = (E & 3) == 0 && (ld & 3) == 0;
+  const bool vec = (E & 3) == 0;
+  const bool vec_in = (ld & 3) == 0 && aligned_f4(partial);
   const int gs = E / n_group;
   int gid[NL];      // group of entry i, -1 past E
   float sb[NL];
@@ -558,7 +680,7 @@ __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
       live[u] = t0 + 4 * u < T;
       tt[u] = live[u] ? t0 + 4 * u : t0;
     }
-    load_logit_rows<NV, U>(partial, ld, KS, bias, G, tpg, T, E, vec, sub, tt, sc);
+    load_logit_rows<NV, U, R>(partial, ld, KS, bias, G, tpg, T, E, vec_in, sub, tt, sc);
     // scores (in place of the logits) and selection scores
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -811,8 +933,17 @@ struct RouteShape {
   bool dma;  // H % 64 == 0: the DMA-to-LDS pipeline; otherwise the register-staged kernel
   int bm;    // tokens per workgroup of the gemm (128 or 256)
   int mt, nt, ks, k_chunk;
+  int ld;           // entries of a row of partial sums: E rounded up to whole 16-byte pieces (the last ones are not read)
+  bool direct;      // gate_direct_kernel: `frags` fragments of 16 tokens per workgroup, `per_wave` k32 per wave
+  int frags, per_wave;
   size_t planes_bytes, partial_bytes;
 };
+
+// Logits (T x E) up to which a gate takes the direct kernel, and gates that take it at any batch (16 experts are one
+// fragment: a 128-expert tile would be mostly padding).  Whole call, direct against tiled: 256 tokens x 128 experts 12.4 / 15.7 us,
+// 512 x 128 15.6 / 15.8 and 256 x 256 21.5 / 21.8 (H = 4096, 7168).  Where H is not a multiple of 64 the other kernel is the
+// register-staged one and the line lies higher: 1000 tokens x 250 experts x 7160 47.6 us, 1500 tokens staged 50.6.
+constexpr int kDirectLogits = 32768, kDirectExperts = 16;
 
 constexpr int kMaxSplitK = 16;
 
@@ -822,6 +953,7 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
   // workgroup per CU (fewer, longer K ranges and half the partial sums), 128-token tiles at two
   s.dma = H % 64 == 0 && static_cast<size_t>(3) * E * H * 2 <= 0x7fffffffull;
   s.nt = (E + GBN - 1) / GBN;
+  s.ld = (E + 3) & ~3;
   s.bm = (s.dma && static_cast<long>((T + 255) / 256) * s.nt * 8 >= 256) ? 256 : GBM;
   s.mt = (T + s.bm - 1) / s.bm;
   int tiles = s.mt * s.nt;
@@ -834,9 +966,39 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
   int steps_per = (ksteps + want - 1) / want;
   s.k_chunk = steps_per * GBK;
   s.ks = (ksteps + steps_per - 1) / steps_per;
+  s.direct = static_cast<long>(T) * E <= (H % 64 == 0 ? 1 : 8) * kDirectLogits || E <= kDirectExperts;
+  s.frags = s.per_wave = 0;
+  if (s.direct) {
+    // eight fragments of tokens share a gate fragment where there are that many; a 16-expert gate is a stream of x and
+    // wants workgroups
+    s.frags = E <= kDirectExperts ? (T > 8192 ? 2 : 1) : (T <= 16 ? 1 : (T <= 32 ? 2 : (T <= 64 ? 4 : 8)));
+    const int k32 = (H + 31) / 32, wgs = ((E + 15) / 16) * ((T + 16 * s.frags - 1) / (16 * s.frags));
+    int split = wgs > 0 ? 256 / wgs : 1;  // one workgroup per CU
+    split = split < 1 ? 1 : (split > max_split ? max_split : split);
+    s.per_wave = (k32 + 8 * split - 1) / (8 * split);
+    s.ks = (k32 + 8 * s.per_wave - 1) / (8 * s.per_wave);
+  }
   s.planes_bytes = align_up(static_cast<size_t>(3) * E * H * sizeof(bf16_t), 256);
-  s.partial_bytes = align_up(static_cast<size_t>(s.ks) * (T > 0 ? T : 1) * E * sizeof(float), 256);
+  s.partial_bytes = align_up(static_cast<size_t>(s.ks) * (T > 0 ? T : 1) * s.ld * sizeof(float), 256);
   return s;
+}
+
+template <int PL, bool SPLIT_W>
+static void launch_gate_direct(const RouteShape& sh, hipStream_t st, const bf16_t* x, const GateRows& g, int T, int H,
+                               int N, float* partial, int32_t* zero0, int32_t* zero1, int n_zero) {
+  const dim3 grid((N + 15) / 16, sh.ks, (T + 16 * sh.frags - 1) / (16 * sh.frags));
+#define PROBE_DIRECT_CASE(NT, KU)                                                                                  \
+  case NT:                                                                                                          \
+    hipLaunchKernelGGL((gate_direct_kernel<NT, KU, PL, SPLIT_W>), grid, dim3(512), 0, st, x, g, T, H, N, sh.per_wave, \
+                       partial, sh.ld, zero0, zero1, n_zero);                                                              \
+    break;
+  switch (sh.frags) {
+    PROBE_DIRECT_CASE(1, 4)
+    PROBE_DIRECT_CASE(2, 4)
+    PROBE_DIRECT_CASE(4, 2)
+    PROBE_DIRECT_CASE(8, 2)
+  }
+#undef PROBE_DIRECT_CASE
 }
 
 // x [T,H] times a stack of PL bf16 planes [PL][N][H] -> partial [ks][T][N] fp32
@@ -844,18 +1006,26 @@ template <int PL>
 static void launch_gate_gemm(const RouteShape& sh, hipStream_t st, const bf16_t* x, const bf16_t* planes, int T,
                              int H, int N, float* partial, int32_t* zero0 = nullptr, int32_t* zero1 = nullptr,
                              int n_zero = 0) {
-  if (sh.dma) {
+  if (sh.direct) {
+    launch_gate_direct<PL, false>(sh, st, x, GateRows{planes, nullptr, nullptr, 0}, T, H, N, partial, zero0, zero1, n_zero);
+  } else if (sh.dma) {
     const int lds = 2 * (sh.bm + 128 * PL) * 128;
     if (sh.bm == 256)
       hipLaunchKernelGGL((gate_gemm_dma_kernel<4, PL>), dim3(sh.mt, sh.nt, sh.ks), dim3(512), lds, st, x, planes, T,
-                         H, N, sh.k_chunk, partial, zero0, zero1, n_zero);
+                         H, N, sh.k_chunk, partial, sh.ld, zero0, zero1, n_zero);
     else
       hipLaunchKernelGGL((gate_gemm_dma_kernel<2, PL>), dim3(sh.mt, sh.nt, sh.ks), dim3(512), lds, st, x, planes, T,
-                         H, N, sh.k_chunk, partial, zero0, zero1, n_zero);
+                         H, N, sh.k_chunk, partial, sh.ld, zero0, zero1, n_zero);
   } else {
     hipLaunchKernelGGL(gate_gemm_kernel<PL>, dim3(sh.mt, sh.nt, sh.ks), dim3(256), 0, st, x, planes, T, H, N,
-                       sh.k_chunk, partial, zero0, zero1, n_zero);
+                       sh.k_chunk, partial, sh.ld, zero0, zero1, n_zero);
   }
+}
+
+// Whether the fp32 gate is split in the direct kernel's registers instead of by a launch of its own (2..7 us): at most
+// two token blocks, i.e. every weight is converted at most twice, or a gate of one fragment and few blocks.
+static bool split_in_registers(const RouteShape& sh, int T, int N) {
+  return sh.direct && (T <= 2 * 16 * sh.frags || (N <= kDirectExperts && T <= 512));
 }
 
 // Workspace of a call: gate planes | logit partials (+ one plane for the residual) | u partials
@@ -868,7 +1038,7 @@ static RouteLayout route_layout(int T, int H, int E, int D, bool packed = false)
   RouteLayout L;
   L.gate = route_shape(T, H, E);
   if (packed) L.gate.planes_bytes = 0;  // the caller holds the planes (probe_pack_gate)
-  const size_t plane = static_cast<size_t>(T > 0 ? T : 1) * E * sizeof(float);
+  const size_t plane = static_cast<size_t>(T > 0 ? T : 1) * L.gate.ld * sizeof(float);
   L.upartial_bytes = L.a_bytes = L.b_bytes = 0;
   int extra = 0;
   if (D > 0) {
@@ -946,14 +1116,18 @@ static int route_impl(const char* name, const void* x_bf16, const float* w_gate,
     if (expert_counts)
       hipLaunchKernelGGL(gate_split_kernel, dim3((E + 255) / 256), dim3(256), 0, st, w_gate, 0l, nullptr, 0l,
                          expert_counts, E);
-  } else if (packed == nullptr) {
+  } else if (packed == nullptr && !split_in_registers(sh, T, E)) {
     bf16_t* ws_planes = static_cast<bf16_t*>(workspace);
     hipLaunchKernelGGL(gate_split_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st, w_gate, n,
                        ws_planes, n, nullptr, E);
     planes = ws_planes;
   }
   if (T > 0) {
-    launch_gate_gemm<3>(sh, st, x, planes, T, H, E, partial, expert_counts, nullptr, expert_counts ? E : 0);
+    if (planes == nullptr)
+      launch_gate_direct<3, true>(sh, st, x, GateRows{nullptr, w_gate, nullptr, E}, T, H, E, partial, expert_counts,
+                                  nullptr, expert_counts ? E : 0);
+    else
+      launch_gate_gemm<3>(sh, st, x, planes, T, H, E, partial, expert_counts, nullptr, expert_counts ? E : 0);
     int planes_to_sum = sh.ks;
     if (resid) {
       // u = W1_hat h (one bf16 plane); s = silu(u) and W2_hat split into planes; r = W2_hat s as
@@ -967,43 +1141,34 @@ static int route_impl(const char* name, const void* x_bf16, const float* w_gate,
                          upartial, L.resid.ks, T, D, a_planes);
       hipLaunchKernelGGL(resid_w2_split_kernel, dim3(static_cast<unsigned>((n_b + 255) / 256)), dim3(256), 0, st,
                          w2_hat, E, D, b_planes);
-      launch_gate_gemm<3>(L.resid2, st, a_planes, b_planes, T, 3 * D, E, partial + static_cast<size_t>(sh.ks) * T * E);
+      launch_gate_gemm<3>(L.resid2, st, a_planes, b_planes, T, 3 * D, E, partial + static_cast<size_t>(sh.ks) * T * sh.ld);
       planes_to_sum = sh.ks + L.resid2.ks;
     }
     int grid = (T + 31) / 32;
     if (grid > 4096) grid = 4096;
     int G = bias ? bias_groups : 1, tpg = bias ? tokens_per_group : 1;
 #define PROBE_TOPK_LAUNCH(V)                                                                               \
-  hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial, E, planes_to_sum, bias, \
+  hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial, sh.ld, planes_to_sum, bias, \
                      G, tpg, T, E, k, renormalize ? 1 : 0, topk_idx, topk_w, probs, expert_counts)
-#define PROBE_GROUPED_LAUNCH(V)                                                                              \
-  hipLaunchKernelGGL(gate_grouped_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial, E, planes_to_sum, bias, \
-                     G, tpg, select_bias, T, E, k, gating->scoring, gating->n_group, gating->topk_group,         \
-                     gating->group_top, gating->renormalize ? 1 : 0, gating->routed_scale, topk_idx, topk_w,     \
-                     probs, expert_counts)
+#define PROBE_GROUPED_LAUNCH(V, R)                                                                               \
+  hipLaunchKernelGGL((gate_grouped_topk_kernel<V, 1, R>), dim3(std::min((T + 15) / 16, 4096)), dim3(256), 0, st,  \
+                     partial, sh.ld, planes_to_sum, bias, G, tpg, select_bias, T, E, k, gating->scoring,             \
+                     gating->n_group, gating->topk_group, gating->group_top, gating->renormalize ? 1 : 0,        \
+                     gating->routed_scale, topk_idx, topk_w, probs, expert_counts)
     if (gating) {
-      if (E <= 64) {
-        PROBE_GROUPED_LAUNCH(1);
-      } else if (E <= 128) {
-        PROBE_GROUPED_LAUNCH(2);
-      } else {
-        PROBE_GROUPED_LAUNCH(4);
-      }
-    } else if (E <= 64) {
-      PROBE_TOPK_LAUNCH(1);
+      if (E <= 64) PROBE_GROUPED_LAUNCH(1, 8); else if (E <= 128) PROBE_GROUPED_LAUNCH(2, 8); else PROBE_GROUPED_LAUNCH(4, 4);
     } else {
-      // small batches (decode): one token per row in flight and all split-K slices loaded at once give twice
+      // small batches (decode): one token per row in flight and many split-K slices loaded at once give twice
       // the waves per SIMD to hide the loads behind; large batches are bound by reading the partial sums
       // either way (measured at 8192 and 16384 tokens: no difference)
-#define PROBE_TOPK_LAUNCH_SMALL(V)                                                                              \
-  hipLaunchKernelGGL((gate_softmax_topk_kernel<V, 1, 4>), dim3((T + 15) / 16), dim3(256), 0, st, partial, E,     \
+#define PROBE_TOPK_LAUNCH_SMALL(V, R)                                                                             \
+  hipLaunchKernelGGL((gate_softmax_topk_kernel<V, 1, R>), dim3((T + 15) / 16), dim3(256), 0, st, partial, sh.ld, \
                      planes_to_sum, bias, G, tpg, T, E, k, renormalize ? 1 : 0, topk_idx, topk_w, probs,        \
                      expert_counts)
-      const bool small = T <= 2048;
-      if (E <= 128) {
-        if (small) PROBE_TOPK_LAUNCH_SMALL(2); else PROBE_TOPK_LAUNCH(2);
+      if (T > 2048) {
+        if (E <= 64) PROBE_TOPK_LAUNCH(1); else if (E <= 128) PROBE_TOPK_LAUNCH(2); else PROBE_TOPK_LAUNCH(4);
       } else {
-        if (small) PROBE_TOPK_LAUNCH_SMALL(4); else PROBE_TOPK_LAUNCH(4);
+        if (E <= 64) PROBE_TOPK_LAUNCH_SMALL(1, 8); else if (E <= 128) PROBE_TOPK_LAUNCH_SMALL(2, 8); else PROBE_TOPK_LAUNCH_SMALL(4, 8);
       }
 #undef PROBE_TOPK_LAUNCH_SMALL
     }
@@ -1061,7 +1226,7 @@ static int route_predict_impl(const void* x_bf16, const float* w_gate, const flo
     if (pred_counts)
       hipLaunchKernelGGL(gate_split_kernel, dim3((E + 255) / 256), dim3(256), 0, st, w_gate, 0l, nullptr, 0l,
                          pred_counts, E);
-  } else if (packed_stack == nullptr) {
+  } else if (packed_stack == nullptr && !split_in_registers(sh, T, 2 * E)) {
     bf16_t* ws_planes = static_cast<bf16_t*>(workspace);
     const unsigned split_grid = static_cast<unsigned>((n + 255) / 256);
     hipLaunchKernelGGL(gate_split_kernel, dim3(split_grid), dim3(256), 0, st, w_gate, n, ws_planes, 2 * n, nullptr, E);
@@ -1070,8 +1235,12 @@ static int route_predict_impl(const void* x_bf16, const float* w_gate, const flo
     planes = ws_planes;
   }
   if (T > 0) {
-    launch_gate_gemm<3>(sh, st, static_cast<const bf16_t*>(x_bf16), planes, T, H, 2 * E, partial, expert_counts,
-                        pred_counts, E);
+    if (planes == nullptr)
+      launch_gate_direct<3, true>(sh, st, static_cast<const bf16_t*>(x_bf16), GateRows{nullptr, w_gate, w_gate_next, E},
+                                  T, H, 2 * E, partial, expert_counts, pred_counts, E);
+    else
+      launch_gate_gemm<3>(sh, st, static_cast<const bf16_t*>(x_bf16), planes, T, H, 2 * E, partial, expert_counts,
+                          pred_counts, E);
     int grid = (T + 31) / 32;
     if (grid > 4096) grid = 4096;
     const int G1 = bias ? bias_groups : 1, tpg1 = bias ? tokens_per_group : 1;
@@ -1079,9 +1248,9 @@ static int route_predict_impl(const void* x_bf16, const float* w_gate, const flo
     const int rn = renormalize ? 1 : 0;
 #define PROBE_TOPK_LAUNCH2(V)                                                                                     \
   do {                                                                                                            \
-    hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial, 2 * E, sh.ks, bias, G1, \
+    hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial, sh.ld, sh.ks, bias, G1, \
                        tpg1, T, E, k, rn, topk_idx, topk_w, probs, expert_counts);                                \
-    hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial + E, 2 * E, sh.ks,      \
+    hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial + E, sh.ld, sh.ks,      \
                        bias_next, G2, tpg2, T, E, k, rn, pred_idx, pred_w, pred_probs, pred_counts);              \
   } while (0)
     if (E <= 64) {

@@ -114,6 +114,36 @@ def test_route_when_hidden_size_is_not_a_multiple_of_64(oracle, probe, G, T, H, 
     np.testing.assert_array_equal(g["counts"].cpu().numpy(), np.bincount(g["idx"].cpu().numpy().ravel(), minlength=E))
 
 
+@pytest.mark.parametrize("T,H,E,k", [(1, 64, 16, 8), (16, 1000, 17, 3), (17, 8, 60, 6), (32, 4096, 9, 2), (33, 520, 130, 8),
+                                     (65, 7168, 256, 8), (129, 1024, 128, 4), (513, 328, 16, 2), (9000, 192, 8, 2),
+                                     (257, 512, 128, 8)])
+def test_route_small_batches_and_small_gates(oracle, probe, G, T, H, E, k):
+    """The kernel that goes from global memory to the matrix cores: one to eight token fragments per workgroup, batches and
+    gates on both sides of where it hands over to the tiled ones, expert counts that leave a partial fragment or
+    partial 16-byte pieces; every token against the oracle, the packed gate bit for bit the fp32 one."""
+    print("case small route T=%d H=%d E=%d" % (T, H, E), flush=True)
+    rng = np.random.default_rng(T + E)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((T, H), dtype=np.float32))
+    wg = (rng.standard_normal((E, H), dtype=np.float32) * np.float32(0.05))
+    b = rng.standard_normal((2, E)).astype(np.float32)
+    tpg = max(T // 2, 1)
+    d_x, d_w, d_b = G.dev_bf16(x), torch.from_numpy(wg).cuda(), torch.from_numpy(b).cuda()
+    g = probe.route_topk(d_x, d_w, d_b, tpg, k, True, want_probs=True)
+    p = probe.route_topk(d_x, probe.PackedGate(d_w), d_b, tpg, k, True, want_probs=True)
+    torch.cuda.synchronize()
+    for key in ("idx", "w", "probs", "counts"):
+        assert torch.equal(g[key], p[key]), key
+    o = oracle.route_topk(x, wg, b, tpg, k, True)
+    G.check_route(g, o, k, True)
+    np.testing.assert_array_equal(g["counts"].cpu().numpy(), np.bincount(g["idx"].cpu().numpy().ravel(), minlength=E))
+    if 2 * k <= E:   # both gates in one pass: the second is this one with its experts in reverse order
+        r, q = probe.route_predict_topk(d_x, d_w, d_b, d_w.flip(0).contiguous(), d_b.flip(1).contiguous(), tpg, k, True)
+        torch.cuda.synchronize()
+        G.check_route(r, o, k, True)
+        rev = oracle.route_topk(x, wg[::-1].copy(), b[:, ::-1].copy(), tpg, k, True)
+        G.check_route(q, rev, k, True)
+
+
 @pytest.mark.parametrize("T,H,E,k", [(8200, 256, 256, 8), (4100, 1024, 200, 6), (2049, 128, 130, 4)])
 def test_route_on_256_token_tiles_with_a_ragged_last_tile(oracle, probe, G, T, H, E, k):
     """Large batches take the 256-token tile of the gate GEMM; T is not a multiple of the tile, E not
