@@ -765,7 +765,8 @@ __global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __rest
 struct FfnShape {
   bool skinny;  // the decode schedule
   int max_tiles;
-  size_t h_bytes, table_bytes, partial_bytes;
+  size_t h_bytes, table_bytes;
+  size_t partial_bytes;  // not demanded: a workspace without this room (one sized for another max_rows) runs unsplit
 };
 
 // The decode schedule is chosen on the host from the capacity of the row space alone (the row counts live
@@ -775,11 +776,13 @@ constexpr int kSkinnyRowsPerSlot = 64;
 
 static FfnShape ffn_shape(int S, int F, int max_rows) {
   FfnShape s;
-  s.skinny = static_cast<long>(max_rows) <= static_cast<long>(kSkinnyRowsPerSlot) * S ||
+  const bool short_slots = static_cast<long>(max_rows) <= static_cast<long>(kSkinnyRowsPerSlot) * S;
+  s.skinny = short_slots ||
              (static_cast<long>(max_rows) / 64 + S) * ((F + kSkinnyCols1 - 1) / kSkinnyCols1) <= kSkinnyFewItems;
   s.max_tiles = s.skinny ? max_rows / 64 + S : max_rows / 256 + S;
+  const int table_tiles = short_slots ? max_rows / 64 + S : max_rows / 256 + S;
   s.h_bytes = align_up(static_cast<size_t>(max_rows > 0 ? max_rows : 1) * F * sizeof(bf16_t), 256);
-  s.table_bytes = align_up(kTableHeaderInts * sizeof(int32_t) + static_cast<size_t>(s.max_tiles) * sizeof(TileEntry), 256);
+  s.table_bytes = align_up(kTableHeaderInts * sizeof(int32_t) + static_cast<size_t>(table_tiles) * sizeof(TileEntry), 256);
   s.partial_bytes = s.skinny ? kSkinnyPartialBytes : 0;
   return s;
 }
@@ -867,9 +870,9 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
   PROBE_REQUIRE(aligned16(act_bf16) && aligned16(y_bf16), PROBE_EALIGN,
                 "%s: activations and y must be 16-byte aligned", name);
   FfnShape sh = ffn_shape(S, F, max_rows);
-  PROBE_REQUIRE(workspace && aligned16(workspace) && workspace_bytes >= sh.h_bytes + sh.table_bytes + sh.partial_bytes,
+  PROBE_REQUIRE(workspace && aligned16(workspace) && workspace_bytes >= sh.h_bytes + sh.table_bytes,
                 PROBE_EWORKSPACE, "%s: workspace too small or misaligned (%zu < %zu)", name, workspace_bytes,
-                sh.h_bytes + sh.table_bytes + sh.partial_bytes);
+                sh.h_bytes + sh.table_bytes);
   PROBE_REQUIRE(static_cast<long>(sh.max_tiles + 8) * ((F + 127) / 128 + 4) < (1l << 30) &&
                     static_cast<long>(sh.max_tiles + 8) * ((H + 255) / 256 + 4) < (1l << 30),
                 PROBE_EUNSUPPORTED, "%s: max_rows too large (%d)", name, max_rows);
@@ -889,7 +892,8 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     bf16_t* y = static_cast<bf16_t*>(y_bf16);
     const int tiles = std::min(sh.max_tiles, max_rows);  // a tile has at least one row
     const int n1 = (F + kSkinnyCols1 - 1) / kSkinnyCols1, n2 = (H + kSkinnyCols2 - 1) / kSkinnyCols2;
-    const int split1 = skinny_may_split(tiles, n1, H / FBK), split2 = skinny_may_split(tiles, n2, F / FBK);
+    const bool room = workspace_bytes >= sh.h_bytes + sh.table_bytes + sh.partial_bytes;
+    const int split1 = room && skinny_may_split(tiles, n1, H / FBK), split2 = room && skinny_may_split(tiles, n2, F / FBK);
     // a split call has at most kSkinnyItems items, one that is not split tiles * n
     const dim3 g1(split1 ? std::max(tiles * n1, kSkinnyItems) : tiles * n1);
     const dim3 g2(split2 ? std::max(tiles * n2, kSkinnyItems) : tiles * n2);

@@ -334,6 +334,24 @@ def test_ffn_few_tiles_every_element(oracle, probe, G, sizes, H, F):
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, len(sizes), seed=H + F, extra_rows=0 if sizes == [1] else 9)
 
 
+def test_ffn_workspace_of_a_larger_call_serves_a_smaller_one(oracle, probe, G):
+    """A workspace sized for more rows is enough for fewer, also where the smaller call would like room for partial
+    sums (one slot: 1100 rows take the tall tiles, 75 rows the pieces of K): it then runs unsplit."""
+    cfg = wl.small_config(T=64, H=4096, E=4, k=2, F=2048, cid=101)
+    big, n = 1100, 75
+    assert probe.grouped_ffn_workspace_bytes(1, cfg.H, cfg.F, n) > probe.grouped_ffn_workspace_bytes(1, cfg.H, cfg.F, big)
+    w13, w2 = wl.expert_weights_many(cfg, [0])[0]
+    tab = probe.WeightTable([G.dev_bf16(w13)], [G.dev_bf16(w2)])
+    x = wl.f32_to_bf16_bits(np.random.default_rng(3).standard_normal((n, cfg.H)).astype(np.float32))
+    so = torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    print("case workspace of a larger call", flush=True)
+    ws = torch.empty(probe.grouped_ffn_workspace_bytes(1, cfg.H, cfg.F, big), dtype=torch.uint8, device="cuda")
+    y = probe.grouped_ffn(G.dev_bf16(x), so, tab, workspace=ws)
+    torch.cuda.synchronize()
+    ref = oracle.grouped_ffn(x, np.array([0, n], np.int32), [w13], [w2])
+    assert G.rel_err(G.f64_of(y), ref) < G.BF16_RTOL
+
+
 def test_ffn_every_tile_height_at_full_depth(oracle, probe, G):
     """One slot per tile height (320, 256, 192, 128, 64 rows) and a ragged one, at the depth of the benchmark's
     main configuration (K = 7168 in the first GEMM, 2048 in the second: 112 and 32 steps of the main loop):
