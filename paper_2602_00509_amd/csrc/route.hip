@@ -933,6 +933,8 @@ struct RouteShape {
   bool dma;  // H % 64 == 0: the DMA-to-LDS pipeline; otherwise the register-staged kernel
   int bm;    // tokens per workgroup of the gemm (128 or 256)
   int mt, nt, ks, k_chunk;
+  int ks_room;      // slices that the workspace has room for: those of the tiled kernels, which the direct one never exceeds.
+                    // Its own count falls steeply with T, and a workspace sized for more tokens has to serve fewer.
   int ld;           // entries of a row of partial sums: E rounded up to whole 16-byte pieces (the last ones are not read)
   bool direct;      // gate_direct_kernel: `frags` fragments of 16 tokens per workgroup, `per_wave` k32 per wave
   int frags, per_wave;
@@ -966,6 +968,7 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
   int steps_per = (ksteps + want - 1) / want;
   s.k_chunk = steps_per * GBK;
   s.ks = (ksteps + steps_per - 1) / steps_per;
+  s.ks_room = s.ks;
   s.direct = static_cast<long>(T) * E <= (H % 64 == 0 ? 1 : 8) * kDirectLogits || E <= kDirectExperts;
   s.frags = s.per_wave = 0;
   if (s.direct) {
@@ -979,7 +982,7 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
     s.ks = (k32 + 8 * s.per_wave - 1) / (8 * s.per_wave);
   }
   s.planes_bytes = align_up(static_cast<size_t>(3) * E * H * sizeof(bf16_t), 256);
-  s.partial_bytes = align_up(static_cast<size_t>(s.ks) * (T > 0 ? T : 1) * s.ld * sizeof(float), 256);
+  s.partial_bytes = align_up(static_cast<size_t>(s.ks_room) * (T > 0 ? T : 1) * s.ld * sizeof(float), 256);
   return s;
 }
 
@@ -1047,9 +1050,9 @@ static RouteLayout route_layout(int T, int H, int E, int D, bool packed = false)
     L.upartial_bytes = L.resid.partial_bytes;
     L.a_bytes = align_up(static_cast<size_t>(T > 0 ? T : 1) * 3 * D * sizeof(bf16_t), 256);
     L.b_bytes = L.resid2.planes_bytes;
-    extra = L.resid2.ks;
+    extra = L.resid2.ks_room;
   }
-  L.partial_bytes = align_up((L.gate.ks + extra) * plane, 256);
+  L.partial_bytes = align_up((L.gate.ks_room + extra) * plane, 256);
   L.total = L.gate.planes_bytes + L.partial_bytes + L.upartial_bytes + L.a_bytes + L.b_bytes;
   return L;
 }

@@ -45,6 +45,17 @@ def test_workspace_sizes(L):
     assert probe.grouped_ffn_workspace_bytes(36, 7168, 2048, 65536) >= 65536 * 2048 * 2
 
 
+def test_route_workspace_of_more_tokens_serves_fewer(L):
+    """A caller that keeps one workspace, sized for its largest batch, may hand it to every smaller one: across the
+    line between the kernels for small batches or gates and the tiled ones too."""
+    from paper_2602_00509_amd import probe
+    for H, E, top in ((4096, 8, 3000), (1000, 250, 1100), (4096, 128, 700), (7168, 256, 300)):
+        sizes = [probe.route_topk_workspace_bytes(T, H, E, 2) for T in range(1, top + 1)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), (H, E)
+        resid = [L.probe_predict_topk_residual_workspace_bytes(T, H, E, 2, 64) for T in range(1, top + 1, 7)]
+        assert all(a <= b for a, b in zip(resid, resid[1:])), (H, E)
+
+
 def test_bad_arguments_are_rejected_without_a_launch(L):
     from paper_2602_00509_amd.probe import _Plan
     err = lambda: L.probe_last_error_string().decode()
