@@ -311,7 +311,7 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
                                            int row0, int rows, int n0, int H, int F,
                                            bf16_t* __restrict__ hbuf, u32x4* smem, int32_t* draw_counter = nullptr,
                                            volatile int* draw_slot = nullptr, int k0 = 0, int klen = 0,
-                                           float* partial = nullptr) {
+                                           float* partial = nullptr, int k_start = 0) {
   // SPLIT: only k0 .. k0 + klen - 1 of the contraction; the fp32 sums go to partial[row of the tile][gate F | up F].
   // rows = valid rows from row0 to the end of the slot (may exceed the tile height)
   constexpr int HALF = 16 * NI;  // h columns per wave; its 32*NI weight rows are HALF gate rows, then the HALF up rows
@@ -348,8 +348,8 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
   f32x4 acc[2 * MI][2 * NI];
   zero_acc<MI, NI>(acc);
   const bool drew =
-      gemm_mainloop<MI, NI, 1, NST, true, DRAW>(rA, rB, voff, SPLIT ? k0 : 0, SPLIT ? klen : H, smem, wv, lane, acc,
-                                                draw_counter, draw_slot);
+      gemm_mainloop<MI, NI, 1, NST, true, DRAW, NI == 1>(rA, rB, voff, SPLIT ? k0 : 0, SPLIT ? klen : H, smem, wv, lane,
+                                                         acc, draw_counter, draw_slot, k_start);
 
   // NI = 2: acc[i][0..1] are eight consecutive gate columns of one output row, acc[i][2..3] the up columns (see
   // gemm_mainloop, PERM): one 16-byte store.  NI = 1: four of each, 8 bytes.  The stores go through a buffer
@@ -457,7 +457,7 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
                                            int row0, int rows, int n0, int H, int F,
                                            bf16_t* __restrict__ y, u32x4* smem, int32_t* draw_counter = nullptr,
                                            volatile int* draw_slot = nullptr, int k0 = 0, int klen = 0,
-                                           float* partial = nullptr) {
+                                           float* partial = nullptr, int k_start = 0) {
   // SPLIT: only k0 .. k0 + klen - 1 of the contraction; the fp32 sums go to partial[row of the tile][H].
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -470,8 +470,8 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
   f32x4 acc[2 * MI][2 * NI];
   zero_acc<MI, NI>(acc);
   const bool drew =
-      gemm_mainloop<MI, NI, 1, NST, true, DRAW>(rA, rB, voff, SPLIT ? k0 : 0, SPLIT ? klen : F, smem, wv, lane, acc,
-                                                draw_counter, draw_slot);
+      gemm_mainloop<MI, NI, 1, NST, true, DRAW, NI == 1>(rA, rB, voff, SPLIT ? k0 : 0, SPLIT ? klen : F, smem, wv, lane,
+                                                         acc, draw_counter, draw_slot, k_start);
 
   const int valid = min(rows, 64 * MI);  // rows past it are dropped by the descriptor's bounds check
   __amdgpu_buffer_rsrc_t rY = make_rsrc(y + static_cast<size_t>(row0) * H, static_cast<size_t>(valid) * H * 2);
@@ -675,6 +675,16 @@ __device__ __forceinline__ float* skinny_partial(float* partial, const SkinnyTil
   return partial + static_cast<size_t>(e.tile * e.pieces + piece) * 64 * ld;
 }
 
+// The k-step at which an item begins; it goes round to the one before.  Items that all walk K from 0 ask at any moment for the
+// same 128 bytes of rows that lie 2H (or 2F) bytes apart, which for H = 4096 is the same few HBM channels: spread over K,
+// gemm1 of one token (4096 x 14336) takes 83 instead of 91 us, of 14 slots of 4096 x 1536 71 instead of 75, gemm2 of 20 slots
+// of 7168 x 2048 123 instead of 130.  By column only: the row tiles of a slot read its weights together, from the caches
+// (197 tokens, 64 slots of 7168 x 2048: 675 us, spread by tile too 687, all from 0 682).  The tall tiles keep to k = 0: there
+// the items of an XCD share weights and rows in its L2, and started block by block prefill of 8192 tokens was 3 % slower.
+__device__ __forceinline__ int skinny_start(const SkinnyTile& e, int klen) {
+  return (e.col * 11) % (klen / FBK);
+}
+
 template <bool GATHER>
 __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
                                                                   const int32_t* __restrict__ slot_offsets,
@@ -689,12 +699,14 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
-    gemm1_tile<1, GATHER, 1, 3>(src, w, e.row0, e.rows, e.col * kSkinnyCols1, H, F, hbuf, smem);
+    gemm1_tile<1, GATHER, 1, 3>(src, w, e.row0, e.rows, e.col * kSkinnyCols1, H, F, hbuf, smem, nullptr, nullptr, 0, 0,
+                                nullptr, skinny_start(e, H));
   } else {
     const int k0 = e.piece * e.piece_steps * FBK;
     gemm1_tile<1, GATHER, 1, 3, false, true>(src, w, e.row0, e.rows, e.col * kSkinnyCols1, H, F, hbuf, smem, nullptr,
                                              nullptr, k0, min(H - k0, e.piece_steps * FBK),
-                                             skinny_partial(partial, e, e.piece, 2 * F));
+                                             skinny_partial(partial, e, e.piece, 2 * F),
+                                             skinny_start(e, min(H - k0, e.piece_steps * FBK)));
   }
 #endif
 }
@@ -712,11 +724,13 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* 
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
-    gemm2_tile<1, 1, 3>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem);
+    gemm2_tile<1, 1, 3>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem, nullptr, nullptr, 0, 0, nullptr,
+                        skinny_start(e, F));
   } else {
     const int k0 = e.piece * e.piece_steps * FBK;
     gemm2_tile<1, 1, 3, false, true>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem, nullptr, nullptr, k0,
-                                     min(F - k0, e.piece_steps * FBK), skinny_partial(partial, e, e.piece, H));
+                                     min(F - k0, e.piece_steps * FBK), skinny_partial(partial, e, e.piece, H),
+                                     skinny_start(e, min(F - k0, e.piece_steps * FBK)));
   }
 #endif
 }

@@ -24,6 +24,7 @@ __device__ __forceinline__ void wait_vm_lgkm0() {  // s_waitcnt vmcnt(N) lgkmcnt
 // rA / rB are buffer descriptors of the tile's first A row / of the weight matrix; voff[j] is
 // this lane's byte offset for DMA instruction j (MI instructions for A, then BW for B); k0 is
 // the first k of this call's K range and K its length (a multiple of 64).
+// AROUND: the first k-step is number k_start, the walk goes round to k_start - 1.
 // NST = LDS stages (2 or 3); a DMA batch is issued NST k-steps ahead of its use.
 //
 // What bounds it: matrix cores under the chip's power limit, and next to them the way of the weights from HBM.  With all
@@ -58,11 +59,12 @@ __device__ __forceinline__ int lds_key(int row) {
   return PERM ? ((row >> 1) & 1) | (((row >> 3) & 3) << 1) : (row >> 1) & 7;
 }
 
-template <int MI, int NI, int PL, int NST, bool PERM = false, bool DRAW = false>
+template <int MI, int NI, int PL, int NST, bool PERM = false, bool DRAW = false, bool AROUND = false>
 __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgpu_buffer_rsrc_t rB,
                                               const int (&voff)[MI + NI * PL * 2], int k0, int K,
                                               u32x4* smem, int wv, int lane, f32x4 (&acc)[2 * MI][2 * NI],
-                                              int32_t* draw_counter = nullptr, volatile int* draw_slot = nullptr) {
+                                              int32_t* draw_counter = nullptr, volatile int* draw_slot = nullptr,
+                                              int k_start = 0) {
   constexpr int WN = 4, BROWS = 128 * NI * PL, AW = MI, BW = BROWS / 64, LPW = AW + BW, BM = 64 * MI;
   constexpr int BF = 2 * NI;              // B fragments of a plane
   constexpr int NB = BF * PL;             // B fragments per k32
@@ -79,9 +81,18 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rB, PROBE_LDS_PTR(smem + st * kStage + BM * 8 + (wv * BW + (j - AW)) * 64), 16, voff[j], kbytes, 0, 0);
   };
+  const int KT = K / FBK;
+  auto kbytes_of = [&](int kt) {
+    int s = kt;
+    if constexpr (AROUND) {
+      s += k_start;
+      s = s >= KT ? s - KT : s;
+    }
+    return (k0 + s * FBK) * 2;
+  };
   auto issue_all = [&](int st, int kt) {
 #pragma unroll
-    for (int j = 0; j < LPW; ++j) issue_one(st, j, (k0 + kt * FBK) * 2);
+    for (int j = 0; j < LPW; ++j) issue_one(st, j, kbytes_of(kt));
   };
   const int arow = 32 * MI * wm + (lane & 15);
   const int brow = 32 * NI * wn + (PERM ? ((lane & 12) << 1) | (lane & 3) : (lane & 15));
@@ -124,7 +135,6 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
       }
   };
 
-  const int KT = K / FBK;
   // prologue: NST batches in flight, wait for the first
   issue_all(0, 0);
   if (KT > 1) issue_all(1, 1);
@@ -153,7 +163,7 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
     constexpr bool DMA = decltype(dma_c)::value, YOUNGER = decltype(younger_c)::value,
                    NEXT = decltype(next_c)::value;
     const int nxt = (cur + 1 == NST) ? 0 : cur + 1;
-    const int kbytes = (k0 + (kt + NST) * FBK) * 2;
+    const int kbytes = kbytes_of(kt + NST);
     // DMA instructions are spread over the steps after the barrier that releases their part of the stage
     constexpr int ASTEPS = STEPS - BAR, BSTEPS = EARLY ? BAR - FREE_B : ASTEPS;
 #pragma unroll
