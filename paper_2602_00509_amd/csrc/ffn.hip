@@ -56,7 +56,15 @@ static_assert(kFfnLdsBytes >= 2 * (320 + 256) * 128, "two stages of the tallest 
 //
 // Order of the table.  Slots are taken by descending row count (ties: lower slot first) and a
 // slot's tiles stay together: the workgroups that run side by side then share a slot's weight
-// slices in L2, the long slots start early and the single short tiles fill the tail of the launch.
+// slices in L2 and the long slots start early; the single short tiles are spread evenly over the table, so that
+// tiles that wait for weights run beside tiles that keep the matrix cores busy.
+//
+// Where gemm1 has more items than CUs, but few enough tall tiles (more than 192 rows) that all of theirs start at once, the
+// tiles stand by descending height instead: a tall item that begins second is then the end of the launch.  768 tokens,
+// top-4 of 128 experts, 18 slots of 2880 x 2880: gemm1 116 -> 87 us, the layer 262 -> 235; 1500 tokens, 36 slots of 7168 x 2048
+// 863 -> 809 us, 2000 tokens of the first 355 -> 333.  With more tall tiles they hold each other up (clock) and the short
+// ones all come after them: 16384 tokens x 64 slots 3212 -> 3290 us, 2000 tokens of an 8-expert model 1338 -> 1390.  With no
+// second round the order only moves items between XCDs (700 tokens, 33 slots of 2048 x 1024: 167 -> 172 us).
 struct alignas(16) TileEntry {
   int32_t row0, rows, height, slot;
   const void* w13;
@@ -67,11 +75,16 @@ static_assert(sizeof(TileEntry) == 32, "one 32-byte record per tile");
 // gemm1 and gemm2 (one counter per XCD), cleared by the schedule kernel of the same call.
 constexpr int kTableHeaderInts = 32, kQueue1 = 8, kQueue2 = 16;
 
-constexpr bool kInterleave = true;
-
 struct SlotCut {
   int n320, n256, tail;  // tail = height of the one short tile (64, 128 or 192), 0 if there is none
   __device__ __forceinline__ int tiles() const { return n320 + n256 + (tail ? 1 : 0); }
+  // tallest first: 320, 256, 192, 128, 64 rows
+  static __device__ __forceinline__ int height_class(int height) { return height == 320 ? 0 : 5 - (height >> 6); }
+  // tiles of each height, twelve bits per class
+  __device__ __forceinline__ unsigned long long classes() const {
+    return static_cast<unsigned long long>(n320) | static_cast<unsigned long long>(n256) << 12 |
+           (tail ? 1ull << (12 * height_class(tail)) : 0ull);
+  }
 };
 
 __device__ __forceinline__ SlotCut cut_slot(int m) {
@@ -97,15 +110,17 @@ __device__ __forceinline__ SlotCut cut_slot(int m) {
 __global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __restrict__ slot_offsets,
                                                            const void* const* __restrict__ w13_ptrs,
                                                            const void* const* __restrict__ w2_ptrs,
-                                                           int S, int max_tiles,
+                                                           int S, int max_tiles, int n_cols1, int cus,
                                                            int32_t* __restrict__ table) {
-  __shared__ int32_t rows_of[PROBE_MAX_SLOTS];
+  __shared__ alignas(16) int32_t rows_of[PROBE_MAX_SLOTS];
   __shared__ int32_t first_of[PROBE_MAX_SLOTS];
   __shared__ const void* w13_of[PROBE_MAX_SLOTS];
   __shared__ const void* w2_of[PROBE_MAX_SLOTS];
   __shared__ int32_t slot_at[PROBE_MAX_SLOTS];       // slot at each position of the sorted order
   __shared__ int32_t start[PROBE_MAX_SLOTS + 1];     // first tile of each position (exclusive prefix)
+  __shared__ unsigned long long class_start[PROBE_MAX_SLOTS + 1];  // the same per tile height, twelve bits each
   __shared__ int32_t wave_tot[4];
+  __shared__ unsigned long long wave_classes[4];
   const int tid = threadIdx.x, lane = tid & 63;
   int m[4];
 #pragma unroll
@@ -119,15 +134,20 @@ __global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __rest
       first_of[s] = first;
       w13_of[s] = w13_ptrs[s];
       w2_of[s] = w2_ptrs[s];
+    } else {
+      rows_of[s] = -1;
     }
   }
   __syncthreads();
   // position of a slot = number of slots that come before it
   int pos[4] = {0, 0, 0, 0};
-  for (int u = 0; u < S; ++u) {
-    const int ru = rows_of[u];
+  for (int u0 = 0; u0 < S; u0 += 4) {  // entries past S are -1 (m >= 0): they come before nobody
+    const int4 r4 = *reinterpret_cast<const int4*>(&rows_of[u0]);
+    const int ru[4] = {r4.x, r4.y, r4.z, r4.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) pos[i] += (ru > m[i] || (ru == m[i] && u < tid * 4 + i)) ? 1 : 0;
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) pos[i] += (ru[j] > m[i] || (ru[j] == m[i] && u0 + j < tid * 4 + i)) ? 1 : 0;
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -135,31 +155,58 @@ __global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __rest
   __syncthreads();
   // exclusive prefix of tiles over positions tid*4 .. tid*4+3
   int v[4], local = 0;
+  unsigned long long by_height[4], c_local = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int p = tid * 4 + i;
-    v[i] = p < S ? cut_slot(rows_of[slot_at[p]]).tiles() : 0;
+    const SlotCut cut = p < S ? cut_slot(rows_of[slot_at[p]]) : SlotCut{0, 0, 0};
+    v[i] = cut.tiles();
+    by_height[i] = cut.classes();
     local += v[i];
+    c_local += by_height[i];
   }
   int incl = local;
+  unsigned long long c_incl = c_local;
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
-    int o = __shfl_up(incl, d, kWave);
-    if (lane >= d) incl += o;
+    const int o = __shfl_up(incl, d, kWave);
+    const unsigned long long co = __shfl_up(c_incl, d, kWave);
+    if (lane >= d) {
+      incl += o;
+      c_incl += co;
+    }
   }
-  if (lane == kWave - 1) wave_tot[tid >> 6] = incl;
+  if (lane == kWave - 1) {
+    wave_tot[tid >> 6] = incl;
+    wave_classes[tid >> 6] = c_incl;
+  }
   __syncthreads();
   int excl = incl - local;
-  for (int i = 0; i < (tid >> 6); ++i) excl += wave_tot[i];
+  unsigned long long c_excl = c_incl - c_local;
+  for (int i = 0; i < (tid >> 6); ++i) {
+    excl += wave_tot[i];
+    c_excl += wave_classes[i];
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int p = tid * 4 + i;
-    if (p < S) start[p] = excl;
+    if (p < S) {
+      start[p] = excl;
+      class_start[p] = c_excl;
+    }
     excl += v[i];
+    c_excl += by_height[i];
   }
-  if (tid == 255) start[S] = excl;  // the last thread's running sum is the total
+  if (tid == 255) {  // the last thread's running sums are the totals
+    start[S] = excl;
+    class_start[S] = c_excl;
+  }
   __syncthreads();
   const int total = min(start[S], max_tiles);
+  // taller than 192 rows; beyond 4095 tiles the twelve-bit fields run into each other and are not looked at
+  const int n_tall = static_cast<int>(class_start[S] & 4095) + static_cast<int>((class_start[S] >> 12) & 4095);
+  const bool tall_first = start[S] <= min(max_tiles, 4095) && n_tall * n_cols1 <= cus &&
+                          static_cast<long>(start[S]) * n_cols1 > cus;
   if (tid == 0) table[0] = total;
   if (tid >= kQueue1 && tid < kTableHeaderInts) table[tid] = 0;
   TileEntry* entries = reinterpret_cast<TileEntry*>(table + kTableHeaderInts);
@@ -175,7 +222,7 @@ __global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __rest
     // entry p of the table: the short tiles are spread evenly over the table
     const int before = static_cast<int>(static_cast<long>(p) * ns / total);
     const bool is_short = static_cast<int>(static_cast<long>(p + 1) * ns / total) > before;
-    const int t = kInterleave ? (is_short ? nb + before : p - before) : p;
+    const int t = tall_first ? p : (is_short ? nb + before : p - before);
     int lo = 0, hi = S;  // last position with start[position] <= t
     while (hi - lo > 1) {
       int mid = (lo + hi) >> 1;
@@ -191,8 +238,15 @@ __global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __rest
       row0 += c.n320 * 320 + i * 256;
       height = 256;
     } else {
+      i = 0;
       row0 += c.n320 * 320 + c.n256 * 256;
       height = c.tail;
+    }
+    int at = p;
+    if (tall_first) {  // taller tiles first: the tiles of its height in the slots before it, and all taller ones
+      const int cls = SlotCut::height_class(height);
+      at = i + static_cast<int>((class_start[lo] >> (12 * cls)) & 4095);
+      for (int q = 0; q < cls; ++q) at += static_cast<int>((class_start[S] >> (12 * q)) & 4095);
     }
     TileEntry e;
     e.row0 = row0;
@@ -201,7 +255,7 @@ __global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __rest
     e.slot = slot;
     e.w13 = w13_of[slot];
     e.w2 = w2_of[slot];
-    entries[p] = e;
+    entries[at] = e;
   }
 }
 
@@ -930,7 +984,7 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     return check_launch(name);
   }
   hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(256), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S, sh.max_tiles,
-                     table);
+                     (F + 127) / 128, cus, table);
   // persistent launch (one workgroup per CU, items drawn from the work queue) unless the capacity of the
   // row space gives fewer items than that
   const int cap1 = ffn_grid(sh.max_tiles, (F + 127) / 128), cap2 = ffn_grid(sh.max_tiles, (H + FBN - 1) / FBN);

@@ -334,6 +334,18 @@ def test_ffn_few_tiles_every_element(oracle, probe, G, sizes, H, F):
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, len(sizes), seed=H + F, extra_rows=0 if sizes == [1] else 9)
 
 
+@pytest.mark.parametrize("sizes", [
+    [700, 5, 300, 0, 64, 130, 193, 20, 1, 33, 70, 200, 9, 3, 2, 1, 40, 321, 12, 450],   # 23 tiles, 8 of them tall
+    [320] * 8 + [0, 256] + [250] * 7 + [192, 1, 65],                                    # 19 tiles, 16 of them tall: the limit
+    [320] * 17 + [1, 0, 129]])                                                          # one more: slots stay in order
+def test_ffn_tall_tiles_first_every_element(oracle, probe, G, sizes):
+    """More items than CUs and 16 column blocks of the first GEMM: up to 16 tiles of more than 192 rows make the table
+    go by descending tile height (256 CUs); tiles of one height in several slots, empty slots, every height."""
+    cfg = wl.small_config(T=64, H=192, E=4, k=2, F=2048, cid=102)
+    print("case tall first", sizes, flush=True)
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 4, seed=len(sizes) + sizes[0])
+
+
 def test_ffn_workspace_of_a_larger_call_serves_a_smaller_one(oracle, probe, G):
     """A workspace sized for more rows is enough for fewer, also where the smaller call would like room for partial
     sums (one slot: 1100 rows take the tall tiles, 75 rows the pieces of K): it then runs unsplit."""
