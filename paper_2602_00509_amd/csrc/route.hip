@@ -172,7 +172,11 @@ __global__ __launch_bounds__(256, 2) void gate_gemm_kernel(const bf16_t* __restr
 // ends with four consecutive experts of one token per register quad: 16-byte stores.
 // MI = 2: 128 tokens per workgroup; MI = 4: 256 tokens (two stages of 80 KB, all of the LDS), which
 // moves a third less operand data per MFMA and is used for large batches.
+// One plane (u = W1_hat h of the residual): a k-step is a third of the matrix work for 48 KB of operands, so the loop waits for
+// loads, and the 256-token tile takes three stages (144 KB): the predictor with residual, 8192 x 7168, 256 wide, 154 -> 152.7 us.
 constexpr int kGateLdsBytes = 2 * (256 + 384) * 128;
+constexpr int gate_stages(int mi, int planes) { return mi == 4 && planes == 1 ? 3 : 2; }
+static_assert(3 * (256 + 128) * 128 <= kGateLdsBytes, "three stages of the one-plane tile");
 
 template <int MI, int PL>
 __global__ __launch_bounds__(512, 2) void gate_gemm_dma_kernel(const bf16_t* __restrict__ x,
@@ -200,7 +204,7 @@ __global__ __launch_bounds__(512, 2) void gate_gemm_dma_kernel(const bf16_t* __r
   f32x4 acc[2 * MI][2];
 #pragma unroll
   for (int i = 0; i < 2 * MI; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  gemm_mainloop<MI, 1, PL, 2>(rA, rB, voff, kbeg, klen, smem, wv, lane, acc);
+  gemm_mainloop<MI, 1, PL, gate_stages(MI, PL)>(rA, rB, voff, kbeg, klen, smem, wv, lane, acc);
 
 #pragma unroll
   for (int i = 0; i < 2 * MI; ++i) {
@@ -1012,7 +1016,7 @@ static void launch_gate_gemm(const RouteShape& sh, hipStream_t st, const bf16_t*
   if (sh.direct) {
     launch_gate_direct<PL, false>(sh, st, x, GateRows{planes, nullptr, nullptr, 0}, T, H, N, partial, zero0, zero1, n_zero);
   } else if (sh.dma) {
-    const int lds = 2 * (sh.bm + 128 * PL) * 128;
+    const int lds = gate_stages(sh.bm / 64, PL) * (sh.bm + 128 * PL) * 128;
     if (sh.bm == 256)
       hipLaunchKernelGGL((gate_gemm_dma_kernel<4, PL>), dim3(sh.mt, sh.nt, sh.ks), dim3(512), lds, st, x, planes, T,
                          H, N, sh.k_chunk, partial, sh.ld, zero0, zero1, n_zero);
