@@ -12,16 +12,22 @@
 //         comp[r]     sum over experts with ner > 0 of (ner + n0)          (compute term)
 //         vin[r], vout[r]   tokens received from / sent to other ranks      (network term)
 //         load[r]     tokens processed on rank r
-//   HBM   n[e][rs][rt]  the assignment, expert-major: a move rewrites one R x R slab
+//         n[e][rs][rt]  the assignment, expert-major: a move rewrites one R x R slab.  It lies in LDS where it fits
+//                     (kPlanLdsBytes: every R <= 11, 16 ranks up to 135 experts), otherwise in the workspace.
+// What bounds it is latency: an iteration is a chain of dependent reads and barriers on one CU.  Slabs in LDS, values
+// of all ranks read side by side into registers (unrolled to kPlanMaxRanks), one thread per slab entry for the
+// water-filling and four barriers per accepted move instead of eight: 8 ranks, 128 experts, 3 replicas 73 -> 53 us.
 // Per iteration only SelectHeavyExpert looks at every expert (one thread each, block arg-max by a
-// 64-bit LDS atomic); the water-filling of the chosen expert's slab and the new latencies are a few
-// hundred integer operations done by one thread.  All arithmetic is integer, so the plan is
-// bit-identical to the sequential definition.
+// 64-bit LDS atomic).  All arithmetic is integer, so the plan is bit-identical to the sequential definition.
 //
 // Cost model (a reading; the paper names the terms but not their constants):
 //   L_r = g_den * comp[r] + 2 * g_num * max(vin[r], vout[r])
 // with eta_g(n) = n / (n + n0) inside comp (Sec. 3.2) and g_num / g_den = network time per token over
 // compute time per token (Sec. 3.3).
+#include <limits.h>
+
+#include <mutex>
+
 #include "common.hpp"
 
 namespace probe {
@@ -37,172 +43,224 @@ struct PlannerArgs {
 
 __device__ __forceinline__ long long comp_term(long long tokens, long long n0) { return tokens > 0 ? tokens + n0 : 0; }
 
+// LDS that the assignment may take; the rest of the kernel's state is about 20 KB of the 160.
+constexpr int kPlanLdsBytes = 136 * 1024;
+// Words between the slabs of two experts.  In LDS one more than R * R, so that threads that look at the same entry of
+// neighbouring experts are on different banks.
+__host__ __device__ constexpr int plan_slab_stride(int R, bool in_lds) { return R * R + (in_lds ? 1 : 0); }
+static bool plan_fits_lds(int R, int E) { return E * plan_slab_stride(R, true) * 4 <= kPlanLdsBytes; }
+
+template <bool IN_LDS>
 __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restrict__ n_hat, PlannerArgs a,
-                                                          int32_t* __restrict__ g_n,  // [E][R][R] workspace
+                                                          int32_t* __restrict__ n_workspace,  // [E][R][R]
                                                           int32_t* __restrict__ rep_off, int32_t* __restrict__ rep_slot,
                                                           int32_t* __restrict__ rep_weight,
                                                           int32_t* __restrict__ slot_expert,
                                                           int32_t* __restrict__ delta_in, int32_t* __restrict__ delta_out,
                                                           int32_t* __restrict__ moves, long long* __restrict__ stats,
                                                           int32_t* __restrict__ n_assign) {
-  const int R = a.R, E = a.E, E_loc = a.E_loc;
+  const int R = a.R, E = a.E, E_loc = a.E_loc, stride = plan_slab_stride(R, IN_LDS);
+  extern __shared__ int32_t n_lds[];
+  int32_t* const g_n = IN_LDS ? n_lds : n_workspace;
   __shared__ int32_t ner[PROBE_MAX_EXPERTS][kPlanMaxRanks];
   __shared__ uint32_t hostmask[PROBE_MAX_EXPERTS];
-  __shared__ unsigned long long comp[kPlanMaxRanks], vin[kPlanMaxRanks], vout[kPlanMaxRanks], load[kPlanMaxRanks];
-  __shared__ long long lat[kPlanMaxRanks], t_comp[kPlanMaxRanks], t_vin[kPlanMaxRanks], t_vout[kPlanMaxRanks],
-      t_load[kPlanMaxRanks], t_lat[kPlanMaxRanks];
-  __shared__ int32_t slab_old[kPlanMaxRanks][kPlanMaxRanks], slab_new[kPlanMaxRanks][kPlanMaxRanks];
+  __shared__ long long comp[kPlanMaxRanks], vin[kPlanMaxRanks], vout[kPlanMaxRanks], load[kPlanMaxRanks];
+  // entries of ranks past R: the lowest latency there is
+  __shared__ long long lat[kPlanMaxRanks], t_lat[kPlanMaxRanks];
+  __shared__ int32_t slab_old[kPlanMaxRanks][kPlanMaxRanks + 1], slab_new[kPlanMaxRanks][kPlanMaxRanks + 1];
   __shared__ uint32_t invalid[kPlanMaxRanks];
   __shared__ int32_t n_in[kPlanMaxRanks], n_out[kPlanMaxRanks];
   __shared__ int32_t d_in[kPlanMaxRanks][kPlanMaxReplicas];
-  __shared__ long long best_key, lat_before;
+  __shared__ long long best_key[2];  // iteration i uses best_key[i & 1]
   __shared__ int32_t wave_tot[4];
   const int tid = threadIdx.x, lane = tid & 63;
 
   // ---- initial assignment: every token to the expert's home rank (baseline placement P')
   if (tid < kPlanMaxRanks) {
-    comp[tid] = vin[tid] = vout[tid] = load[tid] = 0;
+    lat[tid] = t_lat[tid] = LLONG_MIN;
     invalid[tid] = 0;
     n_in[tid] = n_out[tid] = 0;
     for (int i = 0; i < kPlanMaxReplicas; ++i) d_in[tid][i] = -1;
   }
-  __syncthreads();
+  for (int i = tid; i < kPlanMaxRanks * (kPlanMaxRanks + 1); i += 256) (&slab_old[0][0])[i] = (&slab_new[0][0])[i] = 0;
+  if (tid < 2) best_key[tid] = -1;
   if (tid < E) {
     const int e = tid, home = e / E_loc;
-    long long tot = 0;
-    for (int rs = 0; rs < R; ++rs) {
-      const int v = max(n_hat[rs * E + e], 0);
-      for (int rt = 0; rt < R; ++rt) g_n[(e * R + rs) * R + rt] = (rt == home) ? v : 0;
-      tot += v;
-      if (rs != home && v) {
-        atomicAdd(&vin[home], static_cast<unsigned long long>(v));
-        atomicAdd(&vout[rs], static_cast<unsigned long long>(v));
-      }
+    int v[kPlanMaxRanks], tot = 0;
+#pragma unroll
+    for (int rs = 0; rs < kPlanMaxRanks; ++rs) v[rs] = rs < R ? max(n_hat[rs * E + e], 0) : 0;
+#pragma unroll
+    for (int rs = 0; rs < kPlanMaxRanks; ++rs) {
+      if (rs < R)
+        for (int rt = 0; rt < R; ++rt) g_n[e * stride + rs * R + rt] = (rt == home) ? v[rs] : 0;
+      tot = static_cast<int>(static_cast<unsigned>(tot) + static_cast<unsigned>(v[rs]));
     }
-    for (int r = 0; r < R; ++r) ner[e][r] = (r == home) ? static_cast<int>(tot) : 0;
+    for (int r = 0; r < R; ++r) ner[e][r] = (r == home) ? tot : 0;
     hostmask[e] = 1u << home;
-    if (tot) {
-      atomicAdd(&comp[home], static_cast<unsigned long long>(comp_term(tot, a.n0)));
-      atomicAdd(&load[home], static_cast<unsigned long long>(tot));
-    }
   }
   for (int i = tid; i < R * a.max_replicas; i += 256) delta_in[i] = -1;
   if (delta_out)
     for (int i = tid; i < R * a.budget; i += 256) delta_out[i] = -1;
   for (int i = tid; i < a.k_max * 3; i += 256) moves[i] = -1;
   __syncthreads();
-  if (tid == 0) {
-    long long mx = 0;
-    for (int r = 0; r < R; ++r) {
-      lat[r] = a.g_den * static_cast<long long>(comp[r]) +
-               2 * a.g_num * static_cast<long long>(max(vin[r], vout[r]));
-      mx = r == 0 ? lat[r] : max(mx, lat[r]);
+  {  // aggregates: sixteen threads per rank, each over every sixteenth expert
+    const int r = tid >> 4;
+    long long s_comp = 0, s_vin = 0, s_vout = 0, s_load = 0;
+    if (r < R) {
+      for (int e = tid & 15; e < E; e += 16) {
+        const int home = __ffs(hostmask[e]) - 1;
+        const long long from_r = g_n[e * stride + r * R + home];
+        if (home == r) {
+          long long tot = 0;  // in 64 bits: all origins of one expert
+          for (int rs = 0; rs < R; ++rs) tot += g_n[e * stride + rs * R + r];
+          s_load += tot;
+          s_comp += comp_term(tot, a.n0);
+          s_vin += tot - from_r;
+        } else {
+          s_vout += from_r;
+        }
+      }
     }
-    lat_before = mx;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+      s_comp += __shfl_xor(s_comp, d, 16);
+      s_vin += __shfl_xor(s_vin, d, 16);
+      s_vout += __shfl_xor(s_vout, d, 16);
+      s_load += __shfl_xor(s_load, d, 16);
+    }
+    if ((tid & 15) == 0 && r < R) {
+      comp[r] = s_comp;
+      vin[r] = s_vin;
+      vout[r] = s_vout;
+      load[r] = s_load;
+      lat[r] = a.g_den * s_comp + 2 * a.g_num * max(s_vin, s_vout);
+    }
   }
   __syncthreads();
-  long long total = 0;
-  for (int r = 0; r < R; ++r) total += static_cast<long long>(load[r]);
+  long long total = 0, lat_before = lat[0];
+  for (int r = 0; r < R; ++r) {
+    total += load[r];
+    lat_before = max(lat_before, lat[r]);
+  }
   const long long avg = (total + R - 1) / R;
   const int cap_in = min(a.budget, a.max_replicas);
+  const int my_rs = tid / R, my_rt = tid % R;  // this thread's entry of a slab (tid < R * R)
 
   // ---- the loop of Algorithm 1; every thread follows the same control flow
   int k = 0;
   for (int guard = 0; guard < kPlanMaxMoves + kPlanMaxRanks * kPlanMaxRanks + 1; ++guard) {
     // bottleneck rank and the least-loaded helper whose pair with it is still valid (ties: lower rank)
-    int src = 0;
-    for (int r = 1; r < R; ++r)
-      if (lat[r] > lat[src]) src = r;
-    int dst = -1;
-    for (int r = 0; r < R; ++r) {
-      if (r == src || ((invalid[src] >> r) & 1u)) continue;
-      if (dst < 0 || lat[r] < lat[dst]) dst = r;
+    long long l[kPlanMaxRanks];
+#pragma unroll
+    for (int r = 0; r < kPlanMaxRanks; ++r) l[r] = lat[r];
+    int src = 0, dst = -1;
+    long long mx_old = l[0], l_dst = 0;
+#pragma unroll
+    for (int r = 1; r < kPlanMaxRanks; ++r)
+      if (l[r] > mx_old) {
+        mx_old = l[r];
+        src = r;
+      }
+    const uint32_t barred = invalid[src] | 1u << src;
+#pragma unroll
+    for (int r = 0; r < kPlanMaxRanks; ++r) {
+      if (r >= R || ((barred >> r) & 1u)) continue;
+      if (dst < 0 || l[r] < l_dst) {
+        l_dst = l[r];
+        dst = r;
+      }
     }
     if (dst < 0) break;
 
     // SelectHeavyExpert: most tokens on src among the experts src holds, dst does not, with something to move
-    if (tid == 0) best_key = -1;
-    __syncthreads();
     if (tid < E) {
       const uint32_t hm = hostmask[tid];
       if (((hm >> src) & 1u) && !((hm >> dst) & 1u)) {
         long long movable = 0;
-        for (int rs = 0; rs < R; ++rs)
-          if (rs == dst || !((hm >> rs) & 1u)) movable += g_n[(tid * R + rs) * R + src];
+#pragma unroll
+        for (int rs = 0; rs < kPlanMaxRanks; ++rs) {
+          const int v = g_n[tid * stride + min(rs, R - 1) * R + src];
+          if (rs < R && (rs == dst || !((hm >> rs) & 1u))) movable += v;
+        }
         if (movable > 0)
-          atomicMax(&best_key, (static_cast<long long>(ner[tid][src]) << 9) | static_cast<long long>(511 - tid));
+          atomicMax(&best_key[guard & 1], (static_cast<long long>(ner[tid][src]) << 9) | static_cast<long long>(511 - tid));
       }
     }
     __syncthreads();
-    const long long bk = best_key;
+    const long long bk = best_key[guard & 1];
+    if (tid == 0) best_key[(guard + 1) & 1] = -1;  // last read before the barrier above, next used after the one below
     // dual-side budget check (an empty selection is treated the same way)
     if (bk < 0 || n_out[src] >= a.budget || n_in[dst] >= cap_in) {
-      __syncthreads();  // everybody has read invalid[] and best_key
       if (tid == 0) invalid[src] |= 1u << dst;
       __syncthreads();
       continue;
     }
     const int es = 511 - static_cast<int>(bk & 511);
 
-    // WaterFillingRebalance on the expert's slab
-    if (tid < R * R) slab_new[tid / R][tid % R] = slab_old[tid / R][tid % R] = g_n[es * R * R + tid];
-    __syncthreads();
-    if (tid == 0) {
+    // WaterFillingRebalance on the expert's slab, one thread per entry
+    if (tid < R * R) {
+      const int32_t* slab = g_n + es * stride;
       const uint32_t hm = hostmask[es];
-      for (int rt = 0; rt < R; ++rt) {  // locality first: dst's own tokens come home
-        if (rt == dst) continue;
-        slab_new[dst][dst] += slab_new[dst][rt];
-        slab_new[dst][rt] = 0;
+      const int old = slab[tid];
+      int upd = old;
+      if (my_rs == dst) {  // locality first: dst's own tokens come home
+        long long row = 0;
+#pragma unroll
+        for (int q = 0; q < kPlanMaxRanks; ++q) {
+          const int v = slab[dst * R + min(q, R - 1)];
+          if (q < R) row += v;
+        }
+        upd = my_rt == dst ? static_cast<int>(row) : 0;
+      } else if ((my_rt == src || my_rt == dst) && !((hm >> my_rs) & 1u)) {
+        // origins without a copy, ascending rank, until src is down to the mean: this one gives what those before it leave
+        long long want = load[src] - slab[dst * R + src] - avg;
+#pragma unroll
+        for (int q = 0; q < kPlanMaxRanks; ++q) {
+          const int v = slab[min(q, R - 1) * R + src];
+          if (q < my_rs && q != dst && !((hm >> q) & 1u)) want -= v;
+        }
+        const int mv = static_cast<int>(max(min(static_cast<long long>(slab[my_rs * R + src]), want), 0ll));
+        upd += my_rt == dst ? mv : -mv;
       }
-      long long want = static_cast<long long>(load[src]) - slab_old[dst][src] - avg;
-      for (int rs = 0; rs < R && want > 0; ++rs) {  // origins without a copy, ascending rank
-        if (rs == dst || ((hm >> rs) & 1u)) continue;
-        const long long mv = min(static_cast<long long>(slab_new[rs][src]), want);
-        slab_new[rs][src] -= static_cast<int>(mv);
-        slab_new[rs][dst] += static_cast<int>(mv);
-        want -= mv;
-      }
+      slab_old[my_rs][my_rt] = old;
+      slab_new[my_rs][my_rt] = upd;
     }
     __syncthreads();
+    long long t_comp = 0, t_vin = 0, t_vout = 0, t_load = 0, n_ner = 0;
     if (tid < R) {  // what the move does to rank tid
       const int r = tid;
-      long long o_ner = 0, n_ner = 0, o_in = 0, n_inv = 0, o_out = 0, n_outv = 0;
-      for (int q = 0; q < R; ++q) {
-        o_ner += slab_old[q][r];
-        n_ner += slab_new[q][r];
+      long long o_ner = 0, d_in_tok = 0, d_out_tok = 0;
+#pragma unroll
+      for (int q = 0; q < kPlanMaxRanks; ++q) {  // entries past R are zero
+        const int oc = slab_old[q][r], nc = slab_new[q][r], orow = slab_old[r][q], nrow = slab_new[r][q];
+        o_ner += oc;
+        n_ner += nc;
         if (q != r) {
-          o_in += slab_old[q][r];
-          n_inv += slab_new[q][r];
-          o_out += slab_old[r][q];
-          n_outv += slab_new[r][q];
+          d_in_tok += static_cast<long long>(nc) - oc;
+          d_out_tok += static_cast<long long>(nrow) - orow;
         }
       }
-      t_comp[r] = static_cast<long long>(comp[r]) - comp_term(o_ner, a.n0) + comp_term(n_ner, a.n0);
-      t_vin[r] = static_cast<long long>(vin[r]) - o_in + n_inv;
-      t_vout[r] = static_cast<long long>(vout[r]) - o_out + n_outv;
-      t_load[r] = static_cast<long long>(load[r]) - o_ner + n_ner;
-      t_lat[r] = a.g_den * t_comp[r] + 2 * a.g_num * max(t_vin[r], t_vout[r]);
+      t_comp = comp[r] - comp_term(o_ner, a.n0) + comp_term(n_ner, a.n0);
+      t_vin = vin[r] + d_in_tok;
+      t_vout = vout[r] + d_out_tok;
+      t_load = load[r] - o_ner + n_ner;
+      t_lat[r] = a.g_den * t_comp + 2 * a.g_num * max(t_vin, t_vout);
     }
     __syncthreads();
-    long long mx_old = lat[0], mx_new = t_lat[0];
-    for (int r = 1; r < R; ++r) {
-      mx_old = max(mx_old, lat[r]);
-      mx_new = max(mx_new, t_lat[r]);
-    }
+    long long mx_new = t_lat[0];
+#pragma unroll
+    for (int r = 1; r < kPlanMaxRanks; ++r) mx_new = max(mx_new, t_lat[r]);
     if (mx_old - mx_new <= a.eps || k >= a.k_max) break;  // converged, or the iteration budget is used up
-    __syncthreads();  // every thread has read lat[] before it is overwritten
 
     // accept the move
-    if (tid < R * R) g_n[es * R * R + tid] = slab_new[tid / R][tid % R];
+    if (tid < R * R) g_n[es * stride + tid] = slab_new[my_rs][my_rt];
     if (tid < R) {
-      int s = 0;
-      for (int q = 0; q < R; ++q) s += slab_new[q][tid];
-      ner[es][tid] = s;
-      comp[tid] = static_cast<unsigned long long>(t_comp[tid]);
-      vin[tid] = static_cast<unsigned long long>(t_vin[tid]);
-      vout[tid] = static_cast<unsigned long long>(t_vout[tid]);
-      load[tid] = static_cast<unsigned long long>(t_load[tid]);
-      lat[tid] = t_lat[tid];
+      ner[es][tid] = static_cast<int>(n_ner);
+      comp[tid] = t_comp;
+      vin[tid] = t_vin;
+      vout[tid] = t_vout;
+      load[tid] = t_load;
+      lat[tid] = a.g_den * t_comp + 2 * a.g_num * max(t_vin, t_vout);
     }
     if (tid == 0) {
       if (delta_out) delta_out[src * a.budget + n_out[src]] = es;
@@ -225,7 +283,7 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
     long long mx = 0, ml = 0;
     for (int r = 0; r < R; ++r) {
       mx = r == 0 ? lat[r] : max(mx, lat[r]);
-      ml = max(ml, static_cast<long long>(load[r]));
+      ml = max(ml, load[r]);
     }
     stats[0] = lat_before;
     stats[1] = mx;
@@ -282,11 +340,32 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
     if (e == E - 1) rep_off[E] = pos;
   }
   if (n_assign) {
-    for (int i = tid; i < R * E * R; i += 256) {
-      const int rs = i / (E * R), e = (i / R) % E, rt = i % R;
-      n_assign[i] = g_n[(e * R + rs) * R + rt];
+    for (int i = tid; i < E * R; i += 256) {
+      const int e = i / R, rt = i % R;
+      for (int rs = 0; rs < R; ++rs) n_assign[static_cast<long>(rs) * E * R + i] = g_n[e * stride + rs * R + rt];
     }
   }
+}
+
+// More than 64 KB of dynamic LDS has to be opted into once per device.
+static int plan_prepare() {
+  static std::mutex mu;
+  static bool done[64] = {false};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+    set_error("probe_plan_greedy: no current device");
+    return PROBE_EHIP;
+  }
+  std::lock_guard<std::mutex> lock(mu);
+  if (done[dev]) return PROBE_OK;
+  hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(plan_greedy_kernel<true>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kPlanLdsBytes);
+  if (err != hipSuccess) {
+    set_error("probe_plan_greedy: cannot reserve %d bytes of LDS: %s", kPlanLdsBytes, hipGetErrorString(err));
+    return PROBE_EHIP;
+  }
+  done[dev] = true;
+  return PROBE_OK;
 }
 
 // The plan as source rank `rank` applies it to its own tokens: one slot per (destination rank, expert
@@ -422,8 +501,14 @@ extern "C" int probe_plan_greedy(const int32_t* n_hat, int R, int E, int E_loc, 
   a.R = R; a.E = E; a.E_loc = E_loc; a.rank = rank;
   a.max_replicas = params->max_replicas; a.budget = params->budget; a.k_max = params->k_max;
   a.eps = params->eps; a.n0 = params->n0; a.g_num = params->g_num; a.g_den = params->g_den;
-  hipLaunchKernelGGL(plan_greedy_kernel, dim3(1), dim3(256), 0, static_cast<hipStream_t>(stream), n_hat, a,
-                     static_cast<int32_t*>(workspace), rep_off, rep_slot, rep_weight, slot_expert, delta_in, delta_out,
-                     moves, reinterpret_cast<long long*>(stats), n_assign);
+  const bool in_lds = plan_fits_lds(R, E);
+  if (in_lds) {
+    int rc = plan_prepare();
+    if (rc != PROBE_OK) return rc;
+  }
+  const size_t lds = in_lds ? static_cast<size_t>(E) * plan_slab_stride(R, true) * sizeof(int32_t) : 0;
+  hipLaunchKernelGGL(in_lds ? plan_greedy_kernel<true> : plan_greedy_kernel<false>, dim3(1), dim3(256), lds,
+                     static_cast<hipStream_t>(stream), n_hat, a, static_cast<int32_t*>(workspace), rep_off, rep_slot,
+                     rep_weight, slot_expert, delta_in, delta_out, moves, reinterpret_cast<long long*>(stats), n_assign);
   return check_launch("probe_plan_greedy");
 }

@@ -64,6 +64,17 @@ def test_planner_matches_oracle_bit_for_bit(oracle, probe, seed, R, E, E_loc, co
         assert o["n_moves"] >= 2          # the cases exercise the loop, not only its exit
 
 
+@pytest.mark.parametrize("R,E,E_loc", [(11, 256, 24), (12, 256, 22), (16, 135, 9), (16, 136, 9), (5, 250, 50)])
+def test_planner_on_both_sides_of_the_assignment_in_lds(oracle, probe, R, E, E_loc):
+    """The largest assignments that lie in LDS and the smallest that lie in the workspace; budgets that run out, so that
+    pairs become invalid between moves."""
+    print("case planner R=%d E=%d" % (R, E), flush=True)
+    for seed, budget in ((11, 1), (12, 8)):
+        o = _compare(probe, oracle, _random_nhat(seed, R, E, scale=3000, zipf=1.4), E_loc, ranks=[R - 1], max_replicas=budget,
+                     budget=budget, k_max=64, n0=64, g_num=1, g_den=4)
+        assert o["n_moves"] >= 2
+
+
 def test_planner_hand_worked_example_and_limits(oracle, probe):
     """The three-rank example worked out by hand in the oracle's pins, then the exits of the loop."""
     nh = np.array([[20, 0, 0], [30, 10, 0], [40, 0, 10]], np.int32)
