@@ -15,8 +15,9 @@
 //         n[e][rs][rt]  the assignment, expert-major: a move rewrites one R x R slab.  It lies in LDS where it fits
 //                     (kPlanLdsBytes: every R <= 11, 16 ranks up to 135 experts), otherwise in the workspace.
 // What bounds it is latency: an iteration is a chain of dependent reads and barriers on one CU.  Slabs in LDS, values
-// of all ranks read side by side into registers (unrolled to kPlanMaxRanks), one thread per slab entry for the
-// water-filling and four barriers per accepted move instead of eight: 8 ranks, 128 experts, 3 replicas 73 -> 53 us.
+// read side by side, one thread per slab entry for the water-filling and four barriers per accepted move: 8 ranks, 128
+// experts, 3 replicas 73 -> 53 us.  Bottleneck, helper and new latencies as reductions over the sixteen lanes of a DPP row
+// instead of chains over the ranks in every thread: 53 -> 39 us.
 // Per iteration only SelectHeavyExpert looks at every expert (one thread each, block arg-max by a
 // 64-bit LDS atomic).  All arithmetic is integer, so the plan is bit-identical to the sequential definition.
 //
@@ -49,6 +50,24 @@ constexpr int kPlanLdsBytes = 136 * 1024;
 // neighbouring experts are on different banks.
 __host__ __device__ constexpr int plan_slab_stride(int R, bool in_lds) { return R * R + (in_lds ? 1 : 0); }
 static bool plan_fits_lds(int R, int E) { return E * plan_slab_stride(R, true) * 4 <= kPlanLdsBytes; }
+
+// Reductions over the sixteen lanes of a DPP row; every lane gets the result.  All lanes of the wave take part.
+template <int N>
+__device__ __forceinline__ long long row_ror64(long long v) {
+  const unsigned lo = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x120 | N, 0xf, 0xf, false));
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(v >> 32), 0x120 | N, 0xf, 0xf, false);
+  return static_cast<long long>(static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32 | lo);
+}
+template <typename Op>
+__device__ __forceinline__ long long row_reduce64(long long v, Op op) {
+  v = op(v, row_ror64<8>(v));
+  v = op(v, row_ror64<4>(v));
+  v = op(v, row_ror64<2>(v));
+  return op(v, row_ror64<1>(v));
+}
+__device__ __forceinline__ long long row_sum64(long long v) { return row_reduce64(v, [](long long a, long long b) { return a + b; }); }
+__device__ __forceinline__ long long row_max64(long long v) { return row_reduce64(v, [](long long a, long long b) { return max(a, b); }); }
+__device__ __forceinline__ long long row_min64(long long v) { return row_reduce64(v, [](long long a, long long b) { return min(a, b); }); }
 
 template <bool IN_LDS>
 __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restrict__ n_hat, PlannerArgs a,
@@ -121,13 +140,10 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
         }
       }
     }
-#pragma unroll
-    for (int d = 1; d < 16; d <<= 1) {
-      s_comp += __shfl_xor(s_comp, d, 16);
-      s_vin += __shfl_xor(s_vin, d, 16);
-      s_vout += __shfl_xor(s_vout, d, 16);
-      s_load += __shfl_xor(s_load, d, 16);
-    }
+    s_comp = row_sum64(s_comp);
+    s_vin = row_sum64(s_vin);
+    s_vout = row_sum64(s_vout);
+    s_load = row_sum64(s_load);
     if ((tid & 15) == 0 && r < R) {
       comp[r] = s_comp;
       vin[r] = s_vin;
@@ -145,31 +161,22 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
   const long long avg = (total + R - 1) / R;
   const int cap_in = min(a.budget, a.max_replicas);
   const int my_rs = tid / R, my_rt = tid % R;  // this thread's entry of a slab (tid < R * R)
+  const int rank_of = tid >> 4, partner = tid & 15;
+  const bool writes_rank = partner == 0 && rank_of < R;
 
   // ---- the loop of Algorithm 1; every thread follows the same control flow
   int k = 0;
   for (int guard = 0; guard < kPlanMaxMoves + kPlanMaxRanks * kPlanMaxRanks + 1; ++guard) {
     // bottleneck rank and the least-loaded helper whose pair with it is still valid (ties: lower rank)
-    long long l[kPlanMaxRanks];
-#pragma unroll
-    for (int r = 0; r < kPlanMaxRanks; ++r) l[r] = lat[r];
-    int src = 0, dst = -1;
-    long long mx_old = l[0], l_dst = 0;
-#pragma unroll
-    for (int r = 1; r < kPlanMaxRanks; ++r)
-      if (l[r] > mx_old) {
-        mx_old = l[r];
-        src = r;
-      }
-    const uint32_t barred = invalid[src] | 1u << src;
-#pragma unroll
-    for (int r = 0; r < kPlanMaxRanks; ++r) {
-      if (r >= R || ((barred >> r) & 1u)) continue;
-      if (dst < 0 || l[r] < l_dst) {
-        l_dst = l[r];
-        dst = r;
-      }
-    }
+    const int lr = lane & 15;  // a lane looks at one rank
+    const long long l = lat[lr];
+    const uint32_t inv = invalid[lr];
+    const long long mx_old = row_max64(l);
+    const int src = __ffsll(__ballot(l == mx_old)) - 1;
+    const uint32_t barred = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inv), src)) | 1u << src;
+    const bool free_pair = lr < R && !((barred >> lr) & 1u);
+    const long long mn = row_min64(free_pair ? l : LLONG_MAX);
+    const int dst = __ffsll(__ballot(free_pair && l == mn)) - 1;
     if (dst < 0) break;
 
     // SelectHeavyExpert: most tokens on src among the experts src holds, dst does not, with something to move
@@ -226,41 +233,34 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
       slab_new[my_rs][my_rt] = upd;
     }
     __syncthreads();
-    long long t_comp = 0, t_vin = 0, t_vout = 0, t_load = 0, n_ner = 0;
-    if (tid < R) {  // what the move does to rank tid
-      const int r = tid;
-      long long o_ner = 0, d_in_tok = 0, d_out_tok = 0;
-#pragma unroll
-      for (int q = 0; q < kPlanMaxRanks; ++q) {  // entries past R are zero
-        const int oc = slab_old[q][r], nc = slab_new[q][r], orow = slab_old[r][q], nrow = slab_new[r][q];
-        o_ner += oc;
-        n_ner += nc;
-        if (q != r) {
-          d_in_tok += static_cast<long long>(nc) - oc;
-          d_out_tok += static_cast<long long>(nrow) - orow;
-        }
-      }
-      t_comp = comp[r] - comp_term(o_ner, a.n0) + comp_term(n_ner, a.n0);
-      t_vin = vin[r] + d_in_tok;
-      t_vout = vout[r] + d_out_tok;
-      t_load = load[r] - o_ner + n_ner;
-      t_lat[r] = a.g_den * t_comp + 2 * a.g_num * max(t_vin, t_vout);
+    // what the move does to rank `rank_of`: sixteen threads, one per partner (entries past R are zero)
+    const int oc = slab_old[partner][rank_of], nc = slab_new[partner][rank_of];
+    const long long o_ner = row_sum64(oc), n_ner = row_sum64(nc);
+    const long long in_change = row_sum64(partner != rank_of ? static_cast<long long>(nc) - oc : 0ll);
+    const long long out_change = row_sum64(
+        partner != rank_of ? static_cast<long long>(slab_new[rank_of][partner]) - slab_old[rank_of][partner] : 0ll);
+    long long t_comp = 0, t_vin = 0, t_vout = 0, t_load = 0, t_l = 0;
+    if (writes_rank) {
+      t_comp = comp[rank_of] - comp_term(o_ner, a.n0) + comp_term(n_ner, a.n0);
+      t_vin = vin[rank_of] + in_change;
+      t_vout = vout[rank_of] + out_change;
+      t_load = load[rank_of] - o_ner + n_ner;
+      t_l = a.g_den * t_comp + 2 * a.g_num * max(t_vin, t_vout);
+      t_lat[rank_of] = t_l;
     }
     __syncthreads();
-    long long mx_new = t_lat[0];
-#pragma unroll
-    for (int r = 1; r < kPlanMaxRanks; ++r) mx_new = max(mx_new, t_lat[r]);
+    const long long mx_new = row_max64(t_lat[lane & 15]);
     if (mx_old - mx_new <= a.eps || k >= a.k_max) break;  // converged, or the iteration budget is used up
 
     // accept the move
     if (tid < R * R) g_n[es * stride + tid] = slab_new[my_rs][my_rt];
-    if (tid < R) {
-      ner[es][tid] = static_cast<int>(n_ner);
-      comp[tid] = t_comp;
-      vin[tid] = t_vin;
-      vout[tid] = t_vout;
-      load[tid] = t_load;
-      lat[tid] = a.g_den * t_comp + 2 * a.g_num * max(t_vin, t_vout);
+    if (writes_rank) {
+      ner[es][rank_of] = static_cast<int>(n_ner);
+      comp[rank_of] = t_comp;
+      vin[rank_of] = t_vin;
+      vout[rank_of] = t_vout;
+      load[rank_of] = t_load;
+      lat[rank_of] = t_l;
     }
     if (tid == 0) {
       if (delta_out) delta_out[src * a.budget + n_out[src]] = es;
