@@ -5,7 +5,7 @@
 //   2. gemm2     y[r, n] = h[r] . W2[n]                                  (K = F)
 //
 // Both GEMMs are "NT": activations [rows, K] and weights [out, K] are K-contiguous, which is
-// the 8-consecutive-k-per-lane operand layout of v_mfma_f32_32x32x16_bf16, so an MFMA operand
+// the 8-consecutive-k-per-lane operand layout of v_mfma_f32_16x16x32_bf16, so an MFMA operand
 // is one 16-byte LDS read.
 //
 // One workgroup = 8 waves (2 x 4) computes a 256 x 256 output tile (320, 192, 128 or 64 rows x 256
