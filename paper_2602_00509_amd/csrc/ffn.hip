@@ -640,9 +640,21 @@ constexpr int kSkinnySplitSteps = 64;    // k-steps from which a contraction may
 constexpr int kSkinnyFewItems = 512;     // items at capacity up to which tiles can be few
 constexpr size_t kSkinnyPartialBytes = static_cast<size_t>(kSkinnyItems) * 64 * 128 * sizeof(float);
 
-// how many items the capacity of the row space allows: every 64 rows of it and every slot can give a tile
-static bool skinny_may_split(int max_tiles, int n_cols, int steps) {
-  return steps >= kSkinnySplitSteps && static_cast<long>(max_tiles) * n_cols <= kSkinnyFewItems;
+// most row tiles that max_rows rows in S slots can give: every tile has a row, every slot one tile that is not full
+static int skinny_max_tiles(int S, int max_rows) {
+  return std::min<long>(max_rows, (static_cast<long>(max_rows) + 63l * S) / 64);
+}
+// Whether the contraction of `steps` k-steps, over n_cols column blocks, may be cut: few items at capacity, and a cut
+// that is still possible if every slot that probably holds rows does.  Most of the capacity is as a rule other ranks' (one
+// token, eight experts, one of them local, 36 slots of 7168 x 2048: FFN 70.9 -> 36.7 us; eight slots of 7168 x 256, 421 of 3200
+// rows local: 68.8 -> 45.2; all eight experts local: 127.1 / 125.4).  But with kSkinnyFullRows rows of capacity per slot nearly
+// every slot holds one, and where S tiles alone leave no second piece the launch of the adding kernel would be lost (12 slots
+// of 5632 x 1408, 480 rows of capacity, five in each: 133.5 without, 137.2 with it).
+constexpr int kSkinnyFullRows = 8;
+static bool skinny_may_split(int S, int max_rows, int n_cols, int steps) {
+  if (steps < kSkinnySplitSteps || static_cast<long>(skinny_max_tiles(S, max_rows)) * n_cols > kSkinnyFewItems) return false;
+  const bool every_slot = max_rows >= static_cast<long>(kSkinnyFullRows) * S;
+  return !every_slot || static_cast<long>(S) * n_cols <= kSkinnyItems / 2;
 }
 // k-steps per piece, for n_tiles row tiles of n_cols column blocks; steps: the whole contraction
 __device__ __forceinline__ int skinny_steps(int n_tiles, int n_cols, int steps) {
@@ -971,10 +983,11 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
   if (sh.skinny) {
     float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + sh.h_bytes + sh.table_bytes);
     bf16_t* y = static_cast<bf16_t*>(y_bf16);
-    const int tiles = std::min(sh.max_tiles, max_rows);  // a tile has at least one row
+    const int tiles = skinny_max_tiles(S, max_rows);
     const int n1 = (F + kSkinnyCols1 - 1) / kSkinnyCols1, n2 = (H + kSkinnyCols2 - 1) / kSkinnyCols2;
     const bool room = workspace_bytes >= sh.h_bytes + sh.table_bytes + sh.partial_bytes;
-    const int split1 = room && skinny_may_split(tiles, n1, H / FBK), split2 = room && skinny_may_split(tiles, n2, F / FBK);
+    const int split1 = room && skinny_may_split(S, max_rows, n1, H / FBK);
+    const int split2 = room && skinny_may_split(S, max_rows, n2, F / FBK);
     // a split call has at most kSkinnyItems items, one that is not split tiles * n
     const dim3 g1(split1 ? std::max(tiles * n1, kSkinnyItems) : tiles * n1);
     const dim3 g2(split2 ? std::max(tiles * n2, kSkinnyItems) : tiles * n2);

@@ -334,6 +334,28 @@ def test_ffn_few_tiles_every_element(oracle, probe, G, sizes, H, F):
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, len(sizes), seed=H + F, extra_rows=0 if sizes == [1] else 9)
 
 
+def test_ffn_contraction_is_not_cut_where_every_slot_can_hold_rows(oracle, probe, G):
+    """At 40 rows of capacity per slot no adding kernel is launched although one slot alone holds rows: the call gives the
+    same bits with and without room for partial sums.  Every element against the oracle."""
+    cfg = wl.small_config(T=64, H=4096, E=4, k=2, F=1408, cid=103)
+    S, cap, n = 12, 480, 3
+    w13, w2 = wl.expert_weights_many(cfg, [0])[0]
+    d13, d2 = G.dev_bf16(w13), G.dev_bf16(w2)
+    tab = probe.WeightTable([d13] * S, [d2] * S)
+    x = np.zeros((cap, cfg.H), np.uint16)
+    x[:n] = wl.f32_to_bf16_bits(np.random.default_rng(4).standard_normal((n, cfg.H)).astype(np.float32))
+    so = torch.tensor([0] * 5 + [n] * (S - 4), dtype=torch.int32, device="cuda")
+    need = probe.grouped_ffn_workspace_bytes(S, cfg.H, cfg.F, cap)
+    print("case no cut", S, cap, flush=True)
+    ys = [probe.grouped_ffn(G.dev_bf16(x), so, tab, workspace=torch.empty(b, dtype=torch.uint8, device="cuda"))[:n]
+          for b in (need, need - 256 * 64 * 128 * 4)]
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1])
+    off = np.array([0] * 5 + [n] * (S - 4), np.int32)
+    ref = oracle.grouped_ffn(x[:n], off, [w13] * S, [w2] * S)
+    assert G.rel_err(G.f64_of(ys[0]), ref) < G.BF16_RTOL
+
+
 @pytest.mark.parametrize("sizes", [
     [700, 5, 300, 0, 64, 130, 193, 20, 1, 33, 70, 200, 9, 3, 2, 1, 40, 321, 12, 450],   # 23 tiles, 8 of them tall
     [320] * 8 + [0, 256] + [250] * 7 + [192, 1, 65],                                    # 19 tiles, 16 of them tall: the limit
