@@ -863,15 +863,20 @@ struct FfnShape {
 };
 
 // The decode schedule is chosen on the host from the capacity of the row space alone (the row counts live
-// on the device): at most kSkinnyRowsPerSlot rows per slot on average even if every pair were local, or so few tiles
-// that even 64-row ones leave the chip half empty (a shared expert's single slot).
+// on the device): at most kSkinnyRowsPerSlot rows per slot on average even if every pair were local, or so few items
+// that 64-row tiles give gemm1 at most two to a CU (a shared expert's single slot).  gemm2 may then have many more and still
+// gains, up to kSkinnyFewItems2.  One slot, tall tiles / this schedule: 454 rows of 7168 x 2048 176 / 84 us, 4000 of 7168 x 512
+// 200 / 144, 15000 of 4096 x 128 145 / 122, 16000 of 32768 x 64 (64256 items of gemm2) 959 / 743, 32000 of it (128256) 1208 / 1501.
 constexpr int kSkinnyRowsPerSlot = 64;
+constexpr int kSkinnyFewItems2 = 65536;
+static_assert(kSkinnyFewItems2 * 512ll < (1ll << 32), "threads of one launch");
 
-static FfnShape ffn_shape(int S, int F, int max_rows) {
+static FfnShape ffn_shape(int S, int H, int F, int max_rows) {
   FfnShape s;
   const bool short_slots = static_cast<long>(max_rows) <= static_cast<long>(kSkinnyRowsPerSlot) * S;
-  s.skinny = short_slots ||
-             (static_cast<long>(max_rows) / 64 + S) * ((F + kSkinnyCols1 - 1) / kSkinnyCols1) <= kSkinnyFewItems;
+  const long tiles = static_cast<long>(max_rows) / 64 + S;
+  s.skinny = short_slots || (tiles * ((F + kSkinnyCols1 - 1) / kSkinnyCols1) <= kSkinnyFewItems &&
+                             tiles * ((H + kSkinnyCols2 - 1) / kSkinnyCols2) <= kSkinnyFewItems2);
   s.max_tiles = s.skinny ? max_rows / 64 + S : max_rows / 256 + S;
   const int table_tiles = short_slots ? max_rows / 64 + S : max_rows / 256 + S;
   s.h_bytes = align_up(static_cast<size_t>(max_rows > 0 ? max_rows : 1) * F * sizeof(bf16_t), 256);
@@ -930,9 +935,8 @@ static int ffn_prepare(int* cus) {
 }  // namespace probe
 
 extern "C" size_t probe_grouped_ffn_workspace_bytes(int S, int H, int F, int max_rows) {
-  (void)H;
   if (S <= 0 || F <= 0 || max_rows < 0) return 0;
-  probe::FfnShape s = probe::ffn_shape(S, F, max_rows);
+  probe::FfnShape s = probe::ffn_shape(S, H, F, max_rows);
   return s.h_bytes + s.table_bytes + s.partial_bytes;
 }
 
@@ -962,7 +966,7 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
   PROBE_REQUIRE(act_bf16 && slot_offsets && w13_ptrs && w2_ptrs && y_bf16, PROBE_EINVAL, "%s: null pointer", name);
   PROBE_REQUIRE(aligned16(act_bf16) && aligned16(y_bf16), PROBE_EALIGN,
                 "%s: activations and y must be 16-byte aligned", name);
-  FfnShape sh = ffn_shape(S, F, max_rows);
+  FfnShape sh = ffn_shape(S, H, F, max_rows);
   PROBE_REQUIRE(workspace && aligned16(workspace) && workspace_bytes >= sh.h_bytes + sh.table_bytes,
                 PROBE_EWORKSPACE, "%s: workspace too small or misaligned (%zu < %zu)", name, workspace_bytes,
                 sh.h_bytes + sh.table_bytes);
