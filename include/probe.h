@@ -266,6 +266,13 @@ int probe_permute_static(const int32_t* topk_idx, const probe_plan* plan, const 
  * GEMMs, bf16 output.  An empty slot does no work and its weights are not read.
  * Limits: H % 64 == 0, F % 64 == 0, H and F at most 2^21, 1 <= S <= 1024, one expert's w13 below
  * 2 GiB.
+ *
+ * The workspace query returns the most that a call of up to max_rows rows can use: a workspace sized for
+ * the largest batch serves every smaller one, at its full speed.  Where few rows leave most of the chip
+ * idle, a long contraction is summed in pieces whose fp32 sums lie in the workspace (8 MB of it, asked
+ * for only where H or F is long enough).  A workspace that lacks just that room is accepted as well; the
+ * contraction is then summed in one piece, and low bits of y can differ, as they can between two values
+ * of max_rows.  The same call repeats bit for bit.
  */
 size_t probe_grouped_ffn_workspace_bytes(int S, int H, int F, int max_rows);
 

@@ -651,7 +651,7 @@ static int skinny_max_tiles(int S, int max_rows) {
 // every slot holds one, and where S tiles alone leave no second piece the launch of the adding kernel would be lost (12 slots
 // of 5632 x 1408, 480 rows of capacity, five in each: 133.5 without, 137.2 with it).
 constexpr int kSkinnyFullRows = 8;
-static bool skinny_may_split(int S, int max_rows, int n_cols, int steps) {
+static bool skinny_may_split(int S, int max_rows, int n_cols, int steps) {  // if it holds, it holds for fewer rows too
   if (steps < kSkinnySplitSteps || static_cast<long>(skinny_max_tiles(S, max_rows)) * n_cols > kSkinnyFewItems) return false;
   const bool every_slot = max_rows >= static_cast<long>(kSkinnyFullRows) * S;
   return !every_slot || static_cast<long>(S) * n_cols <= kSkinnyItems / 2;
@@ -859,7 +859,7 @@ struct FfnShape {
   bool skinny;  // the decode schedule
   int max_tiles;
   size_t h_bytes, table_bytes;
-  size_t partial_bytes;  // not demanded: a workspace without this room (one sized for another max_rows) runs unsplit
+  size_t partial_bytes;  // room that cutting the contraction takes; not demanded: without it the call runs uncut
 };
 
 // The decode schedule is chosen on the host from the capacity of the row space alone (the row counts live
@@ -883,6 +883,19 @@ static FfnShape ffn_shape(int S, int H, int F, int max_rows) {
   s.table_bytes = align_up(kTableHeaderInts * sizeof(int32_t) + static_cast<size_t>(table_tiles) * sizeof(TileEntry), 256);
   s.partial_bytes = s.skinny ? kSkinnyPartialBytes : 0;
   return s;
+}
+
+// What the workspace query returns: the most that any call of up to max_rows rows can use, so that a workspace sized for the
+// largest batch serves every smaller one, at its full speed, and the query does not fall as max_rows grows.  h grows with the rows;
+// the tile table is longest at the last row count of the 64-row tiles; pieces of K are smallest calls' business.
+static size_t ffn_query_bytes(int S, int H, int F, int max_rows) {
+  size_t bytes = ffn_shape(S, H, F, max_rows).h_bytes;
+  const int short_rows = static_cast<int>(std::min<long>(max_rows, static_cast<long>(kSkinnyRowsPerSlot) * S));
+  bytes += std::max(ffn_shape(S, H, F, short_rows).table_bytes, ffn_shape(S, H, F, max_rows).table_bytes);
+  if (max_rows > 0 && (skinny_may_split(S, 1, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK) ||
+                       skinny_may_split(S, 1, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK)))
+    bytes += kSkinnyPartialBytes;
+  return bytes;
 }
 
 // The GEMM kernels use 144 KB of dynamic LDS, which has to be opted into once per device.  *cus receives
@@ -936,8 +949,7 @@ static int ffn_prepare(int* cus) {
 
 extern "C" size_t probe_grouped_ffn_workspace_bytes(int S, int H, int F, int max_rows) {
   if (S <= 0 || F <= 0 || max_rows < 0) return 0;
-  probe::FfnShape s = probe::ffn_shape(S, H, F, max_rows);
-  return s.h_bytes + s.table_bytes + s.partial_bytes;
+  return probe::ffn_query_bytes(S, H, F, max_rows);
 }
 
 namespace probe {
