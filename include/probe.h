@@ -39,8 +39,9 @@
  *     before anything is launched; a failing call launches nothing.
  *     probe_last_error_string() describes the last failure on the calling thread.
  *   - `workspace` is device scratch of at least probe_<name>_workspace_bytes(...) bytes; its
- *     contents are undefined on entry and on return.  Calls that share a workspace must be
- *     ordered on one stream.
+ *     contents are undefined on entry and on return.  The router, predictor and FFN queries never
+ *     fall as T or max_rows grows: one workspace, sized for the largest batch, serves every smaller
+ *     one.  Calls that share a workspace must be ordered on one stream.
  *
  * Vocabulary: T tokens, H hidden size, E routed experts, k experts per token, F expert FFN
  * width, S weight slots on this GPU (one expert copy each), pair p = t*k + s (token t,

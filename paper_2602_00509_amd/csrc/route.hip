@@ -968,9 +968,9 @@ struct RouteShape {
   bool dma;  // H % 64 == 0: the DMA-to-LDS pipeline; otherwise the register-staged kernel
   int bm;    // tokens per workgroup of the gemm (128 or 256)
   int mt, nt, ks, k_chunk;
-  int ks_room;      // slices that the workspace has room for: those of the tiled kernels, which the direct one never exceeds.
-                    // Its own count falls steeply with T, and a workspace sized for more tokens has to serve fewer.
-  int ld;           // entries of a row of partial sums: E rounded up to whole 16-byte pieces (the last ones are not read)
+  int ks_room;      // slices that the workspace has room for: those of the tiled kernels, which the direct one never exceeds
+  int ld;           // entries of a row of partial sums: E rounded up to whole 16-byte pieces (the last ones are read as part
+                    // of a piece and not looked at)
   bool direct;      // gate_direct_kernel: `frags` fragments of 16 tokens per workgroup, `per_wave` k32 per wave
   int frags, per_wave;
   size_t planes_bytes, partial_bytes;
@@ -983,24 +983,32 @@ struct RouteShape {
 constexpr int kDirectLogits = 32768, kDirectExperts = 16;
 
 constexpr int kMaxSplitK = 16;
+constexpr int kResidSplitK = 4;  // second layer of the residual: the softmax kernel reads every slice
+
+// k-steps per slice of the tiled kernels, `want` slices wished for
+static int gate_slice_steps(int ksteps, int want, int max_split) {
+  if (want > max_split) want = max_split;  // the softmax kernel adds the slices one after another
+  if (want > ksteps) want = ksteps;
+  if (want < 1) want = 1;
+  return (ksteps + want - 1) / want;
+}
+// 256-token tiles when a split of 8 or less still gives every CU a workgroup; they aim at one
+// workgroup per CU (fewer, longer K ranges and half the partial sums), 128-token tiles at two
+constexpr int kBigTileItems = 32;
+static bool gate_dma(int H, int E) { return H % 64 == 0 && static_cast<size_t>(3) * E * H * 2 <= 0x7fffffffull; }
+static int gate_target(int bm) { return bm == 256 ? 256 : 512; }
 
 static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
   RouteShape s;
-  // 256-token tiles when a split of 8 or less still gives every CU a workgroup; they aim at one
-  // workgroup per CU (fewer, longer K ranges and half the partial sums), 128-token tiles at two
-  s.dma = H % 64 == 0 && static_cast<size_t>(3) * E * H * 2 <= 0x7fffffffull;
+  s.dma = gate_dma(H, E);
   s.nt = (E + GBN - 1) / GBN;
   s.ld = (E + 3) & ~3;
-  s.bm = (s.dma && static_cast<long>((T + 255) / 256) * s.nt * 8 >= 256) ? 256 : GBM;
+  s.bm = (s.dma && static_cast<long>((T + 255) / 256) * s.nt >= kBigTileItems) ? 256 : GBM;
   s.mt = (T + s.bm - 1) / s.bm;
   int tiles = s.mt * s.nt;
   int ksteps = (H + GBK - 1) / GBK;
-  const int target = s.bm == 256 ? 256 : 512;
-  int want = tiles > 0 ? (target + tiles - 1) / tiles : 1;
-  if (want < 1) want = 1;
-  if (want > max_split) want = max_split;  // the softmax kernel adds the slices one after another
-  if (want > ksteps) want = ksteps;
-  int steps_per = (ksteps + want - 1) / want;
+  const int target = gate_target(s.bm);
+  const int steps_per = gate_slice_steps(ksteps, tiles > 0 ? (target + tiles - 1) / tiles : 1, max_split);
   s.k_chunk = steps_per * GBK;
   s.ks = (ksteps + steps_per - 1) / steps_per;
   s.ks_room = s.ks;
@@ -1081,7 +1089,7 @@ static RouteLayout route_layout(int T, int H, int E, int D, bool packed = false)
   int extra = 0;
   if (D > 0) {
     L.resid = route_shape(T, H, D);
-    L.resid2 = route_shape(T, 3 * D, E, 4);  // few slices: the softmax kernel reads every one of them
+    L.resid2 = route_shape(T, 3 * D, E, kResidSplitK);
     L.upartial_bytes = L.resid.partial_bytes;
     L.a_bytes = align_up(static_cast<size_t>(T > 0 ? T : 1) * 3 * D * sizeof(bf16_t), 256);
     L.b_bytes = L.resid2.planes_bytes;
@@ -1090,6 +1098,37 @@ static RouteLayout route_layout(int T, int H, int E, int D, bool packed = false)
   L.partial_bytes = align_up((L.gate.ks_room + extra) * plane, 256);
   L.total = L.gate.planes_bytes + L.partial_bytes + L.upartial_bytes + L.a_bytes + L.b_bytes;
   return L;
+}
+
+// The most slices x tokens (ks_room * T') over all T' <= T.  A tiled GEMM's slice count falls in steps as T grows, and a
+// workspace sized for T has to serve every smaller batch: 7168 x 256 experts demands 46.7 MB for 2176 tokens, 42.2 for 2177.
+// For each number of slices wished for, the largest batch that still gets it; in either range of tile heights.
+static size_t most_slice_tokens(int T, int H, int E, int max_split) {
+  const int nt = (E + GBN - 1) / GBN, ksteps = (H + GBK - 1) / GBK;
+  const int first_big = gate_dma(H, E) ? 256 * ((kBigTileItems + nt - 1) / nt - 1) + 1 : INT_MAX;  // batch of 256-token tiles
+  size_t most = 1;
+  for (const int bm : {GBM, 256}) {
+    const int lo = bm == 256 ? first_big : 1, hi = bm == 256 ? T : std::min(T, first_big - 1);
+    for (int want = max_split; want >= 1 && lo <= hi; --want) {
+      // up to (target - 1) / (want - 1) tiles wish for `want` slices or more
+      const int t = want == 1 ? hi : std::min(hi, (gate_target(bm) - 1) / (want - 1) / nt * bm);
+      const int steps = gate_slice_steps(ksteps, want, max_split);
+      if (t >= lo) most = std::max(most, static_cast<size_t>(t) * ((ksteps + steps - 1) / steps));
+      if (t == hi) break;  // fewer slices of as many tokens
+    }
+  }
+  return most;
+}
+
+// What the workspace queries return: room for any batch of up to T tokens.
+static size_t route_query_bytes(int T, int H, int E, int D, bool packed = false) {
+  const RouteLayout L = route_layout(T, H, E, D, packed);
+  size_t rows = most_slice_tokens(T, H, E, kMaxSplitK), u_bytes = 0;
+  if (D > 0) {
+    rows += most_slice_tokens(T, 3 * D, E, kResidSplitK);
+    u_bytes = align_up(most_slice_tokens(T, H, D, kMaxSplitK) * L.resid.ld * sizeof(float), 256);
+  }
+  return L.gate.planes_bytes + align_up(rows * L.gate.ld * sizeof(float), 256) + u_bytes + L.a_bytes + L.b_bytes;
 }
 
 // Router (w1_hat == nullptr) or predictor with the residual MLP of Eq. 7 (w1_hat bf16 [D,H],
@@ -1306,7 +1345,7 @@ static int route_predict_impl(const void* x_bf16, const float* w_gate, const flo
 extern "C" size_t probe_route_topk_workspace_bytes(int T, int H, int E, int k) {
   (void)k;
   if (T < 0 || H <= 0 || E <= 0) return 0;
-  return probe::route_layout(T, H, E, 0).total;
+  return probe::route_query_bytes(T, H, E, 0);
 }
 
 extern "C" size_t probe_predict_topk_workspace_bytes(int T, int H, int E, int k) {
@@ -1316,7 +1355,7 @@ extern "C" size_t probe_predict_topk_workspace_bytes(int T, int H, int E, int k)
 extern "C" size_t probe_predict_topk_residual_workspace_bytes(int T, int H, int E, int k, int D) {
   (void)k;
   if (T < 0 || H <= 0 || E <= 0 || D <= 0) return 0;
-  return probe::route_layout(T, H, E, D).total;
+  return probe::route_query_bytes(T, H, E, D);
 }
 
 extern "C" int probe_route_topk(const void* x_bf16, const float* w_gate, const float* bias,
@@ -1373,7 +1412,7 @@ extern "C" int probe_predict_topk_residual(const void* h_prev_bf16, const float*
 extern "C" size_t probe_route_predict_topk_workspace_bytes(int T, int H, int E, int k) {
   (void)k;
   if (T < 0 || H <= 0 || E <= 0) return 0;
-  return probe::route_layout(T, H, 2 * E, 0).total;
+  return probe::route_query_bytes(T, H, 2 * E, 0);
 }
 
 extern "C" int probe_route_predict_topk(const void* x_bf16, const float* w_gate, const float* bias,
@@ -1417,7 +1456,7 @@ extern "C" int probe_pack_gate(const float* w_gate, int H, int E, int stack_rows
 extern "C" size_t probe_route_topk_packed_workspace_bytes(int T, int H, int E, int k) {
   (void)k;
   if (T < 0 || H <= 0 || E <= 0) return 0;
-  return probe::route_layout(T, H, E, 0, true).total;
+  return probe::route_query_bytes(T, H, E, 0, true);
 }
 
 extern "C" int probe_route_topk_packed(const void* x_bf16, const void* packed_gate, const float* bias,
@@ -1458,7 +1497,7 @@ extern "C" int probe_route_grouped_packed(const void* x_bf16, const void* packed
 extern "C" size_t probe_route_predict_topk_packed_workspace_bytes(int T, int H, int E, int k) {
   (void)k;
   if (T < 0 || H <= 0 || E <= 0) return 0;
-  return probe::route_layout(T, H, 2 * E, 0, true).total;
+  return probe::route_query_bytes(T, H, 2 * E, 0, true);
 }
 
 extern "C" int probe_route_predict_topk_packed(const void* x_bf16, const void* packed_stack, const float* bias,

@@ -45,15 +45,34 @@ def test_workspace_sizes(L):
     assert probe.grouped_ffn_workspace_bytes(36, 7168, 2048, 65536) >= 65536 * 2048 * 2
 
 
-def test_route_workspace_of_more_tokens_serves_fewer(L):
-    """A caller that keeps one workspace, sized for its largest batch, may hand it to every smaller one: across the
-    line between the kernels for small batches or gates and the tiled ones too."""
+def _demanded(L, T, H, E, D=0):
+    """Bytes that a call itself demands, from the text of its refusal of an empty workspace (nothing is launched)."""
+    fake = C.c_void_p(0x1000)
+    tail = (T, H, E, 2, 1, fake, fake, None, None, fake, 0, None)
+    rc = (L.probe_predict_topk_residual(fake, fake, None, 1, 1, fake, fake, D, *tail) if D else
+          L.probe_route_topk(fake, fake, None, 1, 1, *tail))
+    assert rc == -4
+    return int(re.search(r"\(0 < (\d+)\)", L.probe_last_error_string().decode()).group(1))
+
+
+@pytest.mark.parametrize("H,E,top", [(4096, 8, 20000), (1000, 250, 5000), (4096, 128, 20000), (7168, 256, 20000), (64, 130, 9000),
+                                     (192, 16, 9000), (7160, 60, 9000)])
+def test_route_workspace_of_more_tokens_serves_fewer(L, H, E, top):
+    """A caller that keeps one workspace, sized for its largest batch, may hand it to every smaller one: the query is the most
+    that any batch up to that size demands, across the lines between the kernels and every step of the split of K."""
     from paper_2602_00509_amd import probe
-    for H, E, top in ((4096, 8, 3000), (1000, 250, 1100), (4096, 128, 700), (7168, 256, 300)):
-        sizes = [probe.route_topk_workspace_bytes(T, H, E, 2) for T in range(1, top + 1)]
-        assert all(a <= b for a, b in zip(sizes, sizes[1:])), (H, E)
-        resid = [L.probe_predict_topk_residual_workspace_bytes(T, H, E, 2, 64) for T in range(1, top + 1, 7)]
-        assert all(a <= b for a, b in zip(resid, resid[1:])), (H, E)
+    dense = set(range(1, 600)) | {128 * i + d for i in range(1, top // 128) for d in (0, 1)}
+    for D in (0, 64, 520):
+        most = 0
+        for T in sorted(dense):
+            most = max(most, _demanded(L, T, H, E, D))
+            q = probe.predict_topk_residual_workspace_bytes(T, H, E, 2, D) if D else probe.route_topk_workspace_bytes(T, H, E, 2)
+            assert q >= most, (H, E, T, D)
+            assert D or q == most, (H, E, T)
+    for fn in ("probe_route_predict_topk_workspace_bytes", "probe_route_predict_topk_packed_workspace_bytes",
+               "probe_route_topk_packed_workspace_bytes"):
+        sizes = [getattr(L, fn)(T, H, E, 2) for T in sorted(dense)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), (fn, H, E)
 
 
 def test_ffn_workspace_of_more_rows_serves_fewer_at_full_speed(L):
