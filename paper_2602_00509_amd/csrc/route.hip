@@ -314,7 +314,7 @@ __global__ __launch_bounds__(512) void gate_direct_kernel(const bf16_t* __restri
                                                           int n_zero) {
   __shared__ float sums[8][16 * NT * 16];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int n0 = blockIdx.x * 16, ks = blockIdx.y, t0 = blockIdx.z * 16 * NT;
+  const int t0 = blockIdx.x * 16 * NT, n0 = blockIdx.y * 16, ks = blockIdx.z;
   zero_counts(zero0, zero1, n_zero);
   const int steps = (H + 31) / 32, s0 = (ks * 8 + wv) * k32_per_wave;
   f32x4 acc[NT];
@@ -980,7 +980,9 @@ struct RouteShape {
 // fragment: a 128-expert tile would be mostly padding).  Whole call, direct against tiled: 256 tokens x 128 experts 12.4 / 15.7 us,
 // 512 x 128 15.6 / 15.8 and 256 x 256 21.5 / 21.8 (H = 4096, 7168).  Where H is not a multiple of 64 the other kernel is the
 // register-staged one and the line lies higher: 1000 tokens x 250 experts x 7160 47.6 us, 1500 tokens staged 50.6.
-constexpr int kDirectLogits = 32768, kDirectExperts = 16;
+// A launch holds fewer than 2^32 threads: 512 for 32 tokens here, a quarter of that in the tiled kernels, which therefore take
+// the batches above kDirectTokens.
+constexpr int kDirectLogits = 32768, kDirectExperts = 16, kDirectTokens = 1 << 27;
 
 constexpr int kMaxSplitK = 16;
 constexpr int kResidSplitK = 4;  // second layer of the residual: the softmax kernel reads every slice
@@ -1012,7 +1014,8 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
   s.k_chunk = steps_per * GBK;
   s.ks = (ksteps + steps_per - 1) / steps_per;
   s.ks_room = s.ks;
-  s.direct = static_cast<long>(T) * E <= (H % 64 == 0 ? 1 : 8) * kDirectLogits || E <= kDirectExperts;
+  s.direct = static_cast<long>(T) * E <= (H % 64 == 0 ? 1 : 8) * kDirectLogits ||
+             (E <= kDirectExperts && T <= kDirectTokens);
   s.frags = s.per_wave = 0;
   if (s.direct) {
     // eight fragments of tokens share a gate fragment where there are that many; a 16-expert gate is a stream of x and
@@ -1032,7 +1035,8 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
 template <int PL, bool SPLIT_W>
 static void launch_gate_direct(const RouteShape& sh, hipStream_t st, const bf16_t* x, const GateRows& g, int T, int H,
                                int N, float* partial, int32_t* zero0, int32_t* zero1, int n_zero) {
-  const dim3 grid((N + 15) / 16, sh.ks, (T + 16 * sh.frags - 1) / (16 * sh.frags));
+  // token blocks on x, the one dimension that takes more than 65535 of them
+  const dim3 grid((T + 16 * sh.frags - 1) / (16 * sh.frags), (N + 15) / 16, sh.ks);
 #define PROBE_DIRECT_CASE(NT, KU)                                                                                  \
   case NT:                                                                                                          \
     hipLaunchKernelGGL((gate_direct_kernel<NT, KU, PL, SPLIT_W>), grid, dim3(512), 0, st, x, g, T, H, N, sh.per_wave, \

@@ -144,6 +144,26 @@ def test_route_small_batches_and_small_gates(oracle, probe, G, T, H, E, k):
         G.check_route(q, rev, k, True)
 
 
+def test_route_small_gate_on_more_token_blocks_than_65535(oracle, probe, G):
+    """A gate of at most 16 experts takes 32 tokens per workgroup at any batch: more of them than the y and z dimensions of a
+    launch can hold.  Every token bit for bit as in batches of a million, the last ones against the oracle."""
+    T, H, E, k = 2 ** 21 + 45, 64, 8, 2
+    g = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randn((T, H), generator=g, device="cuda").to(torch.bfloat16)
+    w = torch.randn((E, H), generator=g, device="cuda") * 0.2
+    print("case small gate T=%d" % T, flush=True)
+    r = probe.route_topk(x, w, None, None, k, True)
+    torch.cuda.synchronize()
+    assert int(r["counts"].sum()) == T * k
+    for t0, t1 in ((0, 2 ** 20), (2 ** 20, 2 ** 21), (2 ** 21 - 10000, T)):
+        part = probe.route_topk(x[t0:t1], w, None, None, k, True)
+        for key in ("idx", "w"):
+            assert torch.equal(part[key], r[key][t0:t1]), (key, t0)
+    n = 200
+    o = oracle.route_topk(x[-n:].view(torch.int16).cpu().numpy().view(np.uint16), w.cpu().numpy(), None, n, k, True)
+    G.check_route({key: r[key][-n:] for key in ("idx", "w")}, o, k, True)
+
+
 @pytest.mark.parametrize("T,H,E,k", [(8200, 256, 256, 8), (4100, 1024, 200, 6), (2049, 128, 130, 4)])
 def test_route_on_256_token_tiles_with_a_ragged_last_tile(oracle, probe, G, T, H, E, k):
     """Large batches take the 256-token tile of the gate GEMM; T is not a multiple of the tile, E not
