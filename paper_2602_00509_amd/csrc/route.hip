@@ -314,7 +314,9 @@ __global__ __launch_bounds__(512) void gate_direct_kernel(const bf16_t* __restri
                                                           int n_zero) {
   __shared__ float sums[8][16 * NT * 16];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int t0 = blockIdx.x * 16 * NT, n0 = blockIdx.y * 16, ks = blockIdx.z;
+  const bool one_fragment = N <= 16;  // see launch_gate_direct
+  const int t0 = (one_fragment ? blockIdx.x : blockIdx.z) * 16 * NT, n0 = one_fragment ? 0 : blockIdx.x * 16;
+  const int ks = one_fragment ? blockIdx.z : blockIdx.y;
   zero_counts(zero0, zero1, n_zero);
   const int steps = (H + 31) / 32, s0 = (ks * 8 + wv) * k32_per_wave;
   f32x4 acc[NT];
@@ -977,7 +979,7 @@ struct RouteShape {
 };
 
 // Logits (T x E) up to which a gate takes the direct kernel, and gates that take it at any batch (16 experts are one
-// fragment: a 128-expert tile would be mostly padding).  Whole call, direct against tiled: 256 tokens x 128 experts 12.4 / 15.7 us,
+// fragment: a 128-expert tile would be mostly padding; figures at small_gate_frags).  Whole call, direct against tiled: 256 tokens x 128 experts 12.4 / 15.7 us,
 // 512 x 128 15.6 / 15.8 and 256 x 256 21.5 / 21.8 (H = 4096, 7168).  Where H is not a multiple of 64 the other kernel is the
 // register-staged one and the line lies higher: 1000 tokens x 250 experts x 7160 47.6 us, 1500 tokens staged 50.6.
 // A launch holds fewer than 2^32 threads: 512 for 32 tokens here, a quarter of that in the tiled kernels, which therefore take
@@ -1000,6 +1002,26 @@ constexpr int kBigTileItems = 32;
 static bool gate_dma(int H, int E) { return H % 64 == 0 && static_cast<size_t>(3) * E * H * 2 <= 0x7fffffffull; }
 static int gate_target(int bm) { return bm == 256 ? 256 : 512; }
 
+// Fragments of 16 tokens per workgroup for a gate of at most 16 experts at any batch.  Such a product is a stream of x, and
+// small batches want workgroups: one fragment, two above 8192 tokens.  But every workgroup reads the whole gate, 3 E / (16 frags)
+// bytes of it for a byte of x, from the caches: with one or two fragments at every size 5000 tokens x 7168 x 16 experts took
+// 56 us (tiled 33, now 26), 65536 of them 351 (258, 241).  Where that traffic is large there is a fragment for every four
+// experts, and above 8192 tokens twice as many unless that fills the CUs' rounds less (40000 tokens x 7168 x 16: eight 214,
+// four 194; 9000: 40 and 52); with as full rounds eight pay from H = 4096 (65536 tokens x 2048 x 12: eight 87, four 82;
+// x 4096: 155 and 160).  Where it is small the workgroups count for more (9000 tokens x 256 x 16: two 11.1, eight 11.9).
+static int small_gate_frags(int T, int H, int E) {
+  if (T <= 2048 || static_cast<long>(T) * E * H <= 96l << 20) return T > 8192 ? 2 : 1;
+  const int f = E <= 4 ? 1 : (E <= 8 ? 2 : 4);
+  if (T <= 8192) return f;
+  auto wgs = [&](int frags) {
+    const long blocks = (static_cast<long>(T) + 16 * frags - 1) / (16 * frags);
+    return blocks * std::max(256 / blocks, 1l);  // one workgroup per CU, as the split of K below aims at
+  };
+  const long one = wgs(f), two = wgs(2 * f);
+  const long one_share = one * ((two + 255) / 256), two_share = two * ((one + 255) / 256);  // of the rounds' places in use
+  return E <= 4 || two_share > one_share || (two_share == one_share && (E <= 8 || H >= 4096)) ? 2 * f : f;
+}
+
 static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
   RouteShape s;
   s.dma = gate_dma(H, E);
@@ -1018,9 +1040,8 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
              (E <= kDirectExperts && T <= kDirectTokens);
   s.frags = s.per_wave = 0;
   if (s.direct) {
-    // eight fragments of tokens share a gate fragment where there are that many; a 16-expert gate is a stream of x and
-    // wants workgroups
-    s.frags = E <= kDirectExperts ? (T > 8192 ? 2 : 1) : (T <= 16 ? 1 : (T <= 32 ? 2 : (T <= 64 ? 4 : 8)));
+    // eight fragments of tokens share a gate fragment where there are that many
+    s.frags = E <= kDirectExperts ? small_gate_frags(T, H, E) : (T <= 16 ? 1 : (T <= 32 ? 2 : (T <= 64 ? 4 : 8)));
     const int k32 = (H + 31) / 32, wgs = ((E + 15) / 16) * ((T + 16 * s.frags - 1) / (16 * s.frags));
     int split = wgs > 0 ? 256 / wgs : 1;  // one workgroup per CU
     split = split < 1 ? 1 : (split > max_split ? max_split : split);
@@ -1035,8 +1056,10 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
 template <int PL, bool SPLIT_W>
 static void launch_gate_direct(const RouteShape& sh, hipStream_t st, const bf16_t* x, const GateRows& g, int T, int H,
                                int N, float* partial, int32_t* zero0, int32_t* zero1, int n_zero) {
-  // token blocks on x, the one dimension that takes more than 65535 of them
-  const dim3 grid((T + 16 * sh.frags - 1) / (16 * sh.frags), (N + 15) / 16, sh.ks);
+  // A gate of one fragment is served at any batch: its token blocks are on x, the one dimension that takes more than 65535 of
+  // them.  With more fragments (T x N is bounded) those go first: the workgroups that share x run side by side.
+  const unsigned blocks = (T + 16 * sh.frags - 1) / (16 * sh.frags);
+  const dim3 grid = N <= 16 ? dim3(blocks, 1, sh.ks) : dim3((N + 15) / 16, sh.ks, blocks);
 #define PROBE_DIRECT_CASE(NT, KU)                                                                                  \
   case NT:                                                                                                          \
     hipLaunchKernelGGL((gate_direct_kernel<NT, KU, PL, SPLIT_W>), grid, dim3(512), 0, st, x, g, T, H, N, sh.per_wave, \

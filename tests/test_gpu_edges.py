@@ -116,10 +116,11 @@ def test_route_when_hidden_size_is_not_a_multiple_of_64(oracle, probe, G, T, H, 
 
 @pytest.mark.parametrize("T,H,E,k", [(1, 64, 16, 8), (16, 1000, 17, 3), (17, 8, 60, 6), (32, 4096, 9, 2), (33, 520, 130, 8),
                                      (65, 7168, 256, 8), (129, 1024, 128, 4), (513, 328, 16, 2), (9000, 192, 8, 2),
-                                     (257, 512, 128, 8)])
+                                     (257, 512, 128, 8), (2049, 4104, 16, 2), (3100, 4096, 8, 2), (9001, 2880, 13, 3),
+                                     (12001, 2048, 8, 2), (40003, 1024, 16, 2)])
 def test_route_small_batches_and_small_gates(oracle, probe, G, T, H, E, k):
-    """The kernel that goes from global memory to the matrix cores: one to eight token fragments per workgroup, batches and
-    gates on both sides of where it hands over to the tiled ones, expert counts that leave a partial fragment or
+    """The kernel that goes from global memory to the matrix cores: one to eight token fragments per workgroup (by the batch, or
+    by the gate where it has at most 16 experts), batches and gates on both sides of where it hands over to the tiled ones, expert counts that leave a partial fragment or
     partial 16-byte pieces; every token against the oracle, the packed gate bit for bit the fp32 one."""
     print("case small route T=%d H=%d E=%d" % (T, H, E), flush=True)
     rng = np.random.default_rng(T + E)
