@@ -669,6 +669,7 @@ __device__ __forceinline__ int skinny_steps(int n_tiles, int n_cols, int steps) 
 struct SkinnyTile {
   int row0, rows;
   int tile, col, piece, pieces, piece_steps;
+  bool spread;  // the items begin at different k-steps (skinny_start)
   const void* w;
 };
 
@@ -677,6 +678,7 @@ template <bool REDUCE>
 __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_offsets,
                                               const void* const* __restrict__ w_ptrs, int S, int item, int n_cols,
                                               int steps, bool may_split, SkinnyTile& out) {
+  const int all_rows = slot_offsets[S] - slot_offsets[0];
   __shared__ int32_t wave_tot[8];
   __shared__ int32_t found_row0, found_rows;
   __shared__ const void* found_w;
@@ -732,6 +734,10 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
     }
   }
   out.tile = tile;
+  // rows * K * 2 bytes * (share of the items that run at once) against 6 MB, one and a half of an XCD's L2; with fewer than 16
+  // columns, dealt out to 8 XCDs, an XCD has no two items with the same rows
+  out.spread = n_cols < 16 ||
+               static_cast<long>(all_rows) * steps <= 96l * max(n_tiles * n_cols * out.pieces, 2 * kSkinnyItems);
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if (tile >= excl && tile < excl + t[i]) {  // true for exactly one (thread, i) when the tile exists
@@ -758,10 +764,16 @@ __device__ __forceinline__ float* skinny_partial(float* partial, const SkinnyTil
 // same 128 bytes of rows that lie 2H (or 2F) bytes apart, which for H = 4096 is the same few HBM channels: spread over K,
 // gemm1 of one token (4096 x 14336) takes 83 instead of 91 us, of 14 slots of 4096 x 1536 71 instead of 75, gemm2 of 20 slots
 // of 7168 x 2048 123 instead of 130.  By column only: the row tiles of a slot read its weights together, from the caches
-// (197 tokens, 64 slots of 7168 x 2048: 675 us, spread by tile too 687, all from 0 682).  The tall tiles keep to k = 0: there
-// the items of an XCD share weights and rows in its L2, and started block by block prefill of 8192 tokens was 3 % slower.
+// (197 tokens, 64 slots of 7168 x 2048: 675 us, spread by tile too 687, all from 0 682).  Where the step count is a multiple of
+// 11 few starts are left, but such rows are no power of two apart (11264 x 5632: 815 us, a stride of 13 822).
+// But items that begin together also share the activation rows, and once those of the items that run at once are more than
+// an XCD's L2 keeps that counts for more: 64 slots of 7168 x 2048, 45 rows in each, FFN 1040 us spread, 979 with gemm1 from 0;
+// 30 rows 988 / 961; ten slots of 4096 x 14336, 60 rows in each 702, 683 with gemm2 from 0.  18 slots of 4096 x 1536, 30 rows in
+// each (4.4 MB) 136 / 140; one slot, 2000 rows of 7168 x 512 (8 columns) 77 / 81.
+// The tall tiles keep to k = 0: there the items of an XCD share weights and rows in its L2, and started block by block prefill
+// of 8192 tokens was 3 % slower.
 __device__ __forceinline__ int skinny_start(const SkinnyTile& e, int klen) {
-  return (e.col * 11) % (klen / FBK);
+  return e.spread ? (e.col * 11) % (klen / FBK) : 0;
 }
 
 template <bool GATHER>
