@@ -648,13 +648,15 @@ static int skinny_max_tiles(int S, int max_rows) {
 // that is still possible if every slot that probably holds rows does.  Most of the capacity is as a rule other ranks' (one
 // token, eight experts, one of them local, 36 slots of 7168 x 2048: FFN 70.9 -> 36.7 us; eight slots of 7168 x 256, 421 of 3200
 // rows local: 68.8 -> 45.2; all eight experts local: 127.1 / 125.4).  But with kSkinnyFullRows rows of capacity per slot nearly
-// every slot holds one, and where S tiles alone leave no second piece the launch of the adding kernel would be lost (12 slots
-// of 5632 x 1408, 480 rows of capacity, five in each: 133.5 without, 137.2 with it).
+// every slot holds one, and if an eighth of the capacity is local it fills a tile more per 512 rows.  Where that many tiles
+// leave no second piece the launch of the adding kernel would be lost (12 slots of 5632 x 1408, 480 rows of capacity, five in
+// each: 133.5 without, 137.2 with it; 32 slots of 6912 x 256, 401 rows under a Zipf law 92.2 / 99.9).
 constexpr int kSkinnyFullRows = 8;
 static bool skinny_may_split(int S, int max_rows, int n_cols, int steps) {  // if it holds, it holds for fewer rows too
-  if (steps < kSkinnySplitSteps || static_cast<long>(skinny_max_tiles(S, max_rows)) * n_cols > kSkinnyFewItems) return false;
+  const long most = skinny_max_tiles(S, max_rows);
+  if (steps < kSkinnySplitSteps || most * n_cols > kSkinnyFewItems) return false;
   const bool every_slot = max_rows >= static_cast<long>(kSkinnyFullRows) * S;
-  return !every_slot || static_cast<long>(S) * n_cols <= kSkinnyItems / 2;
+  return !every_slot || std::min<long>(most, S + (static_cast<long>(max_rows) + 511) / 512) * n_cols <= kSkinnyItems / 2;
 }
 // k-steps per piece, for n_tiles row tiles of n_cols column blocks; steps: the whole contraction
 __device__ __forceinline__ int skinny_steps(int n_tiles, int n_cols, int steps) {
