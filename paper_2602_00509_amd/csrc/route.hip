@@ -1252,13 +1252,23 @@ static int route_impl(const char* name, const void* x_bf16, const float* w_gate,
 #define PROBE_TOPK_LAUNCH(V)                                                                               \
   hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial, sh.ld, planes_to_sum, bias, \
                      G, tpg, T, E, k, renormalize ? 1 : 0, topk_idx, topk_w, probs, expert_counts)
-#define PROBE_GROUPED_LAUNCH(V, R)                                                                               \
-  hipLaunchKernelGGL((gate_grouped_topk_kernel<V, 1, R>), dim3(std::min((T + 15) / 16, 4096)), dim3(256), 0, st,  \
+#define PROBE_GROUPED_LAUNCH(V, U, R)                                                                            \
+  hipLaunchKernelGGL((gate_grouped_topk_kernel<V, U, R>), dim3(std::min((T + 16 * U - 1) / (16 * U), 4096)), dim3(256), 0, st, \
                      partial, sh.ld, planes_to_sum, bias, G, tpg, select_bias, T, E, k, gating->scoring,             \
                      gating->n_group, gating->topk_group, gating->group_top, gating->renormalize ? 1 : 0,        \
                      gating->routed_scale, topk_idx, topk_w, probs, expert_counts)
     if (gating) {
-      if (E <= 64) PROBE_GROUPED_LAUNCH(1, 8); else if (E <= 128) PROBE_GROUPED_LAUNCH(2, 8); else PROBE_GROUPED_LAUNCH(4, 4);
+      // one token per row and many slices in flight while latency bounds the kernel; two tokens and two slices once there
+      // are enough rows and instructions bound it, which at more than 128 experts they did not up to 40000 tokens.  Call
+      // with one / two tokens per row: 4096 x 1024 x 64 experts 24.1 / 26.2 us, 8192 30.7 / 28.4, 16384 39.6 / 32.7; 8192 x
+      // 1024 x 128 33.1 / 34.1, 13421 43.1 / 36.4; 16384 x 1024 x 256 59.6 / 63.1.
+      if (E <= 64) {
+        if (T > 6144) PROBE_GROUPED_LAUNCH(1, 2, 2); else PROBE_GROUPED_LAUNCH(1, 1, 8);
+      } else if (E <= 128) {
+        if (T > 8192) PROBE_GROUPED_LAUNCH(2, 2, 2); else PROBE_GROUPED_LAUNCH(2, 1, 8);
+      } else {
+        PROBE_GROUPED_LAUNCH(4, 1, 4);
+      }
     } else {
       // small batches (decode): one token per row in flight and many split-K slices loaded at once give twice
       // the waves per SIMD to hide the loads behind; large batches are bound by reading the partial sums

@@ -85,6 +85,9 @@ CASES = [
     (33, 64, 10, 3, 5, 2, 2, "sigmoid", True, 1.0, True, True),        # E % 4 != 0: scalar loads
     (1, 64, 256, 8, 8, 4, 2, "sigmoid", True, 2.5, False, True),
     (0, 64, 256, 8, 8, 4, 2, "sigmoid", True, 2.5, False, True),
+    (6145, 128, 60, 6, 4, 2, 2, "sigmoid", True, 1.0, True, True),      # from here two tokens per row, last row half full
+    (6144, 128, 62, 4, 2, 1, 2, "softmax", False, 1.0, True, False),    # up to here one; E % 4 != 0
+    (8193, 64, 128, 8, 8, 4, 2, "sigmoid", True, 2.5, False, True),
 ]
 
 
