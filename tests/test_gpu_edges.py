@@ -355,6 +355,52 @@ def test_ffn_few_tiles_every_element(oracle, probe, G, sizes, H, F):
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, len(sizes), seed=H + F, extra_rows=0 if sizes == [1] else 9)
 
 
+@pytest.mark.parametrize("sizes,H,F", [([1, 0, 0, 2], 4160, 320), ([75], 4096, 192), ([2, 0, 5], 320, 5120)])
+def test_ffn_few_tiles_gathered_on_load_and_in_a_graph(oracle, probe, G, sizes, H, F):
+    """Pieces of K with the activation rows gathered on load (two rows per token, out of order): bit for bit the call on the
+    gathered copy, every element against the oracle; recorded once and replayed on other rows, with eager calls between."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=104)
+    S, n, k = len(sizes), sum(sizes), 2
+    rng = np.random.default_rng(n + H)
+    so = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    T = n // 2 + 3
+    pairs = np.full(n + 5, -1, np.int32)
+    pairs[:n] = rng.permutation(T * k)[:n]
+    ws = wl.expert_weights_many(cfg, list(range(S)))
+    tab = probe.WeightTable([G.dev_bf16(w[0]) for w in ws], [G.dev_bf16(w[1]) for w in ws])
+    rows = lambda: wl.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32))
+    x = rows()
+    d_x, d_so, d_pairs = G.dev_bf16(x), torch.from_numpy(so).cuda(), torch.from_numpy(pairs).cuda()
+    y = torch.full((n + 5, H), 7.0, dtype=torch.bfloat16, device="cuda")
+    work = torch.empty(probe.grouped_ffn_workspace_bytes(S, H, F, n + 5), dtype=torch.uint8, device="cuda")
+    call = lambda out: probe.grouped_ffn_gather(d_x, d_pairs, k, d_so, tab, out=out, workspace=work)
+    print("case gather few tiles", sizes, H, F, flush=True)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call(y)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            call(y)
+    torch.cuda.current_stream().wait_stream(side)
+    for replay in range(3):
+        if replay:
+            x = rows()
+            d_x.copy_(G.dev_bf16(x))
+        xp = np.zeros((n + 5, H), np.uint16)
+        xp[:n] = x[pairs[:n] // k]
+        copied = torch.full_like(y, 7.0)
+        probe.grouped_ffn(G.dev_bf16(xp), d_so, tab, out=copied)
+        y.fill_(7.0)
+        work.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, copied), replay
+        ref = oracle.grouped_ffn(xp, so, [w[0] for w in ws], [w[1] for w in ws])
+        assert G.rel_err(G.f64_of(y)[:n], ref) < G.BF16_RTOL
+        assert (y[n:] == 7.0).all()
+
+
 def test_ffn_contraction_is_not_cut_where_every_slot_can_hold_rows(oracle, probe, G):
     """At 40 rows of capacity per slot no adding kernel is launched although one slot alone holds rows: the call gives the
     same bits with and without room for partial sums.  Every element against the oracle."""
