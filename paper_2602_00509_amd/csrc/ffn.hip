@@ -13,8 +13,9 @@
 //   * global -> LDS goes through buffer_load ... lds (no register staging).  The per-lane
 //     offset is fixed for the whole K loop; the k position travels in a scalar offset.
 //   * two LDS stages of up to 72 KB (three smaller ones for the 128- and 64-row tiles).  Rows are
-//     128 bytes; 16-byte chunk c of row r is stored at chunk position c ^ ((r >> 1) & 7), which makes sixteen consecutive rows reading the same
-//     logical chunk cover all 64 banks exactly once.
+//     128 bytes; 16-byte chunk c of row r is stored at chunk position c ^ key(r), one key for the activation and one
+//     for the weight tile (lds_key), so that the sixteen rows of a fragment reading the same logical chunk cover all 64
+//     banks exactly once.
 //   * the fragment reads are spread over the MFMAs of a k-step.  A barrier after its first steps releases the
 //     weights' part of the stage, one before its last steps the activations' part; the DMA instructions that
 //     prefetch tile k+2 follow each of them, spread over MFMAs (mfma_pipeline.hpp).
@@ -632,7 +633,7 @@ constexpr int kSkinnyCols1 = 64, kSkinnyCols2 = 128;   // h columns / y columns 
 // pieces in ascending order.  The number of tiles is known on the device only; the host merely decides whether it can be
 // small (skinny_may_split) and then launches the adding kernel, which ends at once if nothing was split.
 // One token, two experts of 4096 x 14336: FFN 194 -> 137 us (gemm2 104 -> 41, adding 5); 512 items instead of 256: 141,
-// 1024: 161.  One slot of 75 rows, 7168 x 2048: 125 -> 45 us.
+// 1024: 161.  One slot of 75 rows, 7168 x 2048, which took the tall tiles before: 125 -> 43 us.
 constexpr int kSkinnyItems = 256;
 constexpr int kSkinnyMinSteps = 16;      // k-steps of a piece at least
 constexpr int kSkinnySplitSteps = 64;    // k-steps from which a contraction may be cut: a shorter one is read in the time

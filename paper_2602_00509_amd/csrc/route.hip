@@ -11,7 +11,8 @@
 //               which are handed planes made once by probe_pack_gate)
 //   2. gemm     split-K tiled GEMM (128 tokens x 128 experts x 64 k per step; small batches and gates of at most 16
 //               experts go straight from global memory to the matrix cores), three MFMAs per
-//               operand pair (one per plane) into one accumulator  -> partial[KS][T][E] fp32;
+//               operand pair (one per plane) into one accumulator  -> partial[KS][T][ld] fp32, ld = E
+//               rounded up to 4;
 //               its first workgroup clears the expert counts
 //               H % 64 == 0: DMA-to-LDS software pipeline shared with the grouped FFN;
 //               otherwise a register-staged kernel that zero-fills the K tail
@@ -223,12 +224,12 @@ __global__ __launch_bounds__(512, 2) void gate_gemm_dma_kernel(const bf16_t* __r
 
 // ---- 2c. gemm straight from global memory to the matrix cores --------------------------------------
 // Small batches, and gates of at most 16 experts at any batch.  There the product is a stream of the gate (3 planes
-// of E x H, 3..11 MB) or of x, and what the tiled kernels above lose is latency: at 128 tokens they are 16..32
+// of E x H: 0.2 MB for 8 x 4096, 11 MB for 256 x 7168) or of x, and what the tiled kernels above lose is latency: at 128 tokens they are 16..32
 // workgroups that each pull 64 KB per k-step, four to seven steps one after another.  Here a wave multiplies one
 // fragment of 16 experts (three planes) by NT fragments of 16 tokens over a few k32 of its own, with every operand
 // loaded from global memory in the layout of v_mfma_f32_16x16x32_bf16 (16 rows x 64 bytes per instruction) and all
 // loads of KU k32 in flight together; the eight waves of a workgroup split its K range and add their sums in LDS in
-// fixed order.  No barrier before that, 64..256 workgroups.  128 tokens: 10.4 -> 6 us at 128 x 4096, 14.4 -> 9 us at
+// fixed order.  No barrier before that; K is split until there is a workgroup per CU or 16 slices.  128 tokens: 10.4 -> 6 us at 128 x 4096, 14.4 -> 9 us at
 // 256 x 7168; one token: 3.5 and 4.3 us.
 // A lane's eight k lie inside or outside of H as a whole (H % 8 == 0), so any such H is served.
 // SPLIT_W: `w` is the fp32 gate (the second of two stacked gates in w_next) and the planes are made in registers; every weight
@@ -1074,7 +1075,7 @@ static void launch_gate_direct(const RouteShape& sh, hipStream_t st, const bf16_
 #undef PROBE_DIRECT_CASE
 }
 
-// x [T,H] times a stack of PL bf16 planes [PL][N][H] -> partial [ks][T][N] fp32
+// x [T,H] times a stack of PL bf16 planes [PL][N][H] -> partial [ks][T][sh.ld] fp32
 template <int PL>
 static void launch_gate_gemm(const RouteShape& sh, hipStream_t st, const bf16_t* x, const bf16_t* planes, int T,
                              int H, int N, float* partial, int32_t* zero0 = nullptr, int32_t* zero1 = nullptr,
