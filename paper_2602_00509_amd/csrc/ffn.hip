@@ -636,8 +636,9 @@ constexpr int kSkinnyCols1 = 64, kSkinnyCols2 = 128;   // h columns / y columns 
 // 1024: 161.  One slot of 75 rows, 7168 x 2048, which took the tall tiles before: 125 -> 43 us.
 constexpr int kSkinnyItems = 256;
 constexpr int kSkinnyMinSteps = 16;      // k-steps of a piece at least
-constexpr int kSkinnySplitSteps = 64;    // k-steps from which a contraction may be cut: a shorter one is read in the time
-                                         // that the launch of the adding kernel takes (about 5 us)
+// k-steps from which a contraction may be cut.  Shorter ones gain less over the adding kernel's launch (about 5 us), but some
+// still do: uncut / cut one slot of 16 rows, 3072 x 1536 28.3 / 24.1 us; two of 2880 x 2880 47.5 / 41.2, four 52.4 / 52.3.
+constexpr int kSkinnySplitSteps = 64;
 constexpr int kSkinnyFewItems = 512;     // items at capacity up to which tiles can be few
 constexpr size_t kSkinnyPartialBytes = static_cast<size_t>(kSkinnyItems) * 64 * 128 * sizeof(float);
 
@@ -901,8 +902,8 @@ static FfnShape ffn_shape(int S, int H, int F, int max_rows) {
 }
 
 // What the workspace query returns: the most that any call of up to max_rows rows can use, so that a workspace sized for the
-// largest batch serves every smaller one, at its full speed, and the query does not fall as max_rows grows.  h grows with the rows;
-// the tile table is longest at the last row count of the 64-row tiles; pieces of K are smallest calls' business.
+// largest batch serves every smaller one, at its full speed, and the query does not fall as max_rows grows.  h grows with
+// the rows, the tile table is longest at the last row count of the 64-row tiles, and what may be cut at all may be at one row.
 static size_t ffn_query_bytes(int S, int H, int F, int max_rows) {
   size_t bytes = ffn_shape(S, H, F, max_rows).h_bytes;
   const int short_rows = static_cast<int>(std::min<long>(max_rows, static_cast<long>(kSkinnyRowsPerSlot) * S));

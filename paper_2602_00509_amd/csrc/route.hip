@@ -224,13 +224,13 @@ __global__ __launch_bounds__(512, 2) void gate_gemm_dma_kernel(const bf16_t* __r
 
 // ---- 2c. gemm straight from global memory to the matrix cores --------------------------------------
 // Small batches, and gates of at most 16 experts at any batch.  There the product is a stream of the gate (3 planes
-// of E x H: 0.2 MB for 8 x 4096, 11 MB for 256 x 7168) or of x, and what the tiled kernels above lose is latency: at 128 tokens they are 16..32
-// workgroups that each pull 64 KB per k-step, four to seven steps one after another.  Here a wave multiplies one
-// fragment of 16 experts (three planes) by NT fragments of 16 tokens over a few k32 of its own, with every operand
-// loaded from global memory in the layout of v_mfma_f32_16x16x32_bf16 (16 rows x 64 bytes per instruction) and all
+// of E x H: 0.2 MB for 8 x 4096, 11 MB for 256 x 7168) or of x, and what the tiled kernels above lose is latency: at 128
+// tokens they are 16..32 workgroups that each pull 64 KB per k-step, four to seven steps one after another.  Here a wave
+// multiplies one fragment of 16 experts (three planes) by NT fragments of 16 tokens over a few k32 of its own, with every
+// operand loaded from global memory in the layout of v_mfma_f32_16x16x32_bf16 (16 rows x 64 bytes per instruction) and all
 // loads of KU k32 in flight together; the eight waves of a workgroup split its K range and add their sums in LDS in
-// fixed order.  No barrier before that; K is split until there is a workgroup per CU or 16 slices.  128 tokens: 10.4 -> 6 us at 128 x 4096, 14.4 -> 9 us at
-// 256 x 7168; one token: 3.5 and 4.3 us.
+// fixed order.  No barrier before that; K is split until there is a workgroup per CU or 16 slices.  128 tokens: 10.4 -> 6 us
+// at 128 x 4096, 14.4 -> 9 us at 256 x 7168; one token: 3.5 and 4.3 us.
 // A lane's eight k lie inside or outside of H as a whole (H % 8 == 0), so any such H is served.
 // SPLIT_W: `w` is the fp32 gate (the second of two stacked gates in w_next) and the planes are made in registers; every weight
 // is read by ceil(T / (16 NT)) waves, so below two token blocks that is less work than a launch that writes the planes
@@ -980,8 +980,8 @@ struct RouteShape {
 };
 
 // Logits (T x E) up to which a gate takes the direct kernel, and gates that take it at any batch (16 experts are one
-// fragment: a 128-expert tile would be mostly padding; figures at small_gate_frags).  Whole call, direct against tiled: 256 tokens x 128 experts 12.4 / 15.7 us,
-// 512 x 128 15.6 / 15.8 and 256 x 256 21.5 / 21.8 (H = 4096, 7168).  Where H is not a multiple of 64 the other kernel is the
+// fragment: a 128-expert tile would be mostly padding; figures at small_gate_frags).  Whole call, direct against tiled:
+// 256 tokens x 128 experts 12.4 / 15.7 us, 512 x 128 15.6 / 15.8 and 256 x 256 21.5 / 21.8 (H = 4096, 7168).  Where H is not a multiple of 64 the other kernel is the
 // register-staged one and the line lies higher: 1000 tokens x 250 experts x 7160 47.6 us, 1500 tokens staged 50.6.
 // A launch holds fewer than 2^32 threads: 512 for 32 tokens here, a quarter of that in the tiled kernels, which therefore take
 // the batches above kDirectTokens.
