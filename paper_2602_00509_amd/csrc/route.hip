@@ -16,7 +16,7 @@
 //               its first workgroup clears the expert counts
 //               H % 64 == 0: DMA-to-LDS software pipeline shared with the grouped FFN;
 //               otherwise a register-staged kernel that zero-fills the K tail
-//   3. softmax  sixteen lanes per token: sum the KS partials in fixed order, add the bias,
+//   3. softmax  sixteen lanes per token, or a wave where tokens are few: sum the KS partials in fixed order, add the bias,
 //               softmax over E, k rounds of row arg-max (ties to the lower index), weights, counts
 //
 // The predictor's residual MLP (Eq. 7) adds W2_hat silu(W1_hat h) to the logits before step 3:
@@ -389,14 +389,13 @@ __device__ __forceinline__ float row_sum(float v) {
   v += dpp_ror<1>(v);
   return v;
 }
-// arg-max of (value, expert): larger value wins, equal values go to the lower expert id
-template <int N>
-__device__ __forceinline__ void argmax_step(float& v, int& e) {
-  float ov = dpp_ror<N>(v);
-  int oe = dpp_ror<N>(e);
-  bool take = (oe != INT_MAX) && (e == INT_MAX || ov > v || (ov == v && oe < e));
-  v = take ? ov : v;
-  e = take ? oe : e;
+// (row 0 + row 1) + (row 2 + row 3) of a wave, lane by lane, in every row.  A swap of a register with itself leaves one
+// operand of the addition in each of its two results, the same pair in the same order in all lanes.
+__device__ __forceinline__ float add_rows(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 __device__ __forceinline__ int row_min_i(int v) {
@@ -441,11 +440,14 @@ __device__ __forceinline__ bool aligned_f4(const float* p) { return (reinterpret
 // tokens, 256 experts: top-k 9.6 against 9.9 us).  With two, the branches and the division in front of the first load cost
 // more than the wait behind the last: 99 tokens of a fused router and predictor, 256 experts: 18.2 us with the bias first,
 // 14.4 with it last; 3852 tokens, 128 experts 14.9 / 13.2.
-template <int NV, int U, int R = 2>
+// SG = 4: the four rows of a wave own the same token, row r adds the slices r, r + 4, ... and the four sums are added across
+// the rows, (0 + 1) + (2 + 3), so that all of them hold the same bits.
+template <int NV, int U, int R, int SG>
 __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partial, int ld, int KS,
                                                 const float* __restrict__ bias, int G, int tpg, int T, int E,
-                                                bool vec, int sub, const int (&tt)[U], float (&l)[U][NV * 4]) {
+                                                bool vec, int sub, int grp, const int (&tt)[U], float (&l)[U][NV * 4]) {
   constexpr int NL = NV * 4;
+  const int first = SG == 1 ? 0 : grp;
   constexpr bool BIAS_FIRST = U == 1;
   if (vec) {
     float4 accv[U][NV], bv[U][NV];
@@ -476,12 +478,12 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int i = 0; i < NV; ++i) accv[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int q0 = 0; q0 < KS; q0 += R) {
+    for (int q0 = 0; q0 < KS; q0 += R * SG) {
       // all loads of a round of R split-K slices (of every token of the row) are issued before any is consumed
       float4 tmp[R][U][NV];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const int q = min(q0 + r, KS - 1);
+        const int q = min(q0 + r * SG + first, KS - 1);
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -492,7 +494,7 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
       }
 #pragma unroll
       for (int r = 0; r < R; ++r)
-        if (q0 + r < KS) {
+        if (q0 + r * SG + first < KS) {
 #pragma unroll
           for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -503,6 +505,11 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
         }
     }
     if constexpr (!BIAS_FIRST) load_bias();
+    if constexpr (SG == 4) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        accv[0][i] = make_float4(add_rows(accv[0][i].x), add_rows(accv[0][i].y), add_rows(accv[0][i].z), add_rows(accv[0][i].w));
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
@@ -536,12 +543,30 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
 // other's.  A chosen logit is overwritten with -inf; incoming logits are clamped to >= -FLT_MAX
 // (NaN too), so -inf only ever means "taken".  The weight of a winner is recomputed from its
 // logit with the same expression as its probability, so both agree bit for bit.
-template <int NV, int U = 2, int R = 2>
-__global__ __launch_bounds__(256) void gate_softmax_topk_kernel(
-    const float* __restrict__ partial, int ld, int KS, const float* __restrict__ bias, int G, int tpg, int T,
-    int E, int k, int renorm, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
-    float* __restrict__ probs, int32_t* __restrict__ counts) {
-  // `partial` points at this gate's first column; a row of a partial plane has ld entries
+// What a gate's top-k reads and writes.  `partial` points at the gate's first column; a row of a partial plane has ld entries.
+struct TopkGate {
+  const float* partial;
+  const float* bias;
+  int G, tpg;
+  int32_t* topk_idx;
+  float* topk_w;
+  float* probs;
+  int32_t* counts;
+};
+
+// gates: one, or two stacked ones (router and predictor of the fused call), number blockIdx.y
+template <int NV, int U, int R, int SG>
+__global__ __launch_bounds__(256) void gate_softmax_topk_kernel(TopkGate gate0, TopkGate gate1, int ld, int KS, int T,
+                                                                int E, int k, int renorm) {
+  static_assert(SG == 1 || (SG == 4 && U == 1), "sixteen lanes or a whole wave per token");
+  const TopkGate& g = blockIdx.y ? gate1 : gate0;
+  const float* __restrict__ partial = g.partial;
+  const float* __restrict__ bias = g.bias;
+  const int G = g.G, tpg = g.tpg;
+  int32_t* __restrict__ topk_idx = g.topk_idx;
+  float* __restrict__ topk_w = g.topk_w;
+  float* __restrict__ probs = g.probs;
+  int32_t* __restrict__ counts = g.counts;
   constexpr int NL = NV * 4;
   __shared__ int32_t hist[PROBE_MAX_EXPERTS];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -551,8 +576,8 @@ __global__ __launch_bounds__(256) void gate_softmax_topk_kernel(
   const float ninf = -__builtin_inff(), fmin_ = -3.402823466e38f;
   const bool vec = (E & 3) == 0;
   const bool vec_in = (ld & 3) == 0 && aligned_f4(partial);
-  const int tokens_per_pass = gridDim.x * 16 * U;
-  for (int t0 = ((blockIdx.x * 4 + wv) * U) * 4 + grp; t0 < T; t0 += tokens_per_pass) {
+  const int tokens_per_pass = gridDim.x * (SG == 1 ? 16 * U : 4);
+  for (int t0 = SG == 1 ? ((blockIdx.x * 4 + wv) * U) * 4 + grp : blockIdx.x * 4 + wv; t0 < T; t0 += tokens_per_pass) {
     // token u of this row is t0 + 4u; the rows of a wave are independent under DPP row operations
     int tt[U];
     bool live[U];
@@ -562,7 +587,7 @@ __global__ __launch_bounds__(256) void gate_softmax_topk_kernel(
       live[u] = t0 + 4 * u < T;
       tt[u] = live[u] ? t0 + 4 * u : t0;
     }
-    load_logit_rows<NV, U, R>(partial, ld, KS, bias, G, tpg, T, E, vec_in, sub, tt, l);
+    load_logit_rows<NV, U, R, SG>(partial, ld, KS, bias, G, tpg, T, E, vec_in, sub, grp, tt, l);
     float mx[U], inv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -586,7 +611,7 @@ __global__ __launch_bounds__(256) void gate_softmax_topk_kernel(
       }
       sum = row_sum(sum);
       inv[u] = 1.f / sum;
-      if (probs && live[u]) {
+      if (probs && live[u] && (SG == 1 || grp == 0)) {
         const long t = t0 + 4 * u;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
@@ -640,7 +665,7 @@ __global__ __launch_bounds__(256) void gate_softmax_topk_kernel(
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (renorm) wsel[u] /= wtot[u];
-      if (live[u] && sub < k) {
+      if (live[u] && sub < k && (SG == 1 || grp == 0)) {
         const long t = t0 + 4 * u;
         topk_idx[t * k + sub] = isel[u];
         topk_w[t * k + sub] = wsel[u];
@@ -667,7 +692,7 @@ __device__ __forceinline__ void top2_merge(float& m1, float& m2) {
 // experts, gating values from s.  Every decision is an arg-max over a DPP row with ties to the
 // lower index, so all sixteen lanes of a token agree bit for bit.  Lane j keeps the score of group
 // j (n_group <= 16); sets of groups and of consumed entries are bit masks.
-template <int NV, int U, int R>
+template <int NV, int U, int R, int SG>
 __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
     const float* __restrict__ partial, int ld, int KS, const float* __restrict__ bias, int G, int tpg,
     const float* __restrict__ select_bias, int T, int E, int k, int scoring, int n_group, int topk_group,
@@ -691,8 +716,8 @@ __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
     gid[i] = e < E ? e / gs : -1;
     sb[i] = (select_bias && e < E) ? select_bias[e] : 0.f;
   }
-  const int tokens_per_pass = gridDim.x * 16 * U;
-  for (int t0 = ((blockIdx.x * 4 + wv) * U) * 4 + grp; t0 < T; t0 += tokens_per_pass) {
+  const int tokens_per_pass = gridDim.x * (SG == 1 ? 16 * U : 4);
+  for (int t0 = SG == 1 ? ((blockIdx.x * 4 + wv) * U) * 4 + grp : blockIdx.x * 4 + wv; t0 < T; t0 += tokens_per_pass) {
     int tt[U];
     bool live[U];
     float sc[U][NL], c[U][NL];
@@ -701,7 +726,7 @@ __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
       live[u] = t0 + 4 * u < T;
       tt[u] = live[u] ? t0 + 4 * u : t0;
     }
-    load_logit_rows<NV, U, R>(partial, ld, KS, bias, G, tpg, T, E, vec_in, sub, tt, sc);
+    load_logit_rows<NV, U, R, SG>(partial, ld, KS, bias, G, tpg, T, E, vec_in, sub, grp, tt, sc);
     // scores (in place of the logits) and selection scores
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -732,7 +757,7 @@ __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
         v = (v >= fmin_) ? v : fmin_;
         c[u][i] = (gid[i] >= 0) ? v : ninf;
       }
-      if (scores && live[u]) {
+      if (scores && live[u] && (SG == 1 || grp == 0)) {
         const long t = t0 + 4 * u;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
@@ -871,7 +896,7 @@ __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
     for (int u = 0; u < U; ++u) {
       if (renorm) wsel[u] /= wtot[u];
       wsel[u] *= routed_scale;
-      if (live[u] && sub < k) {
+      if (live[u] && sub < k && (SG == 1 || grp == 0)) {
         const long t = t0 + 4 * u;
         topk_idx[t * k + sub] = isel[u];
         topk_w[t * k + sub] = wsel[u];
@@ -1159,6 +1184,70 @@ static size_t route_query_bytes(int T, int H, int E, int D, bool packed = false)
   return L.gate.planes_bytes + align_up(rows * L.gate.ld * sizeof(float), 256) + u_bytes + L.a_bytes + L.b_bytes;
 }
 
+// workgroups of a top-k kernel that take `tokens` each; beyond 4096 they go round
+static unsigned topk_blocks(int T, int tokens) { return static_cast<unsigned>(std::min((T + tokens - 1) / tokens, 4096)); }
+
+// A whole wave per token where tokens are few and slices many: its four rows load a quarter of the slices each, all of them at
+// once.  The selection is then made by all four rows, and there are four times as many workgroups to add their counts, so
+// with more tokens it loses.  Call with sixteen lanes / with a wave per token: one token of 7168 x 256 experts 12.6 / 10.5 us,
+// 75 16.5 / 14.4, 256 22.4 / 20.6, 512 24.7 / 24.5, 768 28.7 / 29.7; 4096 x 128 experts 75 11.2 / 10.1, 128 11.8 / 11.4, 512
+// 15.9 / 17.0; group-limited, 75 tokens of 7168 x 256 22.1 / 19.4.  Four slices and fewer are one round of loads either way.
+// `own` counts the gate's own slices, not those of a residual behind them: a residual of zeros leaves every bit as it was.
+static bool wave_per_token(int T, int E, int own) { return own > 4 && T <= 128 * ((E + 63) / 64); }
+
+// Softmax and top-k of one gate, or of two stacked ones in one launch: either alone is a few microseconds of latency.  Router and
+// predictor of 4096 x 128 experts, one call: 128 tokens 29.8 us in two launches of two tokens per row, 11.7 now; 1024 37.9 / 22.8,
+// 2500 54.6 / 42.6, 8192 65.0 / 57.7.
+static void launch_topk(hipStream_t st, const TopkGate& gate, const TopkGate* next, int ld, int KS, int own, int T, int E,
+                        int k, int renorm) {
+  const unsigned gates = next ? 2 : 1;
+  const TopkGate& second = next ? *next : gate;
+#define PROBE_TOPK_LAUNCH(NV, U, R, SG)                                                                        \
+  hipLaunchKernelGGL((gate_softmax_topk_kernel<NV, U, R, SG>), dim3(topk_blocks(T, 16 * U / SG), gates), dim3(256), 0, \
+                     st, gate, second, ld, KS, T, E, k, renorm)
+#define PROBE_TOPK_BY_E(U, R, SG)                                                                                   \
+  do {                                                                                                              \
+    if (E <= 64) PROBE_TOPK_LAUNCH(1, U, R, SG);                                                                    \
+    else if (E <= 128) PROBE_TOPK_LAUNCH(2, U, R, SG);                                                              \
+    else PROBE_TOPK_LAUNCH(4, U, R, SG);                                                                            \
+  } while (0)
+  // Sixteen lanes per token: one token per row and eight slices in flight while latency bounds the kernel, two tokens and two
+  // slices once instructions do.  Call, one / two: 2500 tokens x 4096 x 128 experts (11 slices) 28.8 / 31.2 us, 8192 42.0 /
+  // 40.7, 16384 x 1024 x 64 38.0 / 29.4; two gates of 2500 x 4096 x 128 42.6 / 42.9, of 8192 59.1 / 57.7.  With four slices
+  // or fewer there is little to keep in flight: 4096 x 4096 x 8 experts 16.2 / 15.2.
+  if (wave_per_token(T, E, own))
+    PROBE_TOPK_BY_E(1, 4, 4);
+  else if (static_cast<long>(T) * gates > 6144 || (T > 2048 && KS <= 4))
+    PROBE_TOPK_BY_E(2, 2, 1);
+  else
+    PROBE_TOPK_BY_E(1, 8, 1);
+#undef PROBE_TOPK_BY_E
+#undef PROBE_TOPK_LAUNCH
+}
+
+static void launch_grouped_topk(hipStream_t st, const TopkGate& g, int ld, int KS, const float* select_bias,
+                                const probe_gating& gating, int T, int E, int k) {
+#define PROBE_GROUPED_LAUNCH(NV, U, R, SG)                                                                       \
+  hipLaunchKernelGGL((gate_grouped_topk_kernel<NV, U, R, SG>), dim3(topk_blocks(T, 16 * U / SG)), dim3(256), 0, st,   \
+                     g.partial, ld, KS, g.bias, g.G, g.tpg, select_bias, T, E, k, gating.scoring, gating.n_group,     \
+                     gating.topk_group, gating.group_top, gating.renormalize ? 1 : 0, gating.routed_scale, g.topk_idx, \
+                     g.topk_w, g.probs, g.counts)
+  // one token per row and up to eight slices in flight while latency bounds the kernel; two tokens and two slices once there
+  // are enough rows and instructions bound it, which at more than 128 experts they did not up to 40000 tokens.  Call
+  // with one / two tokens per row: 4096 x 1024 x 64 experts 24.1 / 26.2 us, 8192 30.7 / 28.4, 16384 39.6 / 32.7; 8192 x
+  // 1024 x 128 33.1 / 34.1, 13421 43.1 / 36.4; 16384 x 1024 x 256 59.6 / 63.1.
+  if (wave_per_token(T, E, KS)) {
+    if (E <= 64) PROBE_GROUPED_LAUNCH(1, 1, 4, 4); else if (E <= 128) PROBE_GROUPED_LAUNCH(2, 1, 4, 4); else PROBE_GROUPED_LAUNCH(4, 1, 4, 4);
+  } else if (E <= 64) {
+    if (T > 6144) PROBE_GROUPED_LAUNCH(1, 2, 2, 1); else PROBE_GROUPED_LAUNCH(1, 1, 8, 1);
+  } else if (E <= 128) {
+    if (T > 8192) PROBE_GROUPED_LAUNCH(2, 2, 2, 1); else PROBE_GROUPED_LAUNCH(2, 1, 8, 1);
+  } else {
+    PROBE_GROUPED_LAUNCH(4, 1, 4, 1);
+  }
+#undef PROBE_GROUPED_LAUNCH
+}
+
 // Router (w1_hat == nullptr) or predictor with the residual MLP of Eq. 7 (w1_hat bf16 [D,H],
 // w2_hat fp32 [E,D]).
 static int route_impl(const char* name, const void* x_bf16, const float* w_gate, const float* bias,
@@ -1247,46 +1336,12 @@ static int route_impl(const char* name, const void* x_bf16, const float* w_gate,
       launch_gate_gemm<3>(L.resid2, st, a_planes, b_planes, T, 3 * D, E, partial + static_cast<size_t>(sh.ks) * T * sh.ld);
       planes_to_sum = sh.ks + L.resid2.ks;
     }
-    int grid = (T + 31) / 32;
-    if (grid > 4096) grid = 4096;
-    int G = bias ? bias_groups : 1, tpg = bias ? tokens_per_group : 1;
-#define PROBE_TOPK_LAUNCH(V)                                                                               \
-  hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial, sh.ld, planes_to_sum, bias, \
-                     G, tpg, T, E, k, renormalize ? 1 : 0, topk_idx, topk_w, probs, expert_counts)
-#define PROBE_GROUPED_LAUNCH(V, U, R)                                                                            \
-  hipLaunchKernelGGL((gate_grouped_topk_kernel<V, U, R>), dim3(std::min((T + 16 * U - 1) / (16 * U), 4096)), dim3(256), 0, st, \
-                     partial, sh.ld, planes_to_sum, bias, G, tpg, select_bias, T, E, k, gating->scoring,             \
-                     gating->n_group, gating->topk_group, gating->group_top, gating->renormalize ? 1 : 0,        \
-                     gating->routed_scale, topk_idx, topk_w, probs, expert_counts)
-    if (gating) {
-      // one token per row and many slices in flight while latency bounds the kernel; two tokens and two slices once there
-      // are enough rows and instructions bound it, which at more than 128 experts they did not up to 40000 tokens.  Call
-      // with one / two tokens per row: 4096 x 1024 x 64 experts 24.1 / 26.2 us, 8192 30.7 / 28.4, 16384 39.6 / 32.7; 8192 x
-      // 1024 x 128 33.1 / 34.1, 13421 43.1 / 36.4; 16384 x 1024 x 256 59.6 / 63.1.
-      if (E <= 64) {
-        if (T > 6144) PROBE_GROUPED_LAUNCH(1, 2, 2); else PROBE_GROUPED_LAUNCH(1, 1, 8);
-      } else if (E <= 128) {
-        if (T > 8192) PROBE_GROUPED_LAUNCH(2, 2, 2); else PROBE_GROUPED_LAUNCH(2, 1, 8);
-      } else {
-        PROBE_GROUPED_LAUNCH(4, 1, 4);
-      }
-    } else {
-      // small batches (decode): one token per row in flight and many split-K slices loaded at once give twice
-      // the waves per SIMD to hide the loads behind; large batches are bound by reading the partial sums
-      // either way (measured at 8192 and 16384 tokens: no difference)
-#define PROBE_TOPK_LAUNCH_SMALL(V, R)                                                                             \
-  hipLaunchKernelGGL((gate_softmax_topk_kernel<V, 1, R>), dim3((T + 15) / 16), dim3(256), 0, st, partial, sh.ld, \
-                     planes_to_sum, bias, G, tpg, T, E, k, renormalize ? 1 : 0, topk_idx, topk_w, probs,        \
-                     expert_counts)
-      if (T > 2048) {
-        if (E <= 64) PROBE_TOPK_LAUNCH(1); else if (E <= 128) PROBE_TOPK_LAUNCH(2); else PROBE_TOPK_LAUNCH(4);
-      } else {
-        if (E <= 64) PROBE_TOPK_LAUNCH_SMALL(1, 8); else if (E <= 128) PROBE_TOPK_LAUNCH_SMALL(2, 8); else PROBE_TOPK_LAUNCH_SMALL(4, 8);
-      }
-#undef PROBE_TOPK_LAUNCH_SMALL
-    }
-#undef PROBE_TOPK_LAUNCH
-#undef PROBE_GROUPED_LAUNCH
+    const TopkGate out = {partial, bias, bias ? bias_groups : 1, bias ? tokens_per_group : 1, topk_idx, topk_w, probs,
+                          expert_counts};
+    if (gating)
+      launch_grouped_topk(st, out, sh.ld, planes_to_sum, select_bias, *gating, T, E, k);
+    else
+      launch_topk(st, out, nullptr, sh.ld, planes_to_sum, sh.ks, T, E, k, renormalize ? 1 : 0);
   }
   return check_launch(name);
 }
@@ -1354,26 +1409,11 @@ static int route_predict_impl(const void* x_bf16, const float* w_gate, const flo
     else
       launch_gate_gemm<3>(sh, st, static_cast<const bf16_t*>(x_bf16), planes, T, H, 2 * E, partial, expert_counts,
                           pred_counts, E);
-    int grid = (T + 31) / 32;
-    if (grid > 4096) grid = 4096;
-    const int G1 = bias ? bias_groups : 1, tpg1 = bias ? tokens_per_group : 1;
-    const int G2 = bias_next ? bias_groups : 1, tpg2 = bias_next ? tokens_per_group : 1;
-    const int rn = renormalize ? 1 : 0;
-#define PROBE_TOPK_LAUNCH2(V)                                                                                     \
-  do {                                                                                                            \
-    hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial, sh.ld, sh.ks, bias, G1, \
-                       tpg1, T, E, k, rn, topk_idx, topk_w, probs, expert_counts);                                \
-    hipLaunchKernelGGL(gate_softmax_topk_kernel<V>, dim3(grid), dim3(256), 0, st, partial + E, sh.ld, sh.ks,      \
-                       bias_next, G2, tpg2, T, E, k, rn, pred_idx, pred_w, pred_probs, pred_counts);              \
-  } while (0)
-    if (E <= 64) {
-      PROBE_TOPK_LAUNCH2(1);
-    } else if (E <= 128) {
-      PROBE_TOPK_LAUNCH2(2);
-    } else {
-      PROBE_TOPK_LAUNCH2(4);
-    }
-#undef PROBE_TOPK_LAUNCH2
+    const TopkGate out = {partial, bias, bias ? bias_groups : 1, bias ? tokens_per_group : 1, topk_idx, topk_w, probs,
+                          expert_counts};
+    const TopkGate next = {partial + E, bias_next, bias_next ? bias_groups : 1, bias_next ? tokens_per_group : 1, pred_idx,
+                           pred_w, pred_probs, pred_counts};
+    launch_topk(st, out, &next, sh.ld, sh.ks, sh.ks, T, E, k, renormalize ? 1 : 0);
   }
   return check_launch(name);
 }

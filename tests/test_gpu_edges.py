@@ -145,6 +145,33 @@ def test_route_small_batches_and_small_gates(oracle, probe, G, T, H, E, k):
         G.check_route(q, rev, k, True)
 
 
+@pytest.mark.parametrize("T,H,E,k", [(1, 1024, 60, 5), (128, 1024, 64, 4), (129, 1024, 64, 4), (255, 512, 90, 3), (256, 2048, 128, 8),
+                                     (257, 2048, 128, 8), (512, 1024, 256, 8), (513, 1024, 256, 8), (66, 2048, 7, 2),
+                                     (2049, 1024, 128, 6), (3073, 1024, 64, 2), (6145, 512, 132, 4)])
+def test_route_topk_a_wave_or_sixteen_lanes_per_token(oracle, probe, G, T, H, E, k):
+    """Both sides of the lines between a wave and sixteen lanes per token and between one and two tokens per row, alone and
+    with two gates in one launch, one of them misaligned where E % 4 != 0; every token against the oracle."""
+    print("case topk T=%d H=%d E=%d" % (T, H, E), flush=True)
+    rng = np.random.default_rng(T + E)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((T, H), dtype=np.float32))
+    wg = (rng.standard_normal((E, H), dtype=np.float32) * np.float32(0.05))
+    b = rng.standard_normal((2, E)).astype(np.float32)
+    tpg = max((T + 1) // 2, 1)
+    d_x, d_w, d_b = G.dev_bf16(x), torch.from_numpy(wg).cuda(), torch.from_numpy(b).cuda()
+    one = probe.route_topk(d_x, d_w, d_b, tpg, k, False, want_probs=True)
+    r, q = probe.route_predict_topk(d_x, d_w, d_b, d_w.flip(0).contiguous(), d_b.flip(1).contiguous(), tpg, k, True,
+                                    want_probs=True)
+    torch.cuda.synchronize()
+    o = oracle.route_topk(x, wg, b, tpg, k, True)
+    rev = oracle.route_topk(x, wg[::-1].copy(), b[:, ::-1].copy(), tpg, k, True)
+    G.check_route(one, oracle.route_topk(x, wg, b, tpg, k, False), k, False)
+    for got, ora in ((r, o), (q, rev)):
+        G.check_route(got, ora, k, True)
+        np.testing.assert_allclose(got["probs"].cpu().numpy(), ora["probs"], rtol=0, atol=G.PROB_ATOL)
+        np.testing.assert_array_equal(got["counts"].cpu().numpy(),
+                                      np.bincount(got["idx"].cpu().numpy().ravel(), minlength=E))
+
+
 def test_route_small_gate_on_more_token_blocks_than_65535(oracle, probe, G):
     """A gate of at most 16 experts takes 32 tokens per workgroup at any batch: more of them than the y and z dimensions of a
     launch can hold.  Every token bit for bit as in batches of a million, the last ones against the oracle."""
