@@ -51,6 +51,12 @@ __device__ __forceinline__ void wait_vm_lgkm0() {  // s_waitcnt vmcnt(N) lgkmcnt
 // leaves it in *draw_slot (LDS) before that step's barrier; after the loop every thread can read it.  Returns
 // whether that happened (it needs K >= 128).  After the barrier of the last k-step no wave reads the LDS stages.
 
+// STEPWISE: a fragment's products of one k-step are summed in registers of their own and added to the accumulators by the
+// vector units, so a chain of additions in the matrix cores is PL * 2 products of 32 long and not K / 32 of them.  Their error
+// grows with the length of a chain almost linearly (7168 x 256 experts, probabilities against 64 bits: 1.7e-6 at chains of 56
+// k-steps, 9.7e-7 at 28, 4.6e-7 at 7; stepwise 4.0e-7, 3.0e-7, 3.2e-7).  Four additions per MFMA row of a k-step: no
+// time on the 128-token tile of the gate, 3 to 5 % on the 256-token tile.
+
 // 16-byte chunk c of tile row r is stored at chunk position c ^ key(r), so that the sixteen rows of a fragment reading
 // the same logical chunk cover all 64 banks exactly once: sixteen consecutive rows, or (PERM) the rows 8a + b + const,
 // a and b = 0..3.
@@ -59,7 +65,8 @@ __device__ __forceinline__ int lds_key(int row) {
   return PERM ? ((row >> 1) & 1) | (((row >> 3) & 3) << 1) : (row >> 1) & 7;
 }
 
-template <int MI, int NI, int PL, int NST, bool PERM = false, bool DRAW = false, bool AROUND = false>
+template <int MI, int NI, int PL, int NST, bool PERM = false, bool DRAW = false, bool AROUND = false,
+          bool STEPWISE = false>
 __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgpu_buffer_rsrc_t rB,
                                               const int (&voff)[MI + NI * PL * 2], int k0, int K,
                                               u32x4* smem, int wv, int lane, f32x4 (&acc)[2 * MI][2 * NI],
@@ -122,6 +129,7 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
     return smem[st * kStage + (BM + brow + row) * 8 + ((4 * kk + (lane >> 4)) ^ bkey)];
   };
   u32x4 a[W], b[2][NB];
+  f32x4 part[2][BF];
   // plane slowest, so consecutive MFMAs hit different accumulators; columns run back and forth, so the MFMAs on either
   // side of a step's end share an operand.  The weight fragment is the row operand.
   auto mfma_step = [&](int t) {
@@ -131,8 +139,17 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
 #pragma unroll
       for (int c = 0; c < BF; ++c) {
         const int j = ((t + p) & 1) ? BF - 1 - c : c;
-        acc[i][j] = mfma_16x16x32(b[kk][p * BF + j], a[t % W], acc[i][j]);
+        if constexpr (STEPWISE)
+          part[t & 1][j] = mfma_16x16x32(b[kk][p * BF + j], a[t % W],
+                                         kk == 0 && p == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[t & 1][j]);
+        else
+          acc[i][j] = mfma_16x16x32(b[kk][p * BF + j], a[t % W], acc[i][j]);
       }
+  };
+  // STEPWISE: the sums of a fragment's k-step, complete with step t, go to the accumulators
+  auto add_step = [&](int t) {
+#pragma unroll
+    for (int j = 0; j < BF; ++j) acc[frag_of(t)][j] += part[t & 1][j];
   };
 
   // prologue: NST batches in flight, wait for the first
@@ -178,6 +195,9 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
       }
+      if constexpr (STEPWISE) {
+        if (t > 0 && t % 4 == 0) add_step(t - 1);
+      }
       if (t == BAR) {
         // every read of stage cur is issued: wait for them and for this wave's share of tile kt+1; what was issued
         // after that share may stay in flight
@@ -200,6 +220,9 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
       }
       mfma_step(t);
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (STEPWISE) {  // one step late, when the matrix cores are done with them
+        if (t % 4 == 3) add_step(t - 1);
+      }
       if (t + W < STEPS) {
         a[t % W] = read_a(cur, t + W);
       } else if constexpr (NEXT) {
@@ -216,6 +239,7 @@ __device__ __forceinline__ bool gemm_mainloop(__amdgpu_buffer_rsrc_t rA, __amdgp
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (STEPWISE) add_step(STEPS - 1);
   };
   using T_ = std::integral_constant<bool, true>;
   using F_ = std::integral_constant<bool, false>;

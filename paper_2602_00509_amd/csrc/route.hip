@@ -179,7 +179,8 @@ constexpr int kGateLdsBytes = 2 * (256 + 384) * 128;
 constexpr int gate_stages(int mi, int planes) { return mi == 4 && planes == 1 ? 3 : 2; }
 static_assert(3 * (256 + 128) * 128 <= kGateLdsBytes, "three stages of the one-plane tile");
 
-template <int MI, int PL>
+// STEPWISE: the products of a k-step are summed by themselves and added to the accumulators (gemm_mainloop).
+template <int MI, int PL, bool STEPWISE>
 __global__ __launch_bounds__(512, 2) void gate_gemm_dma_kernel(const bf16_t* __restrict__ x,
                                                                const bf16_t* __restrict__ planes,
                                                                int T, int H, int E, int k_chunk,
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(512, 2) void gate_gemm_dma_kernel(const bf16_t* __r
   f32x4 acc[2 * MI][2];
 #pragma unroll
   for (int i = 0; i < 2 * MI; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  gemm_mainloop<MI, 1, PL, gate_stages(MI, PL)>(rA, rB, voff, kbeg, klen, smem, wv, lane, acc);
+  gemm_mainloop<MI, 1, PL, gate_stages(MI, PL), false, false, false, STEPWISE>(rA, rB, voff, kbeg, klen, smem, wv, lane, acc);
 
 #pragma unroll
   for (int i = 0; i < 2 * MI; ++i) {
@@ -348,11 +349,13 @@ static int gate_prepare() {
   std::lock_guard<std::mutex> lock(mu);
   if (done[dev]) return PROBE_OK;
   hipError_t err = hipSuccess;
-  const void* kernels[4] = {reinterpret_cast<const void*>(gate_gemm_dma_kernel<2, 3>),
-                            reinterpret_cast<const void*>(gate_gemm_dma_kernel<4, 3>),
-                            reinterpret_cast<const void*>(gate_gemm_dma_kernel<2, 1>),
-                            reinterpret_cast<const void*>(gate_gemm_dma_kernel<4, 1>)};
-  for (int i = 0; i < 4 && err == hipSuccess; ++i)
+  const void* kernels[6] = {reinterpret_cast<const void*>(gate_gemm_dma_kernel<2, 3, true>),
+                            reinterpret_cast<const void*>(gate_gemm_dma_kernel<4, 3, false>),
+                            reinterpret_cast<const void*>(gate_gemm_dma_kernel<4, 3, true>),
+                            reinterpret_cast<const void*>(gate_gemm_dma_kernel<2, 1, true>),
+                            reinterpret_cast<const void*>(gate_gemm_dma_kernel<4, 1, false>),
+                            reinterpret_cast<const void*>(gate_gemm_dma_kernel<4, 1, true>)};
+  for (int i = 0; i < 6 && err == hipSuccess; ++i)
     err = hipFuncSetAttribute(kernels[i], hipFuncAttributeMaxDynamicSharedMemorySize, kGateLdsBytes);
   if (err != hipSuccess) {
     set_error("probe_route_topk: cannot reserve %d bytes of LDS: %s", kGateLdsBytes, hipGetErrorString(err));
@@ -996,6 +999,7 @@ struct RouteShape {
   bool dma;  // H % 64 == 0: the DMA-to-LDS pipeline; otherwise the register-staged kernel
   int bm;    // tokens per workgroup of the gemm (128 or 256)
   int mt, nt, ks, k_chunk;
+  bool stepwise;    // DMA pipeline: sums by k-step
   int ks_room;      // slices that the workspace has room for: those of the tiled kernels, which the direct one never exceeds
   int ld;           // entries of a row of partial sums: E rounded up to whole 16-byte pieces (the last ones are read as part
                     // of a piece and not looked at)
@@ -1022,8 +1026,8 @@ static int gate_slice_steps(int ksteps, int want, int max_split) {
   if (want < 1) want = 1;
   return (ksteps + want - 1) / want;
 }
-// 256-token tiles when a split of 8 or less still gives every CU a workgroup; they aim at one
-// workgroup per CU (fewer, longer K ranges and half the partial sums), 128-token tiles at two
+// Room for slices: 256-token tiles when a split of 8 or less still gives every CU a workgroup, split for one workgroup per
+// CU, otherwise 128-token tiles, split for two.  The register-staged kernel runs as many; the others choose up to that.
 constexpr int kBigTileItems = 32;
 static bool gate_dma(int H, int E) { return H % 64 == 0 && static_cast<size_t>(3) * E * H * 2 <= 0x7fffffffull; }
 static int gate_target(int bm) { return bm == 256 ? 256 : 512; }
@@ -1048,6 +1052,39 @@ static int small_gate_frags(int T, int H, int E) {
   return E <= 4 || two_share > one_share || (two_share == one_share && (E <= 8 || H >= 4096)) ? 2 * f : f;
 }
 
+// Tile height and slices of the DMA pipeline, from what the pieces were seen to take, in microseconds: a k-step of a round of
+// workgroups (one to a CU, their LDS stages fill it) 1.2 with 128 tokens and 2.04 with 256, a slice 0.6 per MB written and
+// read, every eight slices of the top-k kernel's loads 1.  Over 46 batches of 200..16384 tokens x 64, 128, 256 experts the
+// choice is 0.3 % above the best of all heights and slices on average, 3.1 % at most.  Before, the slices were those that give every
+// CU one (256 tokens) or two workgroups (128), rounded up, and a last round of a few workgroups followed.  Packed router,
+// before / now: 2500 tokens x 4096 x 128 experts 28.9 / 23.5 us, 2048 x 7168 x 256 42.1 / 35.1, 5500 88.4 / 68.9, 12000
+// 153.0 / 130.2; both gates of 2500 x 4096 x 128 in one call 42.6 / 30.1.
+// Fewer slices are longer chains of additions: where a chain grows its sums are made by k-step, and their error against 64
+// bits falls (probabilities, 5500 x 7168 x 256: 7.5e-7 before, 2.8e-7; 2500 x 4096 x 128: 2.9e-7, 2.1e-7).  The 128-token tile
+// always does that; the 256-token tile loses 3 to 5 % by it and keeps to the accumulators where its chains stay as short.
+// The shape that the room is made for stays unless another should be a tenth faster: below that the estimate does not decide.
+static void choose_gate_tiles(RouteShape& s, int T, int ksteps) {
+  const int bm_room = s.bm, steps_room = s.k_chunk / GBK;
+  const double slice = 0.6e-6 * sizeof(float) * T * s.ld;
+  auto cost = [&](int bm, int ks, int steps) {
+    const int rounds = ((T + bm - 1) / bm * s.nt * ks + 255) / 256;
+    return rounds * steps * (bm == 128 ? 1.2 : 2.04) + slice * ks + (ks + 7) / 8;
+  };
+  double best = 0.9 * cost(bm_room, s.ks_room, steps_room);
+  for (const int bm : {128, 256}) {
+    for (int ks = 1; ks <= s.ks_room; ++ks) {
+      const int steps = (ksteps + ks - 1) / ks;
+      if ((ksteps + steps - 1) / steps != ks || cost(bm, ks, steps) >= best) continue;  // or the same steps in fewer slices
+      best = cost(bm, ks, steps);
+      s.bm = bm;
+      s.ks = ks;
+      s.k_chunk = steps * GBK;
+    }
+  }
+  s.mt = (T + s.bm - 1) / s.bm;
+  s.stepwise = s.bm == 128 || s.k_chunk / GBK > steps_room;
+}
+
 static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
   RouteShape s;
   s.dma = gate_dma(H, E);
@@ -1062,6 +1099,7 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
   s.k_chunk = steps_per * GBK;
   s.ks = (ksteps + steps_per - 1) / steps_per;
   s.ks_room = s.ks;
+  s.stepwise = false;
   s.direct = static_cast<long>(T) * E <= (H % 64 == 0 ? 1 : 8) * kDirectLogits ||
              (E <= kDirectExperts && T <= kDirectTokens);
   s.frags = s.per_wave = 0;
@@ -1073,6 +1111,8 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
     split = split < 1 ? 1 : (split > max_split ? max_split : split);
     s.per_wave = (k32 + 8 * split - 1) / (8 * split);
     s.ks = (k32 + 8 * s.per_wave - 1) / (8 * s.per_wave);
+  } else if (s.dma && T > 0) {
+    choose_gate_tiles(s, T, ksteps);
   }
   s.planes_bytes = align_up(static_cast<size_t>(3) * E * H * sizeof(bf16_t), 256);
   s.partial_bytes = align_up(static_cast<size_t>(s.ks_room) * (T > 0 ? T : 1) * s.ld * sizeof(float), 256);
@@ -1109,12 +1149,16 @@ static void launch_gate_gemm(const RouteShape& sh, hipStream_t st, const bf16_t*
     launch_gate_direct<PL, false>(sh, st, x, GateRows{planes, nullptr, nullptr, 0}, T, H, N, partial, zero0, zero1, n_zero);
   } else if (sh.dma) {
     const int lds = gate_stages(sh.bm / 64, PL) * (sh.bm + 128 * PL) * 128;
-    if (sh.bm == 256)
-      hipLaunchKernelGGL((gate_gemm_dma_kernel<4, PL>), dim3(sh.mt, sh.nt, sh.ks), dim3(512), lds, st, x, planes, T,
-                         H, N, sh.k_chunk, partial, sh.ld, zero0, zero1, n_zero);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(sh.mt, sh.nt, sh.ks), dim3(512), lds, st, x, planes, T, H, N, sh.k_chunk, partial, sh.ld,
+                         zero0, zero1, n_zero);
+    };
+    if (sh.bm == 128)
+      launch(gate_gemm_dma_kernel<2, PL, true>);
+    else if (sh.stepwise)
+      launch(gate_gemm_dma_kernel<4, PL, true>);
     else
-      hipLaunchKernelGGL((gate_gemm_dma_kernel<2, PL>), dim3(sh.mt, sh.nt, sh.ks), dim3(512), lds, st, x, planes, T,
-                         H, N, sh.k_chunk, partial, sh.ld, zero0, zero1, n_zero);
+      launch(gate_gemm_dma_kernel<4, PL, false>);
   } else {
     hipLaunchKernelGGL(gate_gemm_kernel<PL>, dim3(sh.mt, sh.nt, sh.ks), dim3(256), 0, st, x, planes, T, H, N,
                        sh.k_chunk, partial, sh.ld, zero0, zero1, n_zero);

@@ -211,6 +211,29 @@ def test_route_on_256_token_tiles_with_a_ragged_last_tile(oracle, probe, G, T, H
     np.testing.assert_array_equal(g["counts"].cpu().numpy(), np.bincount(g["idx"].cpu().numpy().ravel(), minlength=E))
 
 
+@pytest.mark.parametrize("T,H,E,k", [(600, 1024, 128, 4), (2049, 320, 130, 4), (5500, 512, 256, 8), (9001, 1024, 130, 6),
+                                     (16385, 512, 130, 2), (16129, 2048, 130, 2)])
+def test_route_tile_heights_and_slices(oracle, probe, G, T, H, E, k):
+    """128- and 256-token tiles with ragged last tiles and slices, sums by k-step and in the accumulators; a sample of the tokens and all
+    of the last tile's against the oracle, all probabilities against the product in 64 bits."""
+    print("case tiles T=%d H=%d E=%d" % (T, H, E), flush=True)
+    rng = np.random.default_rng(T + E)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((T, H), dtype=np.float32))
+    wg = (rng.standard_normal((E, H), dtype=np.float32) * np.float32(0.05))
+    b = rng.standard_normal((2, E)).astype(np.float32)
+    tpg = (T + 1) // 2
+    d_x, d_w, d_b = G.dev_bf16(x), torch.from_numpy(wg).cuda(), torch.from_numpy(b).cuda()
+    g = probe.route_topk(d_x, d_w, d_b, tpg, k, True, want_probs=True)
+    torch.cuda.synchronize()
+    tokens = np.unique(np.concatenate([rng.choice(T, 300, replace=False), np.arange(T - min(T, 256), T)]))
+    o = oracle.route_topk(x[tokens], wg, G.gather_bias(b, tpg, tokens), 1, k, True)
+    sub = {key: g[key][torch.from_numpy(tokens).cuda()] for key in ("idx", "w", "probs")}
+    G.check_route(sub, o, k, True, tokens=None)
+    np.testing.assert_array_equal(g["counts"].cpu().numpy(), np.bincount(g["idx"].cpu().numpy().ravel(), minlength=E))
+    logits = d_x.double() @ d_w.double().t() + d_b.double()[torch.arange(T, device="cuda") // tpg]
+    np.testing.assert_allclose(g["probs"].cpu().numpy(), torch.softmax(logits, 1).cpu().numpy(), rtol=0, atol=G.PROB_ATOL)
+
+
 def test_determinism_and_plan_invariance(oracle, probe, G):
     """Two runs are bit-identical; with every replica local, any plan gives the same layer output."""
     print("case determinism / plan invariance", flush=True)
