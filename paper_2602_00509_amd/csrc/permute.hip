@@ -5,30 +5,40 @@
 // atomics: a pair's destination row follows from (expert e, arrival rank j) alone.
 //
 //   1. hist     each workgroup counts the experts of its own contiguous block of 1024 pairs
-//               (wave ballots, LDS counters)                             -> blk_hist[U][E]
+//               (LDS counters)                                           -> blk_hist[U][E]
 //   2. index    every workgroup sums the block histograms (its exclusive base = the blocks before it,
 //               n_e = all blocks), derives the rows per replica in closed form and the prefix sum over
-//               slots (workgroup 0 writes slot_counts, slot_offsets, n_local), then re-walks its block
-//               (each wave a 256-pair segment, bases of the later waves from the earlier waves' counts),
-//               ranks each pair among equal experts with wave ballots and computes slot and row
+//               slots (workgroup 0 writes slot_counts, slot_offsets, n_local), ranks the pairs of its block among
+//               equal experts (wave ballots, counts of the earlier waves) and computes slot and row
 //               analytically                                             -> pair_row, row_pair
 //   3. scatter  one thread per 16-byte chunk of a token row: read x once, write it to each of
 //               the token's local rows                                   -> xp
-// A batch of at most 1024 pairs (decode) runs steps 1-2 as one workgroup in one launch; a batch of more than
-// 262144 pairs runs step 2 as a one-workgroup scan kernel followed by the ranking kernel.
+// Up to 16384 pairs the index kernel counts all blocks itself (no step 1), and up to 8192 it also copies the rows (no step 3); a
+// batch of more than 262144 pairs runs step 2 as a one-workgroup scan kernel followed by the ranking kernel.
 //
 // Steps 1-2 touch only T*k integers; step 3 carries the HBM traffic (T*H*2 bytes read at
 // most, n_local*H*2 written).
+#include <algorithm>
 #include <mutex>
 
 #include "common.hpp"
 
 namespace probe {
 
-constexpr int kPermWaves = 4;                 // waves per workgroup in steps 1 and 3
-constexpr int kSegPairs = 256;                // pairs per wave segment
+constexpr int kPermWaves = 4;                 // waves per workgroup of the separate ranking kernel
+constexpr int kSegPairs = 256;                // pairs per wave segment there
 constexpr int kSegIters = kSegPairs / kWave;  // 4 wave-wide iterations per segment
+constexpr int kIndexThreads = 1024;           // threads of a workgroup with one pair each
+constexpr int kIndexWaves = kIndexThreads / kWave;
 constexpr int kRepLds = 2048;                 // replica-list entries staged in LDS by the index kernel
+// Blocks up to which every workgroup counts all of them instead of reading histograms that a launch of its own made.  Index part of
+// the call, histograms / own counts: 2 blocks (129 tokens, top-8 of 128) 6.3 / 4.7 us, 8 7.6 / 5.6, 16 7.7 / 6.5 (top-2 of 8: 7.8 /
+// 8.0), 24 7.9 / 7.8, 32 7.9 / 8.5, 64 8.1 / 12.6.
+constexpr int kSelfBlocks = 16;
+// Blocks up to which it also copies the rows, several workgroups to a block: 512 tokens x 4096, top-8 of 128 16.0 -> 6.9 us (9.4 with a
+// launch for the copy).  From 16 blocks on there would be too many workgroups that all count (8192 tokens x 512, top-2
+// of 8: 16.7 us, with its own launch 12).
+constexpr int kScatterBlocks = 8;
 constexpr int kFusedBlocks = 256;             // up to this many blocks (262144 pairs) step 2 is one launch
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
@@ -48,29 +58,19 @@ __device__ __forceinline__ uint64_t match_key8(int key, bool valid) {
   return valid ? m : 0ull;
 }
 
-// Step 1.
-__global__ __launch_bounds__(kPermWaves* kWave) void permute_hist_kernel(
+// Step 1.  One pair per thread, four counters per expert (the lanes of a wave that hold a popular expert seldom meet).
+__global__ __launch_bounds__(kIndexThreads) void permute_hist_kernel(
     const int32_t* __restrict__ topk_idx, int N, int E, int32_t* __restrict__ blk_hist) {
-  __shared__ int32_t cnt_mem[kPermWaves][PROBE_MAX_EXPERTS];
-  int w = threadIdx.x / kWave, lane = lane_id();
-  volatile int32_t* cnt_w = cnt_mem[w];  // volatile: keep every lane's read before the leader's update
-  for (int e = lane; e < E; e += kWave) cnt_w[e] = 0;
-  long base = (static_cast<long>(blockIdx.x) * kPermWaves + w) * kSegPairs;
-  // same-wave LDS accesses execute in program order; no barrier needed for a wave's own row
-  for (int it = 0; it < kSegIters; ++it) {
-    long p = base + it * kWave + lane;
-    int e = p < N ? topk_idx[p] : -1;
-    bool valid = static_cast<unsigned>(e) < static_cast<unsigned>(E);  // bad ids count nowhere
-    uint64_t m = match_key8(e, valid);
-    if (valid && (m & lanemask_lt()) == 0) cnt_w[e] += __popcll(m);
-  }
+  __shared__ int32_t counts[4][PROBE_MAX_EXPERTS];
+  const int tid = threadIdx.x;
+  const long p = static_cast<long>(blockIdx.x) * kIndexThreads + tid;
+  const int e = p < N ? topk_idx[p] : -1;
+  counts[tid >> 8][tid & 255] = 0;
   __syncthreads();
-  for (int e = threadIdx.x; e < E; e += kPermWaves * kWave) {
-    int tot = 0;
-#pragma unroll
-    for (int q = 0; q < kPermWaves; ++q) tot += cnt_mem[q][e];
-    blk_hist[static_cast<long>(blockIdx.x) * E + e] = tot;
-  }
+  if (static_cast<unsigned>(e) < static_cast<unsigned>(E)) atomicAdd(&counts[tid & 3][e], 1);  // bad ids count nowhere
+  __syncthreads();
+  if (tid < E)
+    blk_hist[static_cast<long>(blockIdx.x) * E + tid] = counts[0][tid] + counts[1][tid] + counts[2][tid] + counts[3][tid];
 }
 
 // Steps 2a / 2b for batches of more than kFusedBlocks blocks, where every workgroup summing all block
@@ -301,364 +301,214 @@ __global__ __launch_bounds__(kPermWaves* kWave) void permute_index_kernel(
   }
 }
 
-// Steps 1-2 in one workgroup, for batches of at most 1024 pairs (decode): the block histogram is the
-// global one, so the scan over blocks disappears and the whole index computation is one launch.
-__global__ __launch_bounds__(kPermWaves* kWave) void permute_small_kernel(
-    const int32_t* __restrict__ topk_idx, int N, int E, const int32_t* __restrict__ rep_off,
-    const int32_t* __restrict__ rep_slot, const int32_t* __restrict__ rep_weight, int S,
-    int32_t* __restrict__ slot_counts, int32_t* __restrict__ slot_offsets, int32_t* __restrict__ n_local,
-    int32_t* __restrict__ pair_row, int32_t* __restrict__ row_pair) {
-  __shared__ int32_t cnt_mem[kPermWaves][PROBE_MAX_EXPERTS];
+// Steps 1-2 of a block of 1024 pairs, one pair per thread: ranks within a wave by ballots, ranks between the sixteen waves and
+// the blocks by counts in LDS.  Every workgroup derives the slot counts and offsets from the totals n_e (redundantly,
+// workgroup 0 writes them out).  What bounds it is a chain of latencies: ids and plan offsets, the replica lists behind
+// them, four barriers.  With 256 threads that walked four pairs each one after another, the call without the copy took 8.2 us
+// for 128 tokens, top-8 of 128 experts (now 4.4), 13.9 for 1000 (5.6), 14.1 for 8192 (8.1), 19.8 for 30000 (12.2).
+//   COUNT_SELF  the workgroup counts all blocks itself: no histogram launch in front of it (4 to 6 us), but every workgroup
+//               reads all ids
+//   otherwise   it sums the block histograms of permute_hist_kernel
+//   SCATTER     several workgroups to a block (blockIdx.x): each derives all of it and copies its share of the block's token rows
+//               to their rows of xp, taken from LDS; the first writes the index outputs
+struct IndexOut {
+  int32_t *slot_counts, *slot_offsets, *n_local, *pair_row, *row_pair;
+};
+
+template <bool COUNT_SELF, bool SCATTER>
+__global__ __launch_bounds__(kIndexThreads) void permute_block_kernel(
+    const int32_t* __restrict__ topk_idx, int N, int E, const int32_t* __restrict__ blk_hist, int U,
+    const int32_t* __restrict__ rep_off, const int32_t* __restrict__ rep_slot,
+    const int32_t* __restrict__ rep_weight, int S, IndexOut out, const u32x4* __restrict__ x, int k,
+    int chunks_per_row, u32x4* __restrict__ xp) {
+  __shared__ int32_t cnt[kIndexWaves][PROBE_MAX_EXPERTS];   // counts of a wave's pairs, then arrival rank at its start
+  __shared__ int32_t other[2][4][PROBE_MAX_EXPERTS];        // [0] blocks before this one, [1] this one and those behind it
   __shared__ int32_t e_lo[PROBE_MAX_EXPERTS], e_hi[PROBE_MAX_EXPERTS], e_P[PROBE_MAX_EXPERTS];
   __shared__ int32_t s_off[PROBE_MAX_SLOTS + 1], sc[PROBE_MAX_SLOTS];
   __shared__ int32_t s_rw[kRepLds], s_rs[kRepLds];
-  __shared__ int32_t wave_tot[kPermWaves];
+  __shared__ int32_t wave_tot[kIndexWaves];
+  __shared__ int32_t row_of[SCATTER ? kIndexThreads : 1];
   const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
-  volatile int32_t* cnt_w = cnt_mem[w];  // volatile: keep every lane's read before the leader's update
-  const long base = static_cast<long>(w) * kSegPairs;
-  // The kernel is a chain of dependent global loads, so every load that depends on nothing is issued first: the
-  // segment's expert ids, the size of the replica list and this thread's replica range (E <= 256 = threads).
-  static_assert(kPermWaves * kWave >= PROBE_MAX_EXPERTS, "one expert per thread");
-  int seg_e[kSegIters];
-#pragma unroll
-  for (int it = 0; it < kSegIters; ++it) {
-    const long p = base + it * kWave + lane;
-    seg_e[it] = p < N ? topk_idx[p] : -1;
-  }
+  const int b = blockIdx.y;
+  const bool writer = blockIdx.x == 0;  // of the block's index outputs
+  const long p = static_cast<long>(b) * kIndexThreads + tid;
+  // loads that depend on nothing first
+  const int my_e = p < N ? topk_idx[p] : -1;
   const int R = rep_off[E];
   int my_lo = 0, my_hi = 0;
   if (tid < E) {
     my_lo = rep_off[tid];
     my_hi = rep_off[tid + 1];
   }
+  const int group = tid >> 8, ge = tid & 255;  // four groups of 256 threads
+#pragma unroll
+  for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) cnt[w][lane + i * kWave] = 0;
+  if (tid < S) sc[tid] = 0;
+  if constexpr (COUNT_SELF) {
+    if (U > 1) {
+      // four counters per expert, so that the lanes of a wave that hold a popular expert seldom meet
+      other[0][group][ge] = other[1][group][ge] = 0;
+      __syncthreads();
+      constexpr int kBatch = 8;  // blocks whose loads are in flight together
+      for (int u0 = 0; u0 < U; u0 += kBatch) {
+        int id[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+          const long at = static_cast<long>(u0 + q) * kIndexThreads + tid;
+          id[q] = at < N ? topk_idx[at] : -1;
+        }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q)
+          if (static_cast<unsigned>(id[q]) < static_cast<unsigned>(E)) atomicAdd(&other[u0 + q < b ? 0 : 1][tid & 3][id[q]], 1);
+      }
+    }
+  } else {
+    int before = 0, rest = 0;
+    constexpr int kBatch = 16;  // blocks of a group whose loads are in flight together
+    if (ge < E)
+      for (int u0 = group; u0 < U; u0 += 4 * kBatch) {
+        int c[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+          const int u = u0 + 4 * q;
+          c[q] = u < U ? blk_hist[static_cast<long>(u) * E + ge] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+          const bool is_before = u0 + 4 * q < b;
+          before += is_before ? c[q] : 0;
+          rest += is_before ? 0 : c[q];
+        }
+      }
+    other[0][group][ge] = before;
+    other[1][group][ge] = rest;
+  }
   const bool staged = R <= kRepLds;
   if (staged)
-    for (int i = tid; i < R; i += kPermWaves * kWave) {
+    for (int i = tid; i < R; i += kIndexThreads) {
       s_rw[i] = rep_weight[i];
       s_rs[i] = rep_slot[i];
     }
-  const int32_t* rw = staged ? s_rw : rep_weight;
+  const int32_t* rw = staged ? s_rw : rep_weight;  // flat pointers: LDS or global
   const int32_t* rs = staged ? s_rs : rep_slot;
+  // rank among the equal experts of the wave; its first lane leaves the count (a wave's own row: no barrier since the clearing)
+  const bool valid = static_cast<unsigned>(my_e) < static_cast<unsigned>(E);  // bad ids count nowhere
+  const uint64_t m = match_key8(my_e, valid);
+  const int rank = __popcll(m & lanemask_lt());
+  if (valid && rank == 0) cnt[w][my_e] = __popcll(m);
+  __syncthreads();
   if (tid < E) {
-    int P = 0;
-    for (int i = my_lo; i < my_hi; ++i) P += rep_weight[i];
+    // rows each replica receives: floor(n/P) w_i + clamp(n mod P - c_{i-1}, 0, w_i)
+    int n_e = 0, P = 0;
+    if (COUNT_SELF && U <= 1) {
+#pragma unroll
+      for (int q = 0; q < kIndexWaves; ++q) n_e += cnt[q][tid];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) n_e += other[0][q][tid] + other[1][q][tid];
+    }
+    for (int i = my_lo; i < my_hi; ++i) P += rw[i];
     e_lo[tid] = my_lo;
     e_hi[tid] = my_hi;
     e_P[tid] = P;
-  }
-  for (int s = tid; s < S; s += kPermWaves * kWave) sc[s] = 0;
-  // counts of this wave's segment
-  for (int e = lane; e < E; e += kWave) cnt_w[e] = 0;
-#pragma unroll
-  for (int it = 0; it < kSegIters; ++it) {
-    const int e = seg_e[it];
-    bool valid = static_cast<unsigned>(e) < static_cast<unsigned>(E);
-    uint64_t m = match_key8(e, valid);
-    if (valid && (m & lanemask_lt()) == 0) cnt_w[e] += __popcll(m);
-  }
-  __syncthreads();
-  // rows each replica receives: floor(n/P) w_i + clamp(n mod P - c_{i-1}, 0, w_i)
-  for (int e = tid; e < E; e += kPermWaves * kWave) {
-    int n_e = 0;
-#pragma unroll
-    for (int q = 0; q < kPermWaves; ++q) n_e += cnt_mem[q][e];
-    const int P = e_P[e];
     if (P > 0) {
       int full = n_e / P, rem = n_e - full * P, cum = 0;
-      for (int i = e_lo[e]; i < e_hi[e]; ++i) {
-        int wgt = rw[i];
-        int part_rows = min(max(rem - cum, 0), wgt);
-        int slot = rs[i];
+      for (int i = my_lo; i < my_hi; ++i) {
+        const int wgt = rw[i];
+        const int part_rows = min(max(rem - cum, 0), wgt);
+        const int slot = rs[i];
         if (slot >= 0 && slot < S) sc[slot] = full * wgt + part_rows;
         cum += wgt;
       }
     }
   }
-  __syncthreads();
-  // exclusive prefix sum over the slots, 4 consecutive slots per thread
-  int v[4], local = 0;
+  if (COUNT_SELF && U <= 1) __syncthreads();  // the counts were read above
+  if (group == 1) {
+    // arrival rank at the start of each wave's pairs: the blocks before this one + the earlier waves
+    int run = 0;
+    if (!(COUNT_SELF && U <= 1)) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int s = tid * 4 + i;
-    v[i] = s < S ? sc[s] : 0;
-    local += v[i];
+      for (int q = 0; q < 4; ++q) run += other[0][q][ge];
+    }
+    int c[kIndexWaves];
+#pragma unroll
+    for (int q = 0; q < kIndexWaves; ++q) c[q] = cnt[q][ge];
+#pragma unroll
+    for (int q = 0; q < kIndexWaves; ++q) {
+      cnt[q][ge] = run;
+      run += c[q];
+    }
   }
-  int incl = local;
+  __syncthreads();
+  // exclusive prefix sum over the slots, one per thread
+  const int rows = tid < S ? sc[tid] : 0;
+  int incl = rows;
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
-    int o = __shfl_up(incl, d, kWave);
+    const int o = __shfl_up(incl, d, kWave);
     if (lane >= d) incl += o;
   }
-  if (lane == kWave - 1) wave_tot[w] = incl;
-  __syncthreads();
-  {
-    int excl = incl - local;
+  int excl = incl - rows;
+  if (S > kWave) {
+    if (lane == kWave - 1) wave_tot[w] = incl;
+    __syncthreads();
     for (int i = 0; i < w; ++i) excl += wave_tot[i];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int s = tid * 4 + i;
-      if (s < S) {
-        slot_counts[s] = v[i];
-        slot_offsets[s] = excl;
-        s_off[s] = excl;
-      }
-      excl += v[i];
-    }
-    if (tid == kPermWaves * kWave - 1) {
-      slot_offsets[S] = excl;
-      n_local[0] = excl;
-      s_off[S] = excl;
-    }
   }
-  // arrival rank at the start of this wave's segment = counts of the earlier waves
-  int start[PROBE_MAX_EXPERTS / kWave];
-#pragma unroll
-  for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) {
-    int e = lane + i * kWave;
-    int a = 0;
-    if (e < E)
-      for (int q = 0; q < w; ++q) a += cnt_mem[q][e];
-    start[i] = a;
+  if (tid < S) {
+    s_off[tid] = excl;
+    if (tid == S - 1) s_off[S] = excl + rows;
+    if (writer && b == 0) {
+      out.slot_counts[tid] = rows;
+      out.slot_offsets[tid] = excl;
+      if (tid == S - 1) {
+        out.slot_offsets[S] = excl + rows;
+        out.n_local[0] = excl + rows;
+      }
+    }
   }
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) {
-    int e = lane + i * kWave;
-    if (e < E) cnt_w[e] = start[i];
-  }
-  const int n_loc = s_off[S];
-#pragma unroll
-  for (int it = 0; it < kSegIters; ++it) {
-    long p = base + it * kWave + lane;
-    int e = seg_e[it];
-    bool valid = static_cast<unsigned>(e) < static_cast<unsigned>(E);
-    uint64_t m = match_key8(e, valid);
-    if (p < N && !valid) {  // expert id out of range: the pair is computed nowhere on this GPU
-      pair_row[p] = -1;
-      if (p >= n_loc) row_pair[p] = -1;
-    }
-    if (valid) {
-      int before = __popcll(m & lanemask_lt());
-      int j = cnt_w[e] + before;
-      int lo = e_lo[e], hi = e_hi[e], P = e_P[e];
-      int row = -1;
-      if (P > 0) {
-        int full = j / P, u = j - full * P, cum = 0;
-        for (int i = lo; i < hi; ++i) {
-          int wgt = rw[i];
-          if (u < cum + wgt) {
-            int slot = rs[i];
-            if (slot >= 0 && slot < S) row = s_off[slot] + full * wgt + (u - cum);
-            if (row >= N) row = -1;
-            break;
-          }
-          cum += wgt;
-        }
-      }
-      pair_row[p] = row;
-      if (row >= 0) row_pair[row] = static_cast<int32_t>(p);
-      if (p >= n_loc) row_pair[p] = -1;
-    }
-    if (valid && (m & lanemask_lt()) == 0) cnt_w[e] += __popcll(m);
-  }
-}
-
-// Step 2: every workgroup sums the block histograms itself (its own exclusive base =
-// the blocks before it, the totals n_e = all blocks), derives the slot counts and offsets from the totals
-// (each workgroup redundantly, workgroup 0 writes them out) and then ranks its own 1024 pairs as above.
-// Reading U*E counters per workgroup costs less than a one-workgroup scan kernel between two launches.
-__global__ __launch_bounds__(kPermWaves* kWave) void permute_scan_index_kernel(
-    const int32_t* __restrict__ topk_idx, int N, int E, const int32_t* __restrict__ blk_hist, int U,
-    const int32_t* __restrict__ rep_off, const int32_t* __restrict__ rep_slot,
-    const int32_t* __restrict__ rep_weight, int S, int32_t* __restrict__ slot_counts,
-    int32_t* __restrict__ slot_offsets, int32_t* __restrict__ n_local, int32_t* __restrict__ pair_row,
-    int32_t* __restrict__ row_pair) {
-  __shared__ int32_t cnt_mem[kPermWaves][PROBE_MAX_EXPERTS];
-  __shared__ int32_t before_mem[kPermWaves][PROBE_MAX_EXPERTS], total_mem[kPermWaves][PROBE_MAX_EXPERTS];
-  __shared__ int32_t e_lo[PROBE_MAX_EXPERTS], e_hi[PROBE_MAX_EXPERTS], e_P[PROBE_MAX_EXPERTS];
-  __shared__ int32_t s_off[PROBE_MAX_SLOTS + 1], sc[PROBE_MAX_SLOTS];
-  __shared__ int32_t s_rw[kRepLds], s_rs[kRepLds];
-  __shared__ int32_t wave_tot[kPermWaves];
-  const int tid = threadIdx.x, w = tid / kWave, lane = lane_id();
-  const int b = blockIdx.x;
-  volatile int32_t* cnt_w = cnt_mem[w];  // volatile: keep every lane's read before the leader's update
-  const long base = (static_cast<long>(b) * kPermWaves + w) * kSegPairs;
-  // loads that depend on nothing first: this wave's pairs, the size of the replica list
-  int seg_e[kSegIters];
-#pragma unroll
-  for (int it = 0; it < kSegIters; ++it) {
-    long p = base + it * kWave + lane;
-    seg_e[it] = p < N ? topk_idx[p] : -1;
-  }
-  const int R = rep_off[E];
-  // block histograms: wave w adds the blocks u = w, w + 4, ... for the experts lane, lane + 64, ...
-  {
-    int before[PROBE_MAX_EXPERTS / kWave], total[PROBE_MAX_EXPERTS / kWave];
-#pragma unroll
-    for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) before[i] = total[i] = 0;
-    constexpr int kBatch = 16;  // blocks per wave whose loads are in flight together (64 blocks per round)
-    for (int u0 = w; u0 < U; u0 += kBatch * kPermWaves) {
-      int c[kBatch][PROBE_MAX_EXPERTS / kWave];
-#pragma unroll
-      for (int q = 0; q < kBatch; ++q) {
-        const int u = u0 + q * kPermWaves;
-#pragma unroll
-        for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) {
-          const int e = lane + i * kWave;
-          c[q][i] = (u < U && e < E) ? blk_hist[static_cast<long>(u) * E + e] : 0;
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < kBatch; ++q) {
-        const int u = u0 + q * kPermWaves;
-#pragma unroll
-        for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) {
-          total[i] += c[q][i];
-          before[i] += u < b ? c[q][i] : 0;
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) {
-      before_mem[w][lane + i * kWave] = before[i];
-      total_mem[w][lane + i * kWave] = total[i];
-    }
-  }
-  const bool staged = R <= kRepLds;
-  if (staged)
-    for (int i = tid; i < R; i += kPermWaves * kWave) {
-      s_rw[i] = rep_weight[i];
-      s_rs[i] = rep_slot[i];
-    }
-  const int32_t* rw = staged ? s_rw : rep_weight;
-  const int32_t* rs = staged ? s_rs : rep_slot;
-  for (int e = tid; e < E; e += kPermWaves * kWave) {
-    e_lo[e] = rep_off[e];
-    e_hi[e] = rep_off[e + 1];
-  }
-  for (int s = tid; s < S; s += kPermWaves * kWave) sc[s] = 0;
-  // counts of this wave's own segment (the same walk as in step 1)
-  for (int e = lane; e < E; e += kWave) cnt_w[e] = 0;
-#pragma unroll
-  for (int it = 0; it < kSegIters; ++it) {
-    int e = seg_e[it];
-    bool valid = static_cast<unsigned>(e) < static_cast<unsigned>(E);
-    uint64_t m = match_key8(e, valid);
-    if (valid && (m & lanemask_lt()) == 0) cnt_w[e] += __popcll(m);
-  }
-  __syncthreads();
-  // rows each replica receives: floor(n/P) w_i + clamp(n mod P - c_{i-1}, 0, w_i)
-  for (int e = tid; e < E; e += kPermWaves * kWave) {
-    int n_e = 0, P = 0;
-#pragma unroll
-    for (int q = 0; q < kPermWaves; ++q) n_e += total_mem[q][e];
-    for (int i = e_lo[e]; i < e_hi[e]; ++i) P += rw[i];
-    e_P[e] = P;
+  int row = -1;
+  if (valid) {
+    const int j = cnt[w][my_e] + rank;                     // arrival rank of this pair for expert e
+    const int lo = e_lo[my_e], hi = e_hi[my_e], P = e_P[my_e];
     if (P > 0) {
-      int full = n_e / P, rem = n_e - full * P, cum = 0;
-      for (int i = e_lo[e]; i < e_hi[e]; ++i) {
-        int wgt = rw[i];
-        int part_rows = min(max(rem - cum, 0), wgt);
-        int slot = rs[i];
-        if (slot >= 0 && slot < S) sc[slot] = full * wgt + part_rows;
+      int full = j / P, u = j - full * P, cum = 0;
+      for (int i = lo; i < hi; ++i) {
+        const int wgt = rw[i];
+        if (u < cum + wgt) {
+          const int slot = rs[i];
+          if (slot >= 0 && slot < S) row = s_off[slot] + full * wgt + (u - cum);
+          if (row >= N) row = -1;  // only an inconsistent plan (two replicas in one slot) gets here
+          break;
+        }
         cum += wgt;
       }
     }
   }
-  __syncthreads();
-  // exclusive prefix sum over the slots, 4 consecutive slots per thread
-  int v[4], local = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int s = tid * 4 + i;
-    v[i] = s < S ? sc[s] : 0;
-    local += v[i];
+  if (p < N && writer) {  // an expert id out of range: the pair is computed nowhere on this GPU
+    out.pair_row[p] = row;
+    if (row >= 0) out.row_pair[row] = static_cast<int32_t>(p);
+    if (p >= s_off[S]) out.row_pair[p] = -1;
   }
-  int incl = local;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int o = __shfl_up(incl, d, kWave);
-    if (lane >= d) incl += o;
-  }
-  if (lane == kWave - 1) wave_tot[w] = incl;
-  __syncthreads();
-  {
-    int excl = incl - local;
-    for (int i = 0; i < w; ++i) excl += wave_tot[i];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int s = tid * 4 + i;
-      if (s < S) {
-        if (b == 0) {
-          slot_counts[s] = v[i];
-          slot_offsets[s] = excl;
-        }
-        s_off[s] = excl;
+  if constexpr (SCATTER) {
+    row_of[tid] = row;
+    __syncthreads();
+    // the tokens of this block: whole ones, see the launch
+    const unsigned first = static_cast<unsigned>(b) * kIndexThreads / k;
+    const unsigned tokens = min(N - b * kIndexThreads, kIndexThreads) / k;
+    const unsigned cpr = chunks_per_row, total = tokens * cpr;  // below 2^31
+    const u32x4* xb = x + static_cast<size_t>(first) * cpr;
+    for (unsigned c = blockIdx.x * kIndexThreads + tid; c < total; c += gridDim.x * kIndexThreads) {
+      const unsigned t = c / cpr, col = c - t * cpr;
+      bool any = false;
+      for (int q = 0; q < k; ++q) any |= row_of[t * k + q] >= 0;
+      if (!any) continue;
+      const u32x4 v = __builtin_nontemporal_load(&xb[c]);
+      for (int q = 0; q < k; ++q) {
+        const int r = row_of[t * k + q];
+        if (r >= 0) __builtin_nontemporal_store(v, &xp[static_cast<size_t>(r) * cpr + col]);
       }
-      excl += v[i];
     }
-    if (tid == kPermWaves * kWave - 1) {
-      if (b == 0) {
-        slot_offsets[S] = excl;
-        n_local[0] = excl;
-      }
-      s_off[S] = excl;
-    }
-  }
-  // arrival rank at the start of this wave's segment: the blocks before this one + the earlier waves
-  int start[PROBE_MAX_EXPERTS / kWave];
-#pragma unroll
-  for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) {
-    int e = lane + i * kWave;
-    int a = 0;
-    if (e < E) {
-#pragma unroll
-      for (int q = 0; q < kPermWaves; ++q) a += before_mem[q][e];
-      for (int q = 0; q < w; ++q) a += cnt_mem[q][e];
-    }
-    start[i] = a;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) {
-    int e = lane + i * kWave;
-    if (e < E) cnt_w[e] = start[i];
-  }
-  const int n_loc = s_off[S];
-#pragma unroll
-  for (int it = 0; it < kSegIters; ++it) {
-    long p = base + it * kWave + lane;
-    int e = seg_e[it];
-    bool valid = static_cast<unsigned>(e) < static_cast<unsigned>(E);
-    uint64_t m = match_key8(e, valid);
-    if (p < N && !valid) {  // expert id out of range: the pair is computed nowhere on this GPU
-      pair_row[p] = -1;
-      if (p >= n_loc) row_pair[p] = -1;
-    }
-    if (valid) {
-      int before = __popcll(m & lanemask_lt());
-      int j = cnt_w[e] + before;                       // arrival rank of this pair for expert e
-      int lo = e_lo[e], hi = e_hi[e], P = e_P[e];
-      int row = -1;
-      if (P > 0) {
-        int full = j / P, u = j - full * P, cum = 0;
-        for (int i = lo; i < hi; ++i) {
-          int wgt = rw[i];
-          if (u < cum + wgt) {
-            int slot = rs[i];
-            if (slot >= 0 && slot < S) row = s_off[slot] + full * wgt + (u - cum);
-            if (row >= N) row = -1;  // only an inconsistent plan (two replicas in one slot) gets here
-            break;
-          }
-          cum += wgt;
-        }
-      }
-      pair_row[p] = row;
-      if (row >= 0) row_pair[row] = static_cast<int32_t>(p);
-      if (p >= n_loc) row_pair[p] = -1;
-    }
-    // all lanes of a key have read the counter above; the key's first lane now advances it
-    if (valid && (m & lanemask_lt()) == 0) cnt_w[e] += __popcll(m);
   }
 }
 
@@ -712,31 +562,37 @@ static int permute_impl(const char* name, const int32_t* topk_idx, const probe_p
   const int S = plan->num_slots;
   int N = T * k;
   int U = num_blocks(N);
-  int seg_blocks = U;
-  if (U <= 1) {
-    hipLaunchKernelGGL(permute_small_kernel, dim3(1), dim3(kPermWaves * kWave), 0, st, topk_idx, N, E,
-                       plan->rep_off, plan->rep_slot, plan->rep_weight, S, slot_counts, slot_offsets, n_local,
-                       pair_row, row_pair);
+  const IndexOut out = {slot_counts, slot_offsets, n_local, pair_row, row_pair};
+  const int cpr = H / 8;
+  const u32x4* x = static_cast<const u32x4*>(x_bf16);
+  u32x4* xp = static_cast<u32x4*>(xp_bf16);
+  const long total = static_cast<long>(T) * cpr;
+  // blocks of whole tokens only (at most 1024)
+  if (U >= 1 && U <= kScatterBlocks && xp != nullptr && (U == 1 || kIndexThreads % k == 0) && cpr < (1 << 21)) {
+    const long chunks = std::min<long>(T, kIndexThreads / k) * cpr;  // of a block
+    const unsigned shares = static_cast<unsigned>(std::min((chunks + kIndexThreads - 1) / kIndexThreads, std::max(512l / U, 1l)));
+    hipLaunchKernelGGL((permute_block_kernel<true, true>), dim3(shares, U), dim3(kIndexThreads), 0, st, topk_idx, N, E,
+                       nullptr, U, plan->rep_off, plan->rep_slot, plan->rep_weight, S, out, x, k, cpr, xp);
+    return check_launch(name);
+  }
+  if (U <= kSelfBlocks) {
+    hipLaunchKernelGGL((permute_block_kernel<true, false>), dim3(1, std::max(U, 1)), dim3(kIndexThreads), 0, st, topk_idx, N, E,
+                       nullptr, U, plan->rep_off, plan->rep_slot, plan->rep_weight, S, out, nullptr, k, 0, nullptr);
   } else {
-    hipLaunchKernelGGL(permute_hist_kernel, dim3(seg_blocks), dim3(kPermWaves * kWave), 0, st, topk_idx, N, E,
+    hipLaunchKernelGGL(permute_hist_kernel, dim3(U), dim3(kIndexThreads), 0, st, topk_idx, N, E,
                        seg);
     if (U <= kFusedBlocks) {
-      hipLaunchKernelGGL(permute_scan_index_kernel, dim3(seg_blocks), dim3(kPermWaves * kWave), 0, st, topk_idx, N,
-                         E, seg, U, plan->rep_off, plan->rep_slot, plan->rep_weight, S, slot_counts, slot_offsets,
-                         n_local, pair_row, row_pair);
+      hipLaunchKernelGGL((permute_block_kernel<false, false>), dim3(1, U), dim3(kIndexThreads), 0, st, topk_idx, N, E, seg, U,
+                         plan->rep_off, plan->rep_slot, plan->rep_weight, S, out, nullptr, k, 0, nullptr);
     } else {
       hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(1024), 0, st, seg, U, E, plan->rep_off,
                          plan->rep_slot, plan->rep_weight, S, slot_counts, slot_offsets, n_local);
-      hipLaunchKernelGGL(permute_index_kernel, dim3(seg_blocks), dim3(kPermWaves * kWave), 0, st, topk_idx, N, E,
+      hipLaunchKernelGGL(permute_index_kernel, dim3(U), dim3(kPermWaves * kWave), 0, st, topk_idx, N, E,
                          seg, plan->rep_off, plan->rep_slot, plan->rep_weight, slot_offsets, S, pair_row, row_pair);
     }
   }
   if (U > 0 && xp_bf16 != nullptr) {  // xp == NULL: the caller gathers rows on load instead
-    int cpr = H / 8;
-    long total = static_cast<long>(T) * cpr;
     unsigned grid = static_cast<unsigned>((total + 255) / 256);
-    const u32x4* x = static_cast<const u32x4*>(x_bf16);
-    u32x4* xp = static_cast<u32x4*>(xp_bf16);
 #define PROBE_SCATTER_CASE(K) \
   case K: hipLaunchKernelGGL(permute_scatter_kernel<K>, dim3(grid), dim3(256), 0, st, x, pair_row, total, cpr, xp); break;
     switch (k) {

@@ -81,6 +81,40 @@ def test_all_remote_and_zero_weight_replica(oracle, probe, G):
     np.testing.assert_array_equal(p["slot_offsets"].cpu().numpy(), o["slot_offsets"])
 
 
+@pytest.mark.parametrize("T,k,E,S,H", [(1, 1, 1, 1, 8), (1024, 1, 256, 64, 16), (1025, 1, 9, 65, 8), (341, 3, 130, 20, 24), (342, 3, 130, 20, 24),
+                                       (1024, 8, 256, 1000, 72), (1025, 8, 33, 7, 8), (2048, 8, 64, 63, 8), (2049, 8, 64, 66, 8),
+                                       (4096, 4, 8, 12, 8), (1639, 5, 200, 30, 40), (32768, 8, 128, 24, 8), (40, 7, 12, 30, 4104)])
+def test_permute_on_both_sides_of_every_block_count(oracle, probe, G, T, k, E, S, H):
+    """1, 2, 8, 9, 16, 17 and 256 blocks of 1024 pairs, tokens that straddle blocks, replicas with equal, unequal and no weight, remote
+    experts, a replica list longer than the staged one, with and without the row copy: every output
+    bit for bit the oracle's."""
+    print("case permute T=%d k=%d E=%d S=%d" % (T, k, E, S), flush=True)
+    rng = np.random.default_rng(T * k + E)
+    popularity = rng.permutation(E)
+    idx = np.minimum(rng.geometric(min(4.0 / E, 0.9), size=(T, k)) - 1, E - 1)
+    idx = popularity[idx].astype(np.int32)
+    reps = rng.integers(1, 4 if E < 256 else 20, E)                       # 256 experts: more entries than are staged
+    rep_off = np.r_[0, np.cumsum(reps)].astype(np.int32)
+    slots = np.full(rep_off[-1], -1, np.int32)
+    local = rng.permutation(rep_off[-1])[:min(S, rep_off[-1])]            # a slot belongs to one replica
+    slots[local] = rng.permutation(S)[:local.size]
+    weight = rng.integers(0, 4, rep_off[-1]).astype(np.int32)
+    weight[rep_off[:-1]] += 1                                              # every expert has some weight
+    x = wl.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32))
+    o = oracle.permute(idx, rep_off, slots, weight, S, x)
+    d_idx, d_x = torch.from_numpy(idx).cuda(), G.dev_bf16(x)
+    plan = probe.Plan(rep_off, slots, weight, S)
+    full = probe.permute(d_idx, plan, d_x)
+    lean = probe.permute(d_idx, plan, d_x, copy_rows=False)
+    torch.cuda.synchronize()
+    n = o["n_local"]
+    for got in (full, lean):
+        assert int(got["n_local"].item()) == n
+        for key in ("slot_counts", "slot_offsets", "pair_row", "row_pair"):
+            np.testing.assert_array_equal(got[key].cpu().numpy(), o[key], err_msg=key)
+    np.testing.assert_array_equal(G.bits_of(full["xp"])[:n], o["xp"][:n])
+
+
 def test_topk_equals_all_experts_and_predictor_identity(oracle, probe, G):
     print("case k == E, predictor identity", flush=True)
     cfg = wl.small_config(T=77, H=64, E=8, k=8, F=64, E_loc=8, n_rep=0, ep=1, chunk=0, cid=81)
