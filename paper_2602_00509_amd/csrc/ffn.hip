@@ -39,6 +39,9 @@ constexpr int FBN = 256;
 // stages of 48 / 40 KB, which gives every DMA batch two k-steps to land.
 constexpr int kFfnLdsBytes = 3 * (128 + 256) * 128;  // 144 KB
 static_assert(kFfnLdsBytes >= 2 * (320 + 256) * 128, "two stages of the tallest tile");
+// Narrow column blocks leave room for three stages up to 256 rows.  More (six at 64 rows) measured the same.
+constexpr int ffn_stages(int mi, int ni) { return ni == 1 ? (mi == 5 ? 2 : 3) : (mi >= 3 ? 2 : 3); }
+static_assert(kFfnLdsBytes >= 3 * (256 + 128) * 128 && kFfnLdsBytes >= 2 * (320 + 128) * 128, "stages of the narrow tiles");
 
 
 // ---- 0. schedule ----------------------------------------------------------------------
@@ -72,9 +75,9 @@ struct alignas(16) TileEntry {
   const void* w2;
 };
 static_assert(sizeof(TileEntry) == 32, "one 32-byte record per tile");
-// Table header, 128 bytes: word 0 = number of tiles; words 8..15 and 16..23 = the work-queue tickets of
-// gemm1 and gemm2 (one counter per XCD), cleared by the schedule kernel of the same call.
-constexpr int kTableHeaderInts = 32, kQueue1 = 8, kQueue2 = 16;
+// Table header, 128 bytes: word 0 = number of tiles; words 1 and 2 = whether gemm1 and gemm2 take narrow column blocks; words 8..15
+// and 16..23 = the work-queue tickets of gemm1 and gemm2 (one counter per XCD), cleared by the schedule kernel of the same call.
+constexpr int kTableHeaderInts = 32, kNarrow1 = 1, kNarrow2 = 2, kQueue1 = 8, kQueue2 = 16;
 
 struct SlotCut {
   int n320, n256, tail;  // tail = height of the one short tile (64, 128 or 192), 0 if there is none
@@ -108,10 +111,22 @@ __device__ __forceinline__ SlotCut cut_slot(int m) {
   return c;
 }
 
-__global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __restrict__ slot_offsets,
+// Width of the items.  A call with few tiles leaves CUs without an item while each of the others streams 256 weight rows per
+// k-step; with column blocks half as wide (64 h columns, 128 y columns) there are twice as many items of half the weight rows.
+// Wide / narrow, gemm1: 9 tiles x 23 column blocks (500 tokens, top-4 of 128 experts, 2880 x 2880) 82 / 77 us, 17 x 12 (500
+// tokens, 4096 x 1536) 123 / 102, 15 x 12 103 / 86; but 11 x 23 82 / 86, 24 x 12 124 / 136.  gemm2: 7 x 12 67 / 48, 11 x 12 (768
+// tokens, 2880 x 2880) 73 / 54; but 17 x 12 89 / 94, 19 x 16 60 / 65.
+constexpr int kNarrowItems1 = 224, kNarrowItems2 = 160;  // wide items up to which the narrow ones are taken
+
+// One slot, then one entry of the table per thread.  What bounds it is latency: two dependent rounds of loads and a chain of LDS
+// phases.  With four slots per thread of 256 and 64-bit divisions per entry 36 slots took 10.8 us and 64 slots 13.5.
+constexpr int kScheduleThreads = 1024, kScheduleWaves = kScheduleThreads / kWave;
+static_assert(kScheduleThreads >= PROBE_MAX_SLOTS, "one slot per thread");
+
+__global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const int32_t* __restrict__ slot_offsets,
                                                            const void* const* __restrict__ w13_ptrs,
                                                            const void* const* __restrict__ w2_ptrs,
-                                                           int S, int max_tiles, int n_cols1, int cus,
+                                                           int S, int max_tiles, int n_cols1, int n_cols2, int cus,
                                                            int32_t* __restrict__ table) {
   __shared__ alignas(16) int32_t rows_of[PROBE_MAX_SLOTS];
   __shared__ int32_t first_of[PROBE_MAX_SLOTS];
@@ -120,54 +135,41 @@ __global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __rest
   __shared__ int32_t slot_at[PROBE_MAX_SLOTS];       // slot at each position of the sorted order
   __shared__ int32_t start[PROBE_MAX_SLOTS + 1];     // first tile of each position (exclusive prefix)
   __shared__ unsigned long long class_start[PROBE_MAX_SLOTS + 1];  // the same per tile height, twelve bits each
-  __shared__ int32_t wave_tot[4];
-  __shared__ unsigned long long wave_classes[4];
-  const int tid = threadIdx.x, lane = tid & 63;
-  int m[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int s = tid * 4 + i;
-    m[i] = 0;
-    if (s < S) {
-      const int first = slot_offsets[s];
-      m[i] = max(slot_offsets[s + 1] - first, 0);
-      rows_of[s] = m[i];
-      first_of[s] = first;
-      w13_of[s] = w13_ptrs[s];
-      w2_of[s] = w2_ptrs[s];
-    } else {
-      rows_of[s] = -1;
-    }
+  __shared__ int32_t wave_tot[kScheduleWaves];
+  __shared__ unsigned long long wave_classes[kScheduleWaves];
+  __shared__ int32_t n_big;                          // slots of more than 192 rows
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  int m = -1;
+  if (tid < S) {
+    const int first = slot_offsets[tid];
+    m = max(slot_offsets[tid + 1] - first, 0);
+    first_of[tid] = first;
+    w13_of[tid] = w13_ptrs[tid];
+    w2_of[tid] = w2_ptrs[tid];
   }
+  rows_of[tid] = m;  // entries past S are -1: they come before nobody
+  if (tid == 0) n_big = 0;
   __syncthreads();
   // position of a slot = number of slots that come before it
-  int pos[4] = {0, 0, 0, 0};
-  for (int u0 = 0; u0 < S; u0 += 4) {  // entries past S are -1 (m >= 0): they come before nobody
-    const int4 r4 = *reinterpret_cast<const int4*>(&rows_of[u0]);
-    const int ru[4] = {r4.x, r4.y, r4.z, r4.w};
+  if (tid < S) {
+    int pos = 0;
+    for (int u0 = 0; u0 < S; u0 += 4) {
+      const int4 r4 = *reinterpret_cast<const int4*>(&rows_of[u0]);
+      const int ru[4] = {r4.x, r4.y, r4.z, r4.w};
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) pos[i] += (ru[j] > m[i] || (ru[j] == m[i] && u0 + j < tid * 4 + i)) ? 1 : 0;
+      for (int j = 0; j < 4; ++j) pos += (ru[j] > m || (ru[j] == m && u0 + j < tid)) ? 1 : 0;
+    }
+    slot_at[pos] = tid;
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (tid * 4 + i < S) slot_at[pos[i]] = tid * 4 + i;
+  const int big_here = __popcll(__ballot(m > 192));
+  if (lane == 0 && big_here) atomicAdd(&n_big, big_here);
   __syncthreads();
-  // exclusive prefix of tiles over positions tid*4 .. tid*4+3
-  int v[4], local = 0;
-  unsigned long long by_height[4], c_local = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int p = tid * 4 + i;
-    const SlotCut cut = p < S ? cut_slot(rows_of[slot_at[p]]) : SlotCut{0, 0, 0};
-    v[i] = cut.tiles();
-    by_height[i] = cut.classes();
-    local += v[i];
-    c_local += by_height[i];
-  }
-  int incl = local;
-  unsigned long long c_incl = c_local;
+  // exclusive prefix of tiles over the positions
+  const SlotCut my_cut = tid < S ? cut_slot(rows_of[slot_at[tid]]) : SlotCut{0, 0, 0};
+  const int tiles = my_cut.tiles();
+  const unsigned long long classes = my_cut.classes();
+  int incl = tiles;
+  unsigned long long c_incl = classes;
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) {
     const int o = __shfl_up(incl, d, kWave);
@@ -177,52 +179,56 @@ __global__ __launch_bounds__(256) void ffn_schedule_kernel(const int32_t* __rest
       c_incl += co;
     }
   }
-  if (lane == kWave - 1) {
-    wave_tot[tid >> 6] = incl;
-    wave_classes[tid >> 6] = c_incl;
-  }
-  __syncthreads();
-  int excl = incl - local;
-  unsigned long long c_excl = c_incl - c_local;
-  for (int i = 0; i < (tid >> 6); ++i) {
-    excl += wave_tot[i];
-    c_excl += wave_classes[i];
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int p = tid * 4 + i;
-    if (p < S) {
-      start[p] = excl;
-      class_start[p] = c_excl;
+  if (S > kWave) {
+    if (lane == kWave - 1) {
+      wave_tot[wv] = incl;
+      wave_classes[wv] = c_incl;
     }
-    excl += v[i];
-    c_excl += by_height[i];
+    __syncthreads();
+    for (int i = 0; i < wv; ++i) {
+      incl += wave_tot[i];
+      c_incl += wave_classes[i];
+    }
   }
-  if (tid == 255) {  // the last thread's running sums are the totals
-    start[S] = excl;
-    class_start[S] = c_excl;
+  if (tid < S) {
+    start[tid] = incl - tiles;
+    class_start[tid] = c_incl - classes;
+    if (tid == S - 1) {
+      start[S] = incl;
+      class_start[S] = c_incl;
+    }
   }
   __syncthreads();
   const int total = min(start[S], max_tiles);
   // taller than 192 rows; beyond 4095 tiles the twelve-bit fields run into each other and are not looked at
   const int n_tall = static_cast<int>(class_start[S] & 4095) + static_cast<int>((class_start[S] >> 12) & 4095);
-  const bool tall_first = start[S] <= min(max_tiles, 4095) && n_tall * n_cols1 <= cus &&
-                          static_cast<long>(start[S]) * n_cols1 > cus;
-  if (tid == 0) table[0] = total;
-  if (tid >= kQueue1 && tid < kTableHeaderInts) table[tid] = 0;
-  TileEntry* entries = reinterpret_cast<TileEntry*>(table + kTableHeaderInts);
-  // positions [0, big) hold the slots of more than 192 rows: tiles [0, nb) are theirs, the ns single
-  // short tiles follow
-  int big = 0;
-  for (int hi = S; big < hi;) {
-    const int mid = (big + hi) >> 1;
-    if (rows_of[slot_at[mid]] > 192) big = mid + 1; else hi = mid;
+  const bool narrow1 = static_cast<long>(total) * n_cols1 <= kNarrowItems1;
+  const int cols1 = narrow1 ? 2 * n_cols1 : n_cols1;
+  const bool tall_first = start[S] <= min(max_tiles, 4095) && n_tall * cols1 <= cus &&
+                          static_cast<long>(start[S]) * cols1 > cus;
+  if (tid < kTableHeaderInts) {
+    int v = 0;  // the queues' tickets
+    if (tid == 0) v = total;
+    if (tid == kNarrow1) v = narrow1;
+    if (tid == kNarrow2) v = static_cast<long>(total) * n_cols2 <= kNarrowItems2;
+    table[tid] = v;
   }
-  const int nb = min(start[big], total), ns = total - nb;
-  for (int p = tid; p < total; p += 256) {
+  TileEntry* entries = reinterpret_cast<TileEntry*>(table + kTableHeaderInts);
+  // positions [0, n_big) hold the slots of more than 192 rows: tiles [0, nb) are theirs, the ns single
+  // short tiles follow
+  const int nb = min(start[n_big], total), ns = total - nb;
+  const bool small = total < (1 << 16);  // products of two of them in 32 bits
+  for (int p = tid; p < total; p += kScheduleThreads) {
     // entry p of the table: the short tiles are spread evenly over the table
-    const int before = static_cast<int>(static_cast<long>(p) * ns / total);
-    const bool is_short = static_cast<int>(static_cast<long>(p + 1) * ns / total) > before;
+    int before, until;
+    if (small) {
+      before = static_cast<int>(static_cast<unsigned>(p) * static_cast<unsigned>(ns) / static_cast<unsigned>(total));
+      until = static_cast<int>(static_cast<unsigned>(p + 1) * static_cast<unsigned>(ns) / static_cast<unsigned>(total));
+    } else {
+      before = static_cast<int>(static_cast<long>(p) * ns / total);
+      until = static_cast<int>(static_cast<long>(p + 1) * ns / total);
+    }
+    const bool is_short = until > before;
     const int t = tall_first ? p : (is_short ? nb + before : p - before);
     int lo = 0, hi = S;  // last position with start[position] <= t
     while (hi - lo > 1) {
@@ -452,9 +458,44 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
   return drew;
 }
 
-// one-dimensional launch over (row tile, column block) work items; a column block is 128 gate +
-// 128 up weight rows
+// one-dimensional launch over (row tile, column block) work items; a column block is 64 NI gate + 64 NI up weight rows
 // queue != 0: persistent launch, items drawn from the work queue; 0: one workgroup per item
+template <bool GATHER, int NI>
+__device__ __forceinline__ void ffn_gemm1_items(const RowSource& src, const int32_t* __restrict__ table, int32_t* table_rw,
+                                                int queue, int H, int F, bf16_t* __restrict__ hbuf, u32x4* smem,
+                                                volatile int* ticket) {
+  constexpr int COLS = 64 * NI;
+  const int n_tiles = table[0], n_cols = (F + COLS - 1) / COLS;
+  int tile, col;
+  auto run = [&](auto draw_c, int32_t* ctr) {
+    constexpr bool DRAW = decltype(draw_c)::value;
+    const TileEntry e = reinterpret_cast<const TileEntry*>(table + kTableHeaderInts)[tile];
+    const int n0 = col * COLS;
+    const bf16_t* w13 = static_cast<const bf16_t*>(e.w13);
+    if (e.height > 256)
+      return gemm1_tile<5, GATHER, NI, ffn_stages(5, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+    if (e.height > 192)
+      return gemm1_tile<4, GATHER, NI, ffn_stages(4, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+    if (e.height > 128)
+      return gemm1_tile<3, GATHER, NI, ffn_stages(3, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+    if (e.height > 64)
+      return gemm1_tile<2, GATHER, NI, ffn_stages(2, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+    return gemm1_tile<1, GATHER, NI, ffn_stages(1, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+  };
+  if (queue) {
+    // persistent launch: the ticket of the next item is drawn while the last k-steps of this one run
+    WorkQueue wq;
+    wq.init(table_rw + kQueue1);
+    bool more = wq.next(n_tiles, n_cols, ticket, tile, col);
+    while (more) {
+      const bool drew = run(std::true_type{}, wq.counters + wq.victim);
+      more = wq.next_drawn(drew, n_tiles, n_cols, ticket, tile, col);
+    }
+  } else if (ffn_work_item(n_tiles, n_cols, tile, col)) {
+    run(std::false_type{}, nullptr);
+  }
+}
+
 template <bool GATHER>
 __global__ __launch_bounds__(512, 2) void ffn_gemm1_kernel(RowSource src, const int32_t* __restrict__ table,
                                                            int32_t* table_rw, int queue, int H, int F,
@@ -462,47 +503,10 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm1_kernel(RowSource src, const 
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
   __shared__ int ticket;
-  const int n_tiles = table[0], n_cols = (F + 127) / 128;
-  int tile, col;
-  if (queue) {
-    // persistent launch: the ticket of the next item is drawn while the last k-steps of this one run
-    WorkQueue wq;
-    wq.init(table_rw + kQueue1);
-    bool more = wq.next(n_tiles, n_cols, &ticket, tile, col);
-    while (more) {
-      const TileEntry e = reinterpret_cast<const TileEntry*>(table + kTableHeaderInts)[tile];
-      const int n0 = col * 128;
-      const bf16_t* w13 = static_cast<const bf16_t*>(e.w13);
-      int32_t* ctr = wq.counters + wq.victim;
-      bool drew;
-      if (e.height > 256)
-        drew = gemm1_tile<5, GATHER, 2, 2, true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, &ticket);
-      else if (e.height > 192)
-        drew = gemm1_tile<4, GATHER, 2, 2, true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, &ticket);
-      else if (e.height > 128)
-        drew = gemm1_tile<3, GATHER, 2, 2, true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, &ticket);
-      else if (e.height > 64)
-        drew = gemm1_tile<2, GATHER, 2, 3, true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, &ticket);
-      else
-        drew = gemm1_tile<1, GATHER, 2, 3, true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, &ticket);
-      more = wq.next_drawn(drew, n_tiles, n_cols, &ticket, tile, col);
-    }
-    return;
-  }
-  if (!ffn_work_item(n_tiles, n_cols, tile, col)) return;
-  const TileEntry e = reinterpret_cast<const TileEntry*>(table + kTableHeaderInts)[tile];
-  const int n0 = col * 128;
-  const bf16_t* w13 = static_cast<const bf16_t*>(e.w13);
-  if (e.height > 256)
-    gemm1_tile<5, GATHER>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem);
-  else if (e.height > 192)
-    gemm1_tile<4, GATHER>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem);
-  else if (e.height > 128)
-    gemm1_tile<3, GATHER>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem);
-  else if (e.height > 64)
-    gemm1_tile<2, GATHER>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem);
+  if (table[kNarrow1])
+    ffn_gemm1_items<GATHER, 1>(src, table, table_rw, queue, H, F, hbuf, smem, &ticket);
   else
-    gemm1_tile<1, GATHER>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem);
+    ffn_gemm1_items<GATHER, 2>(src, table, table_rw, queue, H, F, hbuf, smem, &ticket);
 #endif
 }
 
@@ -566,53 +570,48 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
   return drew;
 }
 
-// one-dimensional launch over (row tile, column block of 256 output columns) work items
+// one-dimensional launch over (row tile, column block of 128 NI output columns) work items
+template <int NI>
+__device__ __forceinline__ void ffn_gemm2_items(const bf16_t* __restrict__ hbuf, const int32_t* __restrict__ table,
+                                                int32_t* table_rw, int queue, int H, int F, bf16_t* __restrict__ y,
+                                                u32x4* smem, volatile int* ticket) {
+  constexpr int COLS = 128 * NI;
+  const int n_tiles = table[0], n_cols = (H + COLS - 1) / COLS;
+  int tile, col;
+  auto run = [&](auto draw_c, int32_t* ctr) {
+    constexpr bool DRAW = decltype(draw_c)::value;
+    const TileEntry e = reinterpret_cast<const TileEntry*>(table + kTableHeaderInts)[tile];
+    const int n0 = col * COLS;
+    const bf16_t* w2 = static_cast<const bf16_t*>(e.w2);
+    if (e.height > 256) return gemm2_tile<5, NI, ffn_stages(5, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    if (e.height > 192) return gemm2_tile<4, NI, ffn_stages(4, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    if (e.height > 128) return gemm2_tile<3, NI, ffn_stages(3, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    if (e.height > 64) return gemm2_tile<2, NI, ffn_stages(2, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    return gemm2_tile<1, NI, ffn_stages(1, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+  };
+  if (queue) {
+    WorkQueue wq;
+    wq.init(table_rw + kQueue2);
+    bool more = wq.next(n_tiles, n_cols, ticket, tile, col);
+    while (more) {
+      const bool drew = run(std::true_type{}, wq.counters + wq.victim);
+      more = wq.next_drawn(drew, n_tiles, n_cols, ticket, tile, col);
+    }
+  } else if (ffn_work_item(n_tiles, n_cols, tile, col)) {
+    run(std::false_type{}, nullptr);
+  }
+}
+
 __global__ __launch_bounds__(512, 2) void ffn_gemm2_kernel(const bf16_t* __restrict__ hbuf,
                                                            const int32_t* __restrict__ table, int32_t* table_rw,
                                                            int queue, int H, int F, bf16_t* __restrict__ y) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
   __shared__ int ticket;
-  const int n_tiles = table[0], n_cols = (H + FBN - 1) / FBN;
-  int tile, col;
-  if (queue) {
-    WorkQueue wq;
-    wq.init(table_rw + kQueue2);
-    bool more = wq.next(n_tiles, n_cols, &ticket, tile, col);
-    while (more) {
-      const TileEntry e = reinterpret_cast<const TileEntry*>(table + kTableHeaderInts)[tile];
-      const int n0 = col * FBN;
-      const bf16_t* w2 = static_cast<const bf16_t*>(e.w2);
-      int32_t* ctr = wq.counters + wq.victim;
-      bool drew;
-      if (e.height > 256)
-        drew = gemm2_tile<5, 2, 2, true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, &ticket);
-      else if (e.height > 192)
-        drew = gemm2_tile<4, 2, 2, true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, &ticket);
-      else if (e.height > 128)
-        drew = gemm2_tile<3, 2, 2, true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, &ticket);
-      else if (e.height > 64)
-        drew = gemm2_tile<2, 2, 3, true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, &ticket);
-      else
-        drew = gemm2_tile<1, 2, 3, true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, &ticket);
-      more = wq.next_drawn(drew, n_tiles, n_cols, &ticket, tile, col);
-    }
-    return;
-  }
-  if (!ffn_work_item(n_tiles, n_cols, tile, col)) return;
-  const TileEntry e = reinterpret_cast<const TileEntry*>(table + kTableHeaderInts)[tile];
-  const int n0 = col * FBN;
-  const bf16_t* w2 = static_cast<const bf16_t*>(e.w2);
-  if (e.height > 256)
-    gemm2_tile<5>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem);
-  else if (e.height > 192)
-    gemm2_tile<4>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem);
-  else if (e.height > 128)
-    gemm2_tile<3>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem);
-  else if (e.height > 64)
-    gemm2_tile<2>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem);
+  if (table[kNarrow2])
+    ffn_gemm2_items<1>(hbuf, table, table_rw, queue, H, F, y, smem, &ticket);
   else
-    gemm2_tile<1>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem);
+    ffn_gemm2_items<2>(hbuf, table, table_rw, queue, H, F, y, smem, &ticket);
 #endif
 }
 
@@ -1041,11 +1040,13 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
                          F / FBK, H, y);
     return check_launch(name);
   }
-  hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(256), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S, sh.max_tiles,
-                     (F + 127) / 128, cus, table);
+  const int n1 = (F + 127) / 128, n2 = (H + FBN - 1) / FBN;
+  hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(kScheduleThreads), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S,
+                     sh.max_tiles, n1, n2, cus, table);
   // persistent launch (one workgroup per CU, items drawn from the work queue) unless the capacity of the
-  // row space gives fewer items than that
-  const int cap1 = ffn_grid(sh.max_tiles, (F + 127) / 128), cap2 = ffn_grid(sh.max_tiles, (H + FBN - 1) / FBN);
+  // row space gives fewer items than that; where items may be narrow (the schedule decides), there are twice as many
+  const int cap1 = std::max(ffn_grid(sh.max_tiles, n1), ffn_grid(std::min(sh.max_tiles, kNarrowItems1 / n1), 2 * n1));
+  const int cap2 = std::max(ffn_grid(sh.max_tiles, n2), ffn_grid(std::min(sh.max_tiles, kNarrowItems2 / n2), 2 * n2));
   const int q1 = cap1 > cus ? 1 : 0, q2 = cap2 > cus ? 1 : 0;
   const dim3 grid1(q1 ? cus : cap1), grid2(q2 ? cus : cap2);
   if (gather)

@@ -519,6 +519,32 @@ def test_ffn_tall_tiles_first_every_element(oracle, probe, G, sizes):
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, 4, seed=len(sizes) + sizes[0])
 
 
+@pytest.mark.parametrize("sizes,H,F", [
+    ([320, 256, 192, 128, 64, 37, 0, 321] * 4, 1344, 960),    # every height, wide column blocks, partial last ones
+    ([320, 256, 192, 128, 64, 37, 0, 321], 1088, 1344),       # every height, narrow column blocks, partial last ones
+    ([100] * 14, 2432, 2048), ([100] * 15, 2560, 2048),       # 224 and 240 wide items of gemm1
+    ([130] * 16, 2560, 192), ([130] * 17, 2560, 192),         # 160 and 170 of gemm2
+    ([70, 0, 300], 64, 14400)])                               # one k-step; more column blocks than tiles
+def test_ffn_wide_and_narrow_column_blocks(oracle, probe, G, sizes, H, F):
+    """Tall tiles on both sides of the lines where the schedule halves the column blocks: every output element against the
+    oracle, and the rows gathered on load bit for bit the same."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=103)
+    print("case narrow", len(sizes), H, F, flush=True)
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F)
+    n = sum(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(H)
+    x = torch.randn((n + 9, H), generator=gen, device="cuda").to(torch.bfloat16)
+    w = [(torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
+          torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16)) for _ in range(2)]
+    tab = probe.WeightTable([w[i % 2][0] for i in range(len(sizes))], [w[i % 2][1] for i in range(len(sizes))])
+    so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
+    rows = torch.randperm(n + 9, device="cuda", generator=gen).to(torch.int32)
+    plain = probe.grouped_ffn(x[rows.long()].contiguous(), so, tab)
+    gathered = probe.grouped_ffn_gather(x, rows, 1, so, tab)
+    torch.cuda.synchronize()
+    assert torch.equal(plain[:n], gathered[:n])
+
+
 def test_ffn_workspace_of_a_larger_call_serves_a_smaller_one(oracle, probe, G):
     """A workspace sized for more rows serves fewer as their own does, bit for bit, also where only the smaller call keeps partial
     sums in it (one slot: 1100 rows take the tall tiles, 75 rows the pieces of K); one without that room is accepted."""
