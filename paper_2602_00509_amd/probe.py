@@ -127,27 +127,42 @@ def _check(rc):
         raise ProbeError(rc, lib().probe_last_error_string().decode())
 
 
+# A small call is bound by this file: the kernels of a layer of 256 tokens x 512 take 42 us, issuing them took 63.  So pointers
+# go to ctypes as plain integers (the argument types say what they are), the raw handle of the current stream is
+# asked for directly, and sizes and outputs that a call was handed are not computed or allocated once more.
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_current_device = torch._C._cuda_getDevice if hasattr(torch._C, "_cuda_getDevice") else torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _want(t, dtype, shape, name):
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous() or not t.is_cuda:
+    if t.dtype is not dtype or t.shape != shape or not t.is_contiguous() or not t.is_cuda:
         raise ValueError("%s: expected contiguous cuda %s %s, got %s %s" %
                          (name, dtype, tuple(shape), t.dtype, tuple(t.shape)))
     return t
 
 
-def _ws(workspace, nbytes, device):
+def _ws(workspace, query, args, device):
+    """The caller's workspace, or one of the size that `query` gives."""
     if workspace is None:
-        workspace = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+        workspace = torch.empty(max(int(query(*args)), 256), dtype=torch.uint8, device=device)
     return workspace
+
+
+def _out(out, name, shape, dtype, device):
+    if name not in out:
+        out[name] = torch.empty(shape, dtype=dtype, device=device)
 
 
 # --------------------------------------------------------------------- route / predict
@@ -200,8 +215,7 @@ def _route(fn, x, w_gate, bias, tokens_per_group, k, renormalize, want_probs, wa
         if w_gate.stack_rows != w_gate.E or w_gate.H != H or residual is not None:
             raise ValueError("a single packed gate with H = %d is needed here" % H)
         E = w_gate.E
-        fn = {"probe_route_topk": lib().probe_route_topk_packed,
-              "probe_predict_topk": lib().probe_predict_topk_packed}[fn.__name__]
+        fn = lib().probe_route_topk_packed if fn.__name__ == "probe_route_topk" else lib().probe_predict_topk_packed
     else:
         E = w_gate.shape[0]
         _want(w_gate, torch.float32, (E, H), "w_gate")
@@ -214,22 +228,20 @@ def _route(fn, x, w_gate, bias, tokens_per_group, k, renormalize, want_probs, wa
     tpg = int(tokens_per_group) if tokens_per_group else max(T, 1)
     out = dict(out) if out else {}
     dev = x.device
-    if "idx" not in out:
-        out["idx"] = torch.empty((T, k), dtype=torch.int32, device=dev)
-    if "w" not in out:
-        out["w"] = torch.empty((T, k), dtype=torch.float32, device=dev)
-    if want_probs and "probs" not in out:
-        out["probs"] = torch.empty((T, E), dtype=torch.float32, device=dev)
-    if want_counts and "counts" not in out:
-        out["counts"] = torch.empty((E,), dtype=torch.int32, device=dev)
+    _out(out, "idx", (T, k), torch.int32, dev)
+    _out(out, "w", (T, k), torch.float32, dev)
+    if want_probs:
+        _out(out, "probs", (T, E), torch.float32, dev)
+    if want_counts:
+        _out(out, "counts", (E,), torch.int32, dev)
     _want(out["idx"], torch.int32, (T, k), "idx")
     _want(out["w"], torch.float32, (T, k), "w")
     probs = out.get("probs") if want_probs else None
     counts = out.get("counts") if want_counts else None
     tail = (T, H, E, k, int(bool(renormalize)), _ptr(out["idx"]), _ptr(out["w"]), _ptr(probs), _ptr(counts))
     if residual is None:
-        need = route_topk_packed_workspace_bytes(T, H, E, k) if packed else route_topk_workspace_bytes(T, H, E, k)
-        workspace = _ws(workspace, need, dev)
+        query = route_topk_packed_workspace_bytes if packed else route_topk_workspace_bytes
+        workspace = _ws(workspace, query, (T, H, E, k), dev)
         rc = fn(_ptr(x), _ptr(w_gate), _ptr(bias), G, tpg, *tail, _ptr(workspace), workspace.numel(),
                 _stream(stream))
     else:
@@ -237,7 +249,7 @@ def _route(fn, x, w_gate, bias, tokens_per_group, k, renormalize, want_probs, wa
         D = w1_hat.shape[0]
         _want(w1_hat, torch.bfloat16, (D, H), "w1_hat")
         _want(w2_hat, torch.float32, (E, D), "w2_hat")
-        workspace = _ws(workspace, predict_topk_residual_workspace_bytes(T, H, E, k, D), dev)
+        workspace = _ws(workspace, predict_topk_residual_workspace_bytes, (T, H, E, k, D), dev)
         rc = fn(_ptr(x), _ptr(w_gate), _ptr(bias), G, tpg, _ptr(w1_hat), _ptr(w2_hat), D, *tail,
                 _ptr(workspace), workspace.numel(), _stream(stream))
     _check(rc)
@@ -286,15 +298,15 @@ def route_grouped(x, w_gate, bias=None, tokens_per_group=None, select_bias=None,
                      int(group_top), int(bool(renormalize)), float(routed_scale))
     out = dict(out) if out else {}
     dev = x.device
-    out.setdefault("idx", torch.empty((T, k), dtype=torch.int32, device=dev))
-    out.setdefault("w", torch.empty((T, k), dtype=torch.float32, device=dev))
+    _out(out, "idx", (T, k), torch.int32, dev)
+    _out(out, "w", (T, k), torch.float32, dev)
     if want_scores:
-        out.setdefault("scores", torch.empty((T, E), dtype=torch.float32, device=dev))
+        _out(out, "scores", (T, E), torch.float32, dev)
     if want_counts:
-        out.setdefault("counts", torch.empty((E,), dtype=torch.int32, device=dev))
+        _out(out, "counts", (E,), torch.int32, dev)
     _want(out["idx"], torch.int32, (T, k), "idx")
     _want(out["w"], torch.float32, (T, k), "w")
-    workspace = _ws(workspace, int(lib().probe_route_grouped_workspace_bytes(T, H, E, k)), dev)
+    workspace = _ws(workspace, lib().probe_route_grouped_workspace_bytes, (T, H, E, k), dev)
     fn = lib().probe_route_grouped_packed if packed else lib().probe_route_grouped
     rc = fn(_ptr(x), _ptr(w_gate), _ptr(bias), G, tpg, _ptr(select_bias), C.byref(gating),
                                    T, H, E, k, _ptr(out["idx"]), _ptr(out["w"]),
@@ -357,11 +369,11 @@ def route_predict_topk(x, w_gate, bias, w_gate_next, bias_next, tokens_per_group
     outs = []
     for o in (out, pred_out):
         o = dict(o) if o else {}
-        o.setdefault("idx", torch.empty((T, k), dtype=torch.int32, device=dev))
-        o.setdefault("w", torch.empty((T, k), dtype=torch.float32, device=dev))
-        o.setdefault("counts", torch.empty((E,), dtype=torch.int32, device=dev))
+        _out(o, "idx", (T, k), torch.int32, dev)
+        _out(o, "w", (T, k), torch.float32, dev)
+        _out(o, "counts", (E,), torch.int32, dev)
         if want_probs:
-            o.setdefault("probs", torch.empty((T, E), dtype=torch.float32, device=dev))
+            _out(o, "probs", (T, E), torch.float32, dev)
         _want(o["idx"], torch.int32, (T, k), "idx")
         _want(o["w"], torch.float32, (T, k), "w")
         outs.append(o)
@@ -370,11 +382,11 @@ def route_predict_topk(x, w_gate, bias, w_gate_next, bias_next, tokens_per_group
             _ptr(r.get("probs") if want_probs else None), _ptr(r["counts"]), _ptr(p["idx"]), _ptr(p["w"]),
             _ptr(p.get("probs") if want_probs else None), _ptr(p["counts"]))
     if packed:
-        workspace = _ws(workspace, int(lib().probe_route_predict_topk_packed_workspace_bytes(T, H, E, k)), dev)
+        workspace = _ws(workspace, lib().probe_route_predict_topk_packed_workspace_bytes, (T, H, E, k), dev)
         rc = lib().probe_route_predict_topk_packed(_ptr(x), _ptr(w_gate), _ptr(biases[0]), _ptr(biases[1]), *tail,
                                                    _ptr(workspace), workspace.numel(), _stream(stream))
     else:
-        workspace = _ws(workspace, route_predict_topk_workspace_bytes(T, H, E, k), dev)
+        workspace = _ws(workspace, route_predict_topk_workspace_bytes, (T, H, E, k), dev)
         rc = lib().probe_route_predict_topk(_ptr(x), _ptr(w_gate), _ptr(biases[0]), _ptr(w_gate_next),
                                             _ptr(biases[1]), *tail, _ptr(workspace), workspace.numel(),
                                             _stream(stream))
@@ -402,7 +414,7 @@ def plan_greedy(n_hat, E_loc, rank=0, max_replicas=3, budget=3, k_max=16, eps=0,
     if want_assignment:
         out["n"] = torch.empty((R, E, R), **i32)
     params = _PlannerParams(max_replicas, budget, k_max, eps, n0, g_num, g_den)
-    workspace = _ws(workspace, int(lib().probe_plan_greedy_workspace_bytes(R, E)), dev)
+    workspace = _ws(workspace, lib().probe_plan_greedy_workspace_bytes, (R, E), dev)
     rc = lib().probe_plan_greedy(_ptr(n_hat), R, E, E_loc, rank, C.byref(params), _ptr(out["rep_off"]),
                                  _ptr(out["rep_slot"]), _ptr(out["rep_weight"]), _ptr(out["slot_expert"]),
                                  _ptr(out["delta_in"]), _ptr(out["delta_out"]), _ptr(out["moves"]),
@@ -498,7 +510,7 @@ def permute(topk_idx, plan: Plan, x, *, out=None, workspace=None, stream=None, c
                                         _ptr(out["n_local"]), _stream(stream))
         _check(rc)
         return out
-    workspace = _ws(workspace, permute_workspace_bytes(T, E, k, S), dev)
+    workspace = _ws(workspace, permute_workspace_bytes, (T, E, k, S), dev)
     rc = lib().probe_permute(_ptr(topk_idx), C.byref(plan.c), _ptr(x), T, H, E, k,
                              _ptr(out["slot_counts"]), _ptr(out["slot_offsets"]),
                              _ptr(out["row_pair"]), _ptr(out["pair_row"]), _ptr(out.get("xp")),
@@ -540,7 +552,7 @@ def grouped_ffn(xp, slot_offsets, weights: WeightTable, *, out=None, workspace=N
     if out is None:
         out = torch.empty((max_rows, H), dtype=torch.bfloat16, device=xp.device)
     _want(out, torch.bfloat16, (max_rows, H), "y")
-    workspace = _ws(workspace, grouped_ffn_workspace_bytes(S, H, F, max_rows), xp.device)
+    workspace = _ws(workspace, grouped_ffn_workspace_bytes, (S, H, F, max_rows), xp.device)
     rc = lib().probe_grouped_ffn(_ptr(xp), _ptr(slot_offsets), _ptr(weights.w13_ptrs),
                                  _ptr(weights.w2_ptrs), S, H, F, max_rows, _ptr(out),
                                  _ptr(workspace), workspace.numel(), _stream(stream))
@@ -561,7 +573,7 @@ def grouped_ffn_gather(x, row_pair, k, slot_offsets, weights: WeightTable, *, ou
     if out is None:
         out = torch.empty((max_rows, H), dtype=torch.bfloat16, device=x.device)
     _want(out, torch.bfloat16, (max_rows, H), "y")
-    workspace = _ws(workspace, grouped_ffn_workspace_bytes(S, H, F, max_rows), x.device)
+    workspace = _ws(workspace, grouped_ffn_workspace_bytes, (S, H, F, max_rows), x.device)
     rc = lib().probe_grouped_ffn_gather(_ptr(x), _ptr(row_pair), T, k, _ptr(slot_offsets), _ptr(weights.w13_ptrs),
                                         _ptr(weights.w2_ptrs), S, H, F, max_rows, _ptr(out), _ptr(workspace),
                                         workspace.numel(), _stream(stream))
