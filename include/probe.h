@@ -458,7 +458,7 @@ int probe_plan_greedy(const int32_t* n_hat, int R, int E, int E_loc, int rank,
  *   rep_slot     device, int32 [E + R*max_replicas]     (out)
  *   rep_weight   device, int32 [E + R*max_replicas]     (out)
  *   rank_off     device, int32 [R+1]                    (out) first slot of every destination rank
- *   slot_expert  device, int32 [E + R*max_replicas]     (out) expert of each slot in use
+ *   slot_expert  device, int32 [E + R*max_replicas]     (out) expert of each slot, -1 where it is not in use
  * Limits as probe_plan_greedy.  No workspace.
  */
 int probe_plan_dispatch(const int32_t* n_assign, const int32_t* delta_in, int R, int E, int E_loc,

@@ -8,18 +8,23 @@
 // The paper runs its solver as a single-block kernel with serial iterative updates (Sec. 5); the
 // same shape fits here: the loop is inherently sequential (each move changes the bottleneck), and
 // what one iteration touches is small once the per-rank aggregates are kept incrementally:
-//   LDS   ner[e][r]   tokens of expert e processed on rank r
-//         comp[r]     sum over experts with ner > 0 of (ner + n0)          (compute term)
-//         vin[r], vout[r]   tokens received from / sent to other ranks      (network term)
-//         load[r]     tokens processed on rank r
+//   LDS   ner[r][e]   tokens of expert e processed on rank r
+//         pos[r][e]   the origins of those tokens, one bit each
 //         n[e][rs][rt]  the assignment, expert-major: a move rewrites one R x R slab.  It lies in LDS where it fits
 //                     (kPlanLdsBytes: every R <= 11, 16 ranks up to 135 experts), otherwise in the workspace.
-// What bounds it is latency: an iteration is a chain of dependent reads and barriers on one CU.  Slabs in LDS, values
-// read side by side, one thread per slab entry for the water-filling and four barriers per accepted move: 8 ranks, 128
-// experts, 3 replicas 73 -> 53 us.  Bottleneck, helper and new latencies as reductions over the sixteen lanes of a DPP row
-// instead of chains over the ranks in every thread: 53 -> 39 us.
-// Per iteration only SelectHeavyExpert looks at every expert (one thread each, block arg-max by a
-// 64-bit LDS atomic).  All arithmetic is integer, so the plan is bit-identical to the sequential definition.
+//   registers of wave 0, one rank per lane:
+//         comp        sum over experts with ner > 0 of (ner + n0)          (compute term)
+//         vin, vout   tokens received from / sent to other ranks            (network term)
+//         load        tokens processed on the rank
+//         and its latency, budget counts and invalid partners
+// What bounds it is latency: an iteration is a chain of dependent steps.  One wave makes it, so that nothing of it needs a
+// barrier; the move's effect on every rank follows from one column and one row of the expert's slab (the tokens that
+// origins without a copy give up, and dst's own tokens coming home), reductions and the prefix over the origins run over the
+// sixteen lanes of a DPP row, and whether an expert has anything to move is one mask.  8 ranks, 128 experts, 3 replicas: with 256
+// threads, the new slab in LDS and four barriers per move this call and probe_plan_dispatch took 56 to 65 us, now 28 to 31; 16
+// ranks of 256 experts 180 to 196 and 104 to 117.
+// Per iteration only SelectHeavyExpert looks at every expert (up to four per lane, arg-max over the wave).
+// All arithmetic is integer, so the plan is bit-identical to the sequential definition.
 //
 // Cost model (a reading; the paper names the terms but not their constants):
 //   L_r = g_den * comp[r] + 2 * g_num * max(vin[r], vout[r])
@@ -44,12 +49,17 @@ struct PlannerArgs {
 
 __device__ __forceinline__ long long comp_term(long long tokens, long long n0) { return tokens > 0 ? tokens + n0 : 0; }
 
-// LDS that the assignment may take; the rest of the kernel's state is about 20 KB of the 160.
+// LDS that the assignment may take; ner and pos (at most 24 KB) and the rest of the kernel's state come on top, and with 16 ranks,
+// where the assignment is largest, they are 13 KB.
 constexpr int kPlanLdsBytes = 136 * 1024;
 // Words between the slabs of two experts.  In LDS one more than R * R, so that threads that look at the same entry of
 // neighbouring experts are on different banks.
 __host__ __device__ constexpr int plan_slab_stride(int R, bool in_lds) { return R * R + (in_lds ? 1 : 0); }
 static bool plan_fits_lds(int R, int E) { return E * plan_slab_stride(R, true) * 4 <= kPlanLdsBytes; }
+__host__ __device__ constexpr int plan_pos_words(int R, int E) { return (R * E + 1) / 2; }
+static size_t plan_lds_bytes(int R, int E, bool in_lds) {
+  return (static_cast<size_t>(R) * E + plan_pos_words(R, E) + (in_lds ? E * plan_slab_stride(R, true) : 0)) * sizeof(int32_t);
+}
 
 // Reductions over the sixteen lanes of a DPP row; every lane gets the result.  All lanes of the wave take part.
 template <int N>
@@ -69,9 +79,46 @@ __device__ __forceinline__ long long row_sum64(long long v) { return row_reduce6
 __device__ __forceinline__ long long row_max64(long long v) { return row_reduce64(v, [](long long a, long long b) { return max(a, b); }); }
 __device__ __forceinline__ long long row_min64(long long v) { return row_reduce64(v, [](long long a, long long b) { return min(a, b); }); }
 
+// Exclusive prefix sum over the sixteen lanes of a DPP row.
+template <int N>
+__device__ __forceinline__ long long row_shr64(long long v) {  // lane - N of the row, 0 before its first lane
+  const unsigned lo = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x110 | N, 0xf, 0xf, true));
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(v >> 32), 0x110 | N, 0xf, 0xf, true);
+  return static_cast<long long>(static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32 | lo);
+}
+__device__ __forceinline__ long long row_prefix64(long long v) {
+  long long s = v;
+  s += row_shr64<1>(s);
+  s += row_shr64<2>(s);
+  s += row_shr64<4>(s);
+  s += row_shr64<8>(s);
+  return s - v;
+}
+// The value of the lane on the other side in a swap of rows (16) or halves (32) and this lane's own, combined; every row gets
+// the same result.
+template <typename Op>
+__device__ __forceinline__ long long cross_rows64(long long v, Op op) {
+  unsigned lo = static_cast<unsigned>(v), hi = static_cast<unsigned>(v >> 32);
+  auto join = [](unsigned l, unsigned h) { return static_cast<long long>(static_cast<unsigned long long>(h) << 32 | l); };
+  const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  v = op(join(l16[0], h16[0]), join(l16[1], h16[1]));
+  lo = static_cast<unsigned>(v);
+  hi = static_cast<unsigned>(v >> 32);
+  const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return op(join(l32[0], h32[0]), join(l32[1], h32[1]));
+}
+__device__ __forceinline__ long long wave_max64(long long v) {
+  return cross_rows64(row_max64(v), [](long long a, long long b) { return max(a, b); });
+}
+__device__ __forceinline__ long long read_lane64(long long v, int lane) {
+  const unsigned lo = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(v), lane));
+  const int hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), lane);
+  return static_cast<long long>(static_cast<unsigned long long>(static_cast<unsigned>(hi)) << 32 | lo);
+}
+
 template <bool IN_LDS>
 __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restrict__ n_hat, PlannerArgs a,
-                                                          int32_t* __restrict__ n_workspace,  // [E][R][R]
+                                                          int32_t* n_workspace,  // [E][R][R]
                                                           int32_t* __restrict__ rep_off, int32_t* __restrict__ rep_slot,
                                                           int32_t* __restrict__ rep_weight,
                                                           int32_t* __restrict__ slot_expert,
@@ -79,33 +126,23 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
                                                           int32_t* __restrict__ moves, long long* __restrict__ stats,
                                                           int32_t* __restrict__ n_assign) {
   const int R = a.R, E = a.E, E_loc = a.E_loc, stride = plan_slab_stride(R, IN_LDS);
-  extern __shared__ int32_t n_lds[];
-  int32_t* const g_n = IN_LDS ? n_lds : n_workspace;
-  __shared__ int32_t ner[PROBE_MAX_EXPERTS][kPlanMaxRanks];
+  extern __shared__ int32_t lds[];
+  int32_t* const ner = lds;                                           // [R][E]
+  uint16_t* const pos = reinterpret_cast<uint16_t*>(lds + R * E);     // [R][E]
+  int32_t* const g_n = IN_LDS ? lds + R * E + plan_pos_words(R, E) : n_workspace;
   __shared__ uint32_t hostmask[PROBE_MAX_EXPERTS];
   __shared__ long long comp[kPlanMaxRanks], vin[kPlanMaxRanks], vout[kPlanMaxRanks], load[kPlanMaxRanks];
-  // entries of ranks past R: the lowest latency there is
-  __shared__ long long lat[kPlanMaxRanks], t_lat[kPlanMaxRanks];
-  __shared__ int32_t slab_old[kPlanMaxRanks][kPlanMaxRanks + 1], slab_new[kPlanMaxRanks][kPlanMaxRanks + 1];
-  __shared__ uint32_t invalid[kPlanMaxRanks];
-  __shared__ int32_t n_in[kPlanMaxRanks], n_out[kPlanMaxRanks];
   __shared__ int32_t d_in[kPlanMaxRanks][kPlanMaxReplicas];
-  __shared__ long long best_key[2];  // iteration i uses best_key[i & 1]
   __shared__ int32_t wave_tot[4];
   const int tid = threadIdx.x, lane = tid & 63;
 
   // ---- initial assignment: every token to the expert's home rank (baseline placement P')
-  if (tid < kPlanMaxRanks) {
-    lat[tid] = t_lat[tid] = LLONG_MIN;
-    invalid[tid] = 0;
-    n_in[tid] = n_out[tid] = 0;
+  if (tid < kPlanMaxRanks)
     for (int i = 0; i < kPlanMaxReplicas; ++i) d_in[tid][i] = -1;
-  }
-  for (int i = tid; i < kPlanMaxRanks * (kPlanMaxRanks + 1); i += 256) (&slab_old[0][0])[i] = (&slab_new[0][0])[i] = 0;
-  if (tid < 2) best_key[tid] = -1;
   if (tid < E) {
     const int e = tid, home = e / E_loc;
     int v[kPlanMaxRanks], tot = 0;
+    uint32_t origins = 0;
 #pragma unroll
     for (int rs = 0; rs < kPlanMaxRanks; ++rs) v[rs] = rs < R ? max(n_hat[rs * E + e], 0) : 0;
 #pragma unroll
@@ -113,8 +150,12 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
       if (rs < R)
         for (int rt = 0; rt < R; ++rt) g_n[e * stride + rs * R + rt] = (rt == home) ? v[rs] : 0;
       tot = static_cast<int>(static_cast<unsigned>(tot) + static_cast<unsigned>(v[rs]));
+      origins |= v[rs] > 0 ? 1u << rs : 0u;
     }
-    for (int r = 0; r < R; ++r) ner[e][r] = (r == home) ? tot : 0;
+    for (int r = 0; r < R; ++r) {
+      ner[r * E + e] = (r == home) ? tot : 0;
+      pos[r * E + e] = static_cast<uint16_t>((r == home) ? origins : 0u);
+    }
     hostmask[e] = 1u << home;
   }
   for (int i = tid; i < R * a.max_replicas; i += 256) delta_in[i] = -1;
@@ -144,152 +185,135 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
     s_vin = row_sum64(s_vin);
     s_vout = row_sum64(s_vout);
     s_load = row_sum64(s_load);
-    if ((tid & 15) == 0 && r < R) {
+    if ((tid & 15) == 0) {
       comp[r] = s_comp;
       vin[r] = s_vin;
       vout[r] = s_vout;
       load[r] = s_load;
-      lat[r] = a.g_den * s_comp + 2 * a.g_num * max(s_vin, s_vout);
     }
   }
   __syncthreads();
-  long long total = 0, lat_before = lat[0];
-  for (int r = 0; r < R; ++r) {
-    total += load[r];
-    lat_before = max(lat_before, lat[r]);
-  }
-  const long long avg = (total + R - 1) / R;
-  const int cap_in = min(a.budget, a.max_replicas);
-  const int my_rs = tid / R, my_rt = tid % R;  // this thread's entry of a slab (tid < R * R)
-  const int rank_of = tid >> 4, partner = tid & 15;
-  const bool writes_rank = partner == 0 && rank_of < R;
 
-  // ---- the loop of Algorithm 1; every thread follows the same control flow
-  int k = 0;
-  for (int guard = 0; guard < kPlanMaxMoves + kPlanMaxRanks * kPlanMaxRanks + 1; ++guard) {
-    // bottleneck rank and the least-loaded helper whose pair with it is still valid (ties: lower rank)
-    const int lr = lane & 15;  // a lane looks at one rank
-    const long long l = lat[lr];
-    const uint32_t inv = invalid[lr];
-    const long long mx_old = row_max64(l);
-    const int src = __ffsll(__ballot(l == mx_old)) - 1;
-    const uint32_t barred = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inv), src)) | 1u << src;
-    const bool free_pair = lr < R && !((barred >> lr) & 1u);
-    const long long mn = row_min64(free_pair ? l : LLONG_MAX);
-    const int dst = __ffsll(__ballot(free_pair && l == mn)) - 1;
-    if (dst < 0) break;
+  // ---- the loop of Algorithm 1, by one wave; the four rows of sixteen lanes hold the same ranks
+  if (tid < kWave) {
+    const int lr = lane & 15;  // this lane's rank
+    const bool is_rank = lr < R;
+    long long my_comp = comp[lr], my_vin = vin[lr], my_vout = vout[lr], my_load = load[lr];
+    // lanes past the last rank have the lowest latency there is
+    long long l = is_rank ? a.g_den * my_comp + 2 * a.g_num * max(my_vin, my_vout) : LLONG_MIN;
+    const long long lat_before = row_max64(l);
+    const long long total = row_sum64(my_load), avg = (total + R - 1) / R;
+    const int cap_in = min(a.budget, a.max_replicas);
+    uint32_t invalid = 0;  // partners with which this rank as a source is through
+    int n_in = 0, n_out = 0, k = 0;
+    for (int guard = 0; guard < kPlanMaxMoves + kPlanMaxRanks * kPlanMaxRanks + 1; ++guard) {
+      // bottleneck rank and the least-loaded helper whose pair with it is still valid (ties: lower rank)
+      const long long mx_old = row_max64(l);
+      const int src = __ffsll(__ballot(l == mx_old)) - 1;
+      const uint32_t barred = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(invalid), src)) | 1u << src;
+      const bool free_pair = is_rank && !((barred >> lr) & 1u);
+      const long long mn = row_min64(free_pair ? l : LLONG_MAX);
+      const int dst = __ffsll(__ballot(free_pair && l == mn)) - 1;
+      if (dst < 0) break;
 
-    // SelectHeavyExpert: most tokens on src among the experts src holds, dst does not, with something to move
-    if (tid < E) {
-      const uint32_t hm = hostmask[tid];
-      if (((hm >> src) & 1u) && !((hm >> dst) & 1u)) {
-        long long movable = 0;
+      // dual-side budget check, and SelectHeavyExpert: most tokens on src among the experts src holds, dst does not, with
+      // something to move (tokens of an origin without a copy); an empty selection is treated like an empty budget
+      long long key = -1;
+      const int out_src = __builtin_amdgcn_readlane(n_out, src), in_dst = __builtin_amdgcn_readlane(n_in, dst);
+      if (out_src < a.budget && in_dst < cap_in) {
 #pragma unroll
-        for (int rs = 0; rs < kPlanMaxRanks; ++rs) {
-          const int v = g_n[tid * stride + min(rs, R - 1) * R + src];
-          if (rs < R && (rs == dst || !((hm >> rs) & 1u))) movable += v;
+        for (int i = 0; i < PROBE_MAX_EXPERTS / kWave; ++i) {
+          const int e = lane + i * kWave;
+          if (e < E) {
+            const uint32_t hm = hostmask[e], from = pos[src * E + e];
+            const long long tokens = ner[src * E + e];
+            if (((hm >> src) & 1u) && !((hm >> dst) & 1u) && (from & ~hm)) key = max(key, tokens << 9 | (511 - e));
+          }
         }
-        if (movable > 0)
-          atomicMax(&best_key[guard & 1], (static_cast<long long>(ner[tid][src]) << 9) | static_cast<long long>(511 - tid));
+        key = wave_max64(key);
       }
-    }
-    __syncthreads();
-    const long long bk = best_key[guard & 1];
-    if (tid == 0) best_key[(guard + 1) & 1] = -1;  // last read before the barrier above, next used after the one below
-    // dual-side budget check (an empty selection is treated the same way)
-    if (bk < 0 || n_out[src] >= a.budget || n_in[dst] >= cap_in) {
-      if (tid == 0) invalid[src] |= 1u << dst;
-      __syncthreads();
-      continue;
-    }
-    const int es = 511 - static_cast<int>(bk & 511);
+      if (key < 0) {
+        if (lr == src) invalid |= 1u << dst;
+        continue;
+      }
+      const int es = 511 - static_cast<int>(__builtin_amdgcn_readfirstlane(static_cast<int>(key)) & 511);
 
-    // WaterFillingRebalance on the expert's slab, one thread per entry
-    if (tid < R * R) {
-      const int32_t* slab = g_n + es * stride;
+      // WaterFillingRebalance on the expert's slab: column src by origin, column dst by origin, row dst by rank
+      int32_t* const slab = g_n + es * stride;
       const uint32_t hm = hostmask[es];
-      const int old = slab[tid];
-      int upd = old;
-      if (my_rs == dst) {  // locality first: dst's own tokens come home
-        long long row = 0;
+      const int at_src = is_rank ? slab[lr * R + src] : 0, at_dst = is_rank ? slab[lr * R + dst] : 0;
+      const int own = is_rank ? slab[dst * R + lr] : 0;
+      long long o_ner = 0;  // tokens of es on this lane's rank, in 64 bits
 #pragma unroll
-        for (int q = 0; q < kPlanMaxRanks; ++q) {
-          const int v = slab[dst * R + min(q, R - 1)];
-          if (q < R) row += v;
-        }
-        upd = my_rt == dst ? static_cast<int>(row) : 0;
-      } else if ((my_rt == src || my_rt == dst) && !((hm >> my_rs) & 1u)) {
-        // origins without a copy, ascending rank, until src is down to the mean: this one gives what those before it leave
-        long long want = load[src] - slab[dst * R + src] - avg;
-#pragma unroll
-        for (int q = 0; q < kPlanMaxRanks; ++q) {
-          const int v = slab[min(q, R - 1) * R + src];
-          if (q < my_rs && q != dst && !((hm >> q) & 1u)) want -= v;
-        }
-        const int mv = static_cast<int>(max(min(static_cast<long long>(slab[my_rs * R + src]), want), 0ll));
-        upd += my_rt == dst ? mv : -mv;
+      for (int j = 0; j < kPlanMaxRanks / 4; ++j) {
+        const int rs = 4 * j + (lane >> 4);
+        o_ner += is_rank && rs < R ? slab[rs * R + lr] : 0;
       }
-      slab_old[my_rs][my_rt] = old;
-      slab_new[my_rs][my_rt] = upd;
-    }
-    __syncthreads();
-    // what the move does to rank `rank_of`: sixteen threads, one per partner (entries past R are zero)
-    const int oc = slab_old[partner][rank_of], nc = slab_new[partner][rank_of];
-    const long long o_ner = row_sum64(oc), n_ner = row_sum64(nc);
-    const long long in_change = row_sum64(partner != rank_of ? static_cast<long long>(nc) - oc : 0ll);
-    const long long out_change = row_sum64(
-        partner != rank_of ? static_cast<long long>(slab_new[rank_of][partner]) - slab_old[rank_of][partner] : 0ll);
-    long long t_comp = 0, t_vin = 0, t_vout = 0, t_load = 0, t_l = 0;
-    if (writes_rank) {
-      t_comp = comp[rank_of] - comp_term(o_ner, a.n0) + comp_term(n_ner, a.n0);
-      t_vin = vin[rank_of] + in_change;
-      t_vout = vout[rank_of] + out_change;
-      t_load = load[rank_of] - o_ner + n_ner;
-      t_l = a.g_den * t_comp + 2 * a.g_num * max(t_vin, t_vout);
-      t_lat[rank_of] = t_l;
-    }
-    __syncthreads();
-    const long long mx_new = row_max64(t_lat[lane & 15]);
-    if (mx_old - mx_new <= a.eps || k >= a.k_max) break;  // converged, or the iteration budget is used up
+      o_ner = cross_rows64(o_ner, [](long long x, long long y) { return x + y; });
+      // origins without a copy, ascending rank, until src is down to the mean: each gives what those before it leave
+      const bool gives = is_rank && lr != dst && !((hm >> lr) & 1u);
+      const long long before = row_prefix64(gives ? at_src : 0);
+      const long long want = read_lane64(my_load, src) - __builtin_amdgcn_readlane(own, src) - avg - before;
+      const int mv = gives ? static_cast<int>(max(min(static_cast<long long>(at_src), want), 0ll)) : 0;
+      const long long moved = row_sum64(mv);
+      const long long homed = row_sum64(lr != dst ? own : 0);  // dst's own tokens come home first
+      // what the move does to this lane's rank.  An origin that gives tokens holds no copy, so it is neither src nor dst and sends
+      // as much as before; dst stops sending its own.
+      const long long leave = own + (lr == src ? moved : 0ll);
+      const long long n_ner = lr == dst ? o_ner + homed + moved : o_ner - leave;
+      const long long t_comp = my_comp - comp_term(o_ner, a.n0) + comp_term(n_ner, a.n0);
+      const long long t_vin = my_vin + (lr == dst ? moved : -leave);
+      const long long t_vout = my_vout - (lr == dst ? homed : 0ll);
+      const long long t_load = my_load - o_ner + n_ner;
+      const long long t_l = is_rank ? a.g_den * t_comp + 2 * a.g_num * max(t_vin, t_vout) : LLONG_MIN;
+      const long long mx_new = row_max64(t_l);
+      if (mx_old - mx_new <= a.eps || k >= a.k_max) break;  // converged, or the iteration budget is used up
 
-    // accept the move
-    if (tid < R * R) g_n[es * stride + tid] = slab_new[my_rs][my_rt];
-    if (writes_rank) {
-      ner[es][rank_of] = static_cast<int>(n_ner);
-      comp[rank_of] = t_comp;
-      vin[rank_of] = t_vin;
-      vout[rank_of] = t_vout;
-      load[rank_of] = t_load;
-      lat[rank_of] = t_l;
+      // accept the move
+      const int kept = at_src - mv, taken = lr == dst ? static_cast<int>(homed + own) : at_dst + mv;
+      const uint32_t on_src = static_cast<uint32_t>(__ballot(is_rank && lr != dst && kept > 0)) & 0xffffu;
+      const uint32_t on_dst = static_cast<uint32_t>(__ballot(is_rank && taken > 0)) & 0xffffu;
+      if (lane < R) {
+        if (lr != dst) {
+          slab[lr * R + src] = kept;
+          slab[lr * R + dst] = taken;
+        }
+        slab[dst * R + lr] = lr == dst ? taken : 0;
+        ner[lr * E + es] = static_cast<int>(n_ner);
+        const uint32_t from = pos[lr * E + es] & ~(1u << dst);
+        pos[lr * E + es] = static_cast<uint16_t>(lr == src ? on_src : (lr == dst ? on_dst : from));
+      }
+      if (lane == 0) {
+        hostmask[es] = hm | 1u << dst;
+        if (delta_out) delta_out[src * a.budget + out_src] = es;
+        delta_in[dst * a.max_replicas + in_dst] = es;
+        d_in[dst][in_dst] = es;
+        moves[3 * k] = es;
+        moves[3 * k + 1] = src;
+        moves[3 * k + 2] = dst;
+      }
+      my_comp = t_comp;
+      my_vin = t_vin;
+      my_vout = t_vout;
+      my_load = is_rank ? t_load : 0;
+      l = t_l;
+      n_out += lr == src ? 1 : 0;
+      n_in += lr == dst ? 1 : 0;
+      k += 1;
+      // the wave's stores are seen by its loads of the next round
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     }
-    if (tid == 0) {
-      if (delta_out) delta_out[src * a.budget + n_out[src]] = es;
-      delta_in[dst * a.max_replicas + n_in[dst]] = es;
-      d_in[dst][n_in[dst]] = es;
-      n_out[src] += 1;
-      n_in[dst] += 1;
-      hostmask[es] |= 1u << dst;
-      moves[3 * k] = es;
-      moves[3 * k + 1] = src;
-      moves[3 * k + 2] = dst;
+    const long long mx = row_max64(l), ml = row_max64(is_rank ? my_load : 0);
+    if (lane == 0) {
+      stats[0] = lat_before;
+      stats[1] = mx;
+      stats[2] = ml;
+      stats[3] = k;
     }
-    k += 1;
-    __syncthreads();
   }
   __syncthreads();
 
   // ---- outputs
-  if (tid == 0) {
-    long long mx = 0, ml = 0;
-    for (int r = 0; r < R; ++r) {
-      mx = r == 0 ? lat[r] : max(mx, lat[r]);
-      ml = max(ml, load[r]);
-    }
-    stats[0] = lat_before;
-    stats[1] = mx;
-    stats[2] = ml;
-    stats[3] = k;
-  }
   const int rank = a.rank, S = E_loc + a.max_replicas;
   for (int s = tid; s < S; s += 256) {
     int e = -1;
@@ -311,14 +335,14 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
   }
   if (lane == kWave - 1) wave_tot[tid >> 6] = incl;
   __syncthreads();
-  int pos = incl - cnt;
-  for (int i = 0; i < (tid >> 6); ++i) pos += wave_tot[i];
+  int at = incl - cnt;
+  for (int i = 0; i < (tid >> 6); ++i) at += wave_tot[i];
   if (tid < E) {
     const int e = tid, home = e / E_loc;
     const uint32_t hm = hostmask[e];
-    rep_off[e] = pos;
+    rep_off[e] = at;
     long long planned = 0;
-    int home_pos = pos;
+    int home_pos = at;
     for (int r = 0; r < R; ++r) {
       if (!((hm >> r) & 1u)) continue;
       int slot = -1;
@@ -330,14 +354,14 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
             if (d_in[r][i] == e) slot = E_loc + i;
         }
       }
-      if (r == home) home_pos = pos;
-      rep_slot[pos] = slot;
-      rep_weight[pos] = ner[e][r];
-      planned += ner[e][r];
-      pos += 1;
+      if (r == home) home_pos = at;
+      rep_slot[at] = slot;
+      rep_weight[at] = ner[r * E + e];
+      planned += ner[r * E + e];
+      at += 1;
     }
     if (planned == 0) rep_weight[home_pos] = 1;  // nothing predicted: unforeseen tokens go home
-    if (e == E - 1) rep_off[E] = pos;
+    if (e == E - 1) rep_off[E] = at;
   }
   if (n_assign) {
     for (int i = tid; i < E * R; i += 256) {
@@ -348,6 +372,7 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
 }
 
 // More than 64 KB of dynamic LDS has to be opted into once per device.
+constexpr int kPlanLdsMost = kPlanLdsBytes + 18 * 1024;  // 16 ranks, 135 experts: 156480 bytes
 static int plan_prepare() {
   static std::mutex mu;
   static bool done[64] = {false};
@@ -359,9 +384,9 @@ static int plan_prepare() {
   std::lock_guard<std::mutex> lock(mu);
   if (done[dev]) return PROBE_OK;
   hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(plan_greedy_kernel<true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kPlanLdsBytes);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kPlanLdsMost);
   if (err != hipSuccess) {
-    set_error("probe_plan_greedy: cannot reserve %d bytes of LDS: %s", kPlanLdsBytes, hipGetErrorString(err));
+    set_error("probe_plan_greedy: cannot reserve %d bytes of LDS: %s", kPlanLdsMost, hipGetErrorString(err));
     return PROBE_EHIP;
   }
   done[dev] = true;
@@ -420,6 +445,7 @@ __global__ __launch_bounds__(256) void plan_dispatch_kernel(const int32_t* __res
     rank_off[R] = run;
   }
   __syncthreads();
+  for (int i = r_off[R] + tid; i < E + R * max_replicas; i += 256) slot_expert[i] = -1;  // slots not in use
   int pos = incl - cnt;
   for (int i = 0; i < wv; ++i) pos += wave_tot[i];
   if (e < E) {
@@ -506,7 +532,7 @@ extern "C" int probe_plan_greedy(const int32_t* n_hat, int R, int E, int E_loc, 
     int rc = plan_prepare();
     if (rc != PROBE_OK) return rc;
   }
-  const size_t lds = in_lds ? static_cast<size_t>(E) * plan_slab_stride(R, true) * sizeof(int32_t) : 0;
+  const size_t lds = plan_lds_bytes(R, E, in_lds);
   hipLaunchKernelGGL(in_lds ? plan_greedy_kernel<true> : plan_greedy_kernel<false>, dim3(1), dim3(256), lds,
                      static_cast<hipStream_t>(stream), n_hat, a, static_cast<int32_t*>(workspace), rep_off, rep_slot,
                      rep_weight, slot_expert, delta_in, delta_out, moves, reinterpret_cast<long long*>(stats), n_assign);

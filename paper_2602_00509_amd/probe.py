@@ -440,7 +440,7 @@ def plan_dispatch(n_assign, delta_in, E_loc, rank, *, stream=None):
     cap = E + R * max_replicas
     out = dict(rep_off=torch.empty((E + 1,), **i32), rep_slot=torch.empty((cap,), **i32),
                rep_weight=torch.empty((cap,), **i32), rank_off=torch.empty((R + 1,), **i32),
-               slot_expert=torch.full((cap,), -1, **i32))
+               slot_expert=torch.empty((cap,), **i32))
     rc = lib().probe_plan_dispatch(_ptr(n_assign), _ptr(delta_in), R, E, int(E_loc), max_replicas, int(rank),
                                    _ptr(out["rep_off"]), _ptr(out["rep_slot"]), _ptr(out["rep_weight"]),
                                    _ptr(out["rank_off"]), _ptr(out["slot_expert"]), _stream(stream))
