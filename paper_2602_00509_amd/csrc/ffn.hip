@@ -516,8 +516,10 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
                                            int row0, int rows, int n0, int H, int F,
                                            bf16_t* __restrict__ y, u32x4* smem, int32_t* draw_counter = nullptr,
                                            volatile int* draw_slot = nullptr, int k0 = 0, int klen = 0,
-                                           float* partial = nullptr, int k_start = 0) {
-  // SPLIT: only k0 .. k0 + klen - 1 of the contraction; the fp32 sums go to partial[row of the tile][H].
+                                           float* partial = nullptr, int k_start = 0, int piece = 0, int pieces = 1,
+                                           uint32_t* arrivals = nullptr, int item = 0) {
+  // SPLIT: only k0 .. k0 + klen - 1 of the contraction, piece `piece` of `pieces`.  The fp32 sums go to partial[piece][row of
+  // the tile][H], and the workgroup that counts as the last of its item adds them (see ffn_gemm2_skinny_kernel).
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wv / 4, wn = wv % 4;
@@ -536,20 +538,60 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
   __amdgpu_buffer_rsrc_t rY = make_rsrc(y + static_cast<size_t>(row0) * H, static_cast<size_t>(valid) * H * 2);
   const int row_in = 32 * MI * wm + (lane & 15);
   if constexpr (SPLIT) {
-    __amdgpu_buffer_rsrc_t rP = make_rsrc(partial, static_cast<size_t>(valid) * H * 4);
+    // Stores and loads at device scope (sc1): the pieces of an item run on different XCDs, whose L2s do not see one another.
+    constexpr int kDeviceScope = 16;
+    const size_t piece_floats = static_cast<size_t>(64 * MI) * H;
+    auto offset_of = [&](int i, int q) { return ((row_in + 16 * i) * H + n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4)) * 4; };
+    auto in_range = [&](int q) { return n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4) < H; };
+    __amdgpu_buffer_rsrc_t rP = make_rsrc(partial + piece * piece_floats, static_cast<size_t>(valid) * H * 4);
 #pragma unroll
     for (int i = 0; i < 2 * MI; ++i) {
 #pragma unroll
       for (int q = 0; q < NI; ++q) {
-        const int cbase = n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4);
-        const int off = ((row_in + 16 * i) * H + cbase) * 4;
-        if (cbase < H) {
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q]), rP, off, 0, 0);
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q + 1]), rP, off + 16, 0, 0);
+        if (in_range(q)) {
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q]), rP, offset_of(i, q), 0, kDeviceScope);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q + 1]), rP, offset_of(i, q) + 16, 0, kDeviceScope);
         }
       }
     }
-    return drew;
+    // every wave's stores have arrived before the workgroup counts itself in: four items to a word, one byte each
+    __shared__ int last;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0)
+      last = static_cast<int>((atomicAdd(&arrivals[item >> 2], 1u << (8 * (item & 3))) >> (8 * (item & 3))) & 255u) == pieces - 1;
+    __syncthreads();
+    if (!last) return drew;
+    // the sums in ascending order of the pieces, whichever came last
+#pragma unroll
+    for (int i = 0; i < 2 * MI; ++i)
+#pragma unroll
+      for (int j = 0; j < 2 * NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int BATCH = 2;  // pieces whose loads are in flight together
+    for (int p0 = 0; p0 < pieces; p0 += BATCH) {
+      f32x4 v[BATCH][2 * MI][2 * NI];
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        __amdgpu_buffer_rsrc_t rQ = make_rsrc(partial + min(p0 + u, pieces - 1) * piece_floats, static_cast<size_t>(valid) * H * 4);
+#pragma unroll
+        for (int i = 0; i < 2 * MI; ++i)
+#pragma unroll
+          for (int q = 0; q < NI; ++q) {
+            v[u][i][2 * q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rQ, offset_of(i, q), 0, kDeviceScope));
+            v[u][i][2 * q + 1] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rQ, offset_of(i, q) + 16, 0, kDeviceScope));
+          }
+      }
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u)
+        if (p0 + u < pieces) {
+#pragma unroll
+          for (int i = 0; i < 2 * MI; ++i)
+#pragma unroll
+            for (int j = 0; j < 2 * NI; ++j) acc[i][j] += v[u][i][j];
+        }
+    }
   }
 #pragma unroll
   for (int i = 0; i < 2 * MI; ++i) {
@@ -628,24 +670,31 @@ constexpr int kSkinnyCols1 = 64, kSkinnyCols2 = 128;   // h columns / y columns 
 
 // Few tiles.  A call with one or two active slots (a single token; a shared expert) has fewer items than the chip has
 // CUs, and an item streams its weights no faster than about 50 GB/s.  The contraction is then cut into pieces, as many
-// as give every CU one item: each leaves its fp32 sums in the workspace, and a second kernel adds the
-// pieces in ascending order.  The number of tiles is known on the device only; the host merely decides whether it can be
-// small (skinny_may_split) and then launches the adding kernel, which ends at once if nothing was split.
+// as give every CU one item: each leaves its fp32 sums in the workspace, and they are added in ascending order.  The number
+// of tiles is known on the device only.  gemm1: a second kernel adds the pieces; the host decides whether the tiles can be few
+// (skinny_may_split) and then launches it, and it ends at once if nothing was split.  gemm2: the workgroup that counts as the
+// last of its item adds them, on counters that gemm1's launch clears, so nothing is launched for it and contractions of 24 k-steps
+// are worth cutting (one slot of 75 rows, 7168 x 2048: gemm2 18 us uncut; pieces of eight steps lose, two tokens of 4096 x 1536 26.5
+// / 27.1): the layer of one token 151.8 -> 149.2 us, 75 tokens with a shared expert 406.8 -> 403.2.
 // One token, two experts of 4096 x 14336: FFN 194 -> 137 us (gemm2 104 -> 41, adding 5); 512 items instead of 256: 141,
 // 1024: 161.  One slot of 75 rows, 7168 x 2048, which took the tall tiles before: 125 -> 43 us.
 constexpr int kSkinnyItems = 256;
-constexpr int kSkinnyMinSteps = 16;      // k-steps of a piece at least
-// k-steps from which a contraction may be cut.  Shorter ones gain less over the adding kernel's launch (about 5 us), but some
-// still do: uncut / cut one slot of 16 rows, 3072 x 1536 28.3 / 24.1 us; two of 2880 x 2880 47.5 / 41.2, four 52.4 / 52.3.
-constexpr int kSkinnySplitSteps = 64;
+constexpr int kSkinnyMinSteps1 = 16, kSkinnyMinSteps2 = 12;  // k-steps of a piece at least
+// k-steps from which a contraction may be cut.  Shorter ones of gemm1 gain less over the adding kernel's launch (about 5 us), but
+// some still do: uncut / cut one slot of 16 rows, 3072 x 1536 28.3 / 24.1 us; two of 2880 x 2880 47.5 / 41.2, four 52.4 / 52.3.
+constexpr int kSkinnySplitSteps1 = 64, kSkinnySplitSteps2 = 2 * kSkinnyMinSteps2;
 constexpr int kSkinnyFewItems = 512;     // items at capacity up to which tiles can be few
 constexpr size_t kSkinnyPartialBytes = static_cast<size_t>(kSkinnyItems) * 64 * 128 * sizeof(float);
+// Items that are cut number at most half of kSkinnyItems: a byte each counts the pieces that have arrived.  They lie in the tile table,
+// which the decode schedule does not use and which is never shorter.
+constexpr int kArrivalWords = kSkinnyItems / 2 / 4;
+static_assert(kArrivalWords * sizeof(uint32_t) <= kTableHeaderInts * sizeof(int32_t) && kSkinnyItems <= 256, "bytes of the table header");
 
 // most row tiles that max_rows rows in S slots can give: every tile has a row, every slot one tile that is not full
 static int skinny_max_tiles(int S, int max_rows) {
   return std::min<long>(max_rows, (static_cast<long>(max_rows) + 63l * S) / 64);
 }
-// Whether the contraction of `steps` k-steps, over n_cols column blocks, may be cut: few items at capacity, and a cut
+// Whether gemm1's contraction of `steps` k-steps, over n_cols column blocks, may be cut: few items at capacity, and a cut
 // that is still possible if every slot that probably holds rows does.  Most of the capacity is as a rule other ranks' (one
 // token, eight experts, one of them local, 36 slots of 7168 x 2048: FFN 70.9 -> 36.7 us; eight slots of 7168 x 256, 421 of 3200
 // rows local: 68.8 -> 45.2; all eight experts local: 127.1 / 125.4).  But with kSkinnyFullRows rows of capacity per slot nearly
@@ -655,13 +704,17 @@ static int skinny_max_tiles(int S, int max_rows) {
 constexpr int kSkinnyFullRows = 8;
 static bool skinny_may_split(int S, int max_rows, int n_cols, int steps) {  // if it holds, it holds for fewer rows too
   const long most = skinny_max_tiles(S, max_rows);
-  if (steps < kSkinnySplitSteps || most * n_cols > kSkinnyFewItems) return false;
+  if (steps < kSkinnySplitSteps1 || most * n_cols > kSkinnyFewItems) return false;
   const bool every_slot = max_rows >= static_cast<long>(kSkinnyFullRows) * S;
   return !every_slot || std::min<long>(most, S + (static_cast<long>(max_rows) + 511) / 512) * n_cols <= kSkinnyItems / 2;
 }
+// The same for gemm2.  An uncut call pays five integer divisions per item for it (see skinny_locate), no launch.
+static bool skinny_may_split2(int S, int max_rows, int n_cols, int steps) {
+  return steps >= kSkinnySplitSteps2 && static_cast<long>(skinny_max_tiles(S, max_rows)) * n_cols <= kSkinnyFewItems;
+}
 // k-steps per piece, for n_tiles row tiles of n_cols column blocks; steps: the whole contraction
-__device__ __forceinline__ int skinny_steps(int n_tiles, int n_cols, int steps) {
-  const int split = max(min(kSkinnyItems / max(n_tiles * n_cols, 1), steps / kSkinnyMinSteps), 1);
+__device__ __forceinline__ int skinny_steps(int n_tiles, int n_cols, int steps, int min_steps) {
+  const int split = max(min(kSkinnyItems / max(n_tiles * n_cols, 1), steps / min_steps), 1);
   return (steps + split - 1) / split;
 }
 
@@ -680,7 +733,7 @@ struct SkinnyTile {
 template <bool REDUCE>
 __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_offsets,
                                               const void* const* __restrict__ w_ptrs, int S, int item, int n_cols,
-                                              int steps, bool may_split, SkinnyTile& out) {
+                                              int steps, bool may_split, int min_steps, SkinnyTile& out) {
   const int all_rows = slot_offsets[S] - slot_offsets[0];
   __shared__ int32_t wave_tot[8];
   __shared__ int32_t found_row0, found_rows;
@@ -724,7 +777,7 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
   out.pieces = 1;
   out.col = out.piece = 0;
   if (may_split) {
-    out.piece_steps = skinny_steps(n_tiles, n_cols, steps);
+    out.piece_steps = skinny_steps(n_tiles, n_cols, steps, min_steps);
     out.pieces = (steps + out.piece_steps - 1) / out.piece_steps;
   }
   if (!REDUCE) {
@@ -784,12 +837,14 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w13_ptrs, int S,
                                                                   int H, int F, int may_split,
-                                                                  bf16_t* __restrict__ hbuf, float* partial) {
+                                                                  bf16_t* __restrict__ hbuf, float* partial,
+                                                                  uint32_t* __restrict__ arrivals) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
+  if (blockIdx.x == 0 && threadIdx.x < kArrivalWords) arrivals[threadIdx.x] = 0;  // for gemm2's launch
   SkinnyTile e;
   if (!skinny_locate<false>(slot_offsets, w13_ptrs, S, blockIdx.x, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
-                            may_split, e))
+                            may_split, kSkinnyMinSteps1, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
@@ -809,12 +864,13 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* 
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w2_ptrs, int S,
                                                                   int H, int F, int may_split,
-                                                                  bf16_t* __restrict__ y, float* partial) {
+                                                                  bf16_t* __restrict__ y, float* partial,
+                                                                  uint32_t* arrivals) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
   SkinnyTile e;
   if (!skinny_locate<false>(slot_offsets, w2_ptrs, S, blockIdx.x, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK,
-                            may_split, e))
+                            may_split, kSkinnyMinSteps2, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
@@ -822,28 +878,28 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* 
                         skinny_start(e, F));
   } else {
     const int k0 = e.piece * e.piece_steps * FBK;
-    gemm2_tile<1, 1, 3, false, true>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem, nullptr, nullptr, k0,
-                                     min(F - k0, e.piece_steps * FBK), skinny_partial(partial, e, e.piece, H),
-                                     skinny_start(e, min(F - k0, e.piece_steps * FBK)));
+    const int n_cols = (H + kSkinnyCols2 - 1) / kSkinnyCols2, klen = min(F - k0, e.piece_steps * FBK);
+    gemm2_tile<1, 1, 3, false, true>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem, nullptr, nullptr, k0, klen,
+                                     skinny_partial(partial, e, 0, H), skinny_start(e, klen), e.piece, e.pieces, arrivals,
+                                     e.tile * n_cols + e.col);
   }
 #endif
 }
 
-// The adding kernel: workgroup b adds the pieces of row b % 64 of tile b / 64, four columns per thread at a time.
-// SWIGLU: partial rows are [gate F | up F] and the result is h; otherwise [H] and the result is y.
-template <bool SWIGLU>
+// The adding kernel of gemm1: workgroup b adds the pieces of row b % 64 of tile b / 64, four columns per thread at a time.
+// Partial rows are [gate F | up F] and the result is h.
 __global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __restrict__ partial,
                                                              const int32_t* __restrict__ slot_offsets, int S,
-                                                             int n_cols, int steps, int out_cols,
-                                                             bf16_t* __restrict__ out) {
+                                                             int n_cols, int steps, int F,
+                                                             bf16_t* __restrict__ h) {
   SkinnyTile e;
   const int row = blockIdx.x & 63;
-  if (!skinny_locate<true>(slot_offsets, nullptr, S, blockIdx.x >> 6, n_cols, steps, true, e)) return;
+  if (!skinny_locate<true>(slot_offsets, nullptr, S, blockIdx.x >> 6, n_cols, steps, true, kSkinnyMinSteps1, e)) return;
   if (e.pieces == 1 || row >= e.rows) return;
-  const int ld = SWIGLU ? 2 * out_cols : out_cols;
+  const int ld = 2 * F;
   const float* base = partial + static_cast<size_t>(e.tile * e.pieces) * 64 * ld + static_cast<size_t>(row) * ld;
   const size_t piece = static_cast<size_t>(64) * ld;
-  for (int c = threadIdx.x * 4; c < out_cols; c += 512 * 4) {
+  for (int c = threadIdx.x * 4; c < F; c += 512 * 4) {
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
     constexpr int BATCH = 8;  // pieces whose loads are in flight together
     for (int p0 = 0; p0 < e.pieces; p0 += BATCH) {
@@ -852,20 +908,18 @@ __global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __rest
       for (int q = 0; q < BATCH; ++q) {
         const float* src = base + min(p0 + q, e.pieces - 1) * piece + c;
         va[q] = *reinterpret_cast<const f32x4*>(src);
-        if constexpr (SWIGLU) vb[q] = *reinterpret_cast<const f32x4*>(src + out_cols);
+        vb[q] = *reinterpret_cast<const f32x4*>(src + F);
       }
 #pragma unroll
       for (int q = 0; q < BATCH; ++q)
         if (p0 + q < e.pieces) {
           a += va[q];
-          if constexpr (SWIGLU) b += vb[q];
+          b += vb[q];
         }
     }
-    if constexpr (SWIGLU) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) a[j] = swiglu(a[j], b[j]);
-    }
-    *reinterpret_cast<u32x2*>(out + static_cast<size_t>(e.row0 + row) * out_cols + c) =
+    for (int j = 0; j < 4; ++j) a[j] = swiglu(a[j], b[j]);
+    *reinterpret_cast<u32x2*>(h + static_cast<size_t>(e.row0 + row) * F + c) =
         u32x2{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3])};
   }
 }
@@ -1018,26 +1072,24 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     const int n1 = (F + kSkinnyCols1 - 1) / kSkinnyCols1, n2 = (H + kSkinnyCols2 - 1) / kSkinnyCols2;
     const bool room = workspace_bytes >= sh.h_bytes + sh.table_bytes + sh.partial_bytes;
     const int split1 = room && skinny_may_split(S, max_rows, n1, H / FBK);
-    const int split2 = room && skinny_may_split(S, max_rows, n2, F / FBK);
+    const int split2 = room && skinny_may_split2(S, max_rows, n2, F / FBK);
+    uint32_t* arrivals = reinterpret_cast<uint32_t*>(table);
     // a split call has at most kSkinnyItems items, one that is not split tiles * n
     const dim3 g1(split1 ? std::max(tiles * n1, kSkinnyItems) : tiles * n1);
     const dim3 g2(split2 ? std::max(tiles * n2, kSkinnyItems) : tiles * n2);
     // tiles that can be split at all: two pieces or more need kSkinnyItems / 2 items or fewer
-    const int add1 = split1 ? std::min(tiles, kSkinnyItems / 2 / n1) : 0, add2 = split2 ? std::min(tiles, kSkinnyItems / 2 / n2) : 0;
+    const int add1 = split1 ? std::min(tiles, kSkinnyItems / 2 / n1) : 0;
     if (gather)
       hipLaunchKernelGGL(ffn_gemm1_skinny_kernel<true>, g1, dim3(512), kSkinnyLdsBytes, st, src, slot_offsets,
-                         w13_ptrs, S, H, F, split1, hbuf, partial);
+                         w13_ptrs, S, H, F, split1, hbuf, partial, arrivals);
     else
       hipLaunchKernelGGL(ffn_gemm1_skinny_kernel<false>, g1, dim3(512), kSkinnyLdsBytes, st, src, slot_offsets,
-                         w13_ptrs, S, H, F, split1, hbuf, partial);
+                         w13_ptrs, S, H, F, split1, hbuf, partial, arrivals);
     if (add1 > 0)
-      hipLaunchKernelGGL(ffn_skinny_add_kernel<true>, dim3(add1 * 64), dim3(512), 0, st, partial, slot_offsets, S, n1,
+      hipLaunchKernelGGL(ffn_skinny_add_kernel, dim3(add1 * 64), dim3(512), 0, st, partial, slot_offsets, S, n1,
                          H / FBK, F, hbuf);
     hipLaunchKernelGGL(ffn_gemm2_skinny_kernel, g2, dim3(512), kSkinnyLdsBytes, st, hbuf, slot_offsets, w2_ptrs, S, H,
-                       F, split2, y, partial);
-    if (add2 > 0)
-      hipLaunchKernelGGL(ffn_skinny_add_kernel<false>, dim3(add2 * 64), dim3(512), 0, st, partial, slot_offsets, S, n2,
-                         F / FBK, H, y);
+                       F, split2, y, partial, arrivals);
     return check_launch(name);
   }
   const int n1 = (F + 127) / 128, n2 = (H + FBN - 1) / FBN;

@@ -485,6 +485,36 @@ def test_ffn_few_tiles_gathered_on_load_and_in_a_graph(oracle, probe, G, sizes, 
         assert (y[n:] == 7.0).all()
 
 
+@pytest.mark.parametrize("sizes,H,F", [([1, 0, 0, 2], 4096, 1600), ([3], 4160, 3136), ([64, 65], 4096, 1600), ([0, 1], 320, 14336),
+                                       ([9, 0, 1, 30], 4224, 1472), ([75], 7168, 2048), ([1] * 8, 4096, 1536)])
+def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes, H, F):
+    """gemm2 in pieces that the last workgroup of an item adds: uneven pieces, one item and 128, full and nearly empty tiles, and one
+    call (1472: 23 k-steps) that is not cut.  Every element against the oracle; workspaces full of zeros, ones and noise and
+    repeated calls give the same bits."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=104)
+    print("case last adds", sizes, H, F, flush=True)
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 2, seed=H + F, extra_rows=0)
+    n, S = sum(sizes), len(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(F)
+    x = torch.randn((n, H), generator=gen, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
+         torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16))
+    tab = probe.WeightTable([w[0]] * S, [w[1]] * S)
+    so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
+    need = probe.grouped_ffn_workspace_bytes(S, H, F, n)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    ys = []
+    for fill in (0, 255, None, 127):
+        if fill is None:
+            ws.random_(0, 256, generator=gen)
+        else:
+            ws.fill_(fill)
+        for _ in range(3):
+            ys.append(probe.grouped_ffn(x, so, tab, workspace=ws))
+    torch.cuda.synchronize()
+    assert all(torch.equal(ys[0], y) for y in ys[1:])
+
+
 def test_ffn_contraction_is_not_cut_where_every_slot_can_hold_rows(oracle, probe, G):
     """At 40 rows of capacity per slot no adding kernel is launched although one slot alone holds rows: the call gives the
     same bits with and without room for partial sums.  Every element against the oracle."""
