@@ -13,7 +13,7 @@
 //               analytically                                             -> pair_row, row_pair
 //   3. scatter  one thread per 16-byte chunk of a token row: read x once, write it to each of
 //               the token's local rows                                   -> xp
-// Up to 16384 pairs the index kernel counts all blocks itself (no step 1), and up to 8192 it also copies the rows (no step 3); a
+// Up to 16384 pairs the index kernel counts all blocks itself (no step 1), and up to 4 MB of x it also copies the rows (no step 3); a
 // batch of more than 262144 pairs runs step 2 as a one-workgroup scan kernel followed by the ranking kernel.
 //
 // Steps 1-2 touch only T*k integers; step 3 carries the HBM traffic (T*H*2 bytes read at
@@ -35,10 +35,10 @@ constexpr int kRepLds = 2048;                 // replica-list entries staged in 
 // the call, histograms / own counts: 2 blocks (129 tokens, top-8 of 128) 6.3 / 4.7 us, 8 7.6 / 5.6, 16 7.7 / 6.5 (top-2 of 8: 7.8 /
 // 8.0), 24 7.9 / 7.8, 32 7.9 / 8.5, 64 8.1 / 12.6.
 constexpr int kSelfBlocks = 16;
-// Blocks up to which it also copies the rows, several workgroups to a block: 512 tokens x 4096, top-8 of 128 16.0 -> 6.9 us (9.4 with a
-// launch for the copy).  From 16 blocks on there would be too many workgroups that all count (8192 tokens x 512, top-2
-// of 8: 16.7 us, with its own launch 12).
-constexpr int kScatterBlocks = 8;
+// 16-byte pieces of x up to which it also copies the rows, several workgroups to a block: a piece per thread of one workgroup per
+// CU.  A launch for the copy / by the index kernel: 256 tokens x 4096, top-8 of 128 7.0 / 6.2 us, 512 7.8 / 6.9, 1024 x 1024 10.0 /
+// 8.8; but with more, where the workgroups that all count come in two rounds, 640 x 4096 8.5 / 9.6, 384 x 7168 7.2 / 8.8.
+constexpr long kScatterPieces = 256 * kIndexThreads;
 constexpr int kFusedBlocks = 256;             // up to this many blocks (262144 pairs) step 2 is one launch
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
@@ -568,9 +568,9 @@ static int permute_impl(const char* name, const int32_t* topk_idx, const probe_p
   u32x4* xp = static_cast<u32x4*>(xp_bf16);
   const long total = static_cast<long>(T) * cpr;
   // blocks of whole tokens only (at most 1024)
-  if (U >= 1 && U <= kScatterBlocks && xp != nullptr && (U == 1 || kIndexThreads % k == 0) && cpr < (1 << 21)) {
-    const long chunks = std::min<long>(T, kIndexThreads / k) * cpr;  // of a block
-    const unsigned shares = static_cast<unsigned>(std::min((chunks + kIndexThreads - 1) / kIndexThreads, std::max(512l / U, 1l)));
+  if (U >= 1 && U <= kSelfBlocks && xp != nullptr && (U == 1 || kIndexThreads % k == 0) && total <= kScatterPieces) {
+    const long pieces = std::min<long>(T, kIndexThreads / k) * cpr;  // of a block
+    const unsigned shares = static_cast<unsigned>((pieces + kIndexThreads - 1) / kIndexThreads);
     hipLaunchKernelGGL((permute_block_kernel<true, true>), dim3(shares, U), dim3(kIndexThreads), 0, st, topk_idx, N, E,
                        nullptr, U, plan->rep_off, plan->rep_slot, plan->rep_weight, S, out, x, k, cpr, xp);
     return check_launch(name);

@@ -83,10 +83,11 @@ def test_all_remote_and_zero_weight_replica(oracle, probe, G):
 
 @pytest.mark.parametrize("T,k,E,S,H", [(1, 1, 1, 1, 8), (1024, 1, 256, 64, 16), (1025, 1, 9, 65, 8), (341, 3, 130, 20, 24), (342, 3, 130, 20, 24),
                                        (1024, 8, 256, 1000, 72), (1025, 8, 33, 7, 8), (2048, 8, 64, 63, 8), (2049, 8, 64, 66, 8),
-                                       (4096, 4, 8, 12, 8), (1639, 5, 200, 30, 40), (32768, 8, 128, 24, 8), (40, 7, 12, 30, 4104)])
+                                       (4096, 4, 8, 12, 8), (1639, 5, 200, 30, 40), (32768, 8, 128, 24, 8), (40, 7, 12, 30, 4104),
+                                       (1024, 2, 16, 12, 2048), (1025, 2, 16, 12, 2048), (700, 1, 20, 12, 3000)])
 def test_permute_on_both_sides_of_every_block_count(oracle, probe, G, T, k, E, S, H):
     """1, 2, 8, 9, 16, 17 and 256 blocks of 1024 pairs, tokens that straddle blocks, replicas with equal, unequal and no weight, remote
-    experts, a replica list longer than the staged one, with and without the row copy: every output
+    experts, a replica list longer than the staged one, with the row copy (4 MB of x and a row more) and without: every output
     bit for bit the oracle's."""
     print("case permute T=%d k=%d E=%d S=%d" % (T, k, E, S), flush=True)
     rng = np.random.default_rng(T * k + E)
