@@ -9,7 +9,7 @@
 //
 //   1. split    w_gate -> planes[3][E][H] bf16 in the workspace (skipped by the *_packed entry points,
 //               which are handed planes made once by probe_pack_gate)
-//   2. gemm     split-K tiled GEMM (128 tokens x 128 experts x 64 k per step; small batches and gates of at most 16
+//   2. gemm     split-K tiled GEMM (128 or 256 tokens x 128 experts x 64 k per step; small batches and gates of at most 16
 //               experts go straight from global memory to the matrix cores), three MFMAs per
 //               operand pair (one per plane) into one accumulator  -> partial[KS][T][ld] fp32, ld = E
 //               rounded up to 4;
@@ -542,10 +542,6 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
   }
 }
 
-// Two tokens per row are in flight (U = 2) so that the dependent DPP chains of one overlap the
-// other's.  A chosen logit is overwritten with -inf; incoming logits are clamped to >= -FLT_MAX
-// (NaN too), so -inf only ever means "taken".  The weight of a winner is recomputed from its
-// logit with the same expression as its probability, so both agree bit for bit.
 // What a gate's top-k reads and writes.  `partial` points at the gate's first column; a row of a partial plane has ld entries.
 struct TopkGate {
   const float* partial;
@@ -558,6 +554,9 @@ struct TopkGate {
 };
 
 // gates: one, or two stacked ones (router and predictor of the fused call), number blockIdx.y
+// With U = 2 two tokens per row are in flight, so that the dependent DPP chains of one overlap the other's.  A chosen logit
+// is overwritten with -inf; incoming logits are clamped to >= -FLT_MAX (NaN too), so -inf only ever means "taken".  The
+// weight of a winner is recomputed from its logit with the same expression as its probability, so both agree bit for bit.
 template <int NV, int U, int R, int SG>
 __global__ __launch_bounds__(256) void gate_softmax_topk_kernel(TopkGate gate0, TopkGate gate1, int ld, int KS, int T,
                                                                 int E, int k, int renorm) {
