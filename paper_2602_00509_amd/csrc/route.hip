@@ -439,10 +439,11 @@ __device__ __forceinline__ bool aligned_f4(const float* p) { return (reinterpret
 // Logit row pieces of U tokens: the KS split-K slices are added in ascending order, then the bias row
 // of the token's group.  Lane `sub` receives the experts 64*i + 4*sub + j; entries past E hold anything (a whole piece of
 // four is read up to the rounded end of a row), the callers mask them.
-// What bounds it is the latency of the loads.  With one token per row the bias is loaded first, beside the sums (1000
-// tokens, 256 experts: top-k 9.6 against 9.9 us).  With two, the branches and the division in front of the first load cost
-// more than the wait behind the last: 99 tokens of a fused router and predictor, 256 experts: 18.2 us with the bias first,
-// 14.4 with it last; 3852 tokens, 128 experts 14.9 / 13.2.
+// What bounds it is the latency of the loads, so all of a round are issued before the first is waited for: no branch stands
+// between them (a slice past the last is read again and counts as zero; with its addition under a condition the compiler
+// moved the load there, one wait per slice) nor in front of the bias.  256 tokens x 1024 x 8 experts 5.83 -> 5.59 us, 128 x 4096 x
+// 128 11.05 -> 10.6, 8192 x 4096 x 128 37.6 -> 36.8, 16384 x 1024 x 256 group-limited 62.1 -> 59.8.  The bias is loaded beside the sums
+// with one token per row, behind them with two (first / last, 16384 tokens x 7168 x 256 144.0 / 140.5).
 // SG = 4: the four rows of a wave own the same token, row r adds the slices r, r + 4, ... and the four sums are added across
 // the rows, (0 + 1) + (2 + 3), so that all of them hold the same bits.
 template <int NV, int U, int R, int SG>
@@ -454,26 +455,29 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
   constexpr bool BIAS_FIRST = U == 1;
   if (vec) {
     float4 accv[U][NV], bv[U][NV];
-    auto load_bias = [&]() {
+    auto load_bias = [&]() {  // no branch that differs between lanes: pieces past the end read the last ones
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int g = bias ? min(tt[u] / tpg, G - 1) : 0;
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          const int e0 = 64 * i + 4 * sub;
-          bv[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (bias && e0 < E) {
-            const float* src = bias + static_cast<long>(g) * E + e0;
-            if ((E & 3) == 0) {
-              bv[u][i] = *reinterpret_cast<const float4*>(src);
-            } else {
-              bv[u][i].x = src[0];
-              bv[u][i].y = e0 + 1 < E ? src[1] : 0.f;
-              bv[u][i].z = e0 + 2 < E ? src[2] : 0.f;
-              bv[u][i].w = e0 + 3 < E ? src[3] : 0.f;
-            }
+        for (int i = 0; i < NV; ++i) bv[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (!bias) return;
+      const float* row[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) row[u] = bias + static_cast<long>(G > 1 ? min(tt[u] / tpg, G - 1) : 0) * E;
+      if ((E & 3) == 0) {  // whole 16-byte pieces: the bias is aligned, checked by the host
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int i = 0; i < NV; ++i) bv[u][i] = *reinterpret_cast<const float4*>(row[u] + min(64 * i + 4 * sub, E - 4));
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int i = 0; i < NV; ++i) {
+            const int e0 = 64 * i + 4 * sub;
+            bv[u][i] = make_float4(row[u][min(e0, E - 1)], row[u][min(e0 + 1, E - 1)], row[u][min(e0 + 2, E - 1)],
+                                   row[u][min(e0 + 3, E - 1)]);
           }
-        }
       }
     };
     if constexpr (BIAS_FIRST) load_bias();
@@ -496,16 +500,16 @@ __device__ __forceinline__ void load_logit_rows(const float* __restrict__ partia
           }
       }
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (q0 + r * SG + first < KS) {
+      for (int r = 0; r < R; ++r) {
+        const bool in = q0 + r * SG + first < KS;
 #pragma unroll
-          for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-              accv[u][i].x += tmp[r][u][i].x; accv[u][i].y += tmp[r][u][i].y;
-              accv[u][i].z += tmp[r][u][i].z; accv[u][i].w += tmp[r][u][i].w;
-            }
-        }
+          for (int i = 0; i < NV; ++i) {
+            accv[u][i].x += in ? tmp[r][u][i].x : 0.f; accv[u][i].y += in ? tmp[r][u][i].y : 0.f;
+            accv[u][i].z += in ? tmp[r][u][i].z : 0.f; accv[u][i].w += in ? tmp[r][u][i].w : 0.f;
+          }
+      }
     }
     if constexpr (!BIAS_FIRST) load_bias();
     if constexpr (SG == 4) {
@@ -1278,15 +1282,16 @@ static void launch_grouped_topk(hipStream_t st, const TopkGate& g, int ld, int K
   // one token per row and up to eight slices in flight while latency bounds the kernel; two tokens and two slices once there
   // are enough rows and instructions bound it, which at more than 128 experts they did not up to 40000 tokens.  Call
   // with one / two tokens per row: 4096 x 1024 x 64 experts 24.1 / 26.2 us, 8192 30.7 / 28.4, 16384 39.6 / 32.7; 8192 x
-  // 1024 x 128 33.1 / 34.1, 13421 43.1 / 36.4; 16384 x 1024 x 256 59.6 / 63.1.
+  // 1024 x 128 33.1 / 34.1, 13421 43.1 / 36.4; 16384 x 1024 x 256 59.6 / 63.1.  There the selection holds so many registers that
+  // only two slices are in flight (four: 8192 x 7168 x 256 85.6 -> 90.0, a wave per token 75 19.1 -> 19.6).
   if (wave_per_token(T, E, KS)) {
-    if (E <= 64) PROBE_GROUPED_LAUNCH(1, 1, 4, 4); else if (E <= 128) PROBE_GROUPED_LAUNCH(2, 1, 4, 4); else PROBE_GROUPED_LAUNCH(4, 1, 4, 4);
+    if (E <= 64) PROBE_GROUPED_LAUNCH(1, 1, 4, 4); else if (E <= 128) PROBE_GROUPED_LAUNCH(2, 1, 4, 4); else PROBE_GROUPED_LAUNCH(4, 1, 2, 4);
   } else if (E <= 64) {
     if (T > 6144) PROBE_GROUPED_LAUNCH(1, 2, 2, 1); else PROBE_GROUPED_LAUNCH(1, 1, 8, 1);
   } else if (E <= 128) {
     if (T > 8192) PROBE_GROUPED_LAUNCH(2, 2, 2, 1); else PROBE_GROUPED_LAUNCH(2, 1, 8, 1);
   } else {
-    PROBE_GROUPED_LAUNCH(4, 1, 4, 1);
+    PROBE_GROUPED_LAUNCH(4, 1, 2, 1);
   }
 #undef PROBE_GROUPED_LAUNCH
 }
