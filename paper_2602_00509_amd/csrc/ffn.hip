@@ -519,7 +519,7 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
                                            float* partial = nullptr, int k_start = 0, int piece = 0, int pieces = 1,
                                            uint32_t* arrivals = nullptr, int item = 0) {
   // SPLIT: only k0 .. k0 + klen - 1 of the contraction, piece `piece` of `pieces`.  The fp32 sums go to partial[piece][row of
-  // the tile][H], and the workgroup that counts as the last of its item adds them (see ffn_gemm2_skinny_kernel).
+  // the tile][H]; with `arrivals` the workgroup that counts as the last of its item adds them, otherwise ffn_skinny_add_kernel.
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wv / 4, wn = wv % 4;
@@ -538,7 +538,7 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
   __amdgpu_buffer_rsrc_t rY = make_rsrc(y + static_cast<size_t>(row0) * H, static_cast<size_t>(valid) * H * 2);
   const int row_in = 32 * MI * wm + (lane & 15);
   if constexpr (SPLIT) {
-    // Stores and loads at device scope (sc1): the pieces of an item run on different XCDs, whose L2s do not see one another.
+    // Stores and loads of the last workgroup's sums at device scope (sc1): the pieces of an item run on different XCDs, whose L2s do not see one another.
     constexpr int kDeviceScope = 16;
     const size_t piece_floats = static_cast<size_t>(64 * MI) * H;
     auto offset_of = [&](int i, int q) { return ((row_in + 16 * i) * H + n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4)) * 4; };
@@ -549,11 +549,17 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
 #pragma unroll
       for (int q = 0; q < NI; ++q) {
         if (in_range(q)) {
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q]), rP, offset_of(i, q), 0, kDeviceScope);
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q + 1]), rP, offset_of(i, q) + 16, 0, kDeviceScope);
+          if (arrivals) {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q]), rP, offset_of(i, q), 0, kDeviceScope);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q + 1]), rP, offset_of(i, q) + 16, 0, kDeviceScope);
+          } else {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q]), rP, offset_of(i, q), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q + 1]), rP, offset_of(i, q) + 16, 0, 0);
+          }
         }
       }
     }
+    if (!arrivals) return drew;
     // every wave's stores have arrived before the workgroup counts itself in: four items to a word, one byte each
     __shared__ int last;
     asm volatile("" ::: "memory");
@@ -671,18 +677,25 @@ constexpr int kSkinnyCols1 = 64, kSkinnyCols2 = 128;   // h columns / y columns 
 // Few tiles.  A call with one or two active slots (a single token; a shared expert) has fewer items than the chip has
 // CUs, and an item streams its weights no faster than about 50 GB/s.  The contraction is then cut into pieces, as many
 // as give every CU one item: each leaves its fp32 sums in the workspace, and they are added in ascending order.  The number
-// of tiles is known on the device only.  gemm1: a second kernel adds the pieces; the host decides whether the tiles can be few
-// (skinny_may_split) and then launches it, and it ends at once if nothing was split.  gemm2: the workgroup that counts as the
-// last of its item adds them, on counters that gemm1's launch clears, so nothing is launched for it and contractions of 24 k-steps
-// are worth cutting (one slot of 75 rows, 7168 x 2048: gemm2 18 us uncut; pieces of eight steps lose, two tokens of 4096 x 1536 26.5
-// / 27.1): the layer of one token 151.8 -> 149.2 us, 75 tokens with a shared expert 406.8 -> 403.2.
+// of tiles is known on the device only.  A second kernel adds the pieces; the host decides whether the tiles can be few
+// (skinny_may_split) and then launches it, and it ends at once if nothing was split.  Few pieces of few rows of gemm2 are added by the
+// workgroup that counts as the last of its item instead, on counters that gemm1's launch clears (skinny_adder2).
 // One token, two experts of 4096 x 14336: FFN 194 -> 137 us (gemm2 104 -> 41, adding 5); 512 items instead of 256: 141,
 // 1024: 161.  One slot of 75 rows, 7168 x 2048, which took the tall tiles before: 125 -> 43 us.
 constexpr int kSkinnyItems = 256;
-constexpr int kSkinnyMinSteps1 = 16, kSkinnyMinSteps2 = 12;  // k-steps of a piece at least
-// k-steps from which a contraction may be cut.  Shorter ones of gemm1 gain less over the adding kernel's launch (about 5 us), but
-// some still do: uncut / cut one slot of 16 rows, 3072 x 1536 28.3 / 24.1 us; two of 2880 x 2880 47.5 / 41.2, four 52.4 / 52.3.
-constexpr int kSkinnySplitSteps1 = 64, kSkinnySplitSteps2 = 2 * kSkinnyMinSteps2;
+constexpr int kSkinnyMinSteps = 16;      // k-steps of a piece at least
+// k-steps from which a contraction may be cut.  Shorter ones gain less over the adding kernel's launch (about 5 us), but some
+// still do: uncut / cut one slot of 16 rows, 3072 x 1536 28.3 / 24.1 us; two of 2880 x 2880 47.5 / 41.2, four 52.4 / 52.3.
+constexpr int kSkinnySplitSteps = 64;
+// The same where the last workgroup adds.  A cut of a contraction below 64 k-steps then costs about as much as ten to sixteen k-steps, more
+// with many items: uncut / cut 56 items of 32 k-steps (7168 x 2048, 16 rows) 29.8 / 29.4 us, 64 29.8 / 29.1, 112 33.5 / 35.3; 96 items of
+// 24 29.0 / 30.4, 32 of them 24.7 / 25.4; 64 items of 48 39.5, in three pieces 36.9, in four 37.8.
+constexpr int kSkinnyLastMinSteps = 13, kSkinnyLastSplitSteps = 32, kSkinnyShortItems = 192;
+// From 64 k-steps on, rows x pieces and pieces of an item that its last workgroup adds; above either the adding kernel, with as many
+// workgroups as rows, is faster: one token, two experts of 4096 x 14336 (eight pieces) 133 us by that kernel, 129 by the last; 60 rows
+// 81 / 85; 2048 x 8192, 64 rows, nine pieces 29.9 / 36.7, 2048 x 4096, 50 rows, five 27.0 / 27.9; 1024 x 16384, one row, 19 pieces 26.8
+// / 30.6.  Below, where that kernel's launch does not pay: 4096 x 3968, 64 rows, uncut 43.5, four or five pieces 38.9.
+constexpr int kSkinnyLastAdds = 192, kSkinnyLastPieces = 8;
 constexpr int kSkinnyFewItems = 512;     // items at capacity up to which tiles can be few
 constexpr size_t kSkinnyPartialBytes = static_cast<size_t>(kSkinnyItems) * 64 * 128 * sizeof(float);
 // Items that are cut number at most half of kSkinnyItems: a byte each counts the pieces that have arrived.  They lie in the tile table,
@@ -694,7 +707,7 @@ static_assert(kArrivalWords * sizeof(uint32_t) <= kTableHeaderInts * sizeof(int3
 static int skinny_max_tiles(int S, int max_rows) {
   return std::min<long>(max_rows, (static_cast<long>(max_rows) + 63l * S) / 64);
 }
-// Whether gemm1's contraction of `steps` k-steps, over n_cols column blocks, may be cut: few items at capacity, and a cut
+// Whether the contraction of `steps` k-steps, over n_cols column blocks, may be cut: few items at capacity, and a cut
 // that is still possible if every slot that probably holds rows does.  Most of the capacity is as a rule other ranks' (one
 // token, eight experts, one of them local, 36 slots of 7168 x 2048: FFN 70.9 -> 36.7 us; eight slots of 7168 x 256, 421 of 3200
 // rows local: 68.8 -> 45.2; all eight experts local: 127.1 / 125.4).  But with kSkinnyFullRows rows of capacity per slot nearly
@@ -704,18 +717,26 @@ static int skinny_max_tiles(int S, int max_rows) {
 constexpr int kSkinnyFullRows = 8;
 static bool skinny_may_split(int S, int max_rows, int n_cols, int steps) {  // if it holds, it holds for fewer rows too
   const long most = skinny_max_tiles(S, max_rows);
-  if (steps < kSkinnySplitSteps1 || most * n_cols > kSkinnyFewItems) return false;
+  if (steps < kSkinnySplitSteps || most * n_cols > kSkinnyFewItems) return false;
   const bool every_slot = max_rows >= static_cast<long>(kSkinnyFullRows) * S;
   return !every_slot || std::min<long>(most, S + (static_cast<long>(max_rows) + 511) / 512) * n_cols <= kSkinnyItems / 2;
 }
-// The same for gemm2.  An uncut call pays five integer divisions per item for it (see skinny_locate), no launch.
-static bool skinny_may_split2(int S, int max_rows, int n_cols, int steps) {
-  return steps >= kSkinnySplitSteps2 && static_cast<long>(skinny_max_tiles(S, max_rows)) * n_cols <= kSkinnyFewItems;
+// k-steps that a piece of gemm2 has at least if its pieces are added by the last workgroup of the item (kSkinnyLastMinSteps) or by
+// the adding kernel (kSkinnyMinSteps); 0: not cut.  An uncut call pays five integer divisions per item if it might be (see skinny_locate).
+static int skinny_piece_steps2(int S, int max_rows, int n_cols, int steps) {
+  if (steps >= kSkinnyLastSplitSteps && static_cast<long>(skinny_max_tiles(S, max_rows)) * n_cols <= kSkinnyFewItems) {
+    const int pieces = std::min(kSkinnyItems / n_cols, steps / kSkinnyLastMinSteps);
+    if (steps < kSkinnySplitSteps || (pieces <= kSkinnyLastPieces && pieces * std::min(max_rows, 64) <= kSkinnyLastAdds))
+      return kSkinnyLastMinSteps;
+  }
+  return skinny_may_split(S, max_rows, n_cols, steps) ? kSkinnyMinSteps : 0;
 }
-// k-steps per piece, for n_tiles row tiles of n_cols column blocks; steps: the whole contraction
-__device__ __forceinline__ int skinny_steps(int n_tiles, int n_cols, int steps, int min_steps) {
-  const int split = max(min(kSkinnyItems / max(n_tiles * n_cols, 1), steps / min_steps), 1);
-  return (steps + split - 1) / split;
+// k-steps per piece of a contraction of `steps`, `items` = row tiles x column blocks; 0 if it is not cut
+__device__ __forceinline__ int skinny_steps(int items, int steps, int min_steps) {
+  const int most = steps < kSkinnySplitSteps ? kSkinnyShortItems : kSkinnyItems;
+  if (2 * items > most || items <= 0) return 0;  // before any division
+  const int split = min(most / items, steps / min_steps);
+  return split > 1 ? (steps + split - 1) / split : 0;
 }
 
 // Item number -> (slot, first row, rows to the end of the slot, weight pointer, piece of K) without a tile table: slots
@@ -729,11 +750,12 @@ struct SkinnyTile {
   const void* w;
 };
 
-// REDUCE: `item` is a tile number (column and piece are not looked at)
+// REDUCE: `item` is a tile number (column and piece are not looked at).  min_steps: k-steps of a piece at least, 0 for a call that is
+// not cut
 template <bool REDUCE>
 __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_offsets,
                                               const void* const* __restrict__ w_ptrs, int S, int item, int n_cols,
-                                              int steps, bool may_split, int min_steps, SkinnyTile& out) {
+                                              int steps, int min_steps, SkinnyTile& out) {
   const int all_rows = slot_offsets[S] - slot_offsets[0];
   __shared__ int32_t wave_tot[8];
   __shared__ int32_t found_row0, found_rows;
@@ -776,14 +798,15 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
   out.piece_steps = steps;
   out.pieces = 1;
   out.col = out.piece = 0;
-  if (may_split) {
-    out.piece_steps = skinny_steps(n_tiles, n_cols, steps, min_steps);
-    out.pieces = (steps + out.piece_steps - 1) / out.piece_steps;
+  const int piece_steps = min_steps ? skinny_steps(n_tiles * n_cols, steps, min_steps) : 0;
+  if (piece_steps) {
+    out.piece_steps = piece_steps;
+    out.pieces = (steps + piece_steps - 1) / piece_steps;
   }
   if (!REDUCE) {
     tile = item / n_cols;
     out.col = item - tile * n_cols;
-    if (may_split) {
+    if (piece_steps) {
       const int q = tile;
       tile = q / out.pieces;
       out.piece = q - tile * out.pieces;
@@ -836,7 +859,7 @@ template <bool GATHER>
 __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w13_ptrs, int S,
-                                                                  int H, int F, int may_split,
+                                                                  int H, int F, int min_steps,
                                                                   bf16_t* __restrict__ hbuf, float* partial,
                                                                   uint32_t* __restrict__ arrivals) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -844,7 +867,7 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
   if (blockIdx.x == 0 && threadIdx.x < kArrivalWords) arrivals[threadIdx.x] = 0;  // for gemm2's launch
   SkinnyTile e;
   if (!skinny_locate<false>(slot_offsets, w13_ptrs, S, blockIdx.x, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
-                            may_split, kSkinnyMinSteps1, e))
+                            min_steps, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
@@ -863,14 +886,14 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
 __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* __restrict__ hbuf,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w2_ptrs, int S,
-                                                                  int H, int F, int may_split,
+                                                                  int H, int F, int min_steps,
                                                                   bf16_t* __restrict__ y, float* partial,
                                                                   uint32_t* arrivals) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
   SkinnyTile e;
   if (!skinny_locate<false>(slot_offsets, w2_ptrs, S, blockIdx.x, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK,
-                            may_split, kSkinnyMinSteps2, e))
+                            min_steps, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
@@ -886,20 +909,21 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* 
 #endif
 }
 
-// The adding kernel of gemm1: workgroup b adds the pieces of row b % 64 of tile b / 64, four columns per thread at a time.
-// Partial rows are [gate F | up F] and the result is h.
+// The adding kernel: workgroup b adds the pieces of row b % 64 of tile b / 64, four columns per thread at a time.
+// SWIGLU: partial rows are [gate F | up F] and the result is h; otherwise [H] and the result is y.
+template <bool SWIGLU>
 __global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __restrict__ partial,
                                                              const int32_t* __restrict__ slot_offsets, int S,
-                                                             int n_cols, int steps, int F,
-                                                             bf16_t* __restrict__ h) {
+                                                             int n_cols, int steps, int out_cols,
+                                                             bf16_t* __restrict__ out) {
   SkinnyTile e;
   const int row = blockIdx.x & 63;
-  if (!skinny_locate<true>(slot_offsets, nullptr, S, blockIdx.x >> 6, n_cols, steps, true, kSkinnyMinSteps1, e)) return;
+  if (!skinny_locate<true>(slot_offsets, nullptr, S, blockIdx.x >> 6, n_cols, steps, kSkinnyMinSteps, e)) return;
   if (e.pieces == 1 || row >= e.rows) return;
-  const int ld = 2 * F;
+  const int ld = SWIGLU ? 2 * out_cols : out_cols;
   const float* base = partial + static_cast<size_t>(e.tile * e.pieces) * 64 * ld + static_cast<size_t>(row) * ld;
   const size_t piece = static_cast<size_t>(64) * ld;
-  for (int c = threadIdx.x * 4; c < F; c += 512 * 4) {
+  for (int c = threadIdx.x * 4; c < out_cols; c += 512 * 4) {
     f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
     constexpr int BATCH = 8;  // pieces whose loads are in flight together
     for (int p0 = 0; p0 < e.pieces; p0 += BATCH) {
@@ -908,18 +932,20 @@ __global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __rest
       for (int q = 0; q < BATCH; ++q) {
         const float* src = base + min(p0 + q, e.pieces - 1) * piece + c;
         va[q] = *reinterpret_cast<const f32x4*>(src);
-        vb[q] = *reinterpret_cast<const f32x4*>(src + F);
+        if constexpr (SWIGLU) vb[q] = *reinterpret_cast<const f32x4*>(src + out_cols);
       }
 #pragma unroll
       for (int q = 0; q < BATCH; ++q)
         if (p0 + q < e.pieces) {
           a += va[q];
-          b += vb[q];
+          if constexpr (SWIGLU) b += vb[q];
         }
     }
+    if constexpr (SWIGLU) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) a[j] = swiglu(a[j], b[j]);
-    *reinterpret_cast<u32x2*>(h + static_cast<size_t>(e.row0 + row) * F + c) =
+      for (int j = 0; j < 4; ++j) a[j] = swiglu(a[j], b[j]);
+    }
+    *reinterpret_cast<u32x2*>(out + static_cast<size_t>(e.row0 + row) * out_cols + c) =
         u32x2{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3])};
   }
 }
@@ -1071,14 +1097,16 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     const int tiles = skinny_max_tiles(S, max_rows);
     const int n1 = (F + kSkinnyCols1 - 1) / kSkinnyCols1, n2 = (H + kSkinnyCols2 - 1) / kSkinnyCols2;
     const bool room = workspace_bytes >= sh.h_bytes + sh.table_bytes + sh.partial_bytes;
-    const int split1 = room && skinny_may_split(S, max_rows, n1, H / FBK);
-    const int split2 = room && skinny_may_split2(S, max_rows, n2, F / FBK);
+    const int split1 = room && skinny_may_split(S, max_rows, n1, H / FBK) ? kSkinnyMinSteps : 0;
+    const int split2 = room ? skinny_piece_steps2(S, max_rows, n2, F / FBK) : 0;
+    const bool last_adds = split2 == kSkinnyLastMinSteps;
     uint32_t* arrivals = reinterpret_cast<uint32_t*>(table);
     // a split call has at most kSkinnyItems items, one that is not split tiles * n
     const dim3 g1(split1 ? std::max(tiles * n1, kSkinnyItems) : tiles * n1);
     const dim3 g2(split2 ? std::max(tiles * n2, kSkinnyItems) : tiles * n2);
     // tiles that can be split at all: two pieces or more need kSkinnyItems / 2 items or fewer
     const int add1 = split1 ? std::min(tiles, kSkinnyItems / 2 / n1) : 0;
+    const int add2 = split2 && !last_adds ? std::min(tiles, kSkinnyItems / 2 / n2) : 0;
     if (gather)
       hipLaunchKernelGGL(ffn_gemm1_skinny_kernel<true>, g1, dim3(512), kSkinnyLdsBytes, st, src, slot_offsets,
                          w13_ptrs, S, H, F, split1, hbuf, partial, arrivals);
@@ -1086,10 +1114,13 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
       hipLaunchKernelGGL(ffn_gemm1_skinny_kernel<false>, g1, dim3(512), kSkinnyLdsBytes, st, src, slot_offsets,
                          w13_ptrs, S, H, F, split1, hbuf, partial, arrivals);
     if (add1 > 0)
-      hipLaunchKernelGGL(ffn_skinny_add_kernel, dim3(add1 * 64), dim3(512), 0, st, partial, slot_offsets, S, n1,
+      hipLaunchKernelGGL(ffn_skinny_add_kernel<true>, dim3(add1 * 64), dim3(512), 0, st, partial, slot_offsets, S, n1,
                          H / FBK, F, hbuf);
     hipLaunchKernelGGL(ffn_gemm2_skinny_kernel, g2, dim3(512), kSkinnyLdsBytes, st, hbuf, slot_offsets, w2_ptrs, S, H,
-                       F, split2, y, partial, arrivals);
+                       F, split2, y, partial, last_adds ? arrivals : nullptr);
+    if (add2 > 0)
+      hipLaunchKernelGGL(ffn_skinny_add_kernel<false>, dim3(add2 * 64), dim3(512), 0, st, partial, slot_offsets, S, n2,
+                         F / FBK, H, y);
     return check_launch(name);
   }
   const int n1 = (F + 127) / 128, n2 = (H + FBN - 1) / FBN;
