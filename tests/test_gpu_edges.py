@@ -487,59 +487,14 @@ def test_ffn_few_tiles_gathered_on_load_and_in_a_graph(oracle, probe, G, sizes, 
 
 
 @pytest.mark.parametrize("sizes,H,F", [([1, 0, 0, 2], 4096, 2112), ([3], 4160, 3136), ([64, 65], 4096, 2112), ([0, 1], 320, 14336),
-                                       ([2, 3], 2048, 4160), ([64], 1024, 4160), ([9, 0, 1, 30], 4224, 1984), ([75], 7168, 2048)])
+                                       ([2, 3], 2048, 4160), ([64], 1024, 4160), ([9, 0, 1, 30], 4224, 1984), ([75], 7168, 2048),
+                                       ([1, 0, 0, 2], 4096, 1600), ([64, 65], 4096, 1600), ([9, 0, 1, 30], 4224, 1472),
+                                       ([1] * 8, 4096, 1536)])
 def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes, H, F):
-    """gemm2 in pieces, added by the last workgroup of an item (33, 49 and 65 k-steps of few rows, full and nearly empty tiles) or by
-    the adding kernel (many pieces of one row, 64 rows), and calls that are not cut (31 k-steps, 112 items).  Every element
-    against the oracle; workspaces full of zeros, ones and noise and repeated calls give the same bits."""
-    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=104)
-    S, n, k = len(sizes), sum(sizes), 2
-    rng = np.random.default_rng(n + H)
-    so = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
-    T = n // 2 + 3
-    pairs = np.full(n + 5, -1, np.int32)
-    pairs[:n] = rng.permutation(T * k)[:n]
-    ws = wl.expert_weights_many(cfg, list(range(S)))
-    tab = probe.WeightTable([G.dev_bf16(w[0]) for w in ws], [G.dev_bf16(w[1]) for w in ws])
-    rows = lambda: wl.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32))
-    x = rows()
-    d_x, d_so, d_pairs = G.dev_bf16(x), torch.from_numpy(so).cuda(), torch.from_numpy(pairs).cuda()
-    y = torch.full((n + 5, H), 7.0, dtype=torch.bfloat16, device="cuda")
-    work = torch.empty(probe.grouped_ffn_workspace_bytes(S, H, F, n + 5), dtype=torch.uint8, device="cuda")
-    call = lambda out: probe.grouped_ffn_gather(d_x, d_pairs, k, d_so, tab, out=out, workspace=work)
-    print("case gather few tiles", sizes, H, F, flush=True)
-    side = torch.cuda.Stream()
-    side.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(side):
-        call(y)
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph, stream=side):
-            call(y)
-    torch.cuda.current_stream().wait_stream(side)
-    for replay in range(3):
-        if replay:
-            x = rows()
-            d_x.copy_(G.dev_bf16(x))
-        xp = np.zeros((n + 5, H), np.uint16)
-        xp[:n] = x[pairs[:n] // k]
-        copied = torch.full_like(y, 7.0)
-        probe.grouped_ffn(G.dev_bf16(xp), d_so, tab, out=copied)
-        y.fill_(7.0)
-        work.fill_(255)
-        graph.replay()
-        torch.cuda.synchronize()
-        assert torch.equal(y, copied), replay
-        ref = oracle.grouped_ffn(xp, so, [w[0] for w in ws], [w[1] for w in ws])
-        assert G.rel_err(G.f64_of(y)[:n], ref) < G.BF16_RTOL
-        assert (y[n:] == 7.0).all()
-
-
-@pytest.mark.parametrize("sizes,H,F", [([1, 0, 0, 2], 4096, 1600), ([3], 4160, 3136), ([64, 65], 4096, 1600), ([0, 1], 320, 14336),
-                                       ([9, 0, 1, 30], 4224, 1472), ([75], 7168, 2048), ([1] * 8, 4096, 1536)])
-def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes, H, F):
-    """gemm2 in pieces that the last workgroup of an item adds: uneven pieces, one item and 128, full and nearly empty tiles, and one
-    call (1472: 23 k-steps) that is not cut.  Every element against the oracle; workspaces full of zeros, ones and noise and
-    repeated calls give the same bits."""
+    """gemm2 in pieces: added by the last workgroup of an item (33, 49 and 65 k-steps in two, three and five pieces; three rows, two
+    full tiles and a third of one row, 96 items), by the adding kernel (fourteen pieces of one row, four of 64 rows), and calls whose
+    second contraction is not cut (31 k-steps and fewer, 112 items).  Every element against the oracle; workspaces full of zeros,
+    ones and noise and repeated calls give the same bits."""
     cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=104)
     print("case last adds", sizes, H, F, flush=True)
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, 2, seed=H + F, extra_rows=0)
