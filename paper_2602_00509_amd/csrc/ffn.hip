@@ -511,7 +511,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm1_kernel(RowSource src, const 
 }
 
 // ---- 2. gemm2 -------------------------------------------------------------------------
-template <int MI, int NI = 2, int NST = (MI >= 3 ? 2 : 3), bool DRAW = false, bool SPLIT = false>
+template <int MI, int NI = 2, int NST = (MI >= 3 ? 2 : 3), bool DRAW = false, bool SPLIT = false, bool LAST = false>
 __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, const bf16_t* __restrict__ w2,
                                            int row0, int rows, int n0, int H, int F,
                                            bf16_t* __restrict__ y, u32x4* smem, int32_t* draw_counter = nullptr,
@@ -519,7 +519,7 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
                                            float* partial = nullptr, int k_start = 0, int piece = 0, int pieces = 1,
                                            uint32_t* arrivals = nullptr, int item = 0) {
   // SPLIT: only k0 .. k0 + klen - 1 of the contraction, piece `piece` of `pieces`.  The fp32 sums go to partial[piece][row of
-  // the tile][H]; with `arrivals` the workgroup that counts as the last of its item adds them, otherwise ffn_skinny_add_kernel.
+  // the tile][H]; LAST: the workgroup that counts as the last of its item adds them, otherwise ffn_skinny_add_kernel does.
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wv / 4, wn = wv % 4;
@@ -539,7 +539,7 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
   const int row_in = 32 * MI * wm + (lane & 15);
   if constexpr (SPLIT) {
     // Stores and loads of the last workgroup's sums at device scope (sc1): the pieces of an item run on different XCDs, whose L2s do not see one another.
-    constexpr int kDeviceScope = 16;
+    constexpr int kDeviceScope = 16, kScope = LAST ? kDeviceScope : 0;
     const size_t piece_floats = static_cast<size_t>(64 * MI) * H;
     auto offset_of = [&](int i, int q) { return ((row_in + 16 * i) * H + n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4)) * 4; };
     auto in_range = [&](int q) { return n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4) < H; };
@@ -549,17 +549,12 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
 #pragma unroll
       for (int q = 0; q < NI; ++q) {
         if (in_range(q)) {
-          if (arrivals) {
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q]), rP, offset_of(i, q), 0, kDeviceScope);
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q + 1]), rP, offset_of(i, q) + 16, 0, kDeviceScope);
-          } else {
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q]), rP, offset_of(i, q), 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q + 1]), rP, offset_of(i, q) + 16, 0, 0);
-          }
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q]), rP, offset_of(i, q), 0, kScope);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][2 * q + 1]), rP, offset_of(i, q) + 16, 0, kScope);
         }
       }
     }
-    if (!arrivals) return drew;
+    if constexpr (!LAST) return drew;
     // every wave's stores have arrived before the workgroup counts itself in: four items to a word, one byte each
     __shared__ int last;
     asm volatile("" ::: "memory");
@@ -735,7 +730,7 @@ static int skinny_piece_steps2(int S, int max_rows, int n_cols, int steps) {
 __device__ __forceinline__ int skinny_steps(int items, int steps, int min_steps) {
   const int most = steps < kSkinnySplitSteps ? kSkinnyShortItems : kSkinnyItems;
   if (2 * items > most || items <= 0) return 0;  // before any division
-  const int split = min(most / items, steps / min_steps);
+  const int split = min(most / items, min_steps == kSkinnyMinSteps ? steps / kSkinnyMinSteps : steps / kSkinnyLastMinSteps);
   return split > 1 ? (steps + split - 1) / split : 0;
 }
 
@@ -864,7 +859,7 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
                                                                   uint32_t* __restrict__ arrivals) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
-  if (blockIdx.x == 0 && threadIdx.x < kArrivalWords) arrivals[threadIdx.x] = 0;  // for gemm2's launch
+  if (arrivals && blockIdx.x == 0 && threadIdx.x < kArrivalWords) arrivals[threadIdx.x] = 0;  // for gemm2's launch
   SkinnyTile e;
   if (!skinny_locate<false>(slot_offsets, w13_ptrs, S, blockIdx.x, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
                             min_steps, e))
@@ -883,6 +878,7 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
 #endif
 }
 
+template <bool LAST>
 __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* __restrict__ hbuf,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w2_ptrs, int S,
@@ -902,7 +898,7 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* 
   } else {
     const int k0 = e.piece * e.piece_steps * FBK;
     const int n_cols = (H + kSkinnyCols2 - 1) / kSkinnyCols2, klen = min(F - k0, e.piece_steps * FBK);
-    gemm2_tile<1, 1, 3, false, true>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem, nullptr, nullptr, k0, klen,
+    gemm2_tile<1, 1, 3, false, true, LAST>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem, nullptr, nullptr, k0, klen,
                                      skinny_partial(partial, e, 0, H), skinny_start(e, klen), e.piece, e.pieces, arrivals,
                                      e.tile * n_cols + e.col);
   }
@@ -1030,7 +1026,10 @@ static int ffn_prepare(int* cus) {
     err = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<true>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kSkinnyLdsBytes);
   if (err == hipSuccess)
-    err = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm2_skinny_kernel),
+    err = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm2_skinny_kernel<false>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kSkinnyLdsBytes);
+  if (err == hipSuccess)
+    err = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm2_skinny_kernel<true>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kSkinnyLdsBytes);
   if (err != hipSuccess) {
     set_error("probe_grouped_ffn: cannot reserve %d bytes of LDS: %s", kFfnLdsBytes, hipGetErrorString(err));
@@ -1100,7 +1099,7 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     const int split1 = room && skinny_may_split(S, max_rows, n1, H / FBK) ? kSkinnyMinSteps : 0;
     const int split2 = room ? skinny_piece_steps2(S, max_rows, n2, F / FBK) : 0;
     const bool last_adds = split2 == kSkinnyLastMinSteps;
-    uint32_t* arrivals = reinterpret_cast<uint32_t*>(table);
+    uint32_t* arrivals = last_adds ? reinterpret_cast<uint32_t*>(table) : nullptr;
     // a split call has at most kSkinnyItems items, one that is not split tiles * n
     const dim3 g1(split1 ? std::max(tiles * n1, kSkinnyItems) : tiles * n1);
     const dim3 g2(split2 ? std::max(tiles * n2, kSkinnyItems) : tiles * n2);
@@ -1116,8 +1115,8 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     if (add1 > 0)
       hipLaunchKernelGGL(ffn_skinny_add_kernel<true>, dim3(add1 * 64), dim3(512), 0, st, partial, slot_offsets, S, n1,
                          H / FBK, F, hbuf);
-    hipLaunchKernelGGL(ffn_gemm2_skinny_kernel, g2, dim3(512), kSkinnyLdsBytes, st, hbuf, slot_offsets, w2_ptrs, S, H,
-                       F, split2, y, partial, last_adds ? arrivals : nullptr);
+    hipLaunchKernelGGL(last_adds ? ffn_gemm2_skinny_kernel<true> : ffn_gemm2_skinny_kernel<false>, g2, dim3(512), kSkinnyLdsBytes,
+                       st, hbuf, slot_offsets, w2_ptrs, S, H, F, split2, y, partial, arrivals);
     if (add2 > 0)
       hipLaunchKernelGGL(ffn_skinny_add_kernel<false>, dim3(add2 * 64), dim3(512), 0, st, partial, slot_offsets, S, n2,
                          F / FBK, H, y);
