@@ -674,7 +674,7 @@ constexpr int kSkinnyCols1 = 64, kSkinnyCols2 = 128;   // h columns / y columns 
 // as give every CU one item: each leaves its fp32 sums in the workspace, and they are added in ascending order.  The number
 // of tiles is known on the device only.  A second kernel adds the pieces; the host decides whether the tiles can be few
 // (skinny_may_split) and then launches it, and it ends at once if nothing was split.  Few pieces of few rows of gemm2 are added by the
-// workgroup that counts as the last of its item instead, on counters that gemm1's launch clears (skinny_adder2).
+// workgroup that counts as the last of its item instead, on counters that gemm1's launch clears (skinny_last_adds).
 // One token, two experts of 4096 x 14336: FFN 194 -> 137 us (gemm2 104 -> 41, adding 5); 512 items instead of 256: 141,
 // 1024: 161.  One slot of 75 rows, 7168 x 2048, which took the tall tiles before: 125 -> 43 us.
 constexpr int kSkinnyItems = 256;
@@ -682,15 +682,15 @@ constexpr int kSkinnyMinSteps = 16;      // k-steps of a piece at least
 // k-steps from which a contraction may be cut.  Shorter ones gain less over the adding kernel's launch (about 5 us), but some
 // still do: uncut / cut one slot of 16 rows, 3072 x 1536 28.3 / 24.1 us; two of 2880 x 2880 47.5 / 41.2, four 52.4 / 52.3.
 constexpr int kSkinnySplitSteps = 64;
-// The same where the last workgroup adds.  A cut of a contraction below 64 k-steps then costs about as much as ten to sixteen k-steps, more
-// with many items: uncut / cut 56 items of 32 k-steps (7168 x 2048, 16 rows) 29.8 / 29.4 us, 64 29.8 / 29.1, 112 33.5 / 35.3; 96 items of
-// 24 29.0 / 30.4, 32 of them 24.7 / 25.4; 64 items of 48 39.5, in three pieces 36.9, in four 37.8.
-constexpr int kSkinnyLastMinSteps = 13, kSkinnyLastSplitSteps = 32, kSkinnyShortItems = 192;
-// From 64 k-steps on, rows x pieces and pieces of an item that its last workgroup adds; above either the adding kernel, with as many
-// workgroups as rows, is faster: one token, two experts of 4096 x 14336 (eight pieces) 133 us by that kernel, 129 by the last; 60 rows
-// 81 / 85; 2048 x 8192, 64 rows, nine pieces 29.9 / 36.7, 2048 x 4096, 50 rows, five 27.0 / 27.9; 1024 x 16384, one row, 19 pieces 26.8
-// / 30.6.  Below, where that kernel's launch does not pay: 4096 x 3968, 64 rows, uncut 43.5, four or five pieces 38.9.
-constexpr int kSkinnyLastAdds = 192, kSkinnyLastPieces = 8;
+// Where the last workgroup adds, pieces have 13 k-steps and more, and contractions of 32 to 63 are cut as well, into as many pieces as
+// give 192 items.  That costs about as much as ten to sixteen k-steps, and the sums of many rows more.  In a hot loop (weights in
+// the last-level cache; from HBM every cut below gains 3 to 16 us) uncut / cut: one slot of 64 rows of 2880 x 2880 (23 items of 45
+// k-steps) 33.2 / 30.6 us, two 34.4 / 33.8, three of 16 rows 33.5 / 31.8; 64 rows of 4096 x 3968 (32 of 62) 42.6 / 37.0; but full
+// tiles in 48 items of 56 k-steps 0.6 us slower, in 64 up to 2.8, in 92 (256 rows of 2880 x 2880) 41.9 / 44.3, in 96 (24 slots of 512 x
+// 2112) 38.6 / 43.9; 80 items of 32 k-steps and 16 rows 0.7 slower, 72 of one row level.
+constexpr int kSkinnyShortSteps = 32, kSkinnyLastMinSteps = 13, kSkinnyShortItems = 192;
+constexpr int kSkinnyShortCut = 72;    // items that are cut at most; their rows x column blocks: 32 per k-step
+constexpr int kSkinnyShortFull = 46;   // from 40 k-steps on: items that are cut whatever their rows
 constexpr int kSkinnyFewItems = 512;     // items at capacity up to which tiles can be few
 constexpr size_t kSkinnyPartialBytes = static_cast<size_t>(kSkinnyItems) * 64 * 128 * sizeof(float);
 // Items that are cut number at most half of kSkinnyItems: a byte each counts the pieces that have arrived.  They lie in the tile table,
@@ -716,21 +716,37 @@ static bool skinny_may_split(int S, int max_rows, int n_cols, int steps) {  // i
   const bool every_slot = max_rows >= static_cast<long>(kSkinnyFullRows) * S;
   return !every_slot || std::min<long>(most, S + (static_cast<long>(max_rows) + 511) / 512) * n_cols <= kSkinnyItems / 2;
 }
-// k-steps that a piece of gemm2 has at least if its pieces are added by the last workgroup of the item (kSkinnyLastMinSteps) or by
-// the adding kernel (kSkinnyMinSteps); 0: not cut.  An uncut call pays five integer divisions per item if it might be (see skinny_locate).
-static int skinny_piece_steps2(int S, int max_rows, int n_cols, int steps) {
-  if (steps >= kSkinnyLastSplitSteps && static_cast<long>(skinny_max_tiles(S, max_rows)) * n_cols <= kSkinnyFewItems) {
-    const int pieces = std::min(kSkinnyItems / n_cols, steps / kSkinnyLastMinSteps);
-    if (steps < kSkinnySplitSteps || (pieces <= kSkinnyLastPieces && pieces * std::min(max_rows, 64) <= kSkinnyLastAdds))
-      return kSkinnyLastMinSteps;
-  }
-  return skinny_may_split(S, max_rows, n_cols, steps) ? kSkinnyMinSteps : 0;
+// Whether gemm2's pieces are added by the last workgroup of an item and not by the adding kernel, which has a workgroup for every row.
+// From 64 k-steps on, call by that kernel / by the last, hot loop: two pieces 63.6 / 60.3 us (three slots of 4096 x 4096, a row in
+// each) and three 70 / 67 (two of 5120 x 4608) whatever the rows up to 32; four or five of a single tile 20.5 / 19.0 (one row of 1024 x
+// 4608), 25.1 / 24.0 (16 rows of 2048 x 4608), 32 rows level, 48 one us slower; three or four tiles of 2048 x 4096 are 0.5 to
+// 1 us slower and two 0.5 faster.  Six: up to eight rows 0.2 to 0.9 faster in one tile, 0.5 slower in two of 2048 x 5120.  Seven and
+// eight: two tiles of 4096 x 14336 (one token, two experts) 128.9 / 126.8, but a single one of 4096 x 8192 0.4 slower, of
+// 2048 x 8320 25.8 / 27.4.  16 pieces of one row of 1024 x 16384 25.8 / 29.8.
+static bool skinny_last_adds(int S, int max_rows, int n_cols, int steps) {
+  const long tiles = skinny_max_tiles(S, max_rows);
+  if (steps < kSkinnyShortSteps || tiles * n_cols > kSkinnyFewItems) return false;
+  if (steps < kSkinnySplitSteps) return true;
+  // row tiles, and rows of each, if every slot that probably holds rows does
+  const int likely = max_rows >= static_cast<long>(kSkinnyFullRows) * S ? S : 1, rows = max_rows / likely;
+  const int pieces = std::min(kSkinnyItems / (likely * n_cols), steps / kSkinnyLastMinSteps);
+  if (pieces > 8 || max_rows > 48) return false;
+  if (pieces <= 5) return rows <= 32;
+  if (tiles > 1 && n_cols >= 24) return rows <= 16;
+  return pieces == 6 ? rows <= 8 && (tiles == 1 || tiles * n_cols <= 16) : rows <= 4 && tiles * n_cols <= 8;
 }
-// k-steps per piece of a contraction of `steps`, `items` = row tiles x column blocks; 0 if it is not cut
-__device__ __forceinline__ int skinny_steps(int items, int steps, int min_steps) {
-  const int most = steps < kSkinnySplitSteps ? kSkinnyShortItems : kSkinnyItems;
-  if (2 * items > most || items <= 0) return 0;  // before any division
-  const int split = min(most / items, min_steps == kSkinnyMinSteps ? steps / kSkinnyMinSteps : steps / kSkinnyLastMinSteps);
+// k-steps per piece of a contraction of `steps`, `items` = row tiles x column blocks of `rows` rows; 0 if it is not cut.  LAST: the
+// last workgroup adds, and `steps` may be below kSkinnySplitSteps.
+template <bool LAST>
+__device__ __forceinline__ int skinny_steps(int items, int rows, int n_cols, int steps) {
+  if (items <= 0) return 0;
+  int most = kSkinnyItems;
+  if (LAST && steps < kSkinnySplitSteps) {
+    most = kSkinnyShortItems;
+    if (!(items <= kSkinnyShortCut && rows * n_cols <= kSkinnyShortSteps * steps) && !(items <= kSkinnyShortFull && steps >= 40)) return 0;
+  }
+  if (2 * items > most) return 0;  // before any division
+  const int split = min(most / items, steps / (LAST ? kSkinnyLastMinSteps : kSkinnyMinSteps));
   return split > 1 ? (steps + split - 1) / split : 0;
 }
 
@@ -745,12 +761,11 @@ struct SkinnyTile {
   const void* w;
 };
 
-// REDUCE: `item` is a tile number (column and piece are not looked at).  min_steps: k-steps of a piece at least, 0 for a call that is
-// not cut
-template <bool REDUCE>
+// REDUCE: `item` is a tile number (column and piece are not looked at)
+template <bool REDUCE, bool LAST>
 __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_offsets,
                                               const void* const* __restrict__ w_ptrs, int S, int item, int n_cols,
-                                              int steps, int min_steps, SkinnyTile& out) {
+                                              int steps, bool may_split, SkinnyTile& out) {
   const int all_rows = slot_offsets[S] - slot_offsets[0];
   __shared__ int32_t wave_tot[8];
   __shared__ int32_t found_row0, found_rows;
@@ -793,7 +808,7 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
   out.piece_steps = steps;
   out.pieces = 1;
   out.col = out.piece = 0;
-  const int piece_steps = min_steps ? skinny_steps(n_tiles * n_cols, steps, min_steps) : 0;
+  const int piece_steps = may_split ? skinny_steps<LAST>(n_tiles * n_cols, all_rows, n_cols, steps) : 0;
   if (piece_steps) {
     out.piece_steps = piece_steps;
     out.pieces = (steps + piece_steps - 1) / piece_steps;
@@ -854,15 +869,15 @@ template <bool GATHER>
 __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w13_ptrs, int S,
-                                                                  int H, int F, int min_steps,
+                                                                  int H, int F, int may_split,
                                                                   bf16_t* __restrict__ hbuf, float* partial,
                                                                   uint32_t* __restrict__ arrivals) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
   if (arrivals && blockIdx.x == 0 && threadIdx.x < kArrivalWords) arrivals[threadIdx.x] = 0;  // for gemm2's launch
   SkinnyTile e;
-  if (!skinny_locate<false>(slot_offsets, w13_ptrs, S, blockIdx.x, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
-                            min_steps, e))
+  if (!skinny_locate<false, false>(slot_offsets, w13_ptrs, S, blockIdx.x, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
+                            may_split, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
@@ -882,14 +897,14 @@ template <bool LAST>
 __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* __restrict__ hbuf,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w2_ptrs, int S,
-                                                                  int H, int F, int min_steps,
+                                                                  int H, int F, int may_split,
                                                                   bf16_t* __restrict__ y, float* partial,
                                                                   uint32_t* arrivals) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
   SkinnyTile e;
-  if (!skinny_locate<false>(slot_offsets, w2_ptrs, S, blockIdx.x, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK,
-                            min_steps, e))
+  if (!skinny_locate<false, LAST>(slot_offsets, w2_ptrs, S, blockIdx.x, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK,
+                            may_split, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
@@ -914,7 +929,7 @@ __global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __rest
                                                              bf16_t* __restrict__ out) {
   SkinnyTile e;
   const int row = blockIdx.x & 63;
-  if (!skinny_locate<true>(slot_offsets, nullptr, S, blockIdx.x >> 6, n_cols, steps, kSkinnyMinSteps, e)) return;
+  if (!skinny_locate<true, false>(slot_offsets, nullptr, S, blockIdx.x >> 6, n_cols, steps, true, e)) return;
   if (e.pieces == 1 || row >= e.rows) return;
   const int ld = SWIGLU ? 2 * out_cols : out_cols;
   const float* base = partial + static_cast<size_t>(e.tile * e.pieces) * 64 * ld + static_cast<size_t>(row) * ld;
@@ -1096,9 +1111,9 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     const int tiles = skinny_max_tiles(S, max_rows);
     const int n1 = (F + kSkinnyCols1 - 1) / kSkinnyCols1, n2 = (H + kSkinnyCols2 - 1) / kSkinnyCols2;
     const bool room = workspace_bytes >= sh.h_bytes + sh.table_bytes + sh.partial_bytes;
-    const int split1 = room && skinny_may_split(S, max_rows, n1, H / FBK) ? kSkinnyMinSteps : 0;
-    const int split2 = room ? skinny_piece_steps2(S, max_rows, n2, F / FBK) : 0;
-    const bool last_adds = split2 == kSkinnyLastMinSteps;
+    const bool split1 = room && skinny_may_split(S, max_rows, n1, H / FBK);
+    const bool last_adds = room && skinny_last_adds(S, max_rows, n2, F / FBK);
+    const bool split2 = last_adds || (room && skinny_may_split(S, max_rows, n2, F / FBK));
     uint32_t* arrivals = last_adds ? reinterpret_cast<uint32_t*>(table) : nullptr;
     // a split call has at most kSkinnyItems items, one that is not split tiles * n
     const dim3 g1(split1 ? std::max(tiles * n1, kSkinnyItems) : tiles * n1);

@@ -489,12 +489,16 @@ def test_ffn_few_tiles_gathered_on_load_and_in_a_graph(oracle, probe, G, sizes, 
 @pytest.mark.parametrize("sizes,H,F", [([1, 0, 0, 2], 4096, 2112), ([3], 4160, 3136), ([64, 65], 4096, 2112), ([0, 1], 320, 14336),
                                        ([2, 3], 2048, 4160), ([64], 1024, 4160), ([9, 0, 1, 30], 4224, 1984), ([75], 7168, 2048),
                                        ([1, 0, 0, 2], 4096, 1600), ([64, 65], 4096, 1600), ([9, 0, 1, 30], 4224, 1472),
-                                       ([1] * 8, 4096, 1536)])
+                                       ([1] * 8, 4096, 1536), ([32], 1024, 4160), ([1, 2], 4096, 8192),
+                                       ([1] * 9, 1024, 2560), ([1] * 10, 1024, 2560), ([64, 64], 2880, 2880), ([64] * 6, 1024, 2880),
+                                       ([30] * 6, 1024, 2880), ([31] * 6, 1024, 2880), ([64, 65], 1024, 2880), ([64], 2048, 2048),
+                                       ([64], 2176, 2048), ([64, 64], 2048, 2496), ([64, 64], 2048, 2560)])
 def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes, H, F):
-    """gemm2 in pieces: added by the last workgroup of an item (33, 49 and 65 k-steps in two, three and five pieces; three rows, two
-    full tiles and a third of one row, 96 items), by the adding kernel (fourteen pieces of one row, four of 64 rows), and calls whose
-    second contraction is not cut (31 k-steps and fewer, 112 items).  Every element against the oracle; workspaces full of zeros,
-    ones and noise and repeated calls give the same bits."""
+    """gemm2 in pieces that the last workgroup of an item adds (32 to 128 k-steps in two to five pieces; one row, full tiles; 72
+    items of one row and 46 of 64 rows, the most there are; 30 rows in each of 48 items, 64 rows in 16 items of 32 k-steps and in
+    32 of 40), in pieces that the adding kernel adds (fourteen of one row, four of 64 rows), and not cut (31 k-steps and fewer; 80
+    items of one row, 48 of 64 rows, 31 rows in each of 48 items, 64 rows in 17 items of 32 k-steps and in 32 of 39).  Every element
+    against the oracle; workspaces full of zeros, ones and noise and repeated calls give the same bits."""
     cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=104)
     print("case last adds", sizes, H, F, flush=True)
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, 2, seed=H + F, extra_rows=0)
@@ -505,7 +509,7 @@ def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes,
          torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16))
     tab = probe.WeightTable([w[0]] * S, [w[1]] * S)
     so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
-    need = probe.grouped_ffn_workspace_bytes(S, H, F, n)
+    need = probe.grouped_ffn_workspace_bytes(S, H, F, n) + (8 << 20)
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     ys = []
     for fill in (0, 255, None, 127):
