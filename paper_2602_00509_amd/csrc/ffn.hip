@@ -999,6 +999,7 @@ static size_t ffn_query_bytes(int S, int H, int F, int max_rows) {
   const int short_rows = static_cast<int>(std::min<long>(max_rows, static_cast<long>(kSkinnyRowsPerSlot) * S));
   bytes += std::max(ffn_shape(S, H, F, short_rows).table_bytes, ffn_shape(S, H, F, max_rows).table_bytes);
   if (max_rows > 0 && (skinny_may_split(S, 1, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK) ||
+                       skinny_last_adds(S, 1, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK) ||
                        skinny_may_split(S, 1, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK)))
     bytes += kSkinnyPartialBytes;
   return bytes;

@@ -509,7 +509,7 @@ def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes,
          torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16))
     tab = probe.WeightTable([w[0]] * S, [w[1]] * S)
     so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
-    need = probe.grouped_ffn_workspace_bytes(S, H, F, n) + (8 << 20)
+    need = probe.grouped_ffn_workspace_bytes(S, H, F, n)
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     ys = []
     for fill in (0, 255, None, 127):
@@ -583,11 +583,12 @@ def test_ffn_wide_and_narrow_column_blocks(oracle, probe, G, sizes, H, F):
     assert torch.equal(plain[:n], gathered[:n])
 
 
-def test_ffn_workspace_of_a_larger_call_serves_a_smaller_one(oracle, probe, G):
+@pytest.mark.parametrize("H,F,n", [(4096, 2048, 75), (2880, 2880, 40)])
+def test_ffn_workspace_of_a_larger_call_serves_a_smaller_one(oracle, probe, G, H, F, n):
     """A workspace sized for more rows serves fewer as their own does, bit for bit, also where only the smaller call keeps partial
-    sums in it (one slot: 1100 rows take the tall tiles, 75 rows the pieces of K); one without that room is accepted."""
-    cfg = wl.small_config(T=64, H=4096, E=4, k=2, F=2048, cid=101)
-    big, n = 1100, 75
+    sums in it (one slot: 1100 rows take the tall tiles, 75 and 40 rows the pieces of K); one without that room is accepted."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=101)
+    big = 1100
     own, larger = (probe.grouped_ffn_workspace_bytes(1, cfg.H, cfg.F, r) for r in (n, big))
     assert own <= larger
     w13, w2 = wl.expert_weights_many(cfg, [0])[0]
