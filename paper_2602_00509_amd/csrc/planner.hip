@@ -49,8 +49,8 @@ struct PlannerArgs {
 
 __device__ __forceinline__ long long comp_term(long long tokens, long long n0) { return tokens > 0 ? tokens + n0 : 0; }
 
-// LDS that the assignment may take; ner and pos (at most 24 KB) and the rest of the kernel's state come on top, and with 16 ranks,
-// where the assignment is largest, they are 13 KB.
+// LDS that the assignment may take; ner and pos (6 R E bytes) and the rest of the kernel's state (2 KB) come on top.  The most is 12
+// ranks of 240 experts: 139200 bytes of assignment and 17280 of ner and pos.
 constexpr int kPlanLdsBytes = 136 * 1024;
 // Words between the slabs of two experts.  In LDS one more than R * R, so that threads that look at the same entry of
 // neighbouring experts are on different banks.
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(256) void plan_greedy_kernel(const int32_t* __restr
 }
 
 // More than 64 KB of dynamic LDS has to be opted into once per device.
-constexpr int kPlanLdsMost = kPlanLdsBytes + 18 * 1024;  // 16 ranks, 135 experts: 156480 bytes
+constexpr int kPlanLdsMost = kPlanLdsBytes + 18 * 1024;  // 12 ranks, 240 experts: 156480 bytes
 static int plan_prepare() {
   static std::mutex mu;
   static bool done[64] = {false};

@@ -64,10 +64,11 @@ def test_planner_matches_oracle_bit_for_bit(oracle, probe, seed, R, E, E_loc, co
         assert o["n_moves"] >= 2          # the cases exercise the loop, not only its exit
 
 
-@pytest.mark.parametrize("R,E,E_loc", [(11, 256, 24), (12, 256, 22), (16, 135, 9), (16, 136, 9), (5, 250, 50)])
+@pytest.mark.parametrize("R,E,E_loc", [(11, 256, 24), (12, 256, 22), (16, 135, 9), (16, 136, 9), (5, 250, 50),
+                                          (12, 240, 20), (12, 241, 21)])
 def test_planner_on_both_sides_of_the_assignment_in_lds(oracle, probe, R, E, E_loc):
-    """The largest assignments that lie in LDS and the smallest that lie in the workspace; budgets that run out, so that
-    pairs become invalid between moves."""
+    """The largest assignments that lie in LDS (of all, 12 ranks of 240 experts take the most) and the smallest that lie in the
+    workspace; budgets that run out, so that pairs become invalid between moves."""
     print("case planner R=%d E=%d" % (R, E), flush=True)
     for seed, budget in ((11, 1), (12, 8)):
         o = _compare(probe, oracle, _random_nhat(seed, R, E, scale=3000, zipf=1.4), E_loc, ranks=[R - 1], max_replicas=budget,
