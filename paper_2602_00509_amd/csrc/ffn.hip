@@ -720,9 +720,9 @@ static bool skinny_may_split(int S, int max_rows, int n_cols, int steps) {  // i
 // From 64 k-steps on, call by that kernel / by the last, hot loop: two pieces 63.6 / 60.3 us (three slots of 4096 x 4096, a row in
 // each) and three 70 / 67 (two of 5120 x 4608) whatever the rows up to 32; four or five of a single tile 20.5 / 19.0 (one row of 1024 x
 // 4608), 25.1 / 24.0 (16 rows of 2048 x 4608), 32 rows level, 48 one us slower; three or four tiles of 2048 x 4096 are 0.5 to
-// 1 us slower and two 0.5 faster.  Six: up to eight rows 0.2 to 0.9 faster in one tile, 0.5 slower in two of 2048 x 5120.  Seven and
-// eight: two tiles of 4096 x 14336 (one token, two experts) 128.9 / 126.8, but a single one of 4096 x 8192 0.4 slower, of
-// 2048 x 8320 25.8 / 27.4.  16 pieces of one row of 1024 x 16384 25.8 / 29.8.
+// 1 us slower, two of 3072 x 5120 one, and two of 2048 x 4096 0.5 faster.  Six: up to eight rows 0.2 to 0.9 faster in one tile, 0.5
+// slower in two of 2048 x 5120.  Seven and eight: two tiles of 4096 x 14336 (one token, two experts) 128.9 / 126.8, but a single one
+// of 4096 x 8192 0.4 slower, of 2048 x 8320 25.8 / 27.4.  16 pieces of one row of 1024 x 16384 25.8 / 29.8.
 static bool skinny_last_adds(int S, int max_rows, int n_cols, int steps) {
   const long tiles = skinny_max_tiles(S, max_rows);
   if (steps < kSkinnyShortSteps || tiles * n_cols > kSkinnyFewItems) return false;
@@ -731,7 +731,8 @@ static bool skinny_last_adds(int S, int max_rows, int n_cols, int steps) {
   const int likely = max_rows >= static_cast<long>(kSkinnyFullRows) * S ? S : 1, rows = max_rows / likely;
   const int pieces = std::min(kSkinnyItems / (likely * n_cols), steps / kSkinnyLastMinSteps);
   if (pieces > 8 || max_rows > 48) return false;
-  if (pieces <= 5) return rows <= 32;
+  if (pieces <= 3) return rows <= 32;
+  if (pieces <= 5) return rows <= 32 && (likely == 1 || n_cols >= 32 || likely * n_cols <= 32);
   if (tiles > 1 && n_cols >= 24) return rows <= 16;
   return pieces == 6 ? rows <= 8 && (tiles == 1 || tiles * n_cols <= 16) : rows <= 4 && tiles * n_cols <= 8;
 }
