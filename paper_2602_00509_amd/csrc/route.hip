@@ -1059,9 +1059,9 @@ static int small_gate_frags(int T, int H, int E) {
 // workgroups (one to a CU, their LDS stages fill it) 1.2 with 128 tokens and 2.04 with 256, a slice 0.6 per MB written and
 // read, every eight slices of the top-k kernel's loads 1.  Over 46 batches of 200..16384 tokens x 64, 128, 256 experts the
 // choice is 0.3 % above the best of all heights and slices on average, 3.1 % at most.  Before, the slices were those that give every
-// CU one (256 tokens) or two workgroups (128), rounded up, and a last round of a few workgroups followed.  Packed router,
-// before / now: 2500 tokens x 4096 x 128 experts 28.9 / 23.5 us, 2048 x 7168 x 256 42.1 / 35.1, 5500 88.4 / 68.9, 12000
-// 153.0 / 130.2; both gates of 2500 x 4096 x 128 in one call 42.6 / 30.1.
+// CU one (256 tokens) or two workgroups (128), rounded up, and a last round of a few workgroups followed.  Packed router with the
+// same top-k, before / now: 2500 tokens x 4096 x 128 experts 28.2 / 22.6 us, 2048 x 7168 x 256 41.2 / 33.7, 5500 87.4 / 69.7, 12000
+// 149.6 / 118.7; both gates of 2500 x 4096 x 128 in one call 42.6 / 30.1.
 // Fewer slices are longer chains of additions: where a chain grows its sums are made by k-step, and their error against 64
 // bits falls (probabilities, 5500 x 7168 x 256: 7.5e-7 before, 2.8e-7; 2500 x 4096 x 128: 2.9e-7, 2.1e-7).  The 128-token tile
 // always does that; the 256-token tile loses 3 to 5 % by it and keeps to the accumulators where its chains stay as short.
