@@ -1142,12 +1142,14 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
   const int n1 = (F + 127) / 128, n2 = (H + FBN - 1) / FBN;
   hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(kScheduleThreads), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S,
                      sh.max_tiles, n1, n2, cus, table);
-  // persistent launch (one workgroup per CU, items drawn from the work queue) unless the capacity of the
-  // row space gives fewer items than that; where items may be narrow (the schedule decides), there are twice as many
-  const int cap1 = std::max(ffn_grid(sh.max_tiles, n1), ffn_grid(std::min(sh.max_tiles, kNarrowItems1 / n1), 2 * n1));
-  const int cap2 = std::max(ffn_grid(sh.max_tiles, n2), ffn_grid(std::min(sh.max_tiles, kNarrowItems2 / n2), 2 * n2));
+  // Persistent launch (one workgroup per CU, items drawn from the work queue) unless the capacity of the row space gives no more
+  // wide items than that.  Where items may be narrow (the schedule decides), such a launch has a workgroup for each of twice as many
+  // all the same: with about one item per CU the draws cost more than they even out (a workgroup ends after eight that fail).
+  const int cap1 = ffn_grid(sh.max_tiles, n1), cap2 = ffn_grid(sh.max_tiles, n2);
   const int q1 = cap1 > cus ? 1 : 0, q2 = cap2 > cus ? 1 : 0;
-  const dim3 grid1(q1 ? cus : cap1), grid2(q2 ? cus : cap2);
+  const int narrow1 = ffn_grid(std::min(sh.max_tiles, kNarrowItems1 / n1), 2 * n1);
+  const int narrow2 = ffn_grid(std::min(sh.max_tiles, kNarrowItems2 / n2), 2 * n2);
+  const dim3 grid1(q1 ? cus : std::max(cap1, narrow1)), grid2(q2 ? cus : std::max(cap2, narrow2));
   if (gather)
     hipLaunchKernelGGL(ffn_gemm1_kernel<true>, grid1, dim3(512), kFfnLdsBytes, st, src, table, table, q1, H, F, hbuf);
   else
