@@ -113,10 +113,38 @@ __device__ __forceinline__ SlotCut cut_slot(int m) {
 
 // Width of the items.  A call with few tiles leaves CUs without an item while each of the others streams 256 weight rows per
 // k-step; with column blocks half as wide (64 h columns, 128 y columns) there are twice as many items of half the weight rows.
-// Wide / narrow, gemm1: 9 tiles x 23 column blocks (500 tokens, top-4 of 128 experts, 2880 x 2880) 82 / 77 us, 17 x 12 (500
-// tokens, 4096 x 1536) 123 / 102, 15 x 12 103 / 86; but 11 x 23 82 / 86, 24 x 12 124 / 136.  gemm2: 7 x 12 67 / 48, 11 x 12 (768
-// tokens, 2880 x 2880) 73 / 54; but 17 x 12 89 / 94, 19 x 16 60 / 65.
 constexpr int kNarrowItems1 = 224, kNarrowItems2 = 160;  // wide items up to which the narrow ones are taken
+constexpr int kXcds = 8, kBlkM = 8, kBlkN = 4, kBlk = kBlkM * kBlkN;  // blocks of work items, see ffn_item_of
+
+// Whether that is faster, from an estimate of both launches.  An item lasts as long as the rows that it moves, activations and weights,
+// times the k-steps, and about as much as 1000 row steps (3 us) on top; wide items are one to a CU.  Narrow ones, in a single round (no
+// more than CUs; without the queue no more than a block of 32 to an XCD), as long as the tallest; in more, their mean load of a CU and a
+// part of the shortest.  With the queue there are the draws on top.  Wide / narrow: 31 tiles, 30 of them of 64 rows, 155 items of 94
+// k-steps 173 / 188 us, 12 of 128 and 192 rows, 132 of 19 75 / 82, but 13 tiles of 64 to 320 rows, 156 of 45 k-steps (gemm2 of 768 tokens,
+// 2880 x 2880) 73 / 54, 11 tiles of 320 rows, 22 columns, 88 k-steps without the queue 198 / 208.  Of 1075 GEMMs within the limits
+// above the number of items alone made 146 more than 1 % slower (up to 11 %), the estimate 12 (up to 4 %); the gains stay.
+constexpr float kNarrowItemCost = 1000.f;
+__device__ __forceinline__ bool narrow_items(int total, unsigned long long classes, int n_cols, int steps, int limit, int queue, int cus) {
+  if (static_cast<long>(total) * n_cols > limit) return false;
+  float sum = 0.f, tallest = 0.f, shortest = 0.f;  // narrow items of one column block
+#pragma unroll
+  for (int c = 0; c < 5; ++c) {
+    const int n = static_cast<int>(classes >> (12 * c)) & 4095, height = c == 0 ? 320 : 64 * (5 - c);
+    const float item = static_cast<float>(height + 128) * steps + kNarrowItemCost;
+    sum += n * item;
+    if (n) shortest = item;
+    if (n && tallest == 0.f) tallest = item;
+  }
+  const int items = 2 * total * n_cols, blocks = (total + kBlkM - 1) / kBlkM * ((2 * n_cols + kBlkN - 1) / kBlkN);
+  float narrow = tallest, draws = 2.f;
+  if (queue ? items > cus : blocks > kXcds) {
+    narrow = fmaxf(tallest, sum * (2 * n_cols) / cus + (queue ? 0.65f : 1.f) * shortest);
+    draws = queue ? 1.5f : 1.f;
+  } else if (!queue) {
+    draws = 0.f;
+  }
+  return narrow + draws * kNarrowItemCost < tallest + 128.f * steps;
+}
 
 // One slot, then one entry of the table per thread.  What bounds it is latency: two dependent rounds of loads and a chain of LDS
 // phases.  With four slots per thread of 256 and 64-bit divisions per entry 36 slots took 10.8 us and 64 slots 13.5.
@@ -126,7 +154,8 @@ static_assert(kScheduleThreads >= PROBE_MAX_SLOTS, "one slot per thread");
 __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const int32_t* __restrict__ slot_offsets,
                                                            const void* const* __restrict__ w13_ptrs,
                                                            const void* const* __restrict__ w2_ptrs,
-                                                           int S, int max_tiles, int n_cols1, int n_cols2, int cus,
+                                                           int S, int max_tiles, int n_cols1, int n_cols2, int steps1, int steps2,
+                                                           int queue1, int queue2, int cus,
                                                            int32_t* __restrict__ table) {
   __shared__ alignas(16) int32_t rows_of[PROBE_MAX_SLOTS];
   __shared__ int32_t first_of[PROBE_MAX_SLOTS];
@@ -202,7 +231,7 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
   const int total = min(start[S], max_tiles);
   // taller than 192 rows; beyond 4095 tiles the twelve-bit fields run into each other and are not looked at
   const int n_tall = static_cast<int>(class_start[S] & 4095) + static_cast<int>((class_start[S] >> 12) & 4095);
-  const bool narrow1 = static_cast<long>(total) * n_cols1 <= kNarrowItems1;
+  const bool narrow1 = narrow_items(total, class_start[S], n_cols1, steps1, kNarrowItems1, queue1, cus);
   const int cols1 = narrow1 ? 2 * n_cols1 : n_cols1;
   const bool tall_first = start[S] <= min(max_tiles, 4095) && n_tall * cols1 <= cus &&
                           static_cast<long>(start[S]) * cols1 > cus;
@@ -210,7 +239,7 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
     int v = 0;  // the queues' tickets
     if (tid == 0) v = total;
     if (tid == kNarrow1) v = narrow1;
-    if (tid == kNarrow2) v = static_cast<long>(total) * n_cols2 <= kNarrowItems2;
+    if (tid == kNarrow2) v = narrow_items(total, class_start[S], n_cols2, steps2, kNarrowItems2, queue2, cus);
     table[tid] = v;
   }
   TileEntry* entries = reinterpret_cast<TileEntry*>(table + kTableHeaderInts);
@@ -281,8 +310,6 @@ __device__ __forceinline__ void zero_acc(f32x4 (&acc)[2 * MI][2 * NI]) {
 // are numbered so that the 32 workgroups an XCD runs side by side form a compact 8 x 4 block
 // (8 consecutive row tiles x 4 consecutive column blocks): per k-step they pull 12 distinct
 // operand slices through that L2 instead of 18 for a 16 x 2 strip.
-constexpr int kXcds = 8, kBlkM = 8, kBlkN = 4, kBlk = kBlkM * kBlkN;
-
 __device__ __forceinline__ bool ffn_item_of(int q, int n_tiles, int n_cols, int& tile, int& col) {
   // item number q: blocks of 32 items; block blk = (tile group, column group), column groups fastest
   const int col_groups = (n_cols + kBlkN - 1) / kBlkN;
@@ -1140,8 +1167,6 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     return check_launch(name);
   }
   const int n1 = (F + 127) / 128, n2 = (H + FBN - 1) / FBN;
-  hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(kScheduleThreads), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S,
-                     sh.max_tiles, n1, n2, cus, table);
   // Persistent launch (one workgroup per CU, items drawn from the work queue) unless the capacity of the row space gives no more
   // wide items than that.  Where items may be narrow (the schedule decides), such a launch has a workgroup for each of twice as many
   // all the same: with about one item per CU the draws cost more than they even out (a workgroup ends after eight that fail).
@@ -1150,6 +1175,8 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
   const int narrow1 = ffn_grid(std::min(sh.max_tiles, kNarrowItems1 / n1), 2 * n1);
   const int narrow2 = ffn_grid(std::min(sh.max_tiles, kNarrowItems2 / n2), 2 * n2);
   const dim3 grid1(q1 ? cus : std::max(cap1, narrow1)), grid2(q2 ? cus : std::max(cap2, narrow2));
+  hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(kScheduleThreads), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S,
+                     sh.max_tiles, n1, n2, H / FBK, F / FBK, q1, q2, cus, table);
   if (gather)
     hipLaunchKernelGGL(ffn_gemm1_kernel<true>, grid1, dim3(512), kFfnLdsBytes, st, src, table, table, q1, H, F, hbuf);
   else

@@ -583,6 +583,34 @@ def test_ffn_wide_and_narrow_column_blocks(oracle, probe, G, sizes, H, F):
     assert torch.equal(plain[:n], gathered[:n])
 
 
+@pytest.mark.parametrize("sizes,H,F,capacities", [
+    ([320, 256] + [5] * 9, 2304, 1280, (1500, 2600)),     # narrow, more than eight blocks of items / one round from the queue
+    ([320, 300, 200] + [60] * 8, 1600, 1408, (1309, 2200)),
+    ([320] + [5] * 14, 3200, 1408, (1300, 2400)),         # narrow, two rounds from the queue
+    ([320, 320] + [1] * 6, 1728, 1216, (1550, 2650)),     # narrow, eight blocks / one round from the queue
+    ([64] * 20 + [320], 1088, 1152, (1609, 3000)),        # wide in gemm1, narrow in gemm2
+    ([100] * 26, 1216, 768, (2889,))])                    # wide: twice as many items would be a second round
+def test_ffn_column_blocks_by_estimated_time(oracle, probe, G, sizes, H, F, capacities):
+    """Tall tiles whose column blocks the schedule halves, or not, by an estimate of both launches, drawn from the work queue or
+    one workgroup per item, which the capacity decides: every output element against the oracle, and the same bits either way."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=105)
+    n = sum(sizes)
+    ys = []
+    for cap in capacities:
+        assert cap > 64 * len(sizes)                      # past the decode schedule
+        print("case estimated time", len(sizes), H, F, cap, flush=True)
+        _ffn_against_oracle(oracle, probe, G, cfg, sizes, 2, seed=H + F, extra_rows=cap - n)
+        gen = torch.Generator(device="cuda").manual_seed(H)
+        x = torch.zeros((cap, H), dtype=torch.bfloat16, device="cuda")
+        x[:n] = torch.randn((n, H), generator=gen, device="cuda").to(torch.bfloat16)
+        w = (torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
+             torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16))
+        so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
+        ys.append(probe.grouped_ffn(x, so, probe.WeightTable([w[0]] * len(sizes), [w[1]] * len(sizes)))[:n])
+        torch.cuda.synchronize()
+    assert all(torch.equal(ys[0], y) for y in ys[1:])
+
+
 @pytest.mark.parametrize("H,F,n", [(4096, 2048, 75), (2880, 2880, 40)])
 def test_ffn_workspace_of_a_larger_call_serves_a_smaller_one(oracle, probe, G, H, F, n):
     """A workspace sized for more rows serves fewer as their own does, bit for bit, also where only the smaller call keeps partial
