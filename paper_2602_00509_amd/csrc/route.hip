@@ -1236,11 +1236,12 @@ static unsigned topk_blocks(int T, int tokens) { return static_cast<unsigned>(st
 
 // A whole wave per token where tokens are few and slices many: its four rows load a quarter of the slices each, all of them at
 // once.  The selection is then made by all four rows, and there are four times as many workgroups to add their counts, so
-// with more tokens it loses.  Call with sixteen lanes / with a wave per token: one token of 7168 x 256 experts 12.6 / 10.5 us,
-// 75 16.5 / 14.4, 256 22.4 / 20.6, 512 24.7 / 24.5, 768 28.7 / 29.7; 4096 x 128 experts 75 11.2 / 10.1, 128 11.8 / 11.4, 512
-// 15.9 / 17.0; group-limited, 75 tokens of 7168 x 256 22.1 / 19.4.  Four slices and fewer are one round of loads either way.
+// with more tokens it loses, and with up to eight slices, which sixteen lanes have in flight at once, it loses at any.  Call with sixteen
+// lanes / with a wave per token: 4096 x 128 experts 64 tokens 10.1 / 9.4 us, 192 level, 256 12.0 / 12.55; 7168 x 256 64 14.9 / 12.6, 384
+// 22.6 / 21.8, 512 24.0 / 23.8; 2560 x 64 32 tokens 8.2 / 7.85, 128 level; but 1088 x 128 64 tokens 8.95 / 9.2, 256 10.4 / 11.45,
+// 640 x 256 256 tokens 13.7 / 14.1.  Group-limited, 75 tokens of 7168 x 256 22.1 / 19.4.
 // `own` counts the gate's own slices, not those of a residual behind them: a residual of zeros leaves every bit as it was.
-static bool wave_per_token(int T, int E, int own) { return own > 4 && T <= 128 * ((E + 63) / 64); }
+static bool wave_per_token(int T, int E, int own) { return own > 8 && T <= (E <= 128 ? 96 : 128) * ((E + 63) / 64); }
 
 // Softmax and top-k of one gate, or of two stacked ones in one launch: either alone is a few microseconds of latency.  Router and
 // predictor of 4096 x 128 experts, one call: 128 tokens 29.8 us in two launches of two tokens per row, 11.7 now; 1024 37.9 / 22.8,

@@ -182,7 +182,9 @@ def test_route_small_batches_and_small_gates(oracle, probe, G, T, H, E, k):
 
 @pytest.mark.parametrize("T,H,E,k", [(1, 1024, 60, 5), (128, 1024, 64, 4), (129, 1024, 64, 4), (255, 512, 90, 3), (256, 2048, 128, 8),
                                      (257, 2048, 128, 8), (512, 1024, 256, 8), (513, 1024, 256, 8), (66, 2048, 7, 2),
-                                     (2049, 1024, 128, 6), (3073, 1024, 64, 2), (6145, 512, 132, 4)])
+                                     (2049, 1024, 128, 6), (3073, 1024, 64, 2), (6145, 512, 132, 4), (96, 4096, 60, 4), (97, 4096, 60, 4),
+                                     (192, 4096, 126, 8), (193, 4096, 126, 8), (512, 2560, 250, 8), (513, 2560, 250, 8),
+                                     (512, 1728, 250, 8)])
 def test_route_topk_a_wave_or_sixteen_lanes_per_token(oracle, probe, G, T, H, E, k):
     """Both sides of the lines between a wave and sixteen lanes per token and between one and two tokens per row, alone and
     with two gates in one launch, one of them misaligned where E % 4 != 0; every token against the oracle."""

@@ -88,8 +88,12 @@ CASES = [
     (6145, 128, 60, 6, 4, 2, 2, "sigmoid", True, 1.0, True, True),      # from here two tokens per row, last row half full
     (6144, 128, 62, 4, 2, 1, 2, "softmax", False, 1.0, True, False),    # up to here one; E % 4 != 0
     (8193, 64, 128, 8, 8, 4, 2, "sigmoid", True, 2.5, False, True),
-    (512, 1024, 256, 8, 8, 4, 2, "sigmoid", True, 2.5, False, True),    # up to here a wave per token
+    (512, 1024, 256, 8, 8, 4, 2, "sigmoid", True, 2.5, False, True),
     (513, 1024, 256, 8, 8, 4, 2, "sigmoid", True, 2.5, False, True),
+    (512, 2560, 256, 8, 8, 4, 2, "sigmoid", True, 2.5, False, True),    # up to here a wave per token
+    (513, 2560, 256, 8, 8, 4, 2, "sigmoid", True, 2.5, False, True),
+    (192, 4096, 126, 8, 6, 3, 2, "sigmoid", True, 2.5, True, True),     # the same at 128 experts; E % 4 != 0
+    (193, 4096, 126, 8, 6, 3, 2, "sigmoid", True, 2.5, True, True),
     (128, 1024, 60, 6, 4, 2, 3, "softmax", True, 1.0, True, True),
     (257, 2048, 96, 4, 3, 2, 2, "softmax", False, 1.0, True, False),
 ]
