@@ -136,14 +136,14 @@ __device__ __forceinline__ bool narrow_items(int total, unsigned long long class
     if (n && tallest == 0.f) tallest = item;
   }
   const int items = 2 * total * n_cols, blocks = (total + kBlkM - 1) / kBlkM * ((2 * n_cols + kBlkN - 1) / kBlkN);
-  float narrow = tallest, draws = 2.f;
+  float narrow = tallest * cus, draws = 2.f;  // time x CUs
   if (queue ? items > cus : blocks > kXcds) {
-    narrow = fmaxf(tallest, sum * (2 * n_cols) / cus + (queue ? 0.65f : 1.f) * shortest);
+    narrow = fmaxf(narrow, sum * (2 * n_cols) + (queue ? 0.65f : 1.f) * shortest * cus);
     draws = queue ? 1.5f : 1.f;
   } else if (!queue) {
     draws = 0.f;
   }
-  return narrow + draws * kNarrowItemCost < tallest + 128.f * steps;
+  return narrow + draws * kNarrowItemCost * cus < (tallest + 128.f * steps) * cus;
 }
 
 // One slot, then one entry of the table per thread.  What bounds it is latency: two dependent rounds of loads and a chain of LDS
@@ -228,10 +228,16 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
     }
   }
   __syncthreads();
-  const int total = min(start[S], max_tiles);
+  // the same in all lanes: in scalar registers, so that what follows is branched over where it is not wanted
+  const int total = __builtin_amdgcn_readfirstlane(min(start[S], max_tiles));
+  const unsigned long long heights = class_start[S];
+  const unsigned long long all_classes =
+      static_cast<unsigned long long>(static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(heights >> 32)))) << 32 |
+      static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(heights)));
   // taller than 192 rows; beyond 4095 tiles the twelve-bit fields run into each other and are not looked at
-  const int n_tall = static_cast<int>(class_start[S] & 4095) + static_cast<int>((class_start[S] >> 12) & 4095);
-  const bool narrow1 = narrow_items(total, class_start[S], n_cols1, steps1, kNarrowItems1, queue1, cus);
+  const int n_tall = static_cast<int>(all_classes & 4095) + static_cast<int>((all_classes >> 12) & 4095);
+  const bool narrow1 = narrow_items(total, all_classes, n_cols1, steps1, kNarrowItems1, queue1, cus);
+  const bool narrow2 = narrow_items(total, all_classes, n_cols2, steps2, kNarrowItems2, queue2, cus);
   const int cols1 = narrow1 ? 2 * n_cols1 : n_cols1;
   const bool tall_first = start[S] <= min(max_tiles, 4095) && n_tall * cols1 <= cus &&
                           static_cast<long>(start[S]) * cols1 > cus;
@@ -239,7 +245,7 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
     int v = 0;  // the queues' tickets
     if (tid == 0) v = total;
     if (tid == kNarrow1) v = narrow1;
-    if (tid == kNarrow2) v = narrow_items(total, class_start[S], n_cols2, steps2, kNarrowItems2, queue2, cus);
+    if (tid == kNarrow2) v = narrow2;
     table[tid] = v;
   }
   TileEntry* entries = reinterpret_cast<TileEntry*>(table + kTableHeaderInts);
