@@ -562,12 +562,13 @@ def test_ffn_tall_tiles_first_every_element(oracle, probe, G, sizes):
 @pytest.mark.parametrize("sizes,H,F", [
     ([320, 256, 192, 128, 64, 37, 0, 321] * 4, 1344, 960),    # every height, wide column blocks, partial last ones
     ([320, 256, 192, 128, 64, 37, 0, 321], 1088, 1344),       # every height, narrow column blocks, partial last ones
-    ([100] * 14, 2432, 2048), ([100] * 15, 2560, 2048),       # 224 and 240 wide items of gemm1
-    ([130] * 16, 2560, 192), ([130] * 17, 2560, 192),         # 160 and 170 of gemm2
-    ([70, 0, 300], 64, 14400)])                               # one k-step; more column blocks than tiles
+    ([100] * 14, 2432, 2048), ([100] * 15, 2560, 2048),       # wide: uniform tiles, 224 and 240 wide items of gemm1
+    ([130] * 16, 2560, 768), ([130] * 17, 2560, 768),         # 96 and 102 of gemm1 (narrow / wide), 160 and 170 of gemm2 (wide)
+    ([130] * 16, 2560, 192), ([130] * 17, 2560, 192),         # the decode schedule with three tiles to a slot
+    ([70, 0, 300], 64, 14400)])                               # one k-step; more column blocks than tiles, 226 / 2 wide items
 def test_ffn_wide_and_narrow_column_blocks(oracle, probe, G, sizes, H, F):
-    """Tall tiles on both sides of the lines where the schedule halves the column blocks: every output element against the
-    oracle, and the rows gathered on load bit for bit the same."""
+    """Wide and narrow column blocks of either GEMM, and numbers of items at the limits of the narrow ones: every output element
+    against the oracle, and the rows gathered on load bit for bit the same."""
     cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=103)
     print("case narrow", len(sizes), H, F, flush=True)
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F)
@@ -590,6 +591,7 @@ def test_ffn_wide_and_narrow_column_blocks(oracle, probe, G, sizes, H, F):
     ([320, 300, 200] + [60] * 8, 1600, 1408, (1309, 2200)),
     ([320] + [5] * 14, 3200, 1408, (1300, 2400)),         # narrow, two rounds from the queue
     ([320, 320] + [1] * 6, 1728, 1216, (1550, 2650)),     # narrow, eight blocks / one round from the queue
+    ([320, 130] + [20] * 13, 2560, 1472, (2710,)),        # narrow, two rounds of both from the queue
     ([64] * 20 + [320], 1088, 1152, (1609, 3000)),        # wide in gemm1, narrow in gemm2
     ([100] * 26, 1216, 768, (2889,))])                    # wide: twice as many items would be a second round
 def test_ffn_column_blocks_by_estimated_time(oracle, probe, G, sizes, H, F, capacities):
