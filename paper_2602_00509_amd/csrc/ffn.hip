@@ -76,7 +76,7 @@ struct alignas(16) TileEntry {
 };
 static_assert(sizeof(TileEntry) == 32, "one 32-byte record per tile");
 // Table header, 128 bytes: word 0 = number of tiles; words 1 and 2 = whether gemm1 and gemm2 take narrow column blocks; words 8..15
-// and 16..23 = the work-queue tickets of gemm1 and gemm2 (one counter per XCD), cleared by the schedule kernel of the same call.
+// and 16..23 = the work-queue tickets of gemm1 and gemm2 (one counter per XCD), set by the schedule kernel of the same call.
 constexpr int kTableHeaderInts = 32, kNarrow1 = 1, kNarrow2 = 2, kQueue1 = 8, kQueue2 = 16;
 
 struct SlotCut {
@@ -118,13 +118,12 @@ constexpr int kXcds = 8, kBlkM = 8, kBlkN = 4, kBlk = kBlkM * kBlkN;  // blocks 
 
 // Whether that is faster, from an estimate of both launches.  An item lasts as long as the rows that it moves, activations and weights,
 // times the k-steps, and about as much as 1000 row steps (3 us) on top; wide items are one to a CU.  Narrow ones, in a single round (no
-// more than CUs; without the queue no more than a block of 32 to an XCD), as long as the tallest; in more, their mean load of a CU and a
-// part of the shortest.  With the queue there are the draws on top.  Wide / narrow: 31 tiles, 30 of them of 64 rows, 155 items of 94
+// more than CUs), take as long as the tallest; in more, their mean load of a CU and a part of the shortest, and the draws.  Wide / narrow: 31 tiles, 30 of them of 64 rows, 155 items of 94
 // k-steps 173 / 188 us, 12 of 128 and 192 rows, 132 of 19 75 / 82, but 13 tiles of 64 to 320 rows, 156 of 45 k-steps (gemm2 of 768 tokens,
-// 2880 x 2880) 73 / 54, 11 tiles of 320 rows, 22 columns, 88 k-steps without the queue 198 / 208.  Of 1075 GEMMs within the limits
+// 2880 x 2880) 73 / 54.  Of 1075 GEMMs within the limits
 // above the number of items alone made 146 more than 1 % slower (up to 11 %), the estimate 12 (up to 4 %); the gains stay.
 constexpr float kNarrowItemCost = 1000.f;
-__device__ __forceinline__ bool narrow_items(int total, unsigned long long classes, int n_cols, int steps, int limit, int queue, int cus) {
+__device__ __forceinline__ bool narrow_items(int total, unsigned long long classes, int n_cols, int steps, int limit, int cus) {
   if (static_cast<long>(total) * n_cols > limit) return false;
   float sum = 0.f, tallest = 0.f, shortest = 0.f;  // narrow items of one column block
 #pragma unroll
@@ -135,15 +134,10 @@ __device__ __forceinline__ bool narrow_items(int total, unsigned long long class
     if (n) shortest = item;
     if (n && tallest == 0.f) tallest = item;
   }
-  const int items = 2 * total * n_cols, blocks = (total + kBlkM - 1) / kBlkM * ((2 * n_cols + kBlkN - 1) / kBlkN);
-  float narrow = tallest * cus, draws = 2.f;  // time x CUs
-  if (queue ? items > cus : blocks > kXcds) {
-    narrow = fmaxf(narrow, sum * (2 * n_cols) + (queue ? 0.65f : 1.f) * shortest * cus);
-    draws = queue ? 1.5f : 1.f;
-  } else if (!queue) {
-    draws = 0.f;
-  }
-  return narrow + draws * kNarrowItemCost * cus < (tallest + 128.f * steps) * cus;
+  const int items = 2 * total * n_cols;
+  float narrow = tallest * cus;  // time x CUs
+  if (items > cus) narrow = fmaxf(narrow, sum * (2 * n_cols) + 0.65f * shortest * cus) + 1.5f * kNarrowItemCost * cus;
+  return narrow < (tallest + 128.f * steps) * cus;
 }
 
 // One slot, then one entry of the table per thread.  What bounds it is latency: two dependent rounds of loads and a chain of LDS
@@ -155,7 +149,7 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
                                                            const void* const* __restrict__ w13_ptrs,
                                                            const void* const* __restrict__ w2_ptrs,
                                                            int S, int max_tiles, int n_cols1, int n_cols2, int steps1, int steps2,
-                                                           int queue1, int queue2, int cus,
+                                                           int cus,
                                                            int32_t* __restrict__ table) {
   __shared__ alignas(16) int32_t rows_of[PROBE_MAX_SLOTS];
   __shared__ int32_t first_of[PROBE_MAX_SLOTS];
@@ -236,13 +230,14 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
       static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(heights)));
   // taller than 192 rows; beyond 4095 tiles the twelve-bit fields run into each other and are not looked at
   const int n_tall = static_cast<int>(all_classes & 4095) + static_cast<int>((all_classes >> 12) & 4095);
-  const bool narrow1 = narrow_items(total, all_classes, n_cols1, steps1, kNarrowItems1, queue1, cus);
-  const bool narrow2 = narrow_items(total, all_classes, n_cols2, steps2, kNarrowItems2, queue2, cus);
+  const bool narrow1 = narrow_items(total, all_classes, n_cols1, steps1, kNarrowItems1, cus);
+  const bool narrow2 = narrow_items(total, all_classes, n_cols2, steps2, kNarrowItems2, cus);
   const int cols1 = narrow1 ? 2 * n_cols1 : n_cols1;
   const bool tall_first = start[S] <= min(max_tiles, 4095) && n_tall * cols1 <= cus &&
                           static_cast<long>(start[S]) * cols1 > cus;
   if (tid < kTableHeaderInts) {
-    int v = 0;  // the queues' tickets
+    // the queues' tickets: the first ones go without a draw, to the workgroups in order
+    int v = tid >= kQueue1 && tid < kQueue2 + kXcds ? (cus + kXcds - 1 - tid % kXcds) / kXcds : 0;
     if (tid == 0) v = total;
     if (tid == kNarrow1) v = narrow1;
     if (tid == kNarrow2) v = narrow2;
@@ -315,77 +310,90 @@ __device__ __forceinline__ void zero_acc(f32x4 (&acc)[2 * MI][2 * NI]) {
 // L2.  The launch is one-dimensional; workgroup L is the (L / 8)-th of XCD L % 8.  Work items
 // are numbered so that the 32 workgroups an XCD runs side by side form a compact 8 x 4 block
 // (8 consecutive row tiles x 4 consecutive column blocks): per k-step they pull 12 distinct
-// operand slices through that L2 instead of 18 for a 16 x 2 strip.
+// operand slices through that L2 instead of 18 for a 16 x 2 strip.  Blocks at the edges are smaller and
+// no number is left out: with 384 numbers for the 230 items of 10 tiles x 23 columns every third draw of the
+// queue named none.
 __device__ __forceinline__ bool ffn_item_of(int q, int n_tiles, int n_cols, int& tile, int& col) {
-  // item number q: blocks of 32 items; block blk = (tile group, column group), column groups fastest
-  const int col_groups = (n_cols + kBlkN - 1) / kBlkN;
-  const int blk = q / kBlk, w = q % kBlk;
-  const int tg = blk / col_groups, cg = blk % col_groups;
-  tile = tg * kBlkM + w / kBlkN;
-  col = cg * kBlkN + w % kBlkN;
-  return tile < n_tiles && col < n_cols;
+  if (q >= n_tiles * n_cols) return false;
+  // tile groups slowest, then the column groups of a tile group, then the tiles of a block
+  const int tg = q / (kBlkM * n_cols), in_group = q - tg * kBlkM * n_cols;
+  const int rows = min(kBlkM, n_tiles - tg * kBlkM);  // tiles of the group
+  const int cg = in_group / (rows * kBlkN), in_block = in_group - cg * rows * kBlkN;
+  const int width = min(kBlkN, n_cols - cg * kBlkN);
+  const int t = in_block / width;
+  tile = tg * kBlkM + t;
+  col = cg * kBlkN + in_block - t * width;
+  return true;
 }
 
-__device__ __forceinline__ bool ffn_work_item(int n_tiles, int n_cols, int& tile, int& col) {
-  const int L = blockIdx.x;
-  const int xcd = L % kXcds, j = L / kXcds;
-  const int q = ((j / kBlk) * kXcds + xcd) * kBlk + (j % kBlk);  // item number: blocks of 32 per XCD
-  return ffn_item_of(q, n_tiles, n_cols, tile, col);
+// Item number of ticket t of XCD x: chunks of 32 items are dealt to the XCDs round-robin; fewer items than that makes for all
+// eight are dealt in eight even chunks.
+__device__ __forceinline__ int ffn_item_number(int t, int x, int n_items) {
+  if (n_items > kXcds * kBlk) return ((t / kBlk) * kXcds + x) * kBlk + t % kBlk;
+  const int chunk = (n_items + kXcds - 1) / kXcds;
+  return t < chunk ? x * chunk + t : n_items;
 }
 
-// Work queue of the persistent launch (one workgroup per CU).  Blocks of 32 items are dealt to the XCDs
-// round-robin as above (block b belongs to XCD b % 8), but which workgroup runs which item is decided at
-// run time: a workgroup draws tickets from the counter of the XCD it runs on (ticket t = item t % 32 of
-// that XCD's (t / 32)-th block), so the 32 workgroups of an XCD still walk one block side by side; when
-// its own XCD's blocks are used up it draws from the next XCD's counter, and so on round the ring, until
-// all eight are exhausted.  Counters only grow and nobody waits for anybody, so every workgroup ends after
-// at most 8 unsuccessful draws.  Returns false when no work is left.
+// Work queue of the persistent launch (one workgroup per CU).  Chunks of 32 items are dealt to the XCDs
+// round-robin as above (chunk b belongs to XCD b % 8), but which workgroup runs which item is decided at
+// run time: a workgroup draws tickets from the counter of the XCD it runs on, so the 32 workgroups of an XCD
+// still walk one block side by side; when its own XCD's chunks are used up it looks at all eight counters and
+// draws from the next one that has tickets left.  Counters only grow and nobody waits for anybody: a draw that
+// names no item means a counter that the next look leaves out, so every workgroup ends after at most 8 of them.
+// What bounds a call of a few items per CU is the way in and out.  The first item is nobody's to draw: workgroup L takes ticket L / 8 of
+// XCD L % 8, and the counters begin behind those (schedule kernel).  At the end one look at the counters (1 us) takes the place of a draw
+// from each, which at one to two items per CU was 4 to 20 us of a call: 704 x 1408 with 44 row tiles 72.8 -> 49.1 us, 1024 x 2304 with
+// 15 68 -> 59, 768 tokens of 2880 x 2880 150 -> 141; calls of many items gain up to 1 %.  One workgroup per item, without the queue,
+// is not faster any more at any size (4096 x 14336, 160 wide items of gemm2 718 -> 693).
 struct WorkQueue {
-  int32_t* counters;  // [8], cleared by the schedule kernel
-  int victim, misses;
-  __device__ __forceinline__ void init(int32_t* c) {
-    counters = c;
+  int32_t* counters;  // [8], set by the schedule kernel
+  int victim;         // the XCD whose counter is drawn from
+  __device__ __forceinline__ void init(int32_t* c) { counters = c; }
+  // The workgroup's first item; false if there is none (and no other for it either: fewer items than workgroups).
+  __device__ __forceinline__ bool first(int n_tiles, int n_cols, int& tile, int& col) {
     victim = __builtin_amdgcn_s_getreg((20 << 0) | (0 << 6) | (3 << 11)) & (kXcds - 1);  // XCC_ID
-    misses = 0;
+    return ffn_item_of(ffn_item_number(blockIdx.x / kXcds, blockIdx.x % kXcds, n_tiles * n_cols), n_tiles, n_cols, tile, col);
   }
-  // What ticket t of counter `victim` stands for; false (and the bookkeeping of an unsuccessful draw) if nothing.
-  __device__ __forceinline__ bool accept(int t, int n_tiles, int n_cols, int& tile, int& col) {
-    const int col_groups = (n_cols + kBlkN - 1) / kBlkN, tile_groups = (n_tiles + kBlkM - 1) / kBlkM;
-    const int b = (t / kBlk) * kXcds + victim;
-    if (b >= tile_groups * col_groups) {  // this XCD's blocks are used up: go on to the next one's
-      victim = (victim + 1) & (kXcds - 1);
-      ++misses;
-      return false;
+  // All threads of the workgroup call this together; slot is two ints of static LDS.  used_up: the victim is known to be used up.
+  __device__ __forceinline__ bool next(bool used_up, int n_tiles, int n_cols, volatile int* slot, int& tile, int& col) {
+    const int n_items = n_tiles * n_cols;
+    __syncthreads();  // the previous item is finished by every wave (LDS stages, slot)
+    if (threadIdx.x < kWave) {
+      const int lane = threadIdx.x;
+      int q = n_items;
+      while (true) {
+        if (!used_up) {
+          int t = 0;
+          if (lane == 0) t = atomicAdd(&counters[victim], 1);
+          q = ffn_item_number(__builtin_amdgcn_readfirstlane(t), victim, n_items);
+          if (q < n_items) break;
+        }
+        const int drawn = __hip_atomic_load(&counters[lane & (kXcds - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned left = static_cast<unsigned>(__ballot(ffn_item_number(drawn, lane & (kXcds - 1), n_items) < n_items)) & ((1u << kXcds) - 1);
+        if (!left) break;
+        const unsigned from = left * ((1u << kXcds) + 1) >> victim;  // bit i: counter (victim + i) % 8
+        victim = (victim + __builtin_ctz(from)) & (kXcds - 1);
+        used_up = false;
+      }
+      if (lane == 0) {
+        slot[0] = q;
+        slot[1] = victim;
+      }
     }
-    misses = 0;
-    return ffn_item_of(b * kBlk + t % kBlk, n_tiles, n_cols, tile, col);
-  }
-  // all threads of the workgroup call this together; *slot is one int of static LDS
-  __device__ __forceinline__ bool next(int n_tiles, int n_cols, volatile int* slot, int& tile, int& col) {
-    while (misses < kXcds) {
-      __syncthreads();  // the previous item is finished by every wave (LDS stages, *slot)
-      if (threadIdx.x == 0) *slot = atomicAdd(&counters[victim], 1);
-      __syncthreads();
-      if (accept(__builtin_amdgcn_readfirstlane(*slot), n_tiles, n_cols, tile, col)) return true;
-    }
-    return false;
+    __syncthreads();
+    victim = __builtin_amdgcn_readfirstlane(slot[1]);
+    return ffn_item_of(__builtin_amdgcn_readfirstlane(slot[0]), n_tiles, n_cols, tile, col);
   }
   // The same when thread 0 has already drawn a ticket during the last k-steps of the previous item (gemm_mainloop,
   // DRAW) and every wave is past that loop's last barrier: no barrier is needed to read it, and none before the next
   // item's loads either, because no wave reads the LDS stages after that barrier.  Falls back to next() when the
-  // ticket names no item (the end of a queue).
+  // ticket names no item.
   __device__ __forceinline__ bool next_drawn(bool drew, int n_tiles, int n_cols, volatile int* slot, int& tile,
                                              int& col) {
-    if (drew && accept(__builtin_amdgcn_readfirstlane(*slot), n_tiles, n_cols, tile, col)) return true;
-    return next(n_tiles, n_cols, slot, tile, col);
+    if (drew && ffn_item_of(ffn_item_number(__builtin_amdgcn_readfirstlane(slot[0]), victim, n_tiles * n_cols), n_tiles, n_cols, tile, col)) return true;
+    return next(drew, n_tiles, n_cols, slot, tile, col);
   }
 };
-
-static int ffn_grid(int max_tiles, int n_cols) {
-  const int tile_groups = (max_tiles + kBlkM - 1) / kBlkM, col_groups = (n_cols + kBlkN - 1) / kBlkN;
-  const int blocks = tile_groups * col_groups;                       // blocks of 32 work items
-  return (blocks + kXcds - 1) / kXcds * kXcds * kBlk;                // whole rounds over the 8 XCDs
-}
 
 // ---- 1. gemm1 + SwiGLU ----------------------------------------------------------------
 // Where the activation rows of gemm1 come from: the permuted copy xp (row r of the row space), or,
@@ -492,54 +500,48 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
 }
 
 // one-dimensional launch over (row tile, column block) work items; a column block is 64 NI gate + 64 NI up weight rows
-// queue != 0: persistent launch, items drawn from the work queue; 0: one workgroup per item
 template <bool GATHER, int NI>
 __device__ __forceinline__ void ffn_gemm1_items(const RowSource& src, const int32_t* __restrict__ table, int32_t* table_rw,
-                                                int queue, int H, int F, bf16_t* __restrict__ hbuf, u32x4* smem,
+                                                int H, int F, bf16_t* __restrict__ hbuf, u32x4* smem,
                                                 volatile int* ticket) {
   constexpr int COLS = 64 * NI;
   const int n_tiles = table[0], n_cols = (F + COLS - 1) / COLS;
   int tile, col;
-  auto run = [&](auto draw_c, int32_t* ctr) {
-    constexpr bool DRAW = decltype(draw_c)::value;
+  auto run = [&](int32_t* ctr) {
     const TileEntry e = reinterpret_cast<const TileEntry*>(table + kTableHeaderInts)[tile];
     const int n0 = col * COLS;
     const bf16_t* w13 = static_cast<const bf16_t*>(e.w13);
     if (e.height > 256)
-      return gemm1_tile<5, GATHER, NI, ffn_stages(5, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+      return gemm1_tile<5, GATHER, NI, ffn_stages(5, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
     if (e.height > 192)
-      return gemm1_tile<4, GATHER, NI, ffn_stages(4, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+      return gemm1_tile<4, GATHER, NI, ffn_stages(4, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
     if (e.height > 128)
-      return gemm1_tile<3, GATHER, NI, ffn_stages(3, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+      return gemm1_tile<3, GATHER, NI, ffn_stages(3, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
     if (e.height > 64)
-      return gemm1_tile<2, GATHER, NI, ffn_stages(2, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
-    return gemm1_tile<1, GATHER, NI, ffn_stages(1, NI), DRAW>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+      return gemm1_tile<2, GATHER, NI, ffn_stages(2, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+    return gemm1_tile<1, GATHER, NI, ffn_stages(1, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
   };
-  if (queue) {
-    // persistent launch: the ticket of the next item is drawn while the last k-steps of this one run
-    WorkQueue wq;
-    wq.init(table_rw + kQueue1);
-    bool more = wq.next(n_tiles, n_cols, ticket, tile, col);
-    while (more) {
-      const bool drew = run(std::true_type{}, wq.counters + wq.victim);
-      more = wq.next_drawn(drew, n_tiles, n_cols, ticket, tile, col);
-    }
-  } else if (ffn_work_item(n_tiles, n_cols, tile, col)) {
-    run(std::false_type{}, nullptr);
+  // the ticket of the next item is drawn while the last k-steps of this one run
+  WorkQueue wq;
+  wq.init(table_rw + kQueue1);
+  bool more = wq.first(n_tiles, n_cols, tile, col);
+  while (more) {
+    const bool drew = run(wq.counters + wq.victim);
+    more = wq.next_drawn(drew, n_tiles, n_cols, ticket, tile, col);
   }
 }
 
 template <bool GATHER>
 __global__ __launch_bounds__(512, 2) void ffn_gemm1_kernel(RowSource src, const int32_t* __restrict__ table,
-                                                           int32_t* table_rw, int queue, int H, int F,
+                                                           int32_t* table_rw, int H, int F,
                                                            bf16_t* __restrict__ hbuf) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
-  __shared__ int ticket;
+  __shared__ int ticket[2];
   if (table[kNarrow1])
-    ffn_gemm1_items<GATHER, 1>(src, table, table_rw, queue, H, F, hbuf, smem, &ticket);
+    ffn_gemm1_items<GATHER, 1>(src, table, table_rw, H, F, hbuf, smem, ticket);
   else
-    ffn_gemm1_items<GATHER, 2>(src, table, table_rw, queue, H, F, hbuf, smem, &ticket);
+    ffn_gemm1_items<GATHER, 2>(src, table, table_rw, H, F, hbuf, smem, ticket);
 #endif
 }
 
@@ -649,45 +651,40 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
 // one-dimensional launch over (row tile, column block of 128 NI output columns) work items
 template <int NI>
 __device__ __forceinline__ void ffn_gemm2_items(const bf16_t* __restrict__ hbuf, const int32_t* __restrict__ table,
-                                                int32_t* table_rw, int queue, int H, int F, bf16_t* __restrict__ y,
+                                                int32_t* table_rw, int H, int F, bf16_t* __restrict__ y,
                                                 u32x4* smem, volatile int* ticket) {
   constexpr int COLS = 128 * NI;
   const int n_tiles = table[0], n_cols = (H + COLS - 1) / COLS;
   int tile, col;
-  auto run = [&](auto draw_c, int32_t* ctr) {
-    constexpr bool DRAW = decltype(draw_c)::value;
+  auto run = [&](int32_t* ctr) {
     const TileEntry e = reinterpret_cast<const TileEntry*>(table + kTableHeaderInts)[tile];
     const int n0 = col * COLS;
     const bf16_t* w2 = static_cast<const bf16_t*>(e.w2);
-    if (e.height > 256) return gemm2_tile<5, NI, ffn_stages(5, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
-    if (e.height > 192) return gemm2_tile<4, NI, ffn_stages(4, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
-    if (e.height > 128) return gemm2_tile<3, NI, ffn_stages(3, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
-    if (e.height > 64) return gemm2_tile<2, NI, ffn_stages(2, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
-    return gemm2_tile<1, NI, ffn_stages(1, NI), DRAW>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    if (e.height > 256) return gemm2_tile<5, NI, ffn_stages(5, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    if (e.height > 192) return gemm2_tile<4, NI, ffn_stages(4, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    if (e.height > 128) return gemm2_tile<3, NI, ffn_stages(3, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    if (e.height > 64) return gemm2_tile<2, NI, ffn_stages(2, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    return gemm2_tile<1, NI, ffn_stages(1, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
   };
-  if (queue) {
-    WorkQueue wq;
-    wq.init(table_rw + kQueue2);
-    bool more = wq.next(n_tiles, n_cols, ticket, tile, col);
-    while (more) {
-      const bool drew = run(std::true_type{}, wq.counters + wq.victim);
-      more = wq.next_drawn(drew, n_tiles, n_cols, ticket, tile, col);
-    }
-  } else if (ffn_work_item(n_tiles, n_cols, tile, col)) {
-    run(std::false_type{}, nullptr);
+  WorkQueue wq;
+  wq.init(table_rw + kQueue2);
+  bool more = wq.first(n_tiles, n_cols, tile, col);
+  while (more) {
+    const bool drew = run(wq.counters + wq.victim);
+    more = wq.next_drawn(drew, n_tiles, n_cols, ticket, tile, col);
   }
 }
 
 __global__ __launch_bounds__(512, 2) void ffn_gemm2_kernel(const bf16_t* __restrict__ hbuf,
                                                            const int32_t* __restrict__ table, int32_t* table_rw,
-                                                           int queue, int H, int F, bf16_t* __restrict__ y) {
+                                                           int H, int F, bf16_t* __restrict__ y) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
-  __shared__ int ticket;
+  __shared__ int ticket[2];
   if (table[kNarrow2])
-    ffn_gemm2_items<1>(hbuf, table, table_rw, queue, H, F, y, smem, &ticket);
+    ffn_gemm2_items<1>(hbuf, table, table_rw, H, F, y, smem, ticket);
   else
-    ffn_gemm2_items<2>(hbuf, table, table_rw, queue, H, F, y, smem, &ticket);
+    ffn_gemm2_items<2>(hbuf, table, table_rw, H, F, y, smem, ticket);
 #endif
 }
 
@@ -1173,21 +1170,14 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     return check_launch(name);
   }
   const int n1 = (F + 127) / 128, n2 = (H + FBN - 1) / FBN;
-  // Persistent launch (one workgroup per CU, items drawn from the work queue) unless the capacity of the row space gives no more
-  // wide items than that.  Where items may be narrow (the schedule decides), such a launch has a workgroup for each of twice as many
-  // all the same: with about one item per CU the draws cost more than they even out (a workgroup ends after eight that fail).
-  const int cap1 = ffn_grid(sh.max_tiles, n1), cap2 = ffn_grid(sh.max_tiles, n2);
-  const int q1 = cap1 > cus ? 1 : 0, q2 = cap2 > cus ? 1 : 0;
-  const int narrow1 = ffn_grid(std::min(sh.max_tiles, kNarrowItems1 / n1), 2 * n1);
-  const int narrow2 = ffn_grid(std::min(sh.max_tiles, kNarrowItems2 / n2), 2 * n2);
-  const dim3 grid1(q1 ? cus : std::max(cap1, narrow1)), grid2(q2 ? cus : std::max(cap2, narrow2));
+  const dim3 grid(cus);  // persistent: one workgroup per CU, items drawn from the work queue
   hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(kScheduleThreads), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S,
-                     sh.max_tiles, n1, n2, H / FBK, F / FBK, q1, q2, cus, table);
+                     sh.max_tiles, n1, n2, H / FBK, F / FBK, cus, table);
   if (gather)
-    hipLaunchKernelGGL(ffn_gemm1_kernel<true>, grid1, dim3(512), kFfnLdsBytes, st, src, table, table, q1, H, F, hbuf);
+    hipLaunchKernelGGL(ffn_gemm1_kernel<true>, grid, dim3(512), kFfnLdsBytes, st, src, table, table, H, F, hbuf);
   else
-    hipLaunchKernelGGL(ffn_gemm1_kernel<false>, grid1, dim3(512), kFfnLdsBytes, st, src, table, table, q1, H, F, hbuf);
-  hipLaunchKernelGGL(ffn_gemm2_kernel, grid2, dim3(512), kFfnLdsBytes, st, hbuf, table, table, q2, H, F,
+    hipLaunchKernelGGL(ffn_gemm1_kernel<false>, grid, dim3(512), kFfnLdsBytes, st, src, table, table, H, F, hbuf);
+  hipLaunchKernelGGL(ffn_gemm2_kernel, grid, dim3(512), kFfnLdsBytes, st, hbuf, table, table, H, F,
                      static_cast<bf16_t*>(y_bf16));
   return check_launch(name);
 }

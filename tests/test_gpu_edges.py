@@ -615,6 +615,23 @@ def test_ffn_column_blocks_by_estimated_time(oracle, probe, G, sizes, H, F, capa
     assert all(torch.equal(ys[0], y) for y in ys[1:])
 
 
+@pytest.mark.parametrize("sizes,H,F,spare", [
+    ([90], 64, 64, 36000),          # one item
+    ([90] * 9, 832, 576, 4000),     # a second group of one tile, column groups that end early
+    ([70] * 51, 320, 640, 9),       # 255 wide items of gemm1
+    ([70] * 32, 2048, 1024, 9),     # 256 of both: one item each
+    ([70] * 43, 64, 768, 9),        # 258: the first two that are drawn
+    ([70, 300, 0, 90] * 11, 320, 2112, 9)])
+def test_ffn_every_item_of_the_queue_is_run_once(oracle, probe, G, sizes, H, F, spare):
+    """Tall tiles at numbers of items around one per workgroup, where the first ones are dealt without a draw, and with groups of tiles
+    and columns that are not full: every output element against the oracle."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=106)
+    capacity = sum(sizes) + spare
+    assert (capacity // 64 + len(sizes)) * (F // 64) > 512 and capacity > 64 * len(sizes)     # past the decode schedule
+    print("case queue", len(sizes), H, F, flush=True)
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F, extra_rows=spare)
+
+
 @pytest.mark.parametrize("H,F,n", [(4096, 2048, 75), (2880, 2880, 40)])
 def test_ffn_workspace_of_a_larger_call_serves_a_smaller_one(oracle, probe, G, H, F, n):
     """A workspace sized for more rows serves fewer as their own does, bit for bit, also where only the smaller call keeps partial
