@@ -410,12 +410,13 @@ __device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1
 // rows per workgroup), 1 = 64 h columns (the skinny tiles of the decode schedule).  NST = LDS stages.
 template <int MI, bool GATHER, int NI = 2, int NST = (MI >= 3 ? 2 : 3), bool DRAW = false, bool SPLIT = false>
 __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* __restrict__ w13,
-                                           int row0, int rows, int n0, int H, int F,
+                                           int row0, int rows, int n0, int n_end, int H, int F,
                                            bf16_t* __restrict__ hbuf, u32x4* smem, int32_t* draw_counter = nullptr,
                                            volatile int* draw_slot = nullptr, int k0 = 0, int klen = 0,
                                            float* partial = nullptr, int k_start = 0) {
   // SPLIT: only k0 .. k0 + klen - 1 of the contraction; the fp32 sums go to partial[row of the tile][gate F | up F].
-  // rows = valid rows from row0 to the end of the slot (may exceed the tile height)
+  // rows = valid rows from row0 to the end of the slot (may exceed the tile height); columns n0 .. n_end - 1, which may be fewer
+  // than a column block has
   constexpr int HALF = 16 * NI;  // h columns per wave; its 32*NI weight rows are HALF gate rows, then the HALF up rows
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -443,7 +444,8 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
                               const int q = j / (2 * HALF), r = j % (2 * HALF);
                               const bool up = NI == 2 ? r >= HALF : (r >> 2) & 1;
                               const int c = NI == 2 ? r % HALF : ((r >> 3) << 2) | (r & 3);
-                              const int f = min(n0 + HALF * q + c, F - 1);  // columns past F are masked at the store
+                              const int f = n0 + HALF * q + c;
+                              if (f >= n_end) return 2 * F;  // past the descriptor: zeros without traffic, masked at the store
                               return up ? F + f : f;
                             },
                             voff + MI);
@@ -464,7 +466,7 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
   if constexpr (SPLIT) {
     static_assert(NI == 1, "four columns per lane");
     __amdgpu_buffer_rsrc_t rP = make_rsrc(partial, static_cast<size_t>(valid) * 2 * F * 4);
-    if (cbase < F) {
+    if (cbase < n_end) {
 #pragma unroll
       for (int i = 0; i < 2 * MI; ++i) {
         const int off = ((row_in + 16 * i) * 2 * F + cbase) * 4;
@@ -474,7 +476,7 @@ __device__ __forceinline__ bool gemm1_tile(const RowSource& src, const bf16_t* _
     }
     return drew;
   }
-  if (cbase < F) {  // F % 8 == 0: a group of 4 * NI columns is in or out as a whole
+  if (cbase < n_end) {  // n_end % 8 == 0: a group of 4 * NI columns is in or out as a whole
 #pragma unroll
     for (int i = 0; i < 2 * MI; ++i) {
       const int off = ((row_in + 16 * i) * F + cbase) * 2;
@@ -512,14 +514,14 @@ __device__ __forceinline__ void ffn_gemm1_items(const RowSource& src, const int3
     const int n0 = col * COLS;
     const bf16_t* w13 = static_cast<const bf16_t*>(e.w13);
     if (e.height > 256)
-      return gemm1_tile<5, GATHER, NI, ffn_stages(5, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+      return gemm1_tile<5, GATHER, NI, ffn_stages(5, NI), true>(src, w13, e.row0, e.rows, n0, F, H, F, hbuf, smem, ctr, ticket);
     if (e.height > 192)
-      return gemm1_tile<4, GATHER, NI, ffn_stages(4, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+      return gemm1_tile<4, GATHER, NI, ffn_stages(4, NI), true>(src, w13, e.row0, e.rows, n0, F, H, F, hbuf, smem, ctr, ticket);
     if (e.height > 128)
-      return gemm1_tile<3, GATHER, NI, ffn_stages(3, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+      return gemm1_tile<3, GATHER, NI, ffn_stages(3, NI), true>(src, w13, e.row0, e.rows, n0, F, H, F, hbuf, smem, ctr, ticket);
     if (e.height > 64)
-      return gemm1_tile<2, GATHER, NI, ffn_stages(2, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
-    return gemm1_tile<1, GATHER, NI, ffn_stages(1, NI), true>(src, w13, e.row0, e.rows, n0, H, F, hbuf, smem, ctr, ticket);
+      return gemm1_tile<2, GATHER, NI, ffn_stages(2, NI), true>(src, w13, e.row0, e.rows, n0, F, H, F, hbuf, smem, ctr, ticket);
+    return gemm1_tile<1, GATHER, NI, ffn_stages(1, NI), true>(src, w13, e.row0, e.rows, n0, F, H, F, hbuf, smem, ctr, ticket);
   };
   // the ticket of the next item is drawn while the last k-steps of this one run
   WorkQueue wq;
@@ -548,7 +550,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm1_kernel(RowSource src, const 
 // ---- 2. gemm2 -------------------------------------------------------------------------
 template <int MI, int NI = 2, int NST = (MI >= 3 ? 2 : 3), bool DRAW = false, bool SPLIT = false, bool LAST = false>
 __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, const bf16_t* __restrict__ w2,
-                                           int row0, int rows, int n0, int H, int F,
+                                           int row0, int rows, int n0, int n_end, int H, int F,
                                            bf16_t* __restrict__ y, u32x4* smem, int32_t* draw_counter = nullptr,
                                            volatile int* draw_slot = nullptr, int k0 = 0, int klen = 0,
                                            float* partial = nullptr, int k_start = 0, int piece = 0, int pieces = 1,
@@ -562,7 +564,7 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
   __amdgpu_buffer_rsrc_t rB = make_rsrc(w2, static_cast<size_t>(H) * F * 2);
   int voff[MI + 2 * NI];
   dma_offsets<MI>(wv, lane, F * 2, [&](int r) { return r; }, voff);  // rows past the slot read as zeros (out of range)
-  dma_offsets<2 * NI, true>(wv, lane, F * 2, [&](int j) { return min(n0 + j, H - 1); }, voff + MI);
+  dma_offsets<2 * NI, true>(wv, lane, F * 2, [&](int j) { return n0 + j < n_end ? n0 + j : H; }, voff + MI);
   f32x4 acc[2 * MI][2 * NI];
   zero_acc<MI, NI>(acc);
   const bool drew =
@@ -577,7 +579,7 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
     constexpr int kDeviceScope = 16, kScope = LAST ? kDeviceScope : 0;
     const size_t piece_floats = static_cast<size_t>(64 * MI) * H;
     auto offset_of = [&](int i, int q) { return ((row_in + 16 * i) * H + n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4)) * 4; };
-    auto in_range = [&](int q) { return n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4) < H; };
+    auto in_range = [&](int q) { return n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4) < n_end; };
     __amdgpu_buffer_rsrc_t rP = make_rsrc(partial + piece * piece_floats, static_cast<size_t>(valid) * H * 4);
 #pragma unroll
     for (int i = 0; i < 2 * MI; ++i) {
@@ -635,7 +637,7 @@ __device__ __forceinline__ bool gemm2_tile(const bf16_t* __restrict__ hbuf, cons
     for (int q = 0; q < NI; ++q) {
       const int cbase = n0 + 32 * NI * wn + 32 * q + 8 * (lane >> 4);
       const int off = ((row_in + 16 * i) * H + cbase) * 2;
-      if (cbase < H) {
+      if (cbase < n_end) {
         u32x4 pk;
         pk[0] = pack_bf16x2(acc[i][2 * q][0], acc[i][2 * q][1]);
         pk[1] = pack_bf16x2(acc[i][2 * q][2], acc[i][2 * q][3]);
@@ -660,11 +662,11 @@ __device__ __forceinline__ void ffn_gemm2_items(const bf16_t* __restrict__ hbuf,
     const TileEntry e = reinterpret_cast<const TileEntry*>(table + kTableHeaderInts)[tile];
     const int n0 = col * COLS;
     const bf16_t* w2 = static_cast<const bf16_t*>(e.w2);
-    if (e.height > 256) return gemm2_tile<5, NI, ffn_stages(5, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
-    if (e.height > 192) return gemm2_tile<4, NI, ffn_stages(4, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
-    if (e.height > 128) return gemm2_tile<3, NI, ffn_stages(3, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
-    if (e.height > 64) return gemm2_tile<2, NI, ffn_stages(2, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
-    return gemm2_tile<1, NI, ffn_stages(1, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, F, y, smem, ctr, ticket);
+    if (e.height > 256) return gemm2_tile<5, NI, ffn_stages(5, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, H, F, y, smem, ctr, ticket);
+    if (e.height > 192) return gemm2_tile<4, NI, ffn_stages(4, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, H, F, y, smem, ctr, ticket);
+    if (e.height > 128) return gemm2_tile<3, NI, ffn_stages(3, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, H, F, y, smem, ctr, ticket);
+    if (e.height > 64) return gemm2_tile<2, NI, ffn_stages(2, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, H, F, y, smem, ctr, ticket);
+    return gemm2_tile<1, NI, ffn_stages(1, NI), true>(hbuf, w2, e.row0, e.rows, n0, H, H, F, y, smem, ctr, ticket);
   };
   WorkQueue wq;
   wq.init(table_rw + kQueue2);
@@ -781,22 +783,46 @@ __device__ __forceinline__ int skinny_steps(int items, int rows, int n_cols, int
   return split > 1 ? (steps + split - 1) / split : 0;
 }
 
+// Column blocks of a row tile, `items` = row tiles x n_cols blocks of the usual width.  Two items to a CU stream at one rate wherever they
+// are, but a number of items that leaves some CUs with two and some with one (or, further up, a last round that is nearly empty) makes
+// the call as long as the fuller ones.  The columns are then dealt evenly to as many blocks as give 512 workgroups, or a multiple, one
+// item each.  Narrower blocks alone lose: fewer weight rows in flight per workgroup (7 slots of 4096 x 1536, 168 items of gemm1 or 511 of a
+// third of the width, 55.9 / 65.2 us; 224 items of 7168 x 2048 112 / 126), so only where the last round is at most that full.
+// Usual blocks / spread: gemm1 of 9, 10, 12 slots of 7168 x 2048 (288, 320, 384 items) 166 / 148, 179 / 164, 203 / 189, 11 of 4096 x 1536
+// (264) 95 / 84, but 14 slots of it (336 of 64 k-steps, 252 rows) 108 / 106 and 14 of 7168 x 2048 (448) 217 / 218; second round: 13 of
+// 2880 x 2880 (585) 131 / 127, 20 of 7168 x 2048 (640) 313 / 306, 24 (768) 355 / 361; third: 36
+// (1152) 536 / 528, with 351 rows 535 / 543.  gemm2 of 9 and 10 slots of 4096 x 14336 (288, 320)
+// 578 / 537 and 625 / 593, 13 of 2880 x 2880 (299) 131 / 124, 9 and 10 of 4096 x 1536 (288 and 320 of 24 k-steps) 69 / 66 and 75 / 71, but 6 and 7 of 7168 x 2048
+// (336 and 392 of 32 k-steps) 107 / 110 and 112 / 117, second round level.
+constexpr int kSkinnySlots = 512;                          // workgroups that run at once, two to a CU
+constexpr int kSkinnySpread1 = 400, kSkinnySpread2 = 384, kSkinnySpreadShort = 328;  // items up to which a single round (of more than 256) is
+constexpr int kSkinnySpreadSteps = 40;                     // spread: gemm1, gemm2 from these k-steps on, gemm2 of fewer
+constexpr int kSkinnySpreadLast = 160, kSkinnySpreadRounds = 2;  // gemm1: items of a last round that is spread over the first; rounds at most
+template <bool GEMM1>
+__device__ __forceinline__ int skinny_blocks(int n_tiles, int n_cols, int steps) {
+  const int items = n_tiles * n_cols, rounds = (items + kSkinnySlots - 1) / kSkinnySlots, last = items - kSkinnySlots * (rounds - 1);
+  const bool spread = rounds == 1 ? last > kSkinnySlots / 2 && last <= (GEMM1 ? kSkinnySpread1 : steps >= kSkinnySpreadSteps ? kSkinnySpread2 : kSkinnySpreadShort)
+                                  : GEMM1 && rounds <= kSkinnySpreadRounds && last <= kSkinnySpreadLast;
+  return spread ? max(n_cols, kSkinnySlots * rounds / n_tiles) : n_cols;  // fewer than twice as many: 32 columns at least, or one block
+}
+
 // Item number -> (slot, first row, rows to the end of the slot, weight pointer, piece of K) without a tile table: slots
 // in their own order, ceil(M / 64) tiles each.  Every workgroup finds its own tile with one scan over the
 // (at most 1024) slots, two per thread, so the decode schedule needs no schedule kernel in front of it.
 // Returns false if the item number is past the last item (the launch is sized for the capacity).
 struct SkinnyTile {
   int row0, rows;
+  int n0, n_end;  // columns
   int tile, col, piece, pieces, piece_steps;
   bool spread;  // the items begin at different k-steps (skinny_start)
   const void* w;
 };
 
-// REDUCE: `item` is a tile number (column and piece are not looked at)
-template <bool REDUCE, bool LAST>
+// REDUCE: `item` is a tile number (columns and piece are not looked at).  GEMM1: which of the two, columns of `cols` in n_cols blocks.
+template <bool REDUCE, bool LAST, bool GEMM1 = false>
 __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_offsets,
-                                              const void* const* __restrict__ w_ptrs, int S, int item, int n_cols,
-                                              int steps, bool may_split, SkinnyTile& out) {
+                                              const void* const* __restrict__ w_ptrs, int S, int item, int cols,
+                                              int n_cols, int steps, bool may_split, SkinnyTile& out) {
   const int all_rows = slot_offsets[S] - slot_offsets[0];
   __shared__ int32_t wave_tot[8];
   __shared__ int32_t found_row0, found_rows;
@@ -845,8 +871,18 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
     out.pieces = (steps + piece_steps - 1) / piece_steps;
   }
   if (!REDUCE) {
-    tile = item / n_cols;
-    out.col = item - tile * n_cols;
+    const int blocks = piece_steps ? n_cols : skinny_blocks<GEMM1>(n_tiles, n_cols, steps);
+    tile = item / blocks;
+    out.col = item - tile * blocks;
+    if (blocks > n_cols) {
+      const int groups = cols >> 3, small = groups / blocks, more = groups - small * blocks;  // of eight columns: 16-byte stores of y
+      out.n0 = 8 * (out.col * small + min(out.col, more));
+      out.n_end = out.n0 + 8 * (small + (out.col < more ? 1 : 0));
+    } else {
+      constexpr int kWidth = GEMM1 ? kSkinnyCols1 : kSkinnyCols2;
+      out.n0 = out.col * kWidth;
+      out.n_end = min(out.n0 + kWidth, cols);
+    }
     if (piece_steps) {
       const int q = tile;
       tile = q / out.pieces;
@@ -908,16 +944,16 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
   extern __shared__ u32x4 smem[];
   if (CLEAR && blockIdx.x == 0 && threadIdx.x < kArrivalWords) arrivals[threadIdx.x] = 0;
   SkinnyTile e;
-  if (!skinny_locate<false, false>(slot_offsets, w13_ptrs, S, blockIdx.x, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
-                            may_split, e))
+  if (!skinny_locate<false, false, true>(slot_offsets, w13_ptrs, S, blockIdx.x, F, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
+                                         may_split, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
-    gemm1_tile<1, GATHER, 1, 3>(src, w, e.row0, e.rows, e.col * kSkinnyCols1, H, F, hbuf, smem, nullptr, nullptr, 0, 0,
+    gemm1_tile<1, GATHER, 1, 3>(src, w, e.row0, e.rows, e.n0, e.n_end, H, F, hbuf, smem, nullptr, nullptr, 0, 0,
                                 nullptr, skinny_start(e, H));
   } else {
     const int k0 = e.piece * e.piece_steps * FBK;
-    gemm1_tile<1, GATHER, 1, 3, false, true>(src, w, e.row0, e.rows, e.col * kSkinnyCols1, H, F, hbuf, smem, nullptr,
+    gemm1_tile<1, GATHER, 1, 3, false, true>(src, w, e.row0, e.rows, e.n0, e.n_end, H, F, hbuf, smem, nullptr,
                                              nullptr, k0, min(H - k0, e.piece_steps * FBK),
                                              skinny_partial(partial, e, e.piece, 2 * F),
                                              skinny_start(e, min(H - k0, e.piece_steps * FBK)));
@@ -935,17 +971,17 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* 
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
   SkinnyTile e;
-  if (!skinny_locate<false, LAST>(slot_offsets, w2_ptrs, S, blockIdx.x, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK,
-                            may_split, e))
+  if (!skinny_locate<false, LAST>(slot_offsets, w2_ptrs, S, blockIdx.x, H, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK,
+                                  may_split, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
   if (e.pieces == 1) {
-    gemm2_tile<1, 1, 3>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem, nullptr, nullptr, 0, 0, nullptr,
+    gemm2_tile<1, 1, 3>(hbuf, w, e.row0, e.rows, e.n0, e.n_end, H, F, y, smem, nullptr, nullptr, 0, 0, nullptr,
                         skinny_start(e, F));
   } else {
     const int k0 = e.piece * e.piece_steps * FBK;
     const int n_cols = (H + kSkinnyCols2 - 1) / kSkinnyCols2, klen = min(F - k0, e.piece_steps * FBK);
-    gemm2_tile<1, 1, 3, false, true, LAST>(hbuf, w, e.row0, e.rows, e.col * kSkinnyCols2, H, F, y, smem, nullptr, nullptr, k0, klen,
+    gemm2_tile<1, 1, 3, false, true, LAST>(hbuf, w, e.row0, e.rows, e.n0, e.n_end, H, F, y, smem, nullptr, nullptr, k0, klen,
                                      skinny_partial(partial, e, 0, H), skinny_start(e, klen), e.piece, e.pieces, arrivals,
                                      e.tile * n_cols + e.col);
   }
@@ -961,7 +997,7 @@ __global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __rest
                                                              bf16_t* __restrict__ out) {
   SkinnyTile e;
   const int row = blockIdx.x & 63;
-  if (!skinny_locate<true, false>(slot_offsets, nullptr, S, blockIdx.x >> 6, n_cols, steps, true, e)) return;
+  if (!skinny_locate<true, false>(slot_offsets, nullptr, S, blockIdx.x >> 6, out_cols, n_cols, steps, true, e)) return;
   if (e.pieces == 1 || row >= e.rows) return;
   const int ld = SWIGLU ? 2 * out_cols : out_cols;
   const float* base = partial + static_cast<size_t>(e.tile * e.pieces) * 64 * ld + static_cast<size_t>(row) * ld;
@@ -1145,8 +1181,12 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     const bool split2 = last_adds || (room && skinny_may_split(S, max_rows, n2, F / FBK));
     uint32_t* arrivals = last_adds ? reinterpret_cast<uint32_t*>(table) : nullptr;
     // a split call has at most kSkinnyItems items, one that is not split tiles * n
-    const dim3 g1(split1 ? std::max(tiles * n1, kSkinnyItems) : tiles * n1);
-    const dim3 g2(split2 ? std::max(tiles * n2, kSkinnyItems) : tiles * n2);
+    // and one that is spread whole rounds of kSkinnySlots
+    auto items = [](long n, bool split, int spread_rounds) {
+      if (split) n = std::max<long>(n, kSkinnyItems);
+      return n > kSkinnySlots / 2 && n < kSkinnySlots * spread_rounds ? (n + kSkinnySlots - 1) / kSkinnySlots * kSkinnySlots : n;
+    };
+    const dim3 g1(items(tiles * n1, split1, kSkinnySpreadRounds)), g2(items(tiles * n2, split2, 1));
     // tiles that can be split at all: two pieces or more need kSkinnyItems / 2 items or fewer
     const int add1 = split1 ? std::min(tiles, kSkinnyItems / 2 / n1) : 0;
     const int add2 = split2 && !last_adds ? std::min(tiles, kSkinnyItems / 2 / n2) : 0;

@@ -525,6 +525,36 @@ def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes,
     assert all(torch.equal(ys[0], y) for y in ys[1:])
 
 
+@pytest.mark.parametrize("n,H,F", [
+    (13, 2560, 1280),     # 260 items of either GEMM: columns dealt to 39 blocks of 4 or 5 (8 or 9) groups of eight
+    (16, 3072, 1600),     # 400 of gemm1: the most of a single round; 384 of gemm2, of 25 k-steps: not
+    (16, 3072, 2560),     # 384 of gemm2, of 40 k-steps: the most
+    (13, 2944, 2624),     # 299 of gemm2; 533 of gemm1: a last round of 21
+    (16, 2048, 2688),     # 672 of gemm1: the most of a second round; 256 of gemm2: one to a CU, not spread
+    (13, 2432, 3328),     # 676 of gemm1: not
+    (257, 64, 64)])       # one block of columns each, which stays one
+def test_ffn_decode_schedule_spreads_columns(oracle, probe, G, n, H, F):
+    """Decode schedule: numbers of items at the limits between which the columns of a tile are dealt to more blocks; every output
+    element against the oracle, and the rows gathered on load bit for bit the same."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=107)
+    sizes = [1 + 7 * i % 5 for i in range(n)]
+    sizes[n // 2] = 64
+    print("case spread", n, H, F, flush=True)
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F)
+    gen = torch.Generator(device="cuda").manual_seed(F)
+    rows = sum(sizes)
+    x = torch.randn((rows + 5, H), generator=gen, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
+         torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16))
+    tab = probe.WeightTable([w[0]] * n, [w[1]] * n)
+    so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
+    order = torch.randperm(rows + 5, device="cuda", generator=gen).to(torch.int32)
+    plain = probe.grouped_ffn(x[order.long()].contiguous(), so, tab)
+    gathered = probe.grouped_ffn_gather(x, order, 1, so, tab)
+    torch.cuda.synchronize()
+    assert torch.equal(plain[:rows], gathered[:rows])
+
+
 def test_ffn_contraction_is_not_cut_where_every_slot_can_hold_rows(oracle, probe, G):
     """At 40 rows of capacity per slot no adding kernel is launched although one slot alone holds rows: the call gives the
     same bits with and without room for partial sums.  Every element against the oracle."""
