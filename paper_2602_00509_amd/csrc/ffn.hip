@@ -80,21 +80,31 @@ static_assert(sizeof(TileEntry) == 32, "one 32-byte record per tile");
 constexpr int kTableHeaderInts = 32, kNarrow1 = 1, kNarrow2 = 2, kQueue1 = 8, kQueue2 = 16;
 
 struct SlotCut {
-  int n320, n256, tail;  // tail = height of the one short tile (64, 128 or 192), 0 if there is none
-  __device__ __forceinline__ int tiles() const { return n320 + n256 + (tail ? 1 : 0); }
+  int n320, n256;   // the standard cut
+  int n_cap, cap;   // or tiles of one height
+  int tail;         // height of the one short tile (64, 128 or 192), 0 if there is none
+  __device__ __forceinline__ int tiles() const { return n320 + n256 + n_cap + (tail ? 1 : 0); }
   // tallest first: 320, 256, 192, 128, 64 rows
   static __device__ __forceinline__ int height_class(int height) { return height == 320 ? 0 : 5 - (height >> 6); }
   // tiles of each height, twelve bits per class
   __device__ __forceinline__ unsigned long long classes() const {
-    return static_cast<unsigned long long>(n320) | static_cast<unsigned long long>(n256) << 12 |
+    return static_cast<unsigned long long>(n320) + (static_cast<unsigned long long>(n256) << 12) +
+           (n_cap ? static_cast<unsigned long long>(n_cap) << (12 * height_class(cap)) : 0ull) +
            (tail ? 1ull << (12 * height_class(tail)) : 0ull);
   }
 };
 
-__device__ __forceinline__ SlotCut cut_slot(int m) {
-  SlotCut c = {0, 0, 0};
+// cap = 0: the standard cut; otherwise tiles of `cap` rows (256, 192, 128 or 64) and one shorter.
+__device__ __forceinline__ SlotCut cut_slot(int m, int cap) {
+  SlotCut c = {0, 0, 0, 0, 0};
   const int u = (m + 63) >> 6;
-  if (u == 0) return c;
+  if (u <= 0) return c;
+  if (cap) {
+    c.cap = cap;
+    c.n_cap = cap == 256 ? u >> 2 : cap == 192 ? u / 3 : cap == 128 ? u >> 1 : u;
+    c.tail = 64 * u - cap * c.n_cap;
+    return c;
+  }
   if (u <= 3) {
     c.tail = 64 * u;
     return c;
@@ -111,33 +121,47 @@ __device__ __forceinline__ SlotCut cut_slot(int m) {
   return c;
 }
 
-// Width of the items.  A call with few tiles leaves CUs without an item while each of the others streams 256 weight rows per
-// k-step; with column blocks half as wide (64 h columns, 128 y columns) there are twice as many items of half the weight rows.
-constexpr int kNarrowItems1 = 224, kNarrowItems2 = 160;  // wide items up to which the narrow ones are taken
+// Height of the tiles and width of the items.  A call with few tiles leaves CUs without an item, or with a second one when most are
+// through; shorter tiles, or column blocks half as wide (64 h columns, 128 y columns), make more items that last less long, and move more
+// bytes in all.  The schedule kernel estimates the launches of both GEMMs for the standard cut and for tiles of at most 256, 192, 128 and 64
+// rows, each with wide and with narrow items, and takes the shortest; another cut has to be 2 % better than the standard one.
+//
+// The estimate: an item lasts 0.85 ns x k-steps x (3 x its rows + 4 x its weight rows), and 0.3 us; items are dealt tallest first, one
+// workgroup to a CU.  The launch lasts as long as ceil(n / CUs) times the shortest of its n tallest items, for every n, and, with more
+// items than CUs, as their mean load of a CU and 0.6 of the shortest.  Fitted to 90 drawn FFN calls of 64 to 4096 tokens, each timed with all
+// twenty cuts: of the 4.7 % that the best cut of each gains over the standard cut with the former rule for the width (a limit on wide
+// items, and an estimate for the width alone) this finds 3.4 %, on the half it was not fitted to 3.2 of 4.3.  640 x 1344, 18 blocks
+// of 64 rows 42 -> 29 us (64 rows), 2880 x 2880, 17 blocks 127 -> 107 (128 rows, narrow gemm2), 52 blocks 213 -> 195 (192 rows), 4672 x 832, 25
+// blocks 128 -> 104 (128 rows, narrow).  With many items per CU the standard cut moves the fewest bytes and stays.
 constexpr int kXcds = 8, kBlkM = 8, kBlkN = 4, kBlk = kBlkM * kBlkN;  // blocks of work items, see ffn_item_of
+constexpr int kCuts = 5;                                              // heights: the standard cut, 256, 192, 128, 64
+__device__ __forceinline__ int cut_cap(int cut) { return cut == 0 ? 0 : 320 - 64 * cut; }
+constexpr int kCutParts = kWave / kCuts;                              // lanes that count the tiles of one cut
+constexpr int kCutUnits = 4000;                                       // 64-row units up to which the classes' twelve bits hold any cut's tiles
+constexpr float kItemCost = 350.f, kCutGain = 0.98f;
 
-// Whether that is faster, from an estimate of both launches.  An item lasts as long as the rows that it moves, activations and weights,
-// times the k-steps, and about as much as 1000 row steps (3 us) on top; wide items are one to a CU.  Narrow ones, in a single round (no
-// more than CUs), take as long as the tallest; in more, their mean load of a CU and a part of the shortest, and the draws.  Wide / narrow: 31 tiles, 30 of them of 64 rows, 155 items of 94
-// k-steps 173 / 188 us, 12 of 128 and 192 rows, 132 of 19 75 / 82, but 13 tiles of 64 to 320 rows, 156 of 45 k-steps (gemm2 of 768 tokens,
-// 2880 x 2880) 73 / 54.  Of 1075 GEMMs within the limits
-// above the number of items alone made 146 more than 1 % slower (up to 11 %), the estimate 12 (up to 4 %); the gains stay.
-constexpr float kNarrowItemCost = 1000.f;
-__device__ __forceinline__ bool narrow_items(int total, unsigned long long classes, int n_cols, int steps, int limit, int cus) {
-  if (static_cast<long>(total) * n_cols > limit) return false;
-  float sum = 0.f, tallest = 0.f, shortest = 0.f;  // narrow items of one column block
+__device__ __forceinline__ int tiles_of(unsigned long long classes) {
+  int n = 0;
+#pragma unroll
+  for (int c = 0; c < 5; ++c) n += static_cast<int>(classes >> (12 * c)) & 4095;
+  return n;
+}
+
+__device__ __forceinline__ float launch_estimate(unsigned long long classes, int n_cols, int steps, int weight_rows, int cus) {
+  const float per_cu = 1.f / static_cast<float>(cus);
+  float longest = 0.f, sum = 0.f, item = 0.f;
+  int n = 0;
 #pragma unroll
   for (int c = 0; c < 5; ++c) {
-    const int n = static_cast<int>(classes >> (12 * c)) & 4095, height = c == 0 ? 320 : 64 * (5 - c);
-    const float item = static_cast<float>(height + 128) * steps + kNarrowItemCost;
-    sum += n * item;
-    if (n) shortest = item;
-    if (n && tallest == 0.f) tallest = item;
+    const int k = (static_cast<int>(classes >> (12 * c)) & 4095) * n_cols;
+    if (k == 0) continue;
+    const int height = c == 0 ? 320 : 64 * (5 - c);
+    item = static_cast<float>(3 * height + 4 * weight_rows) * static_cast<float>(steps) + kItemCost;
+    n += k;
+    sum += static_cast<float>(k) * item;
+    longest = fmaxf(longest, ceilf(static_cast<float>(n) * per_cu) * item);
   }
-  const int items = 2 * total * n_cols;
-  float narrow = tallest * cus;  // time x CUs
-  if (items > cus) narrow = fmaxf(narrow, sum * (2 * n_cols) + 0.65f * shortest * cus) + 1.5f * kNarrowItemCost * cus;
-  return narrow < (tallest + 128.f * steps) * cus;
+  return n > cus ? fmaxf(longest, sum * per_cu + 0.6f * item) : longest;
 }
 
 // One slot, then one entry of the table per thread.  What bounds it is latency: two dependent rounds of loads and a chain of LDS
@@ -149,8 +173,7 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
                                                            const void* const* __restrict__ w13_ptrs,
                                                            const void* const* __restrict__ w2_ptrs,
                                                            int S, int max_tiles, int n_cols1, int n_cols2, int steps1, int steps2,
-                                                           int cus,
-                                                           int32_t* __restrict__ table) {
+                                                           int cus, int32_t* __restrict__ table) {
   __shared__ alignas(16) int32_t rows_of[PROBE_MAX_SLOTS];
   __shared__ int32_t first_of[PROBE_MAX_SLOTS];
   __shared__ const void* w13_of[PROBE_MAX_SLOTS];
@@ -161,17 +184,21 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
   __shared__ int32_t wave_tot[kScheduleWaves];
   __shared__ unsigned long long wave_classes[kScheduleWaves];
   __shared__ int32_t n_big;                          // slots of more than 192 rows
+  __shared__ unsigned long long cut_classes[kCuts];  // tiles of each height with each cut
+  __shared__ int32_t cut_units, cut_chosen, cut_narrow;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   int m = -1;
+  const void *w13 = nullptr, *w2 = nullptr;  // on their way until the tiles are counted
   if (tid < S) {
     const int first = slot_offsets[tid];
     m = max(slot_offsets[tid + 1] - first, 0);
+    w13 = w13_ptrs[tid];
+    w2 = w2_ptrs[tid];
     first_of[tid] = first;
-    w13_of[tid] = w13_ptrs[tid];
-    w2_of[tid] = w2_ptrs[tid];
   }
   rows_of[tid] = m;  // entries past S are -1: they come before nobody
-  if (tid == 0) n_big = 0;
+  if (tid == 0) n_big = cut_units = cut_chosen = cut_narrow = 0;
+  if (tid < kCuts) cut_classes[tid] = 0;
   __syncthreads();
   // position of a slot = number of slots that come before it
   if (tid < S) {
@@ -186,9 +213,48 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
   }
   const int big_here = __popcll(__ballot(m > 192));
   if (lane == 0 && big_here) atomicAdd(&n_big, big_here);
+  // Meanwhile the last wave chooses the cut.  Lane l counts the tiles of cut l % 5 in every twelfth slot, then lane
+  // (cut, GEMM, width) estimates a launch.
+  if (wv == kScheduleWaves - 1) {
+    const int cut = lane % kCuts, part = lane / kCuts;
+    if (part < kCutParts) {
+      unsigned long long counts = 0;
+      int units = 0;
+      for (int u = part; u < S; u += kCutParts) {
+        const int r = rows_of[u];
+        counts += cut_slot(r, cut_cap(cut)).classes();
+        units = min(units + min((r + 63) >> 6, kCutUnits + 1), kCutUnits + 1);
+      }
+      atomicAdd(&cut_classes[cut], counts);
+      if (cut == 0) atomicAdd(&cut_units, units);
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (cut_units <= kCutUnits) {
+      const int c = min(lane >> 2, kCuts - 1), second = (lane >> 1) & 1, narrow = lane & 1;
+      const int n_cols = second ? (narrow ? (steps1 + 1) / 2 : n_cols2) : (narrow ? steps2 : n_cols1);  // columns of a k-step's 64: H, F
+      const unsigned long long counts = cut_classes[c];
+      const float t = launch_estimate(counts, n_cols, second ? steps2 : steps1, 256 >> narrow, cus);
+      const float other = __shfl_xor(t, 1, kWave), best = fminf(t, other);      // the better width of this GEMM
+      const float both = best + __shfl_xor(best, 2, kWave);                     // both GEMMs with this cut
+      const bool fits = c == 0 || tiles_of(counts) <= max_tiles;
+      const float standard = __shfl(both, 0, kWave);
+      const float mine = c == 0 ? kCutGain * standard : fits ? both : 3.0e38f;
+      float least = mine;
+#pragma unroll
+      for (int d = 4; d < kWave; d <<= 1) least = fminf(least, __shfl_xor(least, d, kWave));
+      const unsigned long long at = __ballot(lane < 4 * kCuts && mine == least);
+      const int chosen = __builtin_ctzll(at) >> 2;
+      const unsigned widths = static_cast<unsigned>(__ballot(narrow && t < other) >> (4 * chosen));
+      if (lane == 0) {
+        cut_chosen = chosen;
+        cut_narrow = ((widths >> 1) & 1) | ((widths >> 2) & 2);
+      }
+    }
+  }
   __syncthreads();
+  const int cap = cut_cap(__builtin_amdgcn_readfirstlane(cut_chosen));
   // exclusive prefix of tiles over the positions
-  const SlotCut my_cut = tid < S ? cut_slot(rows_of[slot_at[tid]]) : SlotCut{0, 0, 0};
+  const SlotCut my_cut = tid < S ? cut_slot(rows_of[slot_at[tid]], cap) : SlotCut{0, 0, 0, 0, 0};
   const int tiles = my_cut.tiles();
   const unsigned long long classes = my_cut.classes();
   int incl = tiles;
@@ -214,6 +280,8 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
     }
   }
   if (tid < S) {
+    w13_of[tid] = w13;
+    w2_of[tid] = w2;
     start[tid] = incl - tiles;
     class_start[tid] = c_incl - classes;
     if (tid == S - 1) {
@@ -230,9 +298,8 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
       static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(heights)));
   // taller than 192 rows; beyond 4095 tiles the twelve-bit fields run into each other and are not looked at
   const int n_tall = static_cast<int>(all_classes & 4095) + static_cast<int>((all_classes >> 12) & 4095);
-  const bool narrow1 = narrow_items(total, all_classes, n_cols1, steps1, kNarrowItems1, cus);
-  const bool narrow2 = narrow_items(total, all_classes, n_cols2, steps2, kNarrowItems2, cus);
-  const int cols1 = narrow1 ? 2 * n_cols1 : n_cols1;
+  const bool narrow1 = (cut_narrow & 1) != 0, narrow2 = (cut_narrow & 2) != 0;
+  const int cols1 = narrow1 ? steps2 : n_cols1;
   const bool tall_first = start[S] <= min(max_tiles, 4095) && n_tall * cols1 <= cus &&
                           static_cast<long>(start[S]) * cols1 > cus;
   if (tid < kTableHeaderInts) {
@@ -266,7 +333,7 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
       if (start[mid] <= t) lo = mid; else hi = mid;
     }
     const int slot = slot_at[lo], first = first_of[slot];
-    const SlotCut c = cut_slot(rows_of[slot]);
+    const SlotCut c = cut_slot(rows_of[slot], cap);
     int i = t - start[lo], row0 = first, height;
     if (i < c.n320) {
       row0 += i * 320;
@@ -274,9 +341,12 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
     } else if ((i -= c.n320) < c.n256) {
       row0 += c.n320 * 320 + i * 256;
       height = 256;
+    } else if ((i -= c.n256) < c.n_cap) {
+      row0 += i * c.cap;
+      height = c.cap;
     } else {
       i = 0;
-      row0 += c.n320 * 320 + c.n256 * 256;
+      row0 += c.n320 * 320 + c.n256 * 256 + c.n_cap * c.cap;
       height = c.tail;
     }
     int at = p;
@@ -797,10 +867,12 @@ __device__ __forceinline__ int skinny_steps(int items, int rows, int n_cols, int
 constexpr int kSkinnySlots = 512;                          // workgroups that run at once, two to a CU
 constexpr int kSkinnySpread1 = 400, kSkinnySpread2 = 384, kSkinnySpreadShort = 328;  // items up to which a single round (of more than 256) is
 constexpr int kSkinnySpreadSteps = 40;                     // spread: gemm1, gemm2 from these k-steps on, gemm2 of fewer
+constexpr int kSkinnySpreadMinSteps = 15;                  // 15 tiles of 832 x 1472 (345 items of 13) 28.7 / 30.8 us, 18 of 1088 x 1216 (342 of 17) 34.6 / 30.0
 constexpr int kSkinnySpreadLast = 160, kSkinnySpreadRounds = 2;  // gemm1: items of a last round that is spread over the first; rounds at most
 template <bool GEMM1>
 __device__ __forceinline__ int skinny_blocks(int n_tiles, int n_cols, int steps) {
   const int items = n_tiles * n_cols, rounds = (items + kSkinnySlots - 1) / kSkinnySlots, last = items - kSkinnySlots * (rounds - 1);
+  if (steps < kSkinnySpreadMinSteps) return n_cols;
   const bool spread = rounds == 1 ? last > kSkinnySlots / 2 && last <= (GEMM1 ? kSkinnySpread1 : steps >= kSkinnySpreadSteps ? kSkinnySpread2 : kSkinnySpreadShort)
                                   : GEMM1 && rounds <= kSkinnySpreadRounds && last <= kSkinnySpreadLast;
   return spread ? max(n_cols, kSkinnySlots * rounds / n_tiles) : n_cols;  // fewer than twice as many: 32 columns at least, or one block
@@ -1031,7 +1103,7 @@ __global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __rest
 
 struct FfnShape {
   bool skinny;  // the decode schedule
-  int max_tiles;
+  int max_tiles, cut_tiles;  // tiles at most: with the standard cut, with any
   size_t h_bytes, table_bytes;
   size_t partial_bytes;  // room that cutting the contraction takes; not demanded: without it the call runs uncut
 };
@@ -1052,6 +1124,7 @@ static FfnShape ffn_shape(int S, int H, int F, int max_rows) {
   s.skinny = short_slots || (tiles * ((F + kSkinnyCols1 - 1) / kSkinnyCols1) <= kSkinnyFewItems &&
                              tiles * ((H + kSkinnyCols2 - 1) / kSkinnyCols2) <= kSkinnyFewItems2);
   s.max_tiles = s.skinny ? max_rows / 64 + S : max_rows / 256 + S;
+  s.cut_tiles = max_rows / 64 + S;
   const int table_tiles = short_slots ? max_rows / 64 + S : max_rows / 256 + S;
   s.h_bytes = align_up(static_cast<size_t>(max_rows > 0 ? max_rows : 1) * F * sizeof(bf16_t), 256);
   s.table_bytes = align_up(kTableHeaderInts * sizeof(int32_t) + static_cast<size_t>(table_tiles) * sizeof(TileEntry), 256);
@@ -1211,8 +1284,12 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
   }
   const int n1 = (F + 127) / 128, n2 = (H + FBN - 1) / FBN;
   const dim3 grid(cus);  // persistent: one workgroup per CU, items drawn from the work queue
+  // the room of the table decides how many tiles a cut may make: the standard one always fits, and the 2 S of the decode schedule's last
+  // row count, or the room for pieces, hold every cut of most calls
+  const size_t room = (workspace_bytes - sh.h_bytes - kTableHeaderInts * sizeof(int32_t)) / sizeof(TileEntry);
+  const int max_tiles = static_cast<int>(std::min<size_t>(sh.cut_tiles, room));
   hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(kScheduleThreads), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S,
-                     sh.max_tiles, n1, n2, H / FBK, F / FBK, cus, table);
+                     max_tiles, n1, n2, H / FBK, F / FBK, cus, table);
   if (gather)
     hipLaunchKernelGGL(ffn_gemm1_kernel<true>, grid, dim3(512), kFfnLdsBytes, st, src, table, table, H, F, hbuf);
   else

@@ -530,6 +530,7 @@ def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes,
     (16, 3072, 1600),     # 400 of gemm1: the most of a single round; 384 of gemm2, of 25 k-steps: not
     (16, 3072, 2560),     # 384 of gemm2, of 40 k-steps: the most
     (13, 2944, 2624),     # 299 of gemm2; 533 of gemm1: a last round of 21
+    (16, 896, 1280),      # 320 of gemm1, of 14 k-steps: not
     (16, 2048, 2688),     # 672 of gemm1: the most of a second round; 256 of gemm2: one to a CU, not spread
     (13, 2432, 3328),     # 676 of gemm1: not
     (257, 64, 64)])       # one block of columns each, which stays one
@@ -660,6 +661,36 @@ def test_ffn_every_item_of_the_queue_is_run_once(oracle, probe, G, sizes, H, F, 
     assert (capacity // 64 + len(sizes)) * (F // 64) > 512 and capacity > 64 * len(sizes)     # past the decode schedule
     print("case queue", len(sizes), H, F, flush=True)
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F, extra_rows=spare)
+
+
+@pytest.mark.parametrize("sizes,H,F,spare", [
+    ([0, 200], 256, 2176, 700),                              # the estimate takes tiles of 64 rows, narrow items
+    ([200, 333, 70, 70, 200, 0, 333, 200], 320, 1280, 9),    # 128 rows, narrow in gemm2
+    ([390, 3, 256, 0, 450, 450], 768, 1280, 9),              # 192 rows, narrow
+    ([577, 3, 70, 512, 200, 3, 3], 2240, 1280, 9),           # 256 rows, narrow
+    ([3, 70, 577, 577, 390, 390, 390], 704, 1920, 9)])       # 256 rows, narrow in gemm2
+def test_ffn_tile_heights_by_estimated_time(oracle, probe, G, sizes, H, F, spare):
+    """Tiles of lower heights than the standard cut's where the estimate of the launches takes them: every output element against the
+    oracle, and the same bits from a workspace whose tile table holds the standard cut only."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=108)
+    S, n = len(sizes), sum(sizes)
+    cap = n + spare
+    assert (cap // 64 + S) * (F // 64) > 512 and cap > 64 * S                               # past the decode schedule
+    print("case heights", S, H, F, flush=True)
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F, extra_rows=spare)
+    gen = torch.Generator(device="cuda").manual_seed(H)
+    x = torch.randn((cap, H), generator=gen, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
+         torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16))
+    so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
+    tab = probe.WeightTable([w[0]] * S, [w[1]] * S)
+    up = lambda b: (b + 255) // 256 * 256
+    least = up(cap * F * 2) + up(128 + 32 * (cap // 256 + S))
+    assert least <= probe.grouped_ffn_workspace_bytes(S, H, F, cap)
+    ys = [probe.grouped_ffn(x, so, tab, workspace=torch.empty(b, dtype=torch.uint8, device="cuda"))[:n]
+          for b in (probe.grouped_ffn_workspace_bytes(S, H, F, cap), least)]
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1])
 
 
 @pytest.mark.parametrize("H,F,n", [(4096, 2048, 75), (2880, 2880, 40)])
