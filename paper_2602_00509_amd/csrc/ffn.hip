@@ -1109,17 +1109,27 @@ struct FfnShape {
 };
 
 // The decode schedule is chosen on the host from the capacity of the row space alone (the row counts live
-// on the device): at most kSkinnyRowsPerSlot rows per slot on average even if every pair were local, or so few items
+// on the device): at most 64 rows per slot (fewer where blocks are many) on average even if every pair were local, or so few items
 // that 64-row tiles give gemm1 at most two to a CU (a shared expert's single slot).  gemm2 may then have many more and still
 // gains, up to kSkinnyFewItems2.  One slot, tall tiles / this schedule: 454 rows of 7168 x 2048 176 / 84 us, 4000 of 7168 x 512
 // 200 / 144, 15000 of 4096 x 128 145 / 122, 16000 of 32768 x 64 (64256 items of gemm2) 959 / 743, 32000 of it (128256) 1208 / 1501.
+// Many slots of many column blocks have several items per CU with either schedule, and then a weight that two 64-row tiles of a slot stream
+// twice costs more than the schedule kernel: from more than 1024 blocks on (S x F / 64) the line lies lower.  This schedule / tall tiles:
+// 4096 x 14336, 10 slots (2240 blocks), 36 rows of capacity per slot 625 / 642 us, 40 732 / 658, 43 697 / 652, 59 799 / 703; 64 slots of
+// 7168 x 2048 (2048) 32 643 / 650, 40 816 / 807, 50 743 / 708, 58 694 / 664 and 709 / 714; 36 slots (1152) 46 357 / 368, 50 428 / 434, 54 406 / 397,
+// 62 436 / 413; but 18 slots of 2880 x 2880 (810) 52 133 / 133, 61 115 / 110, of 4096 x 1536 (432) 62 95 / 115.
 constexpr int kSkinnyRowsPerSlot = 64;
+constexpr int kSkinnyBlocks[2] = {1024, 1536}, kSkinnyRowsOfMore[2] = {52, 40};
+static int skinny_rows_per_slot(int S, int F) {
+  const long blocks = static_cast<long>(S) * ((F + kSkinnyCols1 - 1) / kSkinnyCols1);
+  return blocks > kSkinnyBlocks[1] ? kSkinnyRowsOfMore[1] : blocks > kSkinnyBlocks[0] ? kSkinnyRowsOfMore[0] : kSkinnyRowsPerSlot;
+}
 constexpr int kSkinnyFewItems2 = 65536;
 static_assert(kSkinnyFewItems2 * 512ll < (1ll << 32), "threads of one launch");
 
 static FfnShape ffn_shape(int S, int H, int F, int max_rows) {
   FfnShape s;
-  const bool short_slots = static_cast<long>(max_rows) <= static_cast<long>(kSkinnyRowsPerSlot) * S;
+  const bool short_slots = static_cast<long>(max_rows) <= static_cast<long>(skinny_rows_per_slot(S, F)) * S;
   const long tiles = static_cast<long>(max_rows) / 64 + S;
   s.skinny = short_slots || (tiles * ((F + kSkinnyCols1 - 1) / kSkinnyCols1) <= kSkinnyFewItems &&
                              tiles * ((H + kSkinnyCols2 - 1) / kSkinnyCols2) <= kSkinnyFewItems2);
@@ -1138,7 +1148,8 @@ static FfnShape ffn_shape(int S, int H, int F, int max_rows) {
 static size_t ffn_query_bytes(int S, int H, int F, int max_rows) {
   size_t bytes = ffn_shape(S, H, F, max_rows).h_bytes;
   const int short_rows = static_cast<int>(std::min<long>(max_rows, static_cast<long>(kSkinnyRowsPerSlot) * S));
-  bytes += std::max(ffn_shape(S, H, F, short_rows).table_bytes, ffn_shape(S, H, F, max_rows).table_bytes);
+  const size_t short_table = kTableHeaderInts * sizeof(int32_t) + static_cast<size_t>(short_rows / 64 + S) * sizeof(TileEntry);
+  bytes += std::max(align_up(short_table, 256), ffn_shape(S, H, F, max_rows).table_bytes);
   if (max_rows > 0 && (skinny_may_split(S, 1, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK) ||
                        skinny_last_adds(S, 1, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK) ||
                        skinny_may_split(S, 1, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK)))

@@ -556,6 +556,18 @@ def test_ffn_decode_schedule_spreads_columns(oracle, probe, G, n, H, F):
     assert torch.equal(plain[:rows], gathered[:rows])
 
 
+@pytest.mark.parametrize("S,F,rows", [(40, 2496, 40), (27, 2560, 52), (16, 4096, 64)])
+def test_ffn_either_side_of_the_decode_schedule(oracle, probe, G, S, F, rows):
+    """The last capacity that takes the decode schedule and the first that takes tall tiles, with 1560, 1080 and 1024 column blocks
+    of all slots: every output element of both against the oracle."""
+    cfg = wl.small_config(T=64, H=128, E=4, k=2, F=F, cid=109)
+    sizes = [(5 * i) % 17 for i in range(S)]
+    sizes[3] = 70
+    for cap in (rows * S, rows * S + 1):
+        print("case either side", S, F, cap, flush=True)
+        _ffn_against_oracle(oracle, probe, G, cfg, sizes, 2, seed=F, extra_rows=cap - sum(sizes))
+
+
 def test_ffn_contraction_is_not_cut_where_every_slot_can_hold_rows(oracle, probe, G):
     """At 40 rows of capacity per slot no adding kernel is launched although one slot alone holds rows: the call gives the
     same bits with and without room for partial sums.  Every element against the oracle."""
