@@ -890,6 +890,17 @@ struct SkinnyTile {
   const void* w;
 };
 
+// Inclusive sum over the lanes of a wave: inside each row of sixteen, then from the rows before.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // lane 15 of rows 0 and 2 to rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // lane 31 to rows 2 and 3
+  return v;
+}
+
 // REDUCE: `item` is a tile number (columns and piece are not looked at).  GEMM1: which of the two, columns of `cols` in n_cols blocks.
 template <bool REDUCE, bool LAST, bool GEMM1 = false>
 __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_offsets,
@@ -900,12 +911,17 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
   __shared__ int32_t found_row0, found_rows;
   __shared__ const void* found_w;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  if (tid == 0) found_rows = 0;
+  // Up to 128 slots every wave scans them for itself, two to a lane, without LDS and barriers: what the scan costs stands before an item's
+  // first load, 1.9 us of both kernels each in the middle (time stamps), and 0.6 to 1 us of a call less this way (8 slots of 512 x 1024
+  // 15.9 -> 15.2 us, two of 2880 x 2880 38.3 -> 37.3, 16 of 7168 x 2048 level).
+  const bool alone = S <= 2 * kWave;
+  const int at = alone ? lane : tid;
+  if (!alone && tid == 0) found_rows = 0;
   int first[2], m[2], t[2];
   const void* w[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int sl = 2 * tid + i;
+    const int sl = 2 * at + i;
     first[i] = m[i] = 0;
     w[i] = nullptr;
     if (sl < S) {
@@ -916,21 +932,20 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
     t[i] = (m[i] + 63) >> 6;
   }
   const int local = t[0] + t[1];
-  int incl = local;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int o = __shfl_up(incl, d, kWave);
-    if (lane >= d) incl += o;
-  }
-  if (lane == kWave - 1) wave_tot[wv] = incl;
-  __syncthreads();
+  int incl = wave_scan(local);
   int excl = incl - local, n_tiles = 0;
+  if (alone) {
+    n_tiles = __builtin_amdgcn_readlane(incl, kWave - 1);
+  } else {
+    if (lane == kWave - 1) wave_tot[wv] = incl;
+    __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    excl += i < wv ? wave_tot[i] : 0;
-    n_tiles += wave_tot[i];
+    for (int i = 0; i < 8; ++i) {
+      excl += i < wv ? wave_tot[i] : 0;
+      n_tiles += wave_tot[i];
+    }
+    n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
   }
-  n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
   // These integer divisions follow one another before an item's first load.  A call that is not cut makes one of them and not
   // all six: 60 slots of 704 x 2816 (2640 items of 11 k-steps), gemm1 93.7 -> 89.0 us.
   int tile = item;
@@ -966,6 +981,26 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
   // columns, dealt out to 8 XCDs, an XCD has no two items with the same rows
   out.spread = n_cols < 16 ||
                static_cast<long>(all_rows) * steps <= 96l * max(n_tiles * n_cols * out.pieces, 2 * kSkinnyItems);
+  if (alone) {
+    out.row0 = out.rows = 0;
+    out.w = nullptr;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const unsigned long long hit = __ballot(tile >= excl && tile < excl + t[i]);  // one lane for one i when the tile exists
+      if (hit) {
+        const int src = __builtin_ctzll(hit), r = (tile - __builtin_amdgcn_readlane(excl, src)) * 64;
+        out.row0 = __builtin_amdgcn_readlane(first[i], src) + r;
+        out.rows = __builtin_amdgcn_readlane(m[i], src) - r;
+        if (!REDUCE) {
+          const uint64_t p = reinterpret_cast<uint64_t>(w[i]);
+          const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(p), src), hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(p >> 32), src);
+          out.w = reinterpret_cast<const void*>(static_cast<uint64_t>(hi) << 32 | lo);
+        }
+      }
+      excl += t[i];
+    }
+    return out.rows > 0;
+  }
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if (tile >= excl && tile < excl + t[i]) {  // true for exactly one (thread, i) when the tile exists
