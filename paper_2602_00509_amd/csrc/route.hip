@@ -691,6 +691,22 @@ __device__ __forceinline__ void top2_merge(float& m1, float& m2) {
   m1 = fmaxf(m1, o1);
 }
 
+template <int CTRL>
+__device__ __forceinline__ void top2_merge_dpp(float& m1, float& m2) {
+  const float o1 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m1), CTRL, 0xf, 0xf, false));
+  const float o2 = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m2), CTRL, 0xf, 0xf, false));
+  m2 = fmaxf(fminf(m1, o1), fmaxf(m2, o2));
+  m1 = fmaxf(m1, o1);
+}
+// The same over the lanes that share a group, `lanes` = 1, 2, 4, 8 or 16 consecutive ones of a row: neighbours, pairs, then the mirror
+// images of eight and sixteen lanes, each of which lies in the other half.
+__device__ __forceinline__ void top2_merge_group(float& m1, float& m2, int lanes) {
+  if (lanes >= 2) top2_merge_dpp<0xb1>(m1, m2);    // quad_perm 1 0 3 2
+  if (lanes >= 4) top2_merge_dpp<0x4e>(m1, m2);    // quad_perm 2 3 0 1
+  if (lanes >= 8) top2_merge_dpp<0x141>(m1, m2);   // row_half_mirror
+  if (lanes >= 16) top2_merge_dpp<0x140>(m1, m2);  // row_mirror
+}
+
 // ---- 3b. group-limited gate -----------------------------------------------------------------
 // Same lane layout and logit loading as above.  Per token: scores s (sigmoid of each logit, or the
 // softmax), selection scores c = s + select_bias, a score per group of E / n_group consecutive
@@ -714,6 +730,7 @@ __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
   const bool vec = (E & 3) == 0;
   const bool vec_in = (ld & 3) == 0 && aligned_f4(partial);
   const int gs = E / n_group;
+  const bool aligned_groups = group_top <= 2 && gs >= 4 && gs <= 64 && (gs & (gs - 1)) == 0;
   int gid[NL];      // group of entry i, -1 past E
   float sb[NL];
 #pragma unroll
@@ -784,9 +801,45 @@ __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
     // group_top <= 2 a (largest, second) pair is merged across the row with max / min, which is
     // exact and order-free; otherwise group_top rounds of arg-max inside the group.
     float gscore[U];
+    unsigned allowed[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) gscore[u] = ninf;
-    if (group_top <= 2) {
+    for (int u = 0; u < U; ++u) {
+      gscore[u] = ninf;
+      allowed[u] = 0u;
+    }
+    if (aligned_groups) {
+      // Every group is 1, 2, 4, 8 or 16 lanes of one register piece: all of a piece's groups are merged at once, with the same bits as
+      // group by group, where each pass looked at every entry (call, group by group / at once, 8 groups: 75 tokens x 7168 x 256 19.5 /
+      // 18.5 us, 128 x 4096 x 128 14.2 / 13.4, 16384 x 1024 x 64 27.5 / 25.9).
+      float piece[U][NV];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          float m1 = c[u][4 * i], m2 = ninf;
+#pragma unroll
+          for (int j = 1; j < 4; ++j) {
+            m2 = fmaxf(m2, fminf(m1, c[u][4 * i + j]));
+            m1 = fmaxf(m1, c[u][4 * i + j]);
+          }
+          top2_merge_group(m1, m2, gs >> 2);
+          piece[u][i] = group_top == 2 ? m1 + m2 : m1;
+        }
+      for (int r = 0; r < topk_group; ++r) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          float open[NV];
+          int cand[NV];
+#pragma unroll
+          for (int i = 0; i < NV; ++i) open[i] = gid[4 * i] >= 0 && !((allowed[u] >> gid[4 * i]) & 1u) ? piece[u][i] : ninf;
+          const float best = row_max(tree_max(open));
+#pragma unroll
+          for (int i = 0; i < NV; ++i)
+            cand[i] = gid[4 * i] >= 0 && !((allowed[u] >> gid[4 * i]) & 1u) && piece[u][i] == best ? gid[4 * i] : INT_MAX;
+          allowed[u] |= 1u << (row_min_i(tree_min(cand)) & 15);
+        }
+      }
+    } else if (group_top <= 2) {
       for (int j = 0; j < n_group; ++j) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -844,10 +897,7 @@ __global__ __launch_bounds__(256) void gate_grouped_topk_kernel(
       }
     }
     // allowed groups
-    unsigned allowed[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) allowed[u] = 0u;
-    for (int r = 0; r < topk_group; ++r) {
+    for (int r = 0; r < topk_group && !aligned_groups; ++r) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const bool open = sub < n_group && !((allowed[u] >> sub) & 1u);

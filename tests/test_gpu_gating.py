@@ -118,6 +118,27 @@ def test_route_grouped_parity(T, H, E, k, n_group, topk_group, group_top, scorin
     check(g, o, k, topk_group, n_group, scale)
 
 
+@pytest.mark.parametrize("T,E,n_group,topk_group,group_top", [
+    (130, 64, 16, 5, 2), (70, 52, 13, 4, 1),      # groups of 4 experts: one lane
+    (65, 128, 16, 3, 2), (40, 72, 9, 2, 2),       # 8, 16, 32, 64: pairs of lanes, quads, eight, a whole row
+    (99, 192, 12, 4, 2), (33, 224, 7, 3, 2), (257, 192, 3, 2, 1), (6150, 128, 8, 4, 2),
+    (50, 256, 2, 1, 2), (50, 120, 5, 2, 2)])      # 128, 24: group by group
+def test_group_sizes(T, E, n_group, topk_group, group_top):
+    """Groups that are whole lanes of one register piece, merged together, and others: parity, and with equal scores everywhere the
+    lowest groups and the lowest experts."""
+    k = min(8, topk_group * (E // n_group))
+    x, w, sb, bias = make_case(T + 3 * E, T, 128, E)
+    kw = dict(scoring="sigmoid", n_group=n_group, topk_group=topk_group, group_top=group_top, k=k, renormalize=True, routed_scale=1.0)
+    o = oracle.route_grouped(x, w, bias, max((T + 1) // 2, 1), sb, **kw)
+    g = probe.route_grouped(dev_bf16(x), torch.from_numpy(w).cuda(), torch.from_numpy(bias).cuda(), max((T + 1) // 2, 1),
+                            torch.from_numpy(sb).cuda(), want_scores=True, **kw)
+    torch.cuda.synchronize()
+    check(g, o, k, topk_group, n_group, 1.0)
+    same = probe.route_grouped(dev_bf16(x), torch.zeros((E, 128), device="cuda"), None, None, None, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(same["idx"].cpu(), torch.arange(k, dtype=torch.int32).expand(T, k))
+
+
 def test_one_group_softmax_equals_route_topk_bitwise():
     x, w, sb, bias = make_case(5, 500, 256, 128)
     dx, dw, db = dev_bf16(x), torch.from_numpy(w).cuda(), torch.from_numpy(bias).cuda()
