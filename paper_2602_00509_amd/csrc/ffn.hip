@@ -27,6 +27,7 @@
 // dropped the same way; the row space is never padded.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
 #include "mfma_pipeline.hpp"
@@ -766,7 +767,7 @@ __global__ __launch_bounds__(512, 2) void ffn_gemm2_kernel(const bf16_t* __restr
 // of every active slot's weights through the chip.  What matters then is that every CU pulls a distinct
 // slice at all times, so the work is cut finer and kept resident: tiles of 64 rows x 64 h columns (gemm1:
 // 64 gate + 64 up weight rows) or 64 rows x 128 output columns (gemm2), three LDS stages of 24 KB, two
-// workgroups per CU (sixteen waves, 72 KB of LDS each), one work item per workgroup in table order.  A
+// workgroups per CU (sixteen waves, 72 KB of LDS each), one work item per workgroup in slot order.  A
 // slot with more than 64 rows is simply several row tiles: correct for any input, tuned for short slots.
 constexpr int kSkinnyLdsBytes = 3 * (64 + 128) * 128;  // 72 KB
 constexpr int kSkinnyCols1 = 64, kSkinnyCols2 = 128;   // h columns / y columns per work item
@@ -860,15 +861,17 @@ __device__ __forceinline__ int skinny_steps(int items, int rows, int n_cols, int
 // third of the width, 55.9 / 65.2 us; 224 items of 7168 x 2048 112 / 126), so only where the last round is at most that full.
 // Usual blocks / spread: gemm1 of 9, 10, 12 slots of 7168 x 2048 (288, 320, 384 items) 166 / 148, 179 / 164, 203 / 189, 11 of 4096 x 1536
 // (264) 95 / 84, but 14 slots of it (336 of 64 k-steps, 252 rows) 108 / 106 and 14 of 7168 x 2048 (448) 217 / 218; second round: 13 of
-// 2880 x 2880 (585) 131 / 127, 20 of 7168 x 2048 (640) 313 / 306, 24 (768) 355 / 361; third: 36
-// (1152) 536 / 528, with 351 rows 535 / 543.  gemm2 of 9 and 10 slots of 4096 x 14336 (288, 320)
-// 578 / 537 and 625 / 593, 13 of 2880 x 2880 (299) 131 / 124, 9 and 10 of 4096 x 1536 (288 and 320 of 24 k-steps) 69 / 66 and 75 / 71, but 6 and 7 of 7168 x 2048
-// (336 and 392 of 32 k-steps) 107 / 110 and 112 / 117, second round level.
-constexpr int kSkinnySlots = 512;                          // workgroups that run at once, two to a CU
-constexpr int kSkinnySpread1 = 400, kSkinnySpread2 = 384, kSkinnySpreadShort = 328;  // items up to which a single round (of more than 256) is
-constexpr int kSkinnySpreadSteps = 40;                     // spread: gemm1, gemm2 from these k-steps on, gemm2 of fewer
-constexpr int kSkinnySpreadMinSteps = 15;                  // 15 tiles of 832 x 1472 (345 items of 13) 28.7 / 30.8 us, 18 of 1088 x 1216 (342 of 17) 34.6 / 30.0
-constexpr int kSkinnySpreadLast = 160, kSkinnySpreadRounds = 2;  // gemm1: items of a last round that is spread over the first; rounds at most
+// 2880 x 2880 (585) 131 / 127, 20 of 7168 x 2048 (640) 313 / 306, 24 (768) 355 / 361; third: 36 (1152) 536 / 528, with 351 rows 535 / 543.
+// gemm2 of 9 and 10 slots of 4096 x 14336 (288, 320) 578 / 537 and 625 / 593, 13 of 2880 x 2880 (299) 131 / 124, 9 and 10 of 4096 x 1536
+// (288 and 320 of 24 k-steps) 69 / 66 and 75 / 71, but 6 and 7 of 7168 x 2048 (336 and 392 of 32 k-steps) 107 / 110 and 112 / 117, second
+// round level.
+constexpr int kSkinnySlots = 512;  // workgroups that run at once, two to a CU
+// items up to which a single round (of more than 256) is spread: gemm1, gemm2 from kSkinnySpreadSteps k-steps on, gemm2 of fewer
+constexpr int kSkinnySpread1 = 400, kSkinnySpread2 = 384, kSkinnySpreadShort = 328, kSkinnySpreadSteps = 40;
+// 15 tiles of 832 x 1472 (345 items of 13 k-steps) 28.7 / 30.8 us, 18 of 1088 x 1216 (342 of 17) 34.6 / 30.0
+constexpr int kSkinnySpreadMinSteps = 15;
+// gemm1: items of a last round that is spread over the first; rounds at most
+constexpr int kSkinnySpreadLast = 160, kSkinnySpreadRounds = 2;
 template <bool GEMM1>
 __device__ __forceinline__ int skinny_blocks(int n_tiles, int n_cols, int steps) {
   const int items = n_tiles * n_cols, rounds = (items + kSkinnySlots - 1) / kSkinnySlots, last = items - kSkinnySlots * (rounds - 1);
@@ -878,6 +881,96 @@ __device__ __forceinline__ int skinny_blocks(int n_tiles, int n_cols, int steps)
   return spread ? max(n_cols, kSkinnySlots * rounds / n_tiles) : n_cols;  // fewer than twice as many: 32 columns at least, or one block
 }
 
+// Few rows in every slot and few items that are not cut: at most 64 items leave three of four CUs without one, and an item of 192 or 128
+// weight rows is then bound by what one CU can have in flight and by the three stages that it fills before its first product.  Such a
+// GEMM takes items a quarter as wide, one to a CU: 32 weight rows (16 gate and 16 up, or 32 columns of y), the eight waves an eighth of K
+// each, weights and activations loaded straight to the registers that the matrix instructions read (nothing is shared between the
+// waves, so LDS would only be a detour), and the eight sums added through LDS at the end.  Measured, per call, before / after: one slot of
+// 1536 x 1536 19.2 / 12.9 us, two of 2048 x 768 18.3 / 12.2, one of 2880 x 2880 25.2 / 19.5, four of 1024 x 3072 34.1 / 20.8, five of
+// 1024 x 768 with 25 rows 14.5 / 11.2.  From 65 to 99 items some CUs have two narrow items and some one, and it is level or loses up to 1 us
+// (90 of 23 k-steps 17.5 / 18.3); from 100 to 128 nearly all have two, and up to four rows, whose loads are few beside the weights',
+// gain again (110 of 32 k-steps 31.6 / 28.9, 120 of 63 51.3 / 46.4; 16 rows: 112 of 29 48.3 / 52.1).  More lose at once (160 of 32 k-steps 36.8 /
+// 37.6).  Batches of four k-steps: two batches in turn lose 10 to 25 % (most waves have two to eight steps, and loads past them cost issue).
+constexpr int kFewRows = 16, kFewRowsItems = 64;
+constexpr int kFewerRows = 4, kFewerRowsItems[2] = {100, 128}, kFewerRowsSteps = 16;
+constexpr int kFewRowsCols1 = 16, kFewRowsCols2 = 32;  // h columns / y columns per item
+// The test for them is in instances of their own, which the host launches where the tiles at capacity make up to 128 items and hold up to
+// kFewRows rows on average: in a call that turns out to have more rows or items it costs 0.2 to 0.4 us (code in front of the main loop:
+// nine slots of 1024 x 1024 16.5 / 16.9).
+constexpr int kFewRowsLikely = 128;
+constexpr int kFewRowsUnroll = 4;
+constexpr uint32_t kPast = 0xffffff00u;  // past every descriptor: zeros without traffic
+
+// sums[wave][fragment][lane]: what this wave's eighth of K gives of two fragments (16 weight rows each) x 16 activation rows
+template <typename WeightOff>
+__device__ __forceinline__ void few_rows_products(__amdgpu_buffer_rsrc_t rA, bool a_in, uint32_t a_off, __amdgpu_buffer_rsrc_t rW, const WeightOff& w_off,
+                                                  int K, f32x4 (*sums)[2][kWave]) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int steps = K / 32, per = (steps + 7) / 8, s0 = wv * per, s1 = min(s0 + per, steps);
+  f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  for (int s = s0; s < s1; s += kFewRowsUnroll) {
+    u32x4 a[kFewRowsUnroll], w[kFewRowsUnroll][2];
+#pragma unroll
+    for (int u = 0; u < kFewRowsUnroll; ++u) {
+      const uint32_t k = (s + u) * 64u;  // bytes
+      const bool in = s + u < s1;        // the wave's part
+      w[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rW, in ? w_off(0) + k : kPast, 0, 0));
+      w[u][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rW, in ? w_off(1) + k : kPast, 0, 0));
+      a[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rA, in && a_in ? a_off + k : kPast, 0, 0));
+    }
+    __builtin_amdgcn_sched_barrier(0);  // all loads of the batch before the first product waits
+#pragma unroll
+    for (int u = 0; u < kFewRowsUnroll; ++u) {
+      acc[0] = mfma_16x16x32(w[u][0], a[u], acc[0]);
+      acc[1] = mfma_16x16x32(w[u][1], a[u], acc[1]);
+    }
+  }
+  sums[wv][0][lane] = acc[0];
+  sums[wv][1][lane] = acc[1];
+  __syncthreads();
+}
+
+__device__ __forceinline__ f32x4 few_rows_sum(const f32x4 (*sums)[2][kWave], int f, int lane) {
+  f32x4 v = sums[0][f][lane];
+#pragma unroll
+  for (int q = 1; q < 8; ++q) v += sums[q][f][lane];
+  return v;
+}
+
+template <bool GATHER>
+__device__ __forceinline__ void few_rows_gemm1(const RowSource& src, const bf16_t* __restrict__ w13, int row0, int rows, int n0, int H, int F,
+                                               bf16_t* __restrict__ hbuf, f32x4 (*sums)[2][kWave]) {
+  const int lane = threadIdx.x & 63, r = lane & 15, kq = 16 * (lane >> 4);
+  const __amdgpu_buffer_rsrc_t rA = GATHER ? make_rsrc(src.base, static_cast<size_t>(src.n_tokens) * H * 2)
+                                           : make_rsrc(src.base + static_cast<size_t>(row0) * H, static_cast<size_t>(rows) * H * 2);
+  const __amdgpu_buffer_rsrc_t rW = make_rsrc(w13, static_cast<size_t>(2) * F * H * 2);
+  int row = r;
+  if (GATHER && r < rows) row = min(max(src.row_pair[row0 + r], 0) / src.k, src.n_tokens - 1);
+  const uint32_t w0 = (n0 + r) * (H * 2u) + kq, up = F * (H * 2u);
+  few_rows_products(rA, r < rows, row * (H * 2u) + kq, rW, [&](int f) { return w0 + (f ? up : 0); }, H, sums);
+  // lane l of a fragment holds weight rows 4 (l / 16) .. + 3 of activation row l % 16
+  if (threadIdx.x < kWave && r < rows) {
+    const f32x4 gate = few_rows_sum(sums, 0, lane), upv = few_rows_sum(sums, 1, lane);
+    *reinterpret_cast<u32x2*>(hbuf + static_cast<size_t>(row0 + r) * F + n0 + 4 * (lane >> 4)) =
+        u32x2{pack_bf16x2(swiglu(gate[0], upv[0]), swiglu(gate[1], upv[1])), pack_bf16x2(swiglu(gate[2], upv[2]), swiglu(gate[3], upv[3]))};
+  }
+}
+
+__device__ __forceinline__ void few_rows_gemm2(const bf16_t* __restrict__ hbuf, const bf16_t* __restrict__ w2, int row0, int rows, int n0, int H,
+                                               int F, bf16_t* __restrict__ y, f32x4 (*sums)[2][kWave]) {
+  const int lane = threadIdx.x & 63, r = lane & 15, kq = 16 * (lane >> 4);
+  const __amdgpu_buffer_rsrc_t rA = make_rsrc(hbuf + static_cast<size_t>(row0) * F, static_cast<size_t>(rows) * F * 2);
+  const __amdgpu_buffer_rsrc_t rW = make_rsrc(w2, static_cast<size_t>(H) * F * 2);
+  const uint32_t w0 = (n0 + r) * (F * 2u) + kq, next = 16 * (F * 2u);
+  few_rows_products(rA, r < rows, r * (F * 2u) + kq, rW, [&](int f) { return w0 + (f ? next : 0); }, F, sums);
+  if (threadIdx.x < 2 * kWave && r < rows) {
+    const int f = threadIdx.x >> 6;
+    const f32x4 v = few_rows_sum(sums, f, lane);
+    *reinterpret_cast<u32x2*>(y + static_cast<size_t>(row0 + r) * H + n0 + 16 * f + 4 * (lane >> 4)) =
+        u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+  }
+}
+
 // Item number -> (slot, first row, rows to the end of the slot, weight pointer, piece of K) without a tile table: slots
 // in their own order, ceil(M / 64) tiles each.  Every workgroup finds its own tile with one scan over the
 // (at most 1024) slots, two per thread, so the decode schedule needs no schedule kernel in front of it.
@@ -885,6 +978,7 @@ __device__ __forceinline__ int skinny_blocks(int n_tiles, int n_cols, int steps)
 struct SkinnyTile {
   int row0, rows;
   int n0, n_end;  // columns
+  bool few;       // few rows: an item of few_rows_gemm1 / 2
   int tile, col, piece, pieces, piece_steps;
   bool spread;  // the items begin at different k-steps (skinny_start)
   const void* w;
@@ -902,10 +996,11 @@ __device__ __forceinline__ int wave_scan(int v) {
 }
 
 // REDUCE: `item` is a tile number (columns and piece are not looked at).  GEMM1: which of the two, columns of `cols` in n_cols blocks.
-template <bool REDUCE, bool LAST, bool GEMM1 = false>
+// FEW: items of few rows are possible.
+template <bool REDUCE, bool LAST, bool GEMM1 = false, bool FEW = false>
 __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_offsets,
                                               const void* const* __restrict__ w_ptrs, int S, int item, int cols,
-                                              int n_cols, int steps, bool may_split, SkinnyTile& out) {
+                                              int n_cols, int steps, bool may_split, int few_items, SkinnyTile& out) {
   const int all_rows = slot_offsets[S] - slot_offsets[0];
   __shared__ int32_t wave_tot[8];
   __shared__ int32_t found_row0, found_rows;
@@ -958,10 +1053,18 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
     out.pieces = (steps + piece_steps - 1) / piece_steps;
   }
   if (!REDUCE) {
-    const int blocks = piece_steps ? n_cols : skinny_blocks<GEMM1>(n_tiles, n_cols, steps);
+    const int n_items = n_tiles * n_cols, most = max(m[0], m[1]);
+    out.few = FEW && alone && 4 * n_items <= few_items && !piece_steps &&
+              (n_items <= kFewRowsItems ? !__ballot(most > kFewRows)
+                                        : n_items >= kFewerRowsItems[0] && n_items <= kFewerRowsItems[1] && steps >= kFewerRowsSteps &&
+                                              !__ballot(most > kFewerRows));
+    const int blocks = out.few ? cols / (GEMM1 ? kFewRowsCols1 : kFewRowsCols2)
+                               : piece_steps ? n_cols : skinny_blocks<GEMM1>(n_tiles, n_cols, steps);
     tile = item / blocks;
     out.col = item - tile * blocks;
-    if (blocks > n_cols) {
+    if (out.few) {
+      out.n0 = out.col * (GEMM1 ? kFewRowsCols1 : kFewRowsCols2);
+    } else if (blocks > n_cols) {
       const int groups = cols >> 3, small = groups / blocks, more = groups - small * blocks;  // of eight columns: 16-byte stores of y
       out.n0 = 8 * (out.col * small + min(out.col, more));
       out.n_end = out.n0 + 8 * (small + (out.col < more ? 1 : 0));
@@ -1040,21 +1143,25 @@ __device__ __forceinline__ int skinny_start(const SkinnyTile& e, int klen) {
 }
 
 // CLEAR: the arrival counters are cleared for gemm2's launch
-template <bool GATHER, bool CLEAR>
+template <bool GATHER, bool CLEAR, bool FEW>
 __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w13_ptrs, int S,
-                                                                  int H, int F, int may_split,
+                                                                  int H, int F, int may_split, int few_items,
                                                                   bf16_t* __restrict__ hbuf, float* partial,
                                                                   uint32_t* __restrict__ arrivals) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
   if (CLEAR && blockIdx.x == 0 && threadIdx.x < kArrivalWords) arrivals[threadIdx.x] = 0;
   SkinnyTile e;
-  if (!skinny_locate<false, false, true>(slot_offsets, w13_ptrs, S, blockIdx.x, F, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
-                                         may_split, e))
+  if (!skinny_locate<false, false, true, FEW>(slot_offsets, w13_ptrs, S, blockIdx.x, F, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK,
+                                               may_split, few_items, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
+  if (FEW && e.few) {
+    few_rows_gemm1<GATHER>(src, w, e.row0, e.rows, e.n0, H, F, hbuf, reinterpret_cast<f32x4(*)[2][kWave]>(smem));
+    return;
+  }
   if (e.pieces == 1) {
     gemm1_tile<1, GATHER, 1, 3>(src, w, e.row0, e.rows, e.n0, e.n_end, H, F, hbuf, smem, nullptr, nullptr, 0, 0,
                                 nullptr, skinny_start(e, H));
@@ -1068,20 +1175,24 @@ __global__ __launch_bounds__(512, 4) void ffn_gemm1_skinny_kernel(RowSource src,
 #endif
 }
 
-template <bool LAST>
+template <bool LAST, bool FEW>
 __global__ __launch_bounds__(512, 4) void ffn_gemm2_skinny_kernel(const bf16_t* __restrict__ hbuf,
                                                                   const int32_t* __restrict__ slot_offsets,
                                                                   const void* const* __restrict__ w2_ptrs, int S,
-                                                                  int H, int F, int may_split,
+                                                                  int H, int F, int may_split, int few_items,
                                                                   bf16_t* __restrict__ y, float* partial,
                                                                   uint32_t* arrivals) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ u32x4 smem[];
   SkinnyTile e;
-  if (!skinny_locate<false, LAST>(slot_offsets, w2_ptrs, S, blockIdx.x, H, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK,
-                                  may_split, e))
+  if (!skinny_locate<false, LAST, false, FEW>(slot_offsets, w2_ptrs, S, blockIdx.x, H, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK,
+                                       may_split, few_items, e))
     return;
   const bf16_t* w = static_cast<const bf16_t*>(e.w);
+  if (FEW && e.few) {
+    few_rows_gemm2(hbuf, w, e.row0, e.rows, e.n0, H, F, y, reinterpret_cast<f32x4(*)[2][kWave]>(smem));
+    return;
+  }
   if (e.pieces == 1) {
     gemm2_tile<1, 1, 3>(hbuf, w, e.row0, e.rows, e.n0, e.n_end, H, F, y, smem, nullptr, nullptr, 0, 0, nullptr,
                         skinny_start(e, F));
@@ -1104,7 +1215,7 @@ __global__ __launch_bounds__(512) void ffn_skinny_add_kernel(const float* __rest
                                                              bf16_t* __restrict__ out) {
   SkinnyTile e;
   const int row = blockIdx.x & 63;
-  if (!skinny_locate<true, false>(slot_offsets, nullptr, S, blockIdx.x >> 6, out_cols, n_cols, steps, true, e)) return;
+  if (!skinny_locate<true, false>(slot_offsets, nullptr, S, blockIdx.x >> 6, out_cols, n_cols, steps, true, 0, e)) return;
   if (e.pieces == 1 || row >= e.rows) return;
   const int ld = SWIGLU ? 2 * out_cols : out_cols;
   const float* base = partial + static_cast<size_t>(e.tile * e.pieces) * 64 * ld + static_cast<size_t>(row) * ld;
@@ -1222,14 +1333,20 @@ static int ffn_prepare(int* cus) {
   if (err == hipSuccess)
     err = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm2_kernel),
                               hipFuncAttributeMaxDynamicSharedMemorySize, kFfnLdsBytes);
-  const void* skinny[6] = {reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<false, false>),
-                           reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<false, true>),
-                           reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<true, false>),
-                           reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<true, true>),
-                           reinterpret_cast<const void*>(ffn_gemm2_skinny_kernel<false>),
-                           reinterpret_cast<const void*>(ffn_gemm2_skinny_kernel<true>)};
-  for (int i = 0; i < 6 && err == hipSuccess; ++i)
-    err = hipFuncSetAttribute(skinny[i], hipFuncAttributeMaxDynamicSharedMemorySize, kSkinnyLdsBytes);
+  const void* skinny[] = {reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<false, false, false>),
+                          reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<false, false, true>),
+                          reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<false, true, false>),
+                          reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<false, true, true>),
+                          reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<true, false, false>),
+                          reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<true, false, true>),
+                          reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<true, true, false>),
+                          reinterpret_cast<const void*>(ffn_gemm1_skinny_kernel<true, true, true>),
+                          reinterpret_cast<const void*>(ffn_gemm2_skinny_kernel<false, false>),
+                          reinterpret_cast<const void*>(ffn_gemm2_skinny_kernel<false, true>),
+                          reinterpret_cast<const void*>(ffn_gemm2_skinny_kernel<true, false>),
+                          reinterpret_cast<const void*>(ffn_gemm2_skinny_kernel<true, true>)};
+  for (const void* kernel : skinny)
+    if (err == hipSuccess) err = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kSkinnyLdsBytes);
   if (err != hipSuccess) {
     set_error("probe_grouped_ffn: cannot reserve %d bytes of LDS: %s", kFfnLdsBytes, hipGetErrorString(err));
     return PROBE_EHIP;
@@ -1305,24 +1422,31 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
       if (split) n = std::max<long>(n, kSkinnyItems);
       return n > kSkinnySlots / 2 && n < kSkinnySlots * spread_rounds ? (n + kSkinnySlots - 1) / kSkinnySlots * kSkinnySlots : n;
     };
-    const dim3 g1(items(tiles * n1, split1, kSkinnySpreadRounds)), g2(items(tiles * n2, split2, 1));
+    // Items of few rows are a quarter as wide; 0: none.  A grid for kFewRowsItems of them is enough unless 100 to 128 are likely.
+    auto few_items = [S, max_rows](long n, int steps) {
+      if (S > 2 * kWave || n > kFewRowsLikely || max_rows > static_cast<long>(kFewRows) * S) return 0l;
+      return n >= kFewerRowsItems[0] && n <= kFewerRowsItems[1] && steps >= kFewerRowsSteps ? 4 * n : std::min<long>(4 * n, 4 * kFewRowsItems);
+    };
+    const long few1 = few_items(tiles * n1, H / FBK), few2 = few_items(tiles * n2, F / FBK);
+    const dim3 g1(std::max(items(tiles * n1, split1, kSkinnySpreadRounds), few1)), g2(std::max(items(tiles * n2, split2, 1), few2));
     // tiles that can be split at all: two pieces or more need kSkinnyItems / 2 items or fewer
     const int add1 = split1 ? std::min(tiles, kSkinnyItems / 2 / n1) : 0;
     const int add2 = split2 && !last_adds ? std::min(tiles, kSkinnyItems / 2 / n2) : 0;
-    auto gemm1 = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, g1, dim3(512), kSkinnyLdsBytes, st, src, slot_offsets, w13_ptrs, S, H, F, split1, hbuf, partial,
-                         arrivals);
+    auto gemm1 = [&](auto gathers, auto clears, auto few) {
+      hipLaunchKernelGGL((ffn_gemm1_skinny_kernel<gathers.value, clears.value, few.value>), g1, dim3(512), kSkinnyLdsBytes, st, src, slot_offsets,
+                         w13_ptrs, S, H, F, split1, static_cast<int>(few1), hbuf, partial, arrivals);
     };
-    if (gather)
-      last_adds ? gemm1(ffn_gemm1_skinny_kernel<true, true>) : gemm1(ffn_gemm1_skinny_kernel<true, false>);
-    else
-      last_adds ? gemm1(ffn_gemm1_skinny_kernel<false, true>) : gemm1(ffn_gemm1_skinny_kernel<false, false>);
+    auto gemm2 = [&](auto last, auto few) {
+      hipLaunchKernelGGL((ffn_gemm2_skinny_kernel<last.value, few.value>), g2, dim3(512), kSkinnyLdsBytes, st, hbuf, slot_offsets, w2_ptrs, S, H, F,
+                         split2, static_cast<int>(few2), y, partial, arrivals);
+    };
+    auto either = [](bool v, auto&& f) { v ? f(std::true_type()) : f(std::false_type()); };
+    either(gather, [&](auto g) { either(last_adds, [&](auto c) { either(few1 > 0, [&](auto few) { gemm1(g, c, few); }); }); });
     if (add1 > 0)
       hipLaunchKernelGGL(ffn_skinny_add_kernel<true>, dim3(add1 * 64), dim3(512), 0, st, partial, slot_offsets, S, n1,
                          H / FBK, F, hbuf);
     // A call that is not cut takes the instance whose loads of the row total lie in front of the scan (two slots of 832 x 768 14.05 -> 13.9).
-    hipLaunchKernelGGL(last_adds || !split2 ? ffn_gemm2_skinny_kernel<true> : ffn_gemm2_skinny_kernel<false>, g2, dim3(512), kSkinnyLdsBytes,
-                       st, hbuf, slot_offsets, w2_ptrs, S, H, F, split2, y, partial, arrivals);
+    either(last_adds || !split2, [&](auto l) { either(few2 > 0, [&](auto few) { gemm2(l, few); }); });
     if (add2 > 0)
       hipLaunchKernelGGL(ffn_skinny_add_kernel<false>, dim3(add2 * 64), dim3(512), 0, st, partial, slot_offsets, S, n2,
                          F / FBK, H, y);

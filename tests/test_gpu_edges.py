@@ -556,6 +556,37 @@ def test_ffn_decode_schedule_spreads_columns(oracle, probe, G, n, H, F):
     assert torch.equal(plain[:rows], gathered[:rows])
 
 
+@pytest.mark.parametrize("sizes,H,F", [
+    ([16, 1, 0, 9], 64, 64),          # two steps of 32 for eight waves
+    ([16, 3], 1088, 2048),            # 64 items of gemm1, 34 steps of 32: six waves of five, one of four
+    ([17, 3], 1088, 2048),            # a row too many
+    ([3, 16], 2048, 2112),            # 66 items of gemm1: too many; 32 of gemm2, of 33 k-steps
+    ([4, 0, 4, 4, 4, 4], 1024, 1280), # 100 items of gemm1, of 16 k-steps, up to four rows
+    ([4, 5, 4, 4, 4], 1024, 1280),    # a row too many
+    ([4, 1, 2, 4], 1152, 2048),       # 128 items of gemm1
+    ([2, 1, 4], 960, 2112),           # 99 items of gemm1, of 15 k-steps: neither
+    ([3] + [0] * 127, 320, 192),      # the most slots that every wave scans for itself
+    ([3] + [0] * 128, 320, 192)])     # one more: not
+def test_ffn_few_rows_in_every_slot(oracle, probe, G, sizes, H, F):
+    """Either side of the lines up to which items of few rows are a quarter as wide and stream straight to registers: every output
+    element against the oracle, and the rows gathered on load bit for bit the same."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=111)
+    print("case few rows", len(sizes), H, F, flush=True)
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F)
+    n, rows = len(sizes), sum(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(F)
+    x = torch.randn((rows + 5, H), generator=gen, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
+         torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16))
+    tab = probe.WeightTable([w[0]] * n, [w[1]] * n)
+    so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
+    order = torch.randperm(rows + 5, device="cuda", generator=gen).to(torch.int32)
+    plain = probe.grouped_ffn(x[order.long()].contiguous(), so, tab)
+    gathered = probe.grouped_ffn_gather(x, order, 1, so, tab)
+    torch.cuda.synchronize()
+    assert torch.equal(plain[:rows], gathered[:rows])
+
+
 @pytest.mark.parametrize("S,F,rows", [(40, 2496, 40), (27, 2560, 52), (16, 4096, 64)])
 def test_ffn_either_side_of_the_decode_schedule(oracle, probe, G, S, F, rows):
     """The last capacity that takes the decode schedule and the first that takes tall tiles, with 1560, 1080 and 1024 column blocks
