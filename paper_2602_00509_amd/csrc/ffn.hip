@@ -886,7 +886,7 @@ __device__ __forceinline__ int skinny_blocks(int n_tiles, int n_cols, int steps)
 // GEMM takes items a quarter as wide, one to a CU: 32 weight rows (16 gate and 16 up, or 32 columns of y), the eight waves an eighth of K
 // each, weights and activations loaded straight to the registers that the matrix instructions read (nothing is shared between the
 // waves, so LDS would only be a detour), and the eight sums added through LDS at the end.  Measured, per call, before / after: one slot of
-// 1536 x 1536 19.2 / 12.9 us, two of 2048 x 768 18.3 / 12.2, one of 2880 x 2880 25.2 / 19.5, four of 1024 x 3072 34.1 / 20.8, five of
+// 1536 x 1536 19.2 / 12.9 us, two of 2048 x 768 18.3 / 12.2, one of 2880 x 2880 25.2 / 19.5, four of 3072 x 1024 34.1 / 20.8, five of
 // 1024 x 768 with 25 rows 14.5 / 11.2.  From 65 to 99 items some CUs have two narrow items and some one, and it is level or loses up to 1 us
 // (90 of 23 k-steps 17.5 / 18.3); from 100 to 128 nearly all have two, and up to four rows, whose loads are few beside the weights',
 // gain again (110 of 32 k-steps 31.6 / 28.9, 120 of 63 51.3 / 46.4; 16 rows: 112 of 29 48.3 / 52.1).  More lose at once (160 of 32 k-steps 36.8 /
