@@ -1063,8 +1063,8 @@ struct RouteShape {
 
 // Logits (T x E) up to which a gate takes the direct kernel, and gates that take it at any batch (16 experts are one
 // fragment: a 128-expert tile would be mostly padding; figures at small_gate_frags).  Whole call, direct against tiled:
-// 256 tokens x 128 experts 12.4 / 15.7 us, 512 x 128 15.6 / 15.8 and 256 x 256 21.5 / 21.8 (H = 4096, 7168).  Where H is not a multiple of 64 the other kernel is the
-// register-staged one and the line lies higher: 1000 tokens x 250 experts x 7160 47.6 us, 1500 tokens staged 50.6.
+// 256 tokens x 128 experts 12.4 / 15.7 us (H = 4096; what is faster above the line is at direct_of_more).  Where H is not a multiple of 64 the
+// other kernel is the register-staged one and the line lies higher: 1000 tokens x 250 experts x 7160 47.6 us, 1500 tokens staged 50.6.
 // A launch holds fewer than 2^32 threads: 512 for 32 tokens here, a quarter of that in the tiled kernels, which therefore take
 // the batches above kDirectTokens.
 constexpr int kDirectLogits = 32768, kDirectExperts = 16, kDirectTokens = 1 << 27;
@@ -1138,7 +1138,39 @@ static void choose_gate_tiles(RouteShape& s, int T, int ksteps) {
   s.stepwise = s.bm == 128 || s.k_chunk / GBK > steps_room;
 }
 
-static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
+// What the direct kernel's launch is: `frags`, `per_wave` and the slices.
+static void direct_shape(RouteShape& s, int T, int H, int E, int max_split) {
+  // eight fragments of tokens share a gate fragment where there are that many
+  s.frags = E <= kDirectExperts ? small_gate_frags(T, H, E) : (T <= 16 ? 1 : (T <= 32 ? 2 : (T <= 64 ? 4 : 8)));
+  const int k32 = (H + 31) / 32, wgs = ((E + 15) / 16) * ((T + 16 * s.frags - 1) / (16 * s.frags));
+  int split = wgs > 0 ? 256 / wgs : 1;  // one workgroup per CU
+  split = split < 1 ? 1 : (split > max_split ? max_split : split);
+  s.per_wave = (k32 + 8 * split - 1) / (8 * split);
+  s.ks = (k32 + 8 * s.per_wave - 1) / (8 * s.per_wave);
+}
+
+// Gates above kDirectLogits that the direct kernel still does faster (H % 64 == 0).  What it costs goes with the k32 per wave.  Call, tiled /
+// direct.  One k32 gains from H = 1024 on: 1000 tokens x 1024 x 128 13.3 / 12.0 us, 256 x 2048 x 256 1.14 x, 384 x 2880 x 96 13.2 / 11.7; with a
+// shorter H it loses where the experts fill their tiles badly (1000 x 512 x 48 8.5 / 9.4).  Two gain where the tiled kernel's columns of 128
+// experts are mostly full, one at any batch, two up to two token blocks: 320 x 4096 x 128 14.6 / 13.1, 640 x 2880 x 128 15.1 / 14.0, 512 x 4096
+// x 96 14.5 / 13.5, 256 x 4096 x 256 17.0 / 15.9; but 1000 x 2880 x 80 14.6 / 15.1, 192 x 2880 x 200 13.9 / 15.0.  Three lose (640 x 4096 x 128
+// 16.3 / 18.2).  An fp32 gate that two token blocks share needs no launch that splits it and gains more (256 x 4096 x 256 24.1 / 15.2), also
+// where packed planes lose; but packed planes and the fp32 gate give the same bits, so they go one way.  Probabilities against 64 bits over
+// 545 gates from 128 to 7168 wide: 3.6e-8 of the largest (mean of the rms; 1.3e-6 at most) tiled, 3.5e-8 (1.3e-6) with those above.
+// The top-k adds the slices, eight at once: two k32 in fourteen slices lose (384 x 7168 x 96 16.8 / 17.1), and so do the most logits (1000 x
+// 2048 x 128 15.0 / 15.2).
+constexpr int kDirectMore = 131072, kDirectTwo = 98304, kDirectBlocks = 256, kDirectWide = 1024, kDirectEmpty = 32, kDirectSlices = 8;
+static bool direct_of_more(const RouteShape& direct, int T, int H, int E) {
+  const long logits = static_cast<long>(T) * E;
+  if (logits > kDirectMore || direct.ks > direct.ks_room) return false;
+  const bool full = direct.nt * GBN - E <= kDirectEmpty;
+  return (direct.per_wave == 1 && H >= kDirectWide) ||
+         (direct.per_wave == 2 && full && logits <= kDirectTwo && direct.ks <= kDirectSlices &&
+          (direct.nt == 1 || (direct.nt == 2 && T <= kDirectBlocks)));
+}
+
+// The residual's GEMMs keep to the line of kDirectLogits.
+static RouteShape route_shape(int T, int H, int E, bool residual = false, int max_split = kMaxSplitK) {
   RouteShape s;
   s.dma = gate_dma(H, E);
   s.nt = (E + GBN - 1) / GBN;
@@ -1156,15 +1188,17 @@ static RouteShape route_shape(int T, int H, int E, int max_split = kMaxSplitK) {
   s.direct = static_cast<long>(T) * E <= (H % 64 == 0 ? 1 : 8) * kDirectLogits ||
              (E <= kDirectExperts && T <= kDirectTokens);
   s.frags = s.per_wave = 0;
-  if (s.direct) {
-    // eight fragments of tokens share a gate fragment where there are that many
-    s.frags = E <= kDirectExperts ? small_gate_frags(T, H, E) : (T <= 16 ? 1 : (T <= 32 ? 2 : (T <= 64 ? 4 : 8)));
-    const int k32 = (H + 31) / 32, wgs = ((E + 15) / 16) * ((T + 16 * s.frags - 1) / (16 * s.frags));
-    int split = wgs > 0 ? 256 / wgs : 1;  // one workgroup per CU
-    split = split < 1 ? 1 : (split > max_split ? max_split : split);
-    s.per_wave = (k32 + 8 * split - 1) / (8 * split);
-    s.ks = (k32 + 8 * s.per_wave - 1) / (8 * s.per_wave);
-  } else if (s.dma && T > 0) {
+  if (!s.direct && s.dma && T > 0 && !residual) {
+    RouteShape d = s;
+    direct_shape(d, T, H, E, max_split);
+    if (direct_of_more(d, T, H, E)) {
+      s = d;
+      s.direct = true;
+    }
+  } else if (s.direct) {
+    direct_shape(s, T, H, E, max_split);
+  }
+  if (!s.direct && s.dma && T > 0) {
     choose_gate_tiles(s, T, ksteps);
   }
   s.planes_bytes = align_up(static_cast<size_t>(3) * E * H * sizeof(bf16_t), 256);
@@ -1238,8 +1272,8 @@ static RouteLayout route_layout(int T, int H, int E, int D, bool packed = false)
   L.upartial_bytes = L.a_bytes = L.b_bytes = 0;
   int extra = 0;
   if (D > 0) {
-    L.resid = route_shape(T, H, D);
-    L.resid2 = route_shape(T, 3 * D, E, kResidSplitK);
+    L.resid = route_shape(T, H, D, true);
+    L.resid2 = route_shape(T, 3 * D, E, true, kResidSplitK);
     L.upartial_bytes = L.resid.partial_bytes;
     L.a_bytes = align_up(static_cast<size_t>(T > 0 ? T : 1) * 3 * D * sizeof(bf16_t), 256);
     L.b_bytes = L.resid2.planes_bytes;

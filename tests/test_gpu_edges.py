@@ -209,6 +209,43 @@ def test_route_topk_a_wave_or_sixteen_lanes_per_token(oracle, probe, G, T, H, E,
                                       np.bincount(got["idx"].cpu().numpy().ravel(), minlength=E))
 
 
+@pytest.mark.parametrize("T,H,E,k", [
+    (1000, 1024, 128, 8), (1025, 1024, 128, 8), (1000, 960, 128, 8),  # one k32 per wave: the most logits, too many, too short an H
+    (384, 2880, 96, 4), (1300, 1088, 100, 4),                         # one and two; a last expert fragment of four
+    (640, 2880, 96, 4), (640, 2880, 95, 4),                           # two: the emptiest column of experts, emptier
+    (768, 2048, 128, 8), (769, 2048, 128, 8),                         # two: the most logits, too many
+    (512, 4096, 128, 8), (513, 4096, 128, 8),                         # two and three
+    (256, 4096, 224, 8), (257, 4096, 224, 8), (140, 2880, 256, 8)])   # two columns: two token blocks and three
+def test_route_more_logits_without_lds(oracle, probe, G, T, H, E, k):
+    """Either side of the lines up to which gates of more than 32768 logits go from global memory to the matrix cores: every token
+    against the oracle, the packed gate bit for bit the fp32 one, a batch in the workspace of exactly its size, and under capture."""
+    print("case more logits T=%d H=%d E=%d" % (T, H, E), flush=True)
+    rng = np.random.default_rng(T + E)
+    x = wl.f32_to_bf16_bits(rng.standard_normal((T, H), dtype=np.float32))
+    wg = (rng.standard_normal((E, H), dtype=np.float32) * np.float32(0.05))
+    d_x, d_w = G.dev_bf16(x), torch.from_numpy(wg).cuda()
+    ws = torch.full((probe.route_topk_workspace_bytes(T, H, E, k),), 0xff, dtype=torch.uint8, device="cuda")
+    g = probe.route_topk(d_x, d_w, None, None, k, True, want_probs=True, workspace=ws)
+    p = probe.route_topk(d_x, probe.PackedGate(d_w), None, None, k, True, want_probs=True)
+    torch.cuda.synchronize()
+    for key in ("idx", "w", "probs", "counts"):
+        assert torch.equal(g[key], p[key]), key
+    o = oracle.route_topk(x, wg, None, T, k, True)
+    G.check_route(g, o, k, True)
+    np.testing.assert_allclose(g["probs"].cpu().numpy(), o["probs"], rtol=0, atol=G.PROB_ATOL)
+    out = {key: torch.empty_like(g[key]) for key in ("idx", "w", "counts")}
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        probe.route_topk(d_x, d_w, None, None, k, True, out=out, workspace=ws)
+    for _ in range(3):
+        for key in out:
+            out[key].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for key in out:
+            assert torch.equal(out[key], g[key]), key
+
+
 def test_route_small_gate_on_more_token_blocks_than_65535(oracle, probe, G):
     """A gate of at most 16 experts takes 32 tokens per workgroup at any batch: more of them than the y and z dimensions of a
     launch can hold.  Every token bit for bit as in batches of a million, the last ones against the oracle."""
