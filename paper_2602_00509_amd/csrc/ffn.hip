@@ -854,31 +854,35 @@ __device__ __forceinline__ int skinny_steps(int items, int rows, int n_cols, int
   return split > 1 ? (steps + split - 1) / split : 0;
 }
 
-// Column blocks of a row tile, `items` = row tiles x n_cols blocks of the usual width.  Two items to a CU stream at one rate wherever they
-// are, but a number of items that leaves some CUs with two and some with one (or, further up, a last round that is nearly empty) makes
-// the call as long as the fuller ones.  The columns are then dealt evenly to as many blocks as give 512 workgroups, or a multiple, one
-// item each.  Narrower blocks alone lose: fewer weight rows in flight per workgroup (7 slots of 4096 x 1536, 168 items of gemm1 or 511 of a
-// third of the width, 55.9 / 65.2 us; 224 items of 7168 x 2048 112 / 126), so only where the last round is at most that full.
-// Usual blocks / spread: gemm1 of 9, 10, 12 slots of 7168 x 2048 (288, 320, 384 items) 166 / 148, 179 / 164, 203 / 189, 11 of 4096 x 1536
-// (264) 95 / 84, but 14 slots of it (336 of 64 k-steps, 252 rows) 108 / 106 and 14 of 7168 x 2048 (448) 217 / 218; second round: 13 of
-// 2880 x 2880 (585) 131 / 127, 20 of 7168 x 2048 (640) 313 / 306, 24 (768) 355 / 361; third: 36 (1152) 536 / 528, with 351 rows 535 / 543.
-// gemm2 of 9 and 10 slots of 4096 x 14336 (288, 320) 578 / 537 and 625 / 593, 13 of 2880 x 2880 (299) 131 / 124, 9 and 10 of 4096 x 1536
-// (288 and 320 of 24 k-steps) 69 / 66 and 75 / 71, but 6 and 7 of 7168 x 2048 (336 and 392 of 32 k-steps) 107 / 110 and 112 / 117, second
-// round level.
+// Column blocks of a row tile that are cut into two halves, `items` = row tiles x n_cols blocks of the usual width.  Two items to a CU stream at
+// one rate wherever they are, but a number of items that leaves some CUs with two and some with one (or, further up, a last round that is nearly
+// empty) makes the call as long as the fuller ones.  As many blocks are then halved as give 512 workgroups, or a multiple, one item each, the
+// whole ones first, so that with up to 256 of them no CU gets two.  A half begins at the k-step of its block (skinny_start): every element's sum
+// is made in the same order as without the cut, whatever else the call holds.  Columns dealt evenly to the 512 were up to 3 % faster still, but
+// a block's start, and with it the low bits of its elements, then followed the number of tiles.  Narrower blocks alone lose: fewer weight rows
+// in flight per workgroup (7 slots of 4096 x 1536, 168 items of gemm1 or 511 of a third of the width, 55.9 / 65.2 us; 224 items of 7168 x 2048
+// 112 / 126), so only where the last round is at most that full.
+// FFN calls, usual blocks / halved: 9, 10, 11 slots of 7168 x 2048 (288, 320, 352 items of gemm1) 164 / 147, 178 / 165, 186 / 175; 11 to 16 of
+// 4096 x 1536 (264 to 384) 97 / 84, 99 / 88, 100 / 93, 104 / 99, 111 / 109; 400 items level to 0.5 % slower.  Second round: 17 and 18 of 7168 x
+// 2048 (544, 576) 281 / 266, 289 / 278, 608 and 624 items 0.988 to 1.02 x, 640 0.954 to 1.006 x, 672 slower.  gemm2 of 9, 10, 11 slots of 4096 x
+// 14336 (288, 320, 352) 586 / 552, 631 / 603, 686 / 663; 12 of it (384) 726 / 734, five shapes more of 368 to 384 items 1.01 to 1.04 x.
+// gemm2 of fewer than 40 k-steps: 264 to 324 items 1.01 to 1.1 x; columns dealt evenly lost from 336 on (6 and 7 slots of 7168 x 2048 107 / 110
+// and 112 / 117), and nothing is halved there.
 constexpr int kSkinnySlots = 512;  // workgroups that run at once, two to a CU
-// items up to which a single round (of more than 256) is spread: gemm1, gemm2 from kSkinnySpreadSteps k-steps on, gemm2 of fewer
-constexpr int kSkinnySpread1 = 400, kSkinnySpread2 = 384, kSkinnySpreadShort = 328, kSkinnySpreadSteps = 40;
-// 15 tiles of 832 x 1472 (345 items of 13 k-steps) 28.7 / 30.8 us, 18 of 1088 x 1216 (342 of 17) 34.6 / 30.0
-constexpr int kSkinnySpreadMinSteps = 15;
-// gemm1: items of a last round that is spread over the first; rounds at most
-constexpr int kSkinnySpreadLast = 160, kSkinnySpreadRounds = 2;
+// items up to which a single round (of more than 256) is filled: gemm1 and gemm2 from kSkinnyHalvesSteps k-steps on, gemm2 of fewer
+constexpr int kSkinnyHalves = 384, kSkinnyHalvesShort = 328, kSkinnyHalvesSteps = 40;
+// k-steps from which blocks are halved: 15 tiles of 832 x 1472 (345 items of 13 k-steps), columns dealt evenly, 28.7 / 30.8 us, 18 of 1088 x 1216
+// (342 of 17) 34.6 / 30.0
+constexpr int kSkinnyHalvesMinSteps = 15;
+// gemm1: items of a last round that is filled; rounds at most
+constexpr int kSkinnyHalvesLast = 112, kSkinnyHalvesRounds = 2;
 template <bool GEMM1>
-__device__ __forceinline__ int skinny_blocks(int n_tiles, int n_cols, int steps) {
+__device__ __forceinline__ int skinny_halved(int n_tiles, int n_cols, int steps) {
   const int items = n_tiles * n_cols, rounds = (items + kSkinnySlots - 1) / kSkinnySlots, last = items - kSkinnySlots * (rounds - 1);
-  if (steps < kSkinnySpreadMinSteps) return n_cols;
-  const bool spread = rounds == 1 ? last > kSkinnySlots / 2 && last <= (GEMM1 ? kSkinnySpread1 : steps >= kSkinnySpreadSteps ? kSkinnySpread2 : kSkinnySpreadShort)
-                                  : GEMM1 && rounds <= kSkinnySpreadRounds && last <= kSkinnySpreadLast;
-  return spread ? max(n_cols, kSkinnySlots * rounds / n_tiles) : n_cols;  // fewer than twice as many: 32 columns at least, or one block
+  if (steps < kSkinnyHalvesMinSteps) return 0;
+  const bool fill = rounds == 1 ? last > kSkinnySlots / 2 && last <= (GEMM1 || steps >= kSkinnyHalvesSteps ? kSkinnyHalves : kSkinnyHalvesShort)
+                                : GEMM1 && rounds <= kSkinnyHalvesRounds && last <= kSkinnyHalvesLast;
+  return fill ? max(kSkinnySlots * rounds / n_tiles - n_cols, 0) : 0;  // fewer than n_cols: more than half of the places have an item
 }
 
 // Few rows in every slot and few items that are not cut: at most 64 items leave three of four CUs without one, and an item of 192 or 128
@@ -1058,20 +1062,21 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
               (n_items <= kFewRowsItems ? !__ballot(most > kFewRows)
                                         : n_items >= kFewerRowsItems[0] && n_items <= kFewerRowsItems[1] && steps >= kFewerRowsSteps &&
                                               !__ballot(most > kFewerRows));
-    const int blocks = out.few ? cols / (GEMM1 ? kFewRowsCols1 : kFewRowsCols2)
-                               : piece_steps ? n_cols : skinny_blocks<GEMM1>(n_tiles, n_cols, steps);
-    tile = item / blocks;
-    out.col = item - tile * blocks;
-    if (out.few) {
-      out.n0 = out.col * (GEMM1 ? kFewRowsCols1 : kFewRowsCols2);
-    } else if (blocks > n_cols) {
-      const int groups = cols >> 3, small = groups / blocks, more = groups - small * blocks;  // of eight columns: 16-byte stores of y
-      out.n0 = 8 * (out.col * small + min(out.col, more));
-      out.n_end = out.n0 + 8 * (small + (out.col < more ? 1 : 0));
-    } else {
-      constexpr int kWidth = GEMM1 ? kSkinnyCols1 : kSkinnyCols2;
-      out.n0 = out.col * kWidth;
+    constexpr int kWidth = GEMM1 ? kSkinnyCols1 : kSkinnyCols2, kFewWidth = GEMM1 ? kFewRowsCols1 : kFewRowsCols2;
+    const int halved = out.few || piece_steps ? 0 : skinny_halved<GEMM1>(n_tiles, n_cols, steps);
+    const int whole = out.few ? cols / kFewWidth : n_cols - halved, wholes = n_tiles * whole;
+    if (!halved || item < wholes) {
+      tile = item / whole;
+      out.col = item - tile * whole;
+      out.n0 = out.col * (out.few ? kFewWidth : kWidth);
       out.n_end = min(out.n0 + kWidth, cols);
+    } else {  // the whole blocks of all tiles, then the halves
+      tile = (item - wholes) / (2 * halved);
+      const int half = item - wholes - 2 * halved * tile;
+      out.col = whole + (half >> 1);
+      const int width = min(kWidth, cols - out.col * kWidth) >> 1;  // a last block of gemm2 may have 64 columns
+      out.n0 = out.col * kWidth + (half & 1) * width;
+      out.n_end = out.n0 + width;
     }
     if (piece_steps) {
       const int q = tile;
@@ -1417,10 +1422,10 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     const bool split2 = last_adds || (room && skinny_may_split(S, max_rows, n2, F / FBK));
     uint32_t* arrivals = last_adds ? reinterpret_cast<uint32_t*>(table) : nullptr;
     // a split call has at most kSkinnyItems items, one that is not split tiles * n
-    // and one that is spread whole rounds of kSkinnySlots
-    auto items = [](long n, bool split, int spread_rounds) {
+    // and one whose blocks are halved at most whole rounds of kSkinnySlots
+    auto items = [](long n, bool split, int rounds) {
       if (split) n = std::max<long>(n, kSkinnyItems);
-      return n > kSkinnySlots / 2 && n < kSkinnySlots * spread_rounds ? (n + kSkinnySlots - 1) / kSkinnySlots * kSkinnySlots : n;
+      return n > kSkinnySlots / 2 && n < kSkinnySlots * rounds ? (n + kSkinnySlots - 1) / kSkinnySlots * kSkinnySlots : n;
     };
     // Items of few rows are a quarter as wide; 0: none.  A grid for kFewRowsItems of them is enough unless 100 to 128 are likely.
     auto few_items = [S, max_rows](long n, int steps) {
@@ -1428,7 +1433,7 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
       return n >= kFewerRowsItems[0] && n <= kFewerRowsItems[1] && steps >= kFewerRowsSteps ? 4 * n : std::min<long>(4 * n, 4 * kFewRowsItems);
     };
     const long few1 = few_items(tiles * n1, H / FBK), few2 = few_items(tiles * n2, F / FBK);
-    const dim3 g1(std::max(items(tiles * n1, split1, kSkinnySpreadRounds), few1)), g2(std::max(items(tiles * n2, split2, 1), few2));
+    const dim3 g1(std::max(items(tiles * n1, split1, kSkinnyHalvesRounds), few1)), g2(std::max(items(tiles * n2, split2, 1), few2));
     // tiles that can be split at all: two pieces or more need kSkinnyItems / 2 items or fewer
     const int add1 = split1 ? std::min(tiles, kSkinnyItems / 2 / n1) : 0;
     const int add2 = split2 && !last_adds ? std::min(tiles, kSkinnyItems / 2 / n2) : 0;

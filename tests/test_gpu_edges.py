@@ -563,21 +563,22 @@ def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes,
 
 
 @pytest.mark.parametrize("n,H,F", [
-    (13, 2560, 1280),     # 260 items of either GEMM: columns dealt to 39 blocks of 4 or 5 (8 or 9) groups of eight
-    (16, 3072, 1600),     # 400 of gemm1: the most of a single round; 384 of gemm2, of 25 k-steps: not
-    (16, 3072, 2560),     # 384 of gemm2, of 40 k-steps: the most
-    (13, 2944, 2624),     # 299 of gemm2; 533 of gemm1: a last round of 21
+    (13, 2560, 1280),     # 260 items of either GEMM: 19 of 20 column blocks are halved
+    (16, 3072, 1536),     # 384 of gemm1: the most of a single round; 384 of gemm2, of 24 k-steps: not
+    (11, 1024, 2240),     # 385 of gemm1: not
+    (16, 3072, 2560),     # 384 of gemm2, of 40 k-steps: the most; 640 of gemm1: not
+    (13, 2880, 2624),     # 299 of gemm2, whose last block has 64 columns; 533 of gemm1: a last round of 21
     (16, 896, 1280),      # 320 of gemm1, of 14 k-steps: not
-    (16, 2048, 2688),     # 672 of gemm1: the most of a second round; 256 of gemm2: one to a CU, not spread
-    (13, 2432, 3328),     # 676 of gemm1: not
-    (257, 64, 64)])       # one block of columns each, which stays one
-def test_ffn_decode_schedule_spreads_columns(oracle, probe, G, n, H, F):
-    """Decode schedule: numbers of items at the limits between which the columns of a tile are dealt to more blocks; every output
-    element against the oracle, and the rows gathered on load bit for bit the same."""
+    (16, 2048, 2496),     # 624 of gemm1: the most of a second round; 256 of gemm2: one to a CU
+    (15, 2432, 2688),     # 630 of gemm1: not
+    (257, 64, 64)])       # one block of columns each, of one k-step
+def test_ffn_decode_schedule_halves_blocks(oracle, probe, G, n, H, F):
+    """Decode schedule: numbers of items at the limits between which column blocks are halved; every output element against the
+    oracle, and the rows gathered on load bit for bit the same."""
     cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=107)
     sizes = [1 + 7 * i % 5 for i in range(n)]
     sizes[n // 2] = 64
-    print("case spread", n, H, F, flush=True)
+    print("case halves", n, H, F, flush=True)
     _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F)
     gen = torch.Generator(device="cuda").manual_seed(F)
     rows = sum(sizes)
@@ -591,6 +592,38 @@ def test_ffn_decode_schedule_spreads_columns(oracle, probe, G, n, H, F):
     gathered = probe.grouped_ffn_gather(x, order, 1, so, tab)
     torch.cuda.synchronize()
     assert torch.equal(plain[:rows], gathered[:rows])
+
+
+@pytest.mark.parametrize("n,H,F", [
+    (13, 2560, 1280),     # 260 items of either GEMM
+    (14, 4096, 1536),     # 336 of gemm1
+    (16, 3072, 2560),     # 384 of gemm2
+    (13, 2880, 2624),     # 299 of gemm2; 533 of gemm1
+    (17, 2048, 2048)])    # 544 of gemm1; 272 of gemm2, of 32 k-steps
+def test_ffn_bits_of_a_row_do_not_follow_the_number_of_tiles(probe, n, H, F):
+    """Decode schedule, no contraction cut: a row has the same bits in a call whose column blocks are halved to fill the CUs and in calls
+    of fewer slots, whose blocks are whole."""
+    print("case bits of a row", n, H, F, flush=True)
+    sizes = [17 + 5 * i % 23 for i in range(n)]     # more rows than the items of few rows take
+    gen = torch.Generator(device="cuda").manual_seed(n + H)
+    x = torch.randn((sum(sizes), H), generator=gen, device="cuda").to(torch.bfloat16)
+    w13 = [torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16) for _ in range(3)]
+    w2 = [torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16) for _ in range(3)]
+    up = lambda b: (b + 255) // 256 * 256
+
+    def call(lo, hi):
+        rows = sum(sizes[lo:hi])
+        first = sum(sizes[:lo])
+        so = torch.from_numpy(np.r_[0, np.cumsum(sizes[lo:hi])].astype(np.int32)).cuda()
+        tab = probe.WeightTable([w13[i % 3] for i in range(lo, hi)], [w2[i % 3] for i in range(lo, hi)])
+        ws = torch.empty(up(rows * F * 2) + up(128 + 32 * (rows // 64 + hi - lo)), dtype=torch.uint8, device="cuda")  # no room for pieces
+        return probe.grouped_ffn(x[first:first + rows].contiguous(), so, tab, workspace=ws)
+
+    few = 256 // max(F // 64, (H + 127) // 128)     # slots that make one item per CU at most
+    whole = call(0, n)
+    parts = torch.cat([call(lo, min(lo + few, n)) for lo in range(0, n, few)])
+    torch.cuda.synchronize()
+    assert torch.equal(whole, parts)
 
 
 @pytest.mark.parametrize("sizes,H,F", [
