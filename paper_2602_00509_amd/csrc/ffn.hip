@@ -1295,12 +1295,13 @@ static FfnShape ffn_shape(int S, int H, int F, int max_rows) {
 
 // What the workspace query returns: the most that any call of up to max_rows rows can use, so that a workspace sized for the
 // largest batch serves every smaller one, at its full speed, and the query does not fall as max_rows grows.  h grows with
-// the rows, the tile table is longest at the last row count of the 64-row tiles, and what may be cut at all may be at one row.
+// the rows, and what may be cut at all may be at one row.  The tile table has room for every cut that the schedule kernel looks at: the
+// standard one always, others up to kCutUnits tiles (six slots of 111 to 557 rows of 704 x 1024 take 16 tiles, 30.9 us; with room for 12
+// tiles, which is what the standard cut and the decode schedule need, nine and 35.2).
 static size_t ffn_query_bytes(int S, int H, int F, int max_rows) {
-  size_t bytes = ffn_shape(S, H, F, max_rows).h_bytes;
-  const int short_rows = static_cast<int>(std::min<long>(max_rows, static_cast<long>(kSkinnyRowsPerSlot) * S));
-  const size_t short_table = kTableHeaderInts * sizeof(int32_t) + static_cast<size_t>(short_rows / 64 + S) * sizeof(TileEntry);
-  bytes += std::max(align_up(short_table, 256), ffn_shape(S, H, F, max_rows).table_bytes);
+  const FfnShape s = ffn_shape(S, H, F, max_rows);
+  const size_t table = kTableHeaderInts * sizeof(int32_t) + static_cast<size_t>(std::min(s.cut_tiles, kCutUnits)) * sizeof(TileEntry);
+  size_t bytes = s.h_bytes + std::max(align_up(table, 256), s.table_bytes);
   if (max_rows > 0 && (skinny_may_split(S, 1, (F + kSkinnyCols1 - 1) / kSkinnyCols1, H / FBK) ||
                        skinny_last_adds(S, 1, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK) ||
                        skinny_may_split(S, 1, (H + kSkinnyCols2 - 1) / kSkinnyCols2, F / FBK)))
@@ -1459,8 +1460,7 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
   }
   const int n1 = (F + 127) / 128, n2 = (H + FBN - 1) / FBN;
   const dim3 grid(cus);  // persistent: one workgroup per CU, items drawn from the work queue
-  // the room of the table decides how many tiles a cut may make: the standard one always fits, and the 2 S of the decode schedule's last
-  // row count, or the room for pieces, hold every cut of most calls
+  // the room of the table decides how many tiles a cut may make: the standard one always fits, a workspace of the query's size holds any
   const size_t room = (workspace_bytes - sh.h_bytes - kTableHeaderInts * sizeof(int32_t)) / sizeof(TileEntry);
   const int max_tiles = static_cast<int>(std::min<size_t>(sh.cut_tiles, room));
   hipLaunchKernelGGL(ffn_schedule_kernel, dim3(1), dim3(kScheduleThreads), 0, st, slot_offsets, w13_ptrs, w2_ptrs, S,

@@ -76,19 +76,21 @@ def test_route_workspace_of_more_tokens_serves_fewer(L, H, E, top):
 
 
 def test_ffn_workspace_of_more_rows_serves_fewer_at_full_speed(L):
-    """The query is the most that any call of up to max_rows rows uses: it never falls, and it holds the 8 MB of partial
-    sums for every max_rows where a contraction is long enough to be cut (4096 or more of H, 2048 or more of F), and only there."""
+    """The query is the most that any call of up to max_rows rows uses: it never falls, its tile table holds tiles of 64 rows throughout
+    (up to 4000 of them, beyond which the schedule kernel keeps to the standard cut), and it holds the 8 MB of partial sums for
+    every max_rows where a contraction is long enough to be cut (4096 or more of H, 2048 or more of F), and only there."""
     from paper_2602_00509_amd import probe
     pieces = 8 << 20
     for S, H, F in ((1, 7168, 2048), (1, 4096, 2048), (36, 7168, 2048), (36, 512, 64), (10, 4096, 14336), (14, 2048, 768),
                     (1, 64, 4096), (1024, 128, 64), (18, 2880, 2880), (4, 1024, 2048), (4, 4032, 1984)):
         rows = sorted({r for r in list(range(1, 130)) + [64 * S + d for d in range(-65, 300)] +
-                       [2 ** i + d for i in range(7, 17) for d in (-1, 0, 1)] if r > 0})
+                       [2 ** i + d for i in range(7, 21) for d in (-1, 0, 1)] +
+                      [64 * 4000 + d for d in (-64 * S, -64, 0, 64)] if r > 0})
         sizes = [probe.grouped_ffn_workspace_bytes(S, H, F, r) for r in rows]
         assert all(a <= b for a, b in zip(sizes, sizes[1:])), (S, H, F)
         room = pieces if H >= 4096 or F >= 2048 else 0
         for r, n in zip(rows, sizes):   # h, the tile table of 32 bytes a tile, the pieces; each rounded up to 256
-            tiles = max(r // 256 + S, min(r, 64 * S) // 64 + S)
+            tiles = max(r // 256 + S, min(r // 64 + S, 4000))
             assert r * F * 2 + 32 * tiles + room <= n <= r * F * 2 + 32 * tiles + room + 128 + 512, (S, H, F, r)
     assert probe.grouped_ffn_workspace_bytes(36, 7168, 2048, 0) < pieces
 

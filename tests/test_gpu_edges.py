@@ -457,6 +457,15 @@ def _ffn_against_oracle(oracle, probe, G, cfg, sizes, n_weights, seed, extra_row
     return err
 
 
+def _tile_table(ws, F, cap):
+    """What the schedule kernel left in a call's workspace: tiles, whether gemm1 and gemm2 take narrow column blocks, and a row
+    (first row, rows to the slot's end, height, slot) per tile."""
+    at = (cap * F * 2 + 255) // 256 * 256
+    head = ws[at:at + 128].cpu().numpy().view(np.int32)
+    n = int(head[0])
+    return n, bool(head[1]), bool(head[2]), ws[at + 128:at + 128 + 32 * n].cpu().numpy().view(np.int32).reshape(n, 8)[:, :4]
+
+
 def test_ffn_decode_schedule_every_element(oracle, probe, G):
     """A decode-sized row space (at most 64 rows per slot on average): the call takes the schedule of skinny
     tiles (64 rows x 64 h columns / 128 output columns).  Slot sizes around the 64-row tile boundary, empty
@@ -803,6 +812,29 @@ def test_ffn_tile_heights_by_estimated_time(oracle, probe, G, sizes, H, F, spare
     ys = [probe.grouped_ffn(x, so, tab, workspace=torch.empty(b, dtype=torch.uint8, device="cuda"))[:n]
           for b in (probe.grouped_ffn_workspace_bytes(S, H, F, cap), least)]
     torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1])
+
+
+@pytest.mark.parametrize("sizes,H,F,spare,tiles", [
+    ([111, 244, 557, 236, 391, 208], 704, 1024, 0, 16),      # tiles of 128 rows; 12 would be the room of the standard cut
+    ([190, 0, 130, 0, 200, 200], 512, 2048, 9, 14)])         # tiles of 64 rows
+def test_ffn_workspace_of_the_query_holds_the_chosen_cut(probe, sizes, H, F, spare, tiles):
+    """More room than the query asks for changes nothing: the same tiles, and the same bits."""
+    cap = sum(sizes) + spare
+    print("case room", sizes, H, F, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(H)
+    x = torch.randn((cap, H), generator=gen, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
+         torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16))
+    so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
+    tab = probe.WeightTable([w[0]] * len(sizes), [w[1]] * len(sizes))
+    tables, ys = [], []
+    for more in (0, 1 << 16):
+        ws = torch.zeros(probe.grouped_ffn_workspace_bytes(len(sizes), H, F, cap) + more, dtype=torch.uint8, device="cuda")
+        ys.append(probe.grouped_ffn(x, so, tab, workspace=ws)[:sum(sizes)])
+        tables.append(_tile_table(ws, F, cap))
+    assert tables[0][0] == tables[1][0] == tiles
+    assert tables[0][1:3] == tables[1][1:3] and np.array_equal(tables[0][3], tables[1][3])
     assert torch.equal(ys[0], ys[1])
 
 
