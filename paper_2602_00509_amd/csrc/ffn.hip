@@ -229,6 +229,8 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
       atomicAdd(&cut_classes[cut], counts);
       if (cut == 0) atomicAdd(&cut_units, units);
     }
+    // the lanes read below what others of the wave have added; LDS operations of a wave are done in order, so this only binds the compiler
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     if (cut_units <= kCutUnits) {
       const int c = min(lane >> 2, kCuts - 1), second = (lane >> 1) & 1, narrow = lane & 1;
