@@ -61,15 +61,18 @@ static_assert(kFfnLdsBytes >= 3 * (256 + 128) * 128 && kFfnLdsBytes >= 2 * (320 
 //
 // Order of the table.  Slots are taken by descending row count (ties: lower slot first) and a
 // slot's tiles stay together: the workgroups that run side by side then share a slot's weight
-// slices in L2 and the long slots start early; the single short tiles are spread evenly over the table, so that
-// tiles that wait for weights run beside tiles that keep the matrix cores busy.
+// slices in L2 and the long slots start early; the single short tiles (slots of up to 192 rows, or up to the height of the tiles where that is
+// less) are spread evenly over the table, so that tiles that wait for weights run beside tiles that keep the matrix cores busy.  Two or three
+// tiles of 64 rows of a slot stay together: spread apart they took up to 1.04 of the time in 16 calls of up to 256 items, on average 1.01.
 //
 // Where gemm1 has more items than CUs, but few enough tall tiles (more than 192 rows) that all of theirs start at once, the
 // tiles stand by descending height instead: a tall item that begins second is then the end of the launch.  768 tokens,
 // top-4 of 128 experts, 18 slots of 2880 x 2880: gemm1 116 -> 87 us, the layer 262 -> 235; 1500 tokens, 36 slots of 7168 x 2048
 // 863 -> 809 us, 2000 tokens of the first 355 -> 333.  With more tall tiles they hold each other up (clock) and the short
 // ones all come after them: 16384 tokens x 64 slots 3212 -> 3290 us, 2000 tokens of an 8-expert model 1338 -> 1390.  With no
-// second round the order only moves items between XCDs (700 tokens, 33 slots of 2048 x 1024: 167 -> 172 us).
+// second round the order only moves items between XCDs (700 tokens, 33 slots of 2048 x 1024: 167 -> 172 us).  A cut without tall tiles keeps
+// the slots in order: sorted by height, 24 calls each of more than 256 items took 1.028 (tiles of 192 rows; 0.95 to 1.12), 1.013 (128) and 1.006 (64)
+// of the time.
 struct alignas(16) TileEntry {
   int32_t row0, rows, height, slot;
   const void* w13;
@@ -148,6 +151,9 @@ __device__ __forceinline__ int tiles_of(unsigned long long classes) {
   return n;
 }
 
+// rows up to which a slot is a single short tile
+__device__ __forceinline__ int single_tile_rows(int cap) { return cap ? min(cap, 192) : 192; }
+
 __device__ __forceinline__ float launch_estimate(unsigned long long classes, int n_cols, int steps, int weight_rows, int cus) {
   const float per_cu = 1.f / static_cast<float>(cus);
   float longest = 0.f, sum = 0.f, item = 0.f;
@@ -184,7 +190,7 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
   __shared__ unsigned long long class_start[PROBE_MAX_SLOTS + 1];  // the same per tile height, twelve bits each
   __shared__ int32_t wave_tot[kScheduleWaves];
   __shared__ unsigned long long wave_classes[kScheduleWaves];
-  __shared__ int32_t n_big;                          // slots of more than 192 rows
+  __shared__ int32_t n_big;                          // slots of more rows than the single short tiles have
   __shared__ unsigned long long cut_classes[kCuts];  // tiles of each height with each cut
   __shared__ int32_t cut_units, cut_chosen, cut_narrow;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -212,8 +218,6 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
     }
     slot_at[pos] = tid;
   }
-  const int big_here = __popcll(__ballot(m > 192));
-  if (lane == 0 && big_here) atomicAdd(&n_big, big_here);
   // Meanwhile the last wave chooses the cut.  Lane l counts the tiles of cut l % 5 in every twelfth slot, then lane
   // (cut, GEMM, width) estimates a launch.
   if (wv == kScheduleWaves - 1) {
@@ -256,6 +260,8 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
   }
   __syncthreads();
   const int cap = cut_cap(__builtin_amdgcn_readfirstlane(cut_chosen));
+  const int big_here = __popcll(__ballot(m > single_tile_rows(cap)));
+  if (lane == 0 && big_here) atomicAdd(&n_big, big_here);
   // exclusive prefix of tiles over the positions
   const SlotCut my_cut = tid < S ? cut_slot(rows_of[slot_at[tid]], cap) : SlotCut{0, 0, 0, 0, 0};
   const int tiles = my_cut.tiles();
@@ -303,7 +309,7 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
   const int n_tall = static_cast<int>(all_classes & 4095) + static_cast<int>((all_classes >> 12) & 4095);
   const bool narrow1 = (cut_narrow & 1) != 0, narrow2 = (cut_narrow & 2) != 0;
   const int cols1 = narrow1 ? steps2 : n_cols1;
-  const bool tall_first = start[S] <= min(max_tiles, 4095) && n_tall * cols1 <= cus &&
+  const bool tall_first = (cap == 0 || cap > 192) && start[S] <= min(max_tiles, 4095) && n_tall * cols1 <= cus &&
                           static_cast<long>(start[S]) * cols1 > cus;
   if (tid < kTableHeaderInts) {
     // the queues' tickets: the first ones go without a draw, to the workgroups in order
@@ -314,8 +320,7 @@ __global__ __launch_bounds__(kScheduleThreads) void ffn_schedule_kernel(const in
     table[tid] = v;
   }
   TileEntry* entries = reinterpret_cast<TileEntry*>(table + kTableHeaderInts);
-  // positions [0, n_big) hold the slots of more than 192 rows: tiles [0, nb) are theirs, the ns single
-  // short tiles follow
+  // positions [0, n_big) hold the slots of more rows: tiles [0, nb) are theirs, the ns single short tiles follow
   const int nb = min(start[n_big], total), ns = total - nb;
   const bool small = total < (1 << 16);  // products of two of them in 32 bits
   for (int p = tid; p < total; p += kScheduleThreads) {

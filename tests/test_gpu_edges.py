@@ -436,7 +436,7 @@ def test_ffn_every_way_a_slot_is_cut_into_tiles(oracle, probe, G):
     assert (got[n:] == 7.0).all()          # rows past the last slot are not written
 
 
-def _ffn_against_oracle(oracle, probe, G, cfg, sizes, n_weights, seed, extra_rows=9):
+def _ffn_against_oracle(oracle, probe, G, cfg, sizes, n_weights, seed, extra_rows=9, workspace=None):
     """probe_grouped_ffn on slots of the given sizes, every output element against the oracle."""
     S = len(sizes)
     so = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
@@ -447,7 +447,7 @@ def _ffn_against_oracle(oracle, probe, G, cfg, sizes, n_weights, seed, extra_row
     d_w = {e: (G.dev_bf16(ws[e][0]), G.dev_bf16(ws[e][1])) for e in range(n_weights)}
     tab = probe.WeightTable([d_w[s % n_weights][0] for s in range(S)], [d_w[s % n_weights][1] for s in range(S)])
     y = torch.full((n + extra_rows, cfg.H), 7.0, dtype=torch.bfloat16, device="cuda")
-    probe.grouped_ffn(G.dev_bf16(xp), torch.from_numpy(so).cuda(), tab, out=y)
+    probe.grouped_ffn(G.dev_bf16(xp), torch.from_numpy(so).cuda(), tab, out=y, workspace=workspace)
     torch.cuda.synchronize()
     ref = oracle.grouped_ffn(xp, so, [ws[s % n_weights][0] for s in range(S)], [ws[s % n_weights][1] for s in range(S)])
     got = G.f64_of(y)
@@ -836,6 +836,31 @@ def test_ffn_workspace_of_the_query_holds_the_chosen_cut(probe, sizes, H, F, spa
     assert tables[0][0] == tables[1][0] == tiles
     assert tables[0][1:3] == tables[1][1:3] and np.array_equal(tables[0][3], tables[1][3])
     assert torch.equal(ys[0], ys[1])
+
+
+@pytest.mark.parametrize("sizes,H,F,height", [
+    ([70, 70, 100, 30, 200, 100, 0, 0, 30, 30, 0, 190], 128, 1472, 64),                                # 216 items of gemm1
+    ([100, 70, 130, 70, 30, 130, 260, 130, 0, 130, 100], 128, 1216, 64),                               # 494
+    ([450, 200, 100, 70, 450, 200, 200, 320, 100, 70, 100, 0], 128, 704, 128),                         # 242
+    ([30, 200, 70, 260, 130, 130, 450, 260, 450, 200, 0, 200, 130, 100], 192, 1280, 128),              # 290
+    ([122, 0, 226, 159, 98, 111, 135, 0, 118, 139, 0, 232, 522, 135, 299], 832, 2816, 192)])           # 374
+def test_ffn_tiles_of_a_slot_stay_together_in_lower_cuts(oracle, probe, G, sizes, H, F, height):
+    """Tiles of at most 192 rows: but for single tiles between them a slot's tiles stand side by side, and the slots of several tiles by
+    descending rows, whatever the number of items.  Every output element against the oracle."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=112)
+    cap = max(sum(sizes) + 9, 65 * len(sizes))
+    print("case together", sizes, H, F, flush=True)
+    ws = torch.zeros(probe.grouped_ffn_workspace_bytes(len(sizes), H, F, cap), dtype=torch.uint8, device="cuda")
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F, extra_rows=cap - sum(sizes), workspace=ws)
+    n, _, _, tiles = _tile_table(ws, F, cap)
+    assert n == sum((m + height - 1) // height for m in sizes) and tiles[:, 2].max() == height
+    several = [int(q) for q in tiles[:, 3] if sizes[q] > height]     # single tiles may stand between them
+    runs = [q for i, q in enumerate(several) if i == 0 or q != several[i - 1]]
+    assert runs == sorted((q for q, m in enumerate(sizes) if m > height), key=lambda q: (-sizes[q], q))
+    assert sorted(q for q in tiles[:, 3] if sizes[q] <= height) == [q for q, m in enumerate(sizes) if 0 < m <= height]
+    for q in runs:
+        mine = tiles[tiles[:, 3] == q]
+        assert np.array_equal(mine[:, 0] - mine[0, 0], height * np.arange(len(mine))) and mine[0, 1] == sizes[q]
 
 
 @pytest.mark.parametrize("H,F,n", [(4096, 2048, 75), (2880, 2880, 40)])
