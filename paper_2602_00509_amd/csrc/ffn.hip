@@ -1430,10 +1430,10 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
     const bool split2 = last_adds || (room && skinny_may_split(S, max_rows, n2, F / FBK));
     uint32_t* arrivals = last_adds ? reinterpret_cast<uint32_t*>(table) : nullptr;
     // a split call has at most kSkinnyItems items, one that is not split tiles * n
-    // and one whose blocks are halved at most whole rounds of kSkinnySlots
-    auto items = [](long n, bool split, int rounds) {
+    // and one whose blocks may be halved at most whole rounds of kSkinnySlots
+    auto items = [](long n, bool split, int rounds, int steps) {
       if (split) n = std::max<long>(n, kSkinnyItems);
-      return n > kSkinnySlots / 2 && n < kSkinnySlots * rounds ? (n + kSkinnySlots - 1) / kSkinnySlots * kSkinnySlots : n;
+      return steps >= kSkinnyHalvesMinSteps && n > kSkinnySlots / 2 && n < kSkinnySlots * rounds ? (n + kSkinnySlots - 1) / kSkinnySlots * kSkinnySlots : n;
     };
     // Items of few rows are a quarter as wide; 0: none.  A grid for kFewRowsItems of them is enough unless 100 to 128 are likely.
     auto few_items = [S, max_rows](long n, int steps) {
@@ -1441,7 +1441,7 @@ static int ffn_impl(const char* name, const void* act_bf16, const int32_t* row_p
       return n >= kFewerRowsItems[0] && n <= kFewerRowsItems[1] && steps >= kFewerRowsSteps ? 4 * n : std::min<long>(4 * n, 4 * kFewRowsItems);
     };
     const long few1 = few_items(tiles * n1, H / FBK), few2 = few_items(tiles * n2, F / FBK);
-    const dim3 g1(std::max(items(tiles * n1, split1, kSkinnyHalvesRounds), few1)), g2(std::max(items(tiles * n2, split2, 1), few2));
+    const dim3 g1(std::max(items(tiles * n1, split1, kSkinnyHalvesRounds, H / FBK), few1)), g2(std::max(items(tiles * n2, split2, 1, F / FBK), few2));
     // tiles that can be split at all: two pieces or more need kSkinnyItems / 2 items or fewer
     const int add1 = split1 ? std::min(tiles, kSkinnyItems / 2 / n1) : 0;
     const int add2 = split2 && !last_adds ? std::min(tiles, kSkinnyItems / 2 / n2) : 0;
