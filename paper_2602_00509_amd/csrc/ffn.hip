@@ -869,26 +869,29 @@ __device__ __forceinline__ int skinny_steps(int items, int rows, int n_cols, int
 // a block's start, and with it the low bits of its elements, then followed the number of tiles.  Narrower blocks alone lose: fewer weight rows
 // in flight per workgroup (7 slots of 4096 x 1536, 168 items of gemm1 or 511 of a third of the width, 55.9 / 65.2 us; 224 items of 7168 x 2048
 // 112 / 126), so only where the last round is at most that full.
-// FFN calls, usual blocks / halved: 9, 10, 11 slots of 7168 x 2048 (288, 320, 352 items of gemm1) 164 / 147, 178 / 165, 186 / 175; 11 to 16 of
-// 4096 x 1536 (264 to 384) 97 / 84, 99 / 88, 100 / 93, 104 / 99, 111 / 109; 400 items level to 0.5 % slower.  Second round: 17 and 18 of 7168 x
-// 2048 (544, 576) 281 / 266, 289 / 278, 608 and 624 items 0.988 to 1.02 x, 640 0.954 to 1.006 x, 672 slower.  gemm2 of 9, 10, 11 slots of 4096 x
-// 14336 (288, 320, 352) 586 / 552, 631 / 603, 686 / 663; 12 of it (384) 726 / 734, five shapes more of 368 to 384 items 1.01 to 1.04 x.
+// FFN calls, usual blocks / halved: 9, 10, 11 slots of 7168 x 2048 (288, 320, 352 items of gemm1) 164 / 147, 178 / 165, 186 / 175; 11 to 14 of
+// 4096 x 1536 (264 to 336) 97 / 84, 99 / 88, 100 / 93, 104 / 99; gemm2 of 9, 10, 11 slots of 4096 x 14336 (288, 320, 352) 586 / 552, 631 / 603,
+// 686 / 663.  Up to 376 items none of 150 calls is slower, whatever its rows; 384 1.04 to 0.97 x, 400 level.  The halves of a second round load
+// the activation rows once more: 17 slots of 7168 x 2048 (544 items) gain 1.05 x with 6 rows each, 1.035 with 20, 1.02 with 36 and lose 0.6 %
+// with 60; 576 to 608 of five shapes 1.02 to 1.05 x with 6, up to 1.02 with 28, 0.96 to 0.99 with 48; 528 items 1.01 to 1.08 x with any; 640
+// 0.954 to 1.006 x with few.
 // gemm2 of fewer than 40 k-steps: 264 to 324 items 1.01 to 1.1 x; columns dealt evenly lost from 336 on (6 and 7 slots of 7168 x 2048 107 / 110
 // and 112 / 117), and nothing is halved there.
 constexpr int kSkinnySlots = 512;  // workgroups that run at once, two to a CU
 // items up to which a single round (of more than 256) is filled: gemm1 and gemm2 from kSkinnyHalvesSteps k-steps on, gemm2 of fewer
-constexpr int kSkinnyHalves = 384, kSkinnyHalvesShort = 328, kSkinnyHalvesSteps = 40;
+constexpr int kSkinnyHalves = 376, kSkinnyHalvesShort = 328, kSkinnyHalvesSteps = 40;
 // k-steps from which blocks are halved: 15 tiles of 832 x 1472 (345 items of 13 k-steps), columns dealt evenly, 28.7 / 30.8 us, 18 of 1088 x 1216
 // (342 of 17) 34.6 / 30.0
 constexpr int kSkinnyHalvesMinSteps = 15;
-// gemm1: items of a last round that is filled; rounds at most
-constexpr int kSkinnyHalvesLast = 112, kSkinnyHalvesRounds = 2;
+// gemm1: items of a last round that is filled, with any rows and with up to kSkinnyHalvesRows per tile; rounds at most
+constexpr int kSkinnyHalvesLast = 16, kSkinnyHalvesLastFew = 96, kSkinnyHalvesRows = 32, kSkinnyHalvesRounds = 2;
 template <bool GEMM1>
-__device__ __forceinline__ int skinny_halved(int n_tiles, int n_cols, int steps) {
+__device__ __forceinline__ int skinny_halved(int n_tiles, int rows, int n_cols, int steps) {
   const int items = n_tiles * n_cols, rounds = (items + kSkinnySlots - 1) / kSkinnySlots, last = items - kSkinnySlots * (rounds - 1);
   if (steps < kSkinnyHalvesMinSteps) return 0;
   const bool fill = rounds == 1 ? last > kSkinnySlots / 2 && last <= (GEMM1 || steps >= kSkinnyHalvesSteps ? kSkinnyHalves : kSkinnyHalvesShort)
-                                : GEMM1 && rounds <= kSkinnyHalvesRounds && last <= kSkinnyHalvesLast;
+                                : GEMM1 && rounds <= kSkinnyHalvesRounds &&
+                                      last <= (rows <= kSkinnyHalvesRows * n_tiles ? kSkinnyHalvesLastFew : kSkinnyHalvesLast);
   return fill ? max(kSkinnySlots * rounds / n_tiles - n_cols, 0) : 0;  // fewer than n_cols: more than half of the places have an item
 }
 
@@ -1070,7 +1073,7 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
                                         : n_items >= kFewerRowsItems[0] && n_items <= kFewerRowsItems[1] && steps >= kFewerRowsSteps &&
                                               !__ballot(most > kFewerRows));
     constexpr int kWidth = GEMM1 ? kSkinnyCols1 : kSkinnyCols2, kFewWidth = GEMM1 ? kFewRowsCols1 : kFewRowsCols2;
-    const int halved = out.few || piece_steps ? 0 : skinny_halved<GEMM1>(n_tiles, n_cols, steps);
+    const int halved = out.few || piece_steps ? 0 : skinny_halved<GEMM1>(n_tiles, all_rows, n_cols, steps);
     const int whole = out.few ? cols / kFewWidth : n_cols - halved, wholes = n_tiles * whole;
     if (!halved || item < wholes) {
       tile = item / whole;

@@ -573,13 +573,14 @@ def test_ffn_second_contraction_cut_repeats_bit_for_bit(oracle, probe, G, sizes,
 
 @pytest.mark.parametrize("n,H,F", [
     (13, 2560, 1280),     # 260 items of either GEMM: 19 of 20 column blocks are halved
-    (16, 3072, 1536),     # 384 of gemm1: the most of a single round; 384 of gemm2, of 24 k-steps: not
-    (11, 1024, 2240),     # 385 of gemm1: not
-    (16, 3072, 2560),     # 384 of gemm2, of 40 k-steps: the most; 640 of gemm1: not
+    (8, 6016, 3008),      # 376 of either GEMM: the most of a single round
+    (29, 1664, 832),      # 377 of either: not
+    (12, 3456, 1728),     # 324 of either, gemm2 of 27 k-steps
+    (11, 3840, 1728),     # 330 of gemm2, of 27 k-steps: not
     (13, 2880, 2624),     # 299 of gemm2, whose last block has 64 columns; 533 of gemm1: a last round of 21
     (16, 896, 1280),      # 320 of gemm1, of 14 k-steps: not
-    (16, 2048, 2496),     # 624 of gemm1: the most of a second round; 256 of gemm2: one to a CU
-    (15, 2432, 2688),     # 630 of gemm1: not
+    (16, 2048, 2432),     # 608 of gemm1: the most of a second round; 256 of gemm2: one to a CU
+    (14, 2432, 2816),     # 616 of gemm1: not
     (257, 64, 64)])       # one block of columns each, of one k-step
 def test_ffn_decode_schedule_halves_blocks(oracle, probe, G, n, H, F):
     """Decode schedule: numbers of items at the limits between which column blocks are halved; every output element against the
@@ -606,14 +607,14 @@ def test_ffn_decode_schedule_halves_blocks(oracle, probe, G, n, H, F):
 @pytest.mark.parametrize("n,H,F", [
     (13, 2560, 1280),     # 260 items of either GEMM
     (14, 4096, 1536),     # 336 of gemm1
-    (16, 3072, 2560),     # 384 of gemm2
+    (15, 3072, 2560),     # 360 of gemm2; 600 of gemm1, of up to 32 rows per tile
     (13, 2880, 2624),     # 299 of gemm2; 533 of gemm1
     (17, 2048, 2048)])    # 544 of gemm1; 272 of gemm2, of 32 k-steps
 def test_ffn_bits_of_a_row_do_not_follow_the_number_of_tiles(probe, n, H, F):
     """Decode schedule, no contraction cut: a row has the same bits in a call whose column blocks are halved to fill the CUs and in calls
     of fewer slots, whose blocks are whole."""
     print("case bits of a row", n, H, F, flush=True)
-    sizes = [17 + 5 * i % 23 for i in range(n)]     # more rows than the items of few rows take
+    sizes = [17 + 5 * i % 29 for i in range(n)]     # more rows than the items of few rows take
     gen = torch.Generator(device="cuda").manual_seed(n + H)
     x = torch.randn((sum(sizes), H), generator=gen, device="cuda").to(torch.bfloat16)
     w13 = [torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16) for _ in range(3)]
