@@ -1279,9 +1279,15 @@ struct FfnShape {
 // 4096 x 14336, 10 slots (2240 blocks), 36 rows of capacity per slot 625 / 642 us, 40 732 / 658, 43 697 / 652, 59 799 / 703; 64 slots of
 // 7168 x 2048 (2048) 32 643 / 650, 40 816 / 807, 50 743 / 708, 58 694 / 664 and 709 / 714; 36 slots (1152) 46 357 / 368, 50 428 / 434, 54 406 / 397,
 // 62 436 / 413; but 18 slots of 2880 x 2880 (810) 52 133 / 133, 61 115 / 110, of 4096 x 1536 (432) 62 95 / 115.
+// What the other path costs per item counts for more the shorter H is.  Calls between the lines with rows routed under Zipf laws, a hundredth to
+// all of them local, tall tiles against this schedule, geometric mean: H below 768 0.99 x (31 calls, 0.81 to 1.18), to 1151 0.97 x (30, 0.63 to
+// 1.33), to 1535 1.06 x (27), to 2240 1.15 x (69), above 1.14 x (145, 0.86 to 1.74).  Most are lost where few of the capacity's rows are local (39 of 64 slots of 7168 x 2048
+// with 490 rows of 2880: 583 / 621 us), which the host cannot know.
 constexpr int kSkinnyRowsPerSlot = 64;
 constexpr int kSkinnyBlocks[2] = {1024, 1536}, kSkinnyRowsOfMore[2] = {52, 40};
-static int skinny_rows_per_slot(int S, int F) {
+constexpr int kSkinnyWide = 1152;  // H from which the line lies lower
+static int skinny_rows_per_slot(int S, int H, int F) {
+  if (H < kSkinnyWide) return kSkinnyRowsPerSlot;
   const long blocks = static_cast<long>(S) * ((F + kSkinnyCols1 - 1) / kSkinnyCols1);
   return blocks > kSkinnyBlocks[1] ? kSkinnyRowsOfMore[1] : blocks > kSkinnyBlocks[0] ? kSkinnyRowsOfMore[0] : kSkinnyRowsPerSlot;
 }
@@ -1290,7 +1296,7 @@ static_assert(kSkinnyFewItems2 * 512ll < (1ll << 32), "threads of one launch");
 
 static FfnShape ffn_shape(int S, int H, int F, int max_rows) {
   FfnShape s;
-  const bool short_slots = static_cast<long>(max_rows) <= static_cast<long>(skinny_rows_per_slot(S, F)) * S;
+  const bool short_slots = static_cast<long>(max_rows) <= static_cast<long>(skinny_rows_per_slot(S, H, F)) * S;
   const long tiles = static_cast<long>(max_rows) / 64 + S;
   s.skinny = short_slots || (tiles * ((F + kSkinnyCols1 - 1) / kSkinnyCols1) <= kSkinnyFewItems &&
                              tiles * ((H + kSkinnyCols2 - 1) / kSkinnyCols2) <= kSkinnyFewItems2);

@@ -667,16 +667,21 @@ def test_ffn_few_rows_in_every_slot(oracle, probe, G, sizes, H, F):
     assert torch.equal(plain[:rows], gathered[:rows])
 
 
-@pytest.mark.parametrize("S,F,rows", [(40, 2496, 40), (27, 2560, 52), (16, 4096, 64)])
-def test_ffn_either_side_of_the_decode_schedule(oracle, probe, G, S, F, rows):
-    """The last capacity that takes the decode schedule and the first that takes tall tiles, with 1560, 1080 and 1024 column blocks
-    of all slots: every output element of both against the oracle."""
-    cfg = wl.small_config(T=64, H=128, E=4, k=2, F=F, cid=109)
+@pytest.mark.parametrize("S,H,F,rows", [(40, 1152, 2496, 40), (40, 1088, 2496, 64), (27, 1152, 2560, 52), (27, 1088, 2560, 64),
+                                        (16, 1152, 4096, 64), (16, 128, 4096, 64)])
+def test_ffn_either_side_of_the_decode_schedule(oracle, probe, G, S, H, F, rows):
+    """The last capacity that takes the decode schedule, which leaves no tile table, and the first that takes tall tiles, with 1560, 1080 and
+    1024 column blocks of all slots, and H on either side of the line from which more blocks count: every output element of both
+    against the oracle."""
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=109)
     sizes = [(5 * i) % 17 for i in range(S)]
     sizes[3] = 70
     for cap in (rows * S, rows * S + 1):
-        print("case either side", S, F, cap, flush=True)
-        _ffn_against_oracle(oracle, probe, G, cfg, sizes, 2, seed=F, extra_rows=cap - sum(sizes))
+        print("case either side", S, H, F, cap, flush=True)
+        ws = torch.full((probe.grouped_ffn_workspace_bytes(S, H, F, cap),), 0xff, dtype=torch.uint8, device="cuda")
+        _ffn_against_oracle(oracle, probe, G, cfg, sizes, 2, seed=F, extra_rows=cap - sum(sizes), workspace=ws)
+        at = (cap * F * 2 + 255) // 256 * 256
+        assert (int(ws[at:at + 4].cpu().numpy().view(np.int32)[0]) > 0) == (cap > rows * S)
 
 
 def test_ffn_contraction_is_not_cut_where_every_slot_can_hold_rows(oracle, probe, G):
