@@ -883,14 +883,16 @@ constexpr int kSkinnyHalves = 376, kSkinnyHalvesShort = 328, kSkinnyHalvesSteps 
 // k-steps from which blocks are halved: 15 tiles of 832 x 1472 (345 items of 13 k-steps), columns dealt evenly, 28.7 / 30.8 us, 18 of 1088 x 1216
 // (342 of 17) 34.6 / 30.0
 constexpr int kSkinnyHalvesMinSteps = 15;
-// gemm1: items of a last round that is filled, with any rows and with up to kSkinnyHalvesRows per tile; rounds at most
+// gemm1: items of a last round that is filled, with any rows and with up to kSkinnyHalvesRows per tile; rounds at most.  Only where no slot has
+// several tiles (one_each, looked at up to 128 slots): those read their weights together, and a second round of such calls, routed under Zipf laws,
+// lost 2 % on average (10 calls, 0.93 to 1.01 x) where single tiles gain (11 calls 1.017 x); single rounds gain with either (1.02 to 1.1 x of 127).
 constexpr int kSkinnyHalvesLast = 16, kSkinnyHalvesLastFew = 96, kSkinnyHalvesRows = 32, kSkinnyHalvesRounds = 2;
 template <bool GEMM1>
-__device__ __forceinline__ int skinny_halved(int n_tiles, int rows, int n_cols, int steps) {
+__device__ __forceinline__ int skinny_halved(int n_tiles, bool one_each, int rows, int n_cols, int steps) {
   const int items = n_tiles * n_cols, rounds = (items + kSkinnySlots - 1) / kSkinnySlots, last = items - kSkinnySlots * (rounds - 1);
   if (steps < kSkinnyHalvesMinSteps) return 0;
   const bool fill = rounds == 1 ? last > kSkinnySlots / 2 && last <= (GEMM1 || steps >= kSkinnyHalvesSteps ? kSkinnyHalves : kSkinnyHalvesShort)
-                                : GEMM1 && rounds <= kSkinnyHalvesRounds &&
+                                : GEMM1 && rounds <= kSkinnyHalvesRounds && one_each &&
                                       last <= (rows <= kSkinnyHalvesRows * n_tiles ? kSkinnyHalvesLastFew : kSkinnyHalvesLast);
   return fill ? max(kSkinnySlots * rounds / n_tiles - n_cols, 0) : 0;  // fewer than n_cols: more than half of the places have an item
 }
@@ -1073,7 +1075,7 @@ __device__ __forceinline__ bool skinny_locate(const int32_t* __restrict__ slot_o
                                         : n_items >= kFewerRowsItems[0] && n_items <= kFewerRowsItems[1] && steps >= kFewerRowsSteps &&
                                               !__ballot(most > kFewerRows));
     constexpr int kWidth = GEMM1 ? kSkinnyCols1 : kSkinnyCols2, kFewWidth = GEMM1 ? kFewRowsCols1 : kFewRowsCols2;
-    const int halved = out.few || piece_steps ? 0 : skinny_halved<GEMM1>(n_tiles, all_rows, n_cols, steps);
+    const int halved = out.few || piece_steps ? 0 : skinny_halved<GEMM1>(n_tiles, alone && !__ballot(most > 64), all_rows, n_cols, steps);
     const int whole = out.few ? cols / kFewWidth : n_cols - halved, wholes = n_tiles * whole;
     if (!halved || item < wholes) {
       tile = item / whole;
