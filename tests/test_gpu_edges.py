@@ -333,7 +333,7 @@ def test_determinism_and_plan_invariance(oracle, probe, G):
     p1, y1, out1 = run(rep)
     assert int(p1["n_local"]) == cfg.N == int(p0["n_local"])
     assert bool((p1["slot_counts"][cfg.E_loc:] > 0).all())
-    # a row's K loop does not depend on where the row sits, so the outputs agree bit for bit
+    # neither plan's call cuts a contraction or takes items of few rows: a row's sum does not depend on where the row sits
     assert torch.equal(out0, out1)
 
 
@@ -412,28 +412,14 @@ def test_graph_replay(oracle, probe, G):
 
 
 def test_ffn_every_way_a_slot_is_cut_into_tiles(oracle, probe, G):
-    """Slot sizes on both sides of every tile-height boundary (the FFN cuts a slot into row tiles of
-    several heights and lets taller tiles absorb small remainders), empty slots in between: every
-    output element against the oracle."""
-    cfg = wl.small_config(T=64, H=128, E=4, k=2, F=192, cid=93)
+    """Slot sizes on both sides of every tile-height boundary of the standard cut, empty slots in between, so many that no other cut
+    is taken: every output element against the oracle, and every slot's tiles."""
     sizes = [0, 1, 63, 64, 65, 128, 129, 191, 192, 193, 255, 256, 257, 0, 300, 320, 321, 384, 385, 449,
              512, 513, 576, 577, 640, 641, 700, 768 + 1, 768 + 65, 768 + 129, 768 + 192, 768 + 193, 1024 + 130, 7]
-    S = len(sizes)
-    so = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
-    n = int(so[-1])
-    ws = wl.expert_weights_many(cfg, [s % 4 for s in range(S)])
-    rng = np.random.default_rng(5)
-    xp = wl.f32_to_bf16_bits(rng.standard_normal((n + 9, cfg.H)).astype(np.float32))
-    d_w = {e: (G.dev_bf16(ws[e][0]), G.dev_bf16(ws[e][1])) for e in range(4)}
-    tab = probe.WeightTable([d_w[s % 4][0] for s in range(S)], [d_w[s % 4][1] for s in range(S)])
-    d_xp = G.dev_bf16(xp)
-    y = torch.full((n + 9, cfg.H), 7.0, dtype=torch.bfloat16, device="cuda")
-    probe.grouped_ffn(d_xp, torch.from_numpy(so).cuda(), tab, out=y)
-    torch.cuda.synchronize()
-    ref = oracle.grouped_ffn(xp, so, [ws[s % 4][0] for s in range(S)], [ws[s % 4][1] for s in range(S)])
-    got = G.f64_of(y)
-    assert G.rel_err(got[:n], ref) < G.BF16_RTOL
-    assert (got[n:] == 7.0).all()          # rows past the last slot are not written
+    print("case every cut", flush=True)
+    table = _tall_tiles(oracle, probe, G, sizes, 448, 512, sum(sizes) + 9, 0, n_weights=4)
+    assert table[1:3] == (False, True)
+    assert _slots_in_order(table, sizes, 192)
 
 
 def _ffn_against_oracle(oracle, probe, G, cfg, sizes, n_weights, seed, extra_rows=9, workspace=None):
@@ -464,6 +450,50 @@ def _tile_table(ws, F, cap):
     head = ws[at:at + 128].cpu().numpy().view(np.int32)
     n = int(head[0])
     return n, bool(head[1]), bool(head[2]), ws[at + 128:at + 128 + 32 * n].cpu().numpy().view(np.int32).reshape(n, 8)[:, :4]
+
+
+def _cut(m, cap):
+    """Heights of a slot's tiles, first row first: as many of 320 rows as leave whole ones of 256 and no rest, or one short tile at the end;
+    with a cap tiles of that height and a shorter one."""
+    u = (m + 63) // 64
+    if cap:
+        return [cap] * (64 * u // cap) + ([64 * u % cap] if 64 * u % cap else [])
+    for a in range(u // 5, -1, -1):
+        if (u - 5 * a) % 4 == 0:
+            return [320] * a + [256] * ((u - 5 * a) // 4)
+    return {1: [64], 2: [128], 3: [192], 6: [256, 128], 7: [320, 128], 11: [320, 256, 128]}[u]
+
+
+def _tall_tiles(oracle, probe, G, sizes, H, F, cap, height, n_weights=3):
+    """One call on the tall tiles, every output element against the oracle.  Asserts that each slot is cut as `height` says (0 = the standard
+    cut) and returns the tile table."""
+    assert cap > 64 * len(sizes) and (cap // 64 + len(sizes)) * (F // 64) > 512        # past the decode schedule
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=120)
+    ws = torch.zeros(probe.grouped_ffn_workspace_bytes(len(sizes), H, F, cap), dtype=torch.uint8, device="cuda")
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, n_weights, seed=H + F, extra_rows=cap - sum(sizes), workspace=ws)
+    table = _tile_table(ws, F, cap)
+    _check_cut(table, sizes, height)
+    return table
+
+
+def _check_cut(table, sizes, height):
+    tiles = table[3]
+    first = np.r_[0, np.cumsum(sizes)]
+    for q, m in enumerate(sizes):
+        mine = tiles[tiles[:, 3] == q]
+        mine = mine[np.argsort(mine[:, 0])]
+        want = _cut(m, height)
+        assert mine[:, 2].tolist() == want, (q, m, mine)
+        at = np.cumsum([0] + want[:-1]) if want else np.zeros(0, int)
+        assert mine[:, 0].tolist() == (first[q] + at).tolist() and mine[:, 1].tolist() == (m - at).tolist()
+    assert table[0] == sum(len(_cut(m, height)) for m in sizes)
+
+
+def _slots_in_order(table, sizes, single):
+    """Slots of more than `single` rows stand by descending rows, each one's tiles together but for single short tiles in between."""
+    several = [int(q) for q in table[3][:, 3] if sizes[q] > single]
+    runs = [q for i, q in enumerate(several) if i == 0 or q != several[i - 1]]
+    return runs == sorted((q for q, m in enumerate(sizes) if m > single), key=lambda q: (-sizes[q], q))
 
 
 def test_ffn_decode_schedule_every_element(oracle, probe, G):
@@ -706,32 +736,52 @@ def test_ffn_contraction_is_not_cut_where_every_slot_can_hold_rows(oracle, probe
     assert G.rel_err(G.f64_of(ys[0]), ref) < G.BF16_RTOL
 
 
-@pytest.mark.parametrize("sizes", [
-    [700, 5, 300, 0, 64, 130, 193, 20, 1, 33, 70, 200, 9, 3, 2, 1, 40, 321, 12, 450],   # 23 tiles, 8 of them tall
-    [320] * 8 + [0, 256] + [250] * 7 + [192, 1, 65],                                    # 19 tiles, 16 of them tall: the limit
-    [320] * 17 + [1, 0, 129]])                                                          # one more: slots stay in order
-def test_ffn_tall_tiles_first_every_element(oracle, probe, G, sizes):
-    """More items than CUs and 16 column blocks of the first GEMM: up to 16 tiles of more than 192 rows make the table
-    go by descending tile height (256 CUs); tiles of one height in several slots, empty slots, every height."""
-    cfg = wl.small_config(T=64, H=192, E=4, k=2, F=2048, cid=102)
+@pytest.mark.parametrize("sizes,H,F,height,tall,by_height", [
+    # every height; 14 tall tiles in 8 narrow column blocks of gemm1, 33 tiles
+    ([384, 190, 130, 30, 64, 30, 321, 190, 256, 250, 30, 577, 192, 321, 1, 321, 130, 30, 250, 300, 30, 30, 65, 512, 577, 65], 1088, 512, 0, 14, True),
+    # 16 tall tiles in 16 column blocks: the most
+    ([384, 200, 512, 450, 190, 128, 190, 200, 200, 190, 450, 384, 512, 256, 1, 512], 704, 2048, 0, 16, True),
+    # 19 in 14: one more than 256 items
+    ([192, 250, 577, 128, 640, 1, 300, 64, 320, 65, 384, 450, 1, 300, 130, 190, 250, 256, 0, 577, 300, 300, 320, 30, 320], 704, 1792, 0, 19, False),
+    # seven tiles of 256 rows in a lower cut
+    ([130, 190, 256, 128, 300, 1, 450, 1, 30, 1, 300, 30, 192, 30, 577, 0, 64, 0, 64], 1344, 768, 256, 7, True),
+    # 256 items of gemm1: no second round
+    ([190, 192, 1, 250, 1, 0, 190, 65, 1, 128, 65, 128, 250, 1, 1, 64, 192], 1536, 1024, 0, 2, False)])
+def test_ffn_tall_tiles_first_every_element(oracle, probe, G, sizes, H, F, height, tall, by_height):
+    """More items of gemm1 than CUs (256), and tiles of more than 192 rows that all start at once: the table goes by descending height.
+    Otherwise the slots stay in order.  Tiles of one height in several slots, empty slots, every element."""
     print("case tall first", sizes, flush=True)
-    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 4, seed=len(sizes) + sizes[0])
+    table = _tall_tiles(oracle, probe, G, sizes, H, F, max(sum(sizes) + 9, 65 * len(sizes)), height)
+    tiles = table[3]
+    cols = F // 64 if table[1] else (F + 127) // 128
+    assert (tiles[:, 2] > 192).sum() == tall
+    assert by_height == (tall * cols <= 256 < len(tiles) * cols)
+    falls = (np.diff(tiles[:, 2]) <= 0).all()
+    assert falls == by_height
+    if by_height:    # tiles of one height by their slots' rows
+        keys = [(-t[2], -sizes[t[3]], t[3], t[0]) for t in tiles.tolist()]
+        assert keys == sorted(keys)
+    else:
+        assert _slots_in_order(table, sizes, 192)
 
 
-@pytest.mark.parametrize("sizes,H,F", [
-    ([320, 256, 192, 128, 64, 37, 0, 321] * 4, 1344, 960),    # every height, wide column blocks, partial last ones
-    ([320, 256, 192, 128, 64, 37, 0, 321], 1088, 1344),       # every height, narrow column blocks, partial last ones
-    ([100] * 14, 2432, 2048), ([100] * 15, 2560, 2048),       # wide: uniform tiles, 224 and 240 wide items of gemm1
-    ([130] * 16, 2560, 768), ([130] * 17, 2560, 768),         # 96 and 102 of gemm1 (narrow / wide), 160 and 170 of gemm2 (wide)
-    ([130] * 16, 2560, 192), ([130] * 17, 2560, 192),         # the decode schedule with three tiles to a slot
-    ([70, 0, 300], 64, 14400)])                               # one k-step; more column blocks than tiles, 226 / 2 wide items
-def test_ffn_wide_and_narrow_column_blocks(oracle, probe, G, sizes, H, F):
-    """Wide and narrow column blocks of either GEMM, and numbers of items at the limits of the narrow ones: every output element
-    against the oracle, and the rows gathered on load bit for bit the same."""
+@pytest.mark.parametrize("sizes,H,F,cut", [
+    ([320, 256, 192, 128, 64, 37, 0, 321] * 4, 1344, 960, (0, False, True)),    # every height, partial last column blocks
+    ([320, 256, 192, 128, 64, 37, 0, 321], 1088, 1344, (64, False, True)),      # partial last column blocks
+    ([100] * 14, 2432, 2048, (0, False, False)), ([100] * 15, 2560, 2048, (0, False, False)),   # uniform tiles, 224 and 240 items of gemm1
+    ([130] * 16, 2560, 768, (0, True, False)), ([130] * 17, 2560, 768, (0, True, False)),       # 192 and 204 of gemm1, 160 and 170 of gemm2
+    ([130] * 16, 2560, 192, None), ([130] * 17, 2560, 192, None),               # the decode schedule with three tiles to a slot
+    ([70, 0, 300], 64, 14400, (64, False, True))])                              # one k-step; more column blocks than tiles
+def test_ffn_wide_and_narrow_column_blocks(oracle, probe, G, sizes, H, F, cut):
+    """Wide and narrow column blocks of either GEMM: every output element against the oracle, and the rows gathered on load bit for
+    bit the same.  `cut`: the height of the tiles and whether the blocks of gemm1 and gemm2 are narrow, as the table says."""
     cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=103)
     print("case narrow", len(sizes), H, F, flush=True)
-    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F)
     n = sum(sizes)
+    if cut:
+        assert _tall_tiles(oracle, probe, G, sizes, H, F, n + 9, cut[0])[1:3] == cut[1:]
+    else:
+        _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F)
     gen = torch.Generator(device="cuda").manual_seed(H)
     x = torch.randn((n + 9, H), generator=gen, device="cuda").to(torch.bfloat16)
     w = [(torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
@@ -745,67 +795,65 @@ def test_ffn_wide_and_narrow_column_blocks(oracle, probe, G, sizes, H, F):
     assert torch.equal(plain[:n], gathered[:n])
 
 
-@pytest.mark.parametrize("sizes,H,F,capacities", [
-    ([320, 256] + [5] * 9, 2304, 1280, (1500, 2600)),     # narrow, more than eight blocks of items / one round from the queue
-    ([320, 300, 200] + [60] * 8, 1600, 1408, (1309, 2200)),
-    ([320] + [5] * 14, 3200, 1408, (1300, 2400)),         # narrow, two rounds from the queue
-    ([320, 320] + [1] * 6, 1728, 1216, (1550, 2650)),     # narrow, eight blocks / one round from the queue
-    ([320, 130] + [20] * 13, 2560, 1472, (2710,)),        # narrow, two rounds of both from the queue
-    ([64] * 20 + [320], 1088, 1152, (1609, 3000)),        # wide in gemm1, narrow in gemm2
-    ([100] * 26, 1216, 768, (2889,))])                    # wide: twice as many items would be a second round
-def test_ffn_column_blocks_by_estimated_time(oracle, probe, G, sizes, H, F, capacities):
-    """Tall tiles whose column blocks the schedule halves, or not, by an estimate of both launches, drawn from the work queue or
-    one workgroup per item, which the capacity decides: every output element against the oracle, and the same bits either way."""
-    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=105)
-    n = sum(sizes)
-    ys = []
-    for cap in capacities:
-        assert cap > 64 * len(sizes)                      # past the decode schedule
-        print("case estimated time", len(sizes), H, F, cap, flush=True)
-        _ffn_against_oracle(oracle, probe, G, cfg, sizes, 2, seed=H + F, extra_rows=cap - n)
-        gen = torch.Generator(device="cuda").manual_seed(H)
-        x = torch.zeros((cap, H), dtype=torch.bfloat16, device="cuda")
-        x[:n] = torch.randn((n, H), generator=gen, device="cuda").to(torch.bfloat16)
-        w = (torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
-             torch.randn((H, F), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16))
-        so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
-        ys.append(probe.grouped_ffn(x, so, probe.WeightTable([w[0]] * len(sizes), [w[1]] * len(sizes)))[:n])
-        torch.cuda.synchronize()
-    assert all(torch.equal(ys[0], y) for y in ys[1:])
+@pytest.mark.parametrize("sizes,H,F,cut", [
+    ([100] * 26, 1216, 768, (0, False, False)),                                                     # 156 / 130 items
+    ([450, 190, 64, 64, 70, 450, 64, 450, 200, 3, 512], 704, 1792, (0, False, True)),               # 210 / 90
+    ([30, 3, 64, 128, 450, 512, 200, 190, 3, 0, 128, 3, 70, 450, 200, 30], 2496, 832, (0, True, False)),
+    ([64, 190, 130, 130, 130, 30, 3, 190], 1920, 1600, (0, True, True)),
+    ([320] + [5] * 14, 3200, 1408, (64, False, False)),                                             # 209 / 247
+    ([64] * 20 + [320], 1088, 1152, (64, False, True)),
+    ([320, 320] + [1] * 6, 1728, 1216, (128, True, True)),
+    ([190, 30, 130, 128, 3, 3, 577, 450, 390, 3, 3, 256, 300, 30, 3], 1408, 1024, (128, False, False)),
+    ([130, 390, 3, 30, 64, 333, 3, 70, 333, 30, 512, 200, 70, 3, 70, 70], 1856, 1344, (192, False, False)),
+    ([64, 30, 3, 128, 128, 3, 512, 577, 30, 30, 200, 256, 577], 1856, 640, (192, True, False)),
+    ([0, 0, 512, 256, 70, 130, 0, 450, 130, 200, 200, 70, 390, 3], 768, 1600, (256, False, True)),
+    ([70, 130, 128, 390, 200, 64, 30, 300, 200, 70, 390, 512, 70, 3], 2496, 768, (256, True, False))])
+def test_ffn_column_blocks_by_estimated_time(oracle, probe, G, sizes, H, F, cut):
+    """The standard cut and lower ones, each GEMM with wide or narrow column blocks, as the estimate of the launches takes them: every output
+    element against the oracle, the cut and the widths from the table."""
+    print("case estimated time", sizes, H, F, flush=True)
+    cap = max(sum(sizes) + 9, 65 * len(sizes), 1600)
+    assert _tall_tiles(oracle, probe, G, sizes, H, F, cap, cut[0])[1:3] == cut[1:]
 
 
-@pytest.mark.parametrize("sizes,H,F,spare", [
-    ([90], 64, 64, 36000),          # one item
-    ([90] * 9, 832, 576, 4000),     # a second group of one tile, column groups that end early
-    ([70] * 51, 320, 640, 9),       # 255 wide items of gemm1
-    ([70] * 32, 2048, 1024, 9),     # 256 of both: one item each
-    ([70] * 43, 64, 768, 9),        # 258: the first two that are drawn
-    ([70, 300, 0, 90] * 11, 320, 2112, 9)])
-def test_ffn_every_item_of_the_queue_is_run_once(oracle, probe, G, sizes, H, F, spare):
-    """Tall tiles at numbers of items around one per workgroup, where the first ones are dealt without a draw, and with groups of tiles
-    and columns that are not full: every output element against the oracle."""
-    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=106)
-    capacity = sum(sizes) + spare
-    assert (capacity // 64 + len(sizes)) * (F // 64) > 512 and capacity > 64 * len(sizes)     # past the decode schedule
+@pytest.mark.parametrize("sizes,H,F,spare,items", [
+    ([50], 64, 64, 36000, (1, 1)),
+    ([90] * 9, 832, 576, 4000, (162, 126)),          # 18 tiles of 64 rows: a third group of two tiles, column groups that end early
+    ([70] * 51, 64, 320, 9, (255, 51)),              # one item to a workgroup but the last, one to every
+    ([70] * 64, 448, 256, 9, (256, 256)),
+    ([130] * 43, 384, 768, 9, (258, 129)),           # the first two that are drawn
+    ([70] * 83 + [130], 320, 192, 9, (255, 255)),
+    ([300, 90, 200, 300, 70, 300, 70, 190, 200, 200, 130, 70, 190, 300, 70, 300, 200, 90, 190, 300, 200, 300, 200, 90, 130, 70, 190, 90, 200],
+     704, 320, 9, (215, 258)),
+    ([70, 300, 0, 90] * 11, 320, 2112, 9, (935, 165))])
+def test_ffn_every_item_of_the_queue_is_run_once(oracle, probe, G, sizes, H, F, spare, items):
+    """Tall tiles at numbers of items of gemm1 and gemm2 around one per workgroup, where the first ones are dealt without a draw, and with
+    groups of tiles and columns that are not full: every output element against the oracle."""
+    cap = max(sum(sizes) + spare, 65 * len(sizes))
     print("case queue", len(sizes), H, F, flush=True)
-    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F, extra_rows=spare)
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=106)
+    assert (cap // 64 + len(sizes)) * (F // 64) > 512                                          # past the decode schedule
+    ws = torch.zeros(probe.grouped_ffn_workspace_bytes(len(sizes), H, F, cap), dtype=torch.uint8, device="cuda")
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F, extra_rows=cap - sum(sizes), workspace=ws)
+    n, narrow1, narrow2, _ = _tile_table(ws, F, cap)
+    assert items == (n * (F // 64 if narrow1 else (F + 127) // 128), n * ((H + 127) // 128 if narrow2 else (H + 255) // 256))
 
 
-@pytest.mark.parametrize("sizes,H,F,spare", [
-    ([0, 200], 256, 2176, 700),                              # the estimate takes tiles of 64 rows, narrow items
-    ([200, 333, 70, 70, 200, 0, 333, 200], 320, 1280, 9),    # 128 rows, narrow in gemm2
-    ([390, 3, 256, 0, 450, 450], 768, 1280, 9),              # 192 rows, narrow
-    ([577, 3, 70, 512, 200, 3, 3], 2240, 1280, 9),           # 256 rows, narrow
-    ([3, 70, 577, 577, 390, 390, 390], 704, 1920, 9)])       # 256 rows, narrow in gemm2
-def test_ffn_tile_heights_by_estimated_time(oracle, probe, G, sizes, H, F, spare):
+@pytest.mark.parametrize("sizes,H,F,height,least_height", [
+    ([3, 200, 0, 3, 200, 70, 130, 130, 30], 64, 1600, 64, 128),                    # 19 tiles, room for 12 in the least workspace
+    ([577, 3, 0, 70, 64, 390, 130, 190, 0, 190, 0, 130, 30], 64, 832, 64, 192),
+    ([200, 64, 200, 64, 333, 577, 30], 64, 1152, 64, 256),
+    ([450, 512, 450, 512, 70], 256, 2176, 64, 0),
+    ([256, 200, 450, 64, 512, 200], 448, 1216, 128, 0),
+    ([200, 130, 200, 0, 450, 390, 512, 256, 333], 192, 704, 128, 192),
+    ([64, 450, 70, 512, 200, 450], 1344, 1152, 192, 0)])
+def test_ffn_tile_heights_by_estimated_time(oracle, probe, G, sizes, H, F, height, least_height):
     """Tiles of lower heights than the standard cut's where the estimate of the launches takes them: every output element against the
-    oracle, and the same bits from a workspace whose tile table holds the standard cut only."""
-    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=108)
+    oracle, and the same bits from the least workspace, whose tile table has no room for them and takes another cut."""
     S, n = len(sizes), sum(sizes)
-    cap = n + spare
-    assert (cap // 64 + S) * (F // 64) > 512 and cap > 64 * S                               # past the decode schedule
+    cap = max(n + 9, 65 * S)
     print("case heights", S, H, F, flush=True)
-    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F, extra_rows=spare)
+    _tall_tiles(oracle, probe, G, sizes, H, F, cap, height)
     gen = torch.Generator(device="cuda").manual_seed(H)
     x = torch.randn((cap, H), generator=gen, device="cuda").to(torch.bfloat16)
     w = (torch.randn((2 * F, H), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16),
@@ -813,11 +861,11 @@ def test_ffn_tile_heights_by_estimated_time(oracle, probe, G, sizes, H, F, spare
     so = torch.from_numpy(np.r_[0, np.cumsum(sizes)].astype(np.int32)).cuda()
     tab = probe.WeightTable([w[0]] * S, [w[1]] * S)
     up = lambda b: (b + 255) // 256 * 256
-    least = up(cap * F * 2) + up(128 + 32 * (cap // 256 + S))
-    assert least <= probe.grouped_ffn_workspace_bytes(S, H, F, cap)
-    ys = [probe.grouped_ffn(x, so, tab, workspace=torch.empty(b, dtype=torch.uint8, device="cuda"))[:n]
-          for b in (probe.grouped_ffn_workspace_bytes(S, H, F, cap), least)]
-    torch.cuda.synchronize()
+    ys = []
+    for b, h in ((probe.grouped_ffn_workspace_bytes(S, H, F, cap), height), (up(cap * F * 2) + up(128 + 32 * (cap // 256 + S)), least_height)):
+        ws = torch.zeros(b, dtype=torch.uint8, device="cuda")
+        ys.append(probe.grouped_ffn(x, so, tab, workspace=ws)[:n])
+        _check_cut(_tile_table(ws, F, cap), sizes, h)
     assert torch.equal(ys[0], ys[1])
 
 
@@ -853,20 +901,9 @@ def test_ffn_workspace_of_the_query_holds_the_chosen_cut(probe, sizes, H, F, spa
 def test_ffn_tiles_of_a_slot_stay_together_in_lower_cuts(oracle, probe, G, sizes, H, F, height):
     """Tiles of at most 192 rows: but for single tiles between them a slot's tiles stand side by side, and the slots of several tiles by
     descending rows, whatever the number of items.  Every output element against the oracle."""
-    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=112)
-    cap = max(sum(sizes) + 9, 65 * len(sizes))
     print("case together", sizes, H, F, flush=True)
-    ws = torch.zeros(probe.grouped_ffn_workspace_bytes(len(sizes), H, F, cap), dtype=torch.uint8, device="cuda")
-    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 3, seed=H + F, extra_rows=cap - sum(sizes), workspace=ws)
-    n, _, _, tiles = _tile_table(ws, F, cap)
-    assert n == sum((m + height - 1) // height for m in sizes) and tiles[:, 2].max() == height
-    several = [int(q) for q in tiles[:, 3] if sizes[q] > height]     # single tiles may stand between them
-    runs = [q for i, q in enumerate(several) if i == 0 or q != several[i - 1]]
-    assert runs == sorted((q for q, m in enumerate(sizes) if m > height), key=lambda q: (-sizes[q], q))
-    assert sorted(q for q in tiles[:, 3] if sizes[q] <= height) == [q for q, m in enumerate(sizes) if 0 < m <= height]
-    for q in runs:
-        mine = tiles[tiles[:, 3] == q]
-        assert np.array_equal(mine[:, 0] - mine[0, 0], height * np.arange(len(mine))) and mine[0, 1] == sizes[q]
+    table = _tall_tiles(oracle, probe, G, sizes, H, F, max(sum(sizes) + 9, 65 * len(sizes)), height)
+    assert _slots_in_order(table, sizes, height)
 
 
 @pytest.mark.parametrize("H,F,n", [(4096, 2048, 75), (2880, 2880, 40)])
@@ -895,18 +932,21 @@ def test_ffn_every_tile_height_at_full_depth(oracle, probe, G):
     """One slot per tile height (320, 256, 192, 128, 64 rows) and a ragged one, at the depth of the benchmark's
     main configuration (K = 7168 in the first GEMM, 2048 in the second: 112 and 32 steps of the main loop):
     every output element against the oracle."""
-    cfg = wl.CONFIGS[3]
     print("case full-depth tile heights", flush=True)
-    _ffn_against_oracle(oracle, probe, G, cfg, [320, 256, 192, 128, 64, 37, 0, 321], 3, seed=77)
+    sizes = [320, 256, 192, 128, 64, 37, 0, 321]
+    _tall_tiles(oracle, probe, G, sizes, wl.CONFIGS[3].H, wl.CONFIGS[3].F, sum(sizes) + 9, 0)
 
 
 @pytest.mark.parametrize("H,F", [(64, 256), (320, 64), (256, 128)])
 def test_ffn_every_tile_height_at_shallow_depth(oracle, probe, G, H, F):
-    """One slot per tile height at depths of 1, 2, 4 and 5 steps of the main loop, where its first and last steps
-    (which load fewer tiles ahead) are all there is: every output element against the oracle."""
-    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=99)
+    """Forty slots per tile height, with which the standard cut is taken, at depths of 1, 2, 4 and 5 steps of the main loop, where its first
+    and last steps (which load fewer tiles ahead) are all there is: every output element against the oracle.  A single slot of
+    each takes the decode schedule, whose main loop is the 64-row tile's."""
     print("case shallow depth H=%d F=%d" % (H, F), flush=True)
-    _ffn_against_oracle(oracle, probe, G, cfg, [320, 256, 192, 128, 64, 37, 0, 321], 4, seed=H * 7 + F)
+    sizes = [320, 256, 192, 128, 64, 37, 0, 321]
+    _tall_tiles(oracle, probe, G, sizes * 40, H, F, 40 * sum(sizes) + 9, 0, n_weights=4)
+    cfg = wl.small_config(T=64, H=H, E=4, k=2, F=F, cid=99)
+    _ffn_against_oracle(oracle, probe, G, cfg, sizes, 4, seed=H * 7 + F)
 
 
 @pytest.mark.parametrize("cid", [1, 4])
