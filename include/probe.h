@@ -272,8 +272,11 @@ int probe_permute_static(const int32_t* topk_idx, const probe_plan* plan, const 
  * the largest batch serves every smaller one, at its full speed.  Where few rows leave most of the chip
  * idle, a long contraction is summed in pieces whose fp32 sums lie in the workspace (8 MB of it, asked
  * for only where H or F is long enough).  A workspace that lacks just that room is accepted as well; the
- * contraction is then summed in one piece, and low bits of y can differ, as they can between two values
- * of max_rows.  The same call repeats bit for bit.
+ * contraction is then summed in one piece.  The least that is accepted is h and a shorter table of row tiles,
+ * with which a call may take other tiles; that changes no bit of y.
+ * The same call repeats bit for bit.  The order in which a row's sums are made follows S, H, F, max_rows and,
+ * where few rows leave CUs idle, the row counts of all slots (contractions in pieces, items of few rows, the
+ * k at which an item begins): low bits of a row of y can differ between two such calls.
  */
 size_t probe_grouped_ffn_workspace_bytes(int S, int H, int F, int max_rows);
 

@@ -1156,7 +1156,7 @@ static void direct_shape(RouteShape& s, int T, int H, int E, int max_split) {
 // x 96 14.5 / 13.5, 256 x 4096 x 256 17.0 / 15.9; but 1000 x 2880 x 80 14.6 / 15.1, 192 x 2880 x 200 13.9 / 15.0.  Three lose (640 x 4096 x 128
 // 16.3 / 18.2).  An fp32 gate that two token blocks share needs no launch that splits it and gains more (256 x 4096 x 256 24.1 / 15.2), also
 // where packed planes lose; but packed planes and the fp32 gate give the same bits, so they go one way.  Probabilities against 64 bits over
-// 545 gates from 128 to 7168 wide: 3.6e-8 of the largest (mean of the rms; 1.3e-6 at most) tiled, 3.5e-8 (1.3e-6) with those above.
+// 546 gates from 128 to 7168 wide (164 of them go this way): 3.6e-8 of the largest (mean of the rms; 1.3e-6 at most) tiled, 3.5e-8 (1.3e-6) with those above.
 // The top-k adds the slices, eight at once: two k32 in fourteen slices lose (384 x 7168 x 96 16.8 / 17.1), and so do the most logits (1000 x
 // 2048 x 128 15.0 / 15.2).
 constexpr int kDirectMore = 131072, kDirectTwo = 98304, kDirectBlocks = 256, kDirectWide = 1024, kDirectEmpty = 32, kDirectSlices = 8;
