@@ -130,7 +130,7 @@ __device__ __forceinline__ SlotCut cut_slot(int m, int cap) {
 // bytes in all.  The schedule kernel estimates the launches of both GEMMs for the standard cut and for tiles of at most 256, 192, 128 and 64
 // rows, each with wide and with narrow items, and takes the shortest; another cut has to be 2 % better than the standard one.
 //
-// The estimate: an item lasts 0.85 ns x k-steps x (3 x its rows + 4 x its weight rows), and 0.3 us; items are dealt tallest first, one
+// The estimate: an item lasts 0.85 ns x k-steps x (3 x its rows + 4 x its weight rows), and 0.3 us; items are dealt as if tallest first, one
 // workgroup to a CU.  The launch lasts as long as ceil(n / CUs) times the shortest of its n tallest items, for every n, and, with more
 // items than CUs, as their mean load of a CU and 0.6 of the shortest.  Fitted to 90 drawn FFN calls of 64 to 4096 tokens, each timed with all
 // twenty cuts: of the 4.7 % that the best cut of each gains over the standard cut with the former rule for the width (a limit on wide
